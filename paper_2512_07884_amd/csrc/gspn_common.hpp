@@ -191,6 +191,11 @@ inline hipError_t allow_dynamic_lds(const void* kernel, int bytes) {
 // launchers implemented by the kernel files; return hipError_t of the launch
 hipError_t launch_fwd_generic(const FwdParams& p, int dtype, hipStream_t s);
 hipError_t launch_bwd_generic(const BwdParams& p, int dtype, hipStream_t s);
+// maps of any size through LDS in chunks of lines (gspn_ragged*.hip): the calls of the "generic" plan that fit it
+hipError_t launch_fwd_ragged(const FwdParams& p, int dtype, hipStream_t s);
+bool ragged_applicable(const FwdParams& p, int dtype);
+hipError_t launch_bwd_ragged(const BwdParams& p, int dtype, hipStream_t s);
+bool ragged_bwd_applicable(const BwdParams& p, int dtype);
 hipError_t launch_fwd_tile(const FwdParams& p, int dtype, hipStream_t s);
 bool fwd_tile_applicable(const FwdParams& p, int dtype);
 hipError_t launch_fwd_plane(const FwdParams& p, int dtype, hipStream_t s);

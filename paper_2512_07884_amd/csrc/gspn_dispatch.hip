@@ -89,7 +89,10 @@ hipError_t launch_fwd(const FwdParams& p, int dtype, hipStream_t s) {
         case FWD_PLANE: return launch_fwd_plane(p, dtype, s);
         case FWD_PAIR: return launch_fwd_pair(p, dtype, s);
         case FWD_CHUNK: return launch_fwd_chunk(p, dtype, s);
-        default: return launch_fwd_generic(p, dtype, s);
+        // any other map: the chunked kernel for maps of any size, and line by line where no shape of it fits
+        default:
+            if (!knobs().force_generic && ragged_applicable(p, dtype)) return launch_fwd_ragged(p, dtype, s);
+            return launch_fwd_generic(p, dtype, s);
     }
 }
 
@@ -98,7 +101,9 @@ hipError_t launch_bwd(const BwdParams& p, int dtype, hipStream_t s) {
         case BWD_TILE: return launch_bwd_tile(p, dtype, s);
         case BWD_PLANE: return launch_bwd_plane(p, dtype, s);
         case BWD_TWOPASS: return launch_bwd_twopass(p, dtype, s);
-        default: return launch_bwd_generic(p, dtype, s);
+        default:
+            if (!knobs().force_generic && ragged_bwd_applicable(p, dtype)) return launch_bwd_ragged(p, dtype, s);
+            return launch_bwd_generic(p, dtype, s);
     }
 }
 

@@ -10,8 +10,9 @@
 // else in place in global memory -- so no atomics and no zero-fill are needed and
 // the summation order is fixed.
 //
-// This is the fallback for shapes the specialised kernels do not take; it makes
-// no attempt at coalescing the horizontal directions.
+// This is the fallback for shapes no other kernel takes (lines beyond the reach of gspn_ragged*.hip, planes of fewer than
+// 16 pixels, the transposed layout off the tile kernel) and the reference the fast kernels are compared with; it makes no
+// attempt at coalescing the horizontal directions.
 #include "gspn_common.hpp"
 
 namespace gspn {

@@ -1,0 +1,331 @@
+// Maps of any size (gspn_ragged_impl.hpp): choice of the launch shape, launches, and the second pass of the backward call.
+#include "gspn_ragged_impl.hpp"
+
+namespace gspn {
+
+hipError_t launch_ragged_f32(const FwdParams& p, bool reverse, void* e_lo, hipStream_t s);
+hipError_t launch_ragged_bf16(const FwdParams& p, bool reverse, void* e_lo, hipStream_t s);
+hipError_t launch_ragged_f16(const FwdParams& p, bool reverse, void* e_lo, hipStream_t s);
+
+// The launch shape for a call, or false where no shape fits (the line-by-line kernels then take it).
+// merge_rounds: the caller's merged output was rounded once per direction anyway (gx of the backward call).
+bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* out, int* threads, int* nv, size_t* lds) {
+    const int H = p.H, W = p.W, es = dtype == 0 ? 4 : 2, E = 16 / es;
+    if (p.xt) return false;
+    if ((size_t)H * W < 16 || (size_t)H * W >= (1u << 29)) return false;
+    const size_t planes = (size_t)p.B * p.C;
+    if (planes > 0x7fffffffull) return false;
+    const bool wide = dtype == 0 || p.logits;
+    const size_t sb = wide ? 16 : 8;
+    const size_t cap = 160 * 1024;
+    RaggedArgs a = {};
+    a.p = p;
+    a.tile_pitch = (W + E - 1) / E * E;
+    const size_t tile_bytes = (size_t)H * a.tile_pitch * 4;
+    const int longest = H > W ? H : W;
+    // The line-by-line kernel sums the four directions of a 16-bit plane in an fp32 LDS tile where its two line buffers leave
+    // room; a merge in global memory rounds once per direction, so it is taken only where that kernel would do so too.
+    const bool must_tile = dtype != 0 && !merge_rounds && (size_t)H * W * 4 + 2 * (size_t)longest * 4 <= cap;
+    // workgroups a CU is to hold: as many as the call has for it, up to 8; sixteen waves per CU (128 registers) in any case
+    int wgs_wanted = 1;
+    while (wgs_wanted < 8 && (size_t)wgs_wanted * 256 < planes) wgs_wanted *= 2;
+
+    for (int mode = 0; mode < (must_tile ? 2 : 3); ++mode) {     // tile and both directions; tile and one; y in global memory
+        a.nd = mode == 0 ? 2 : 1;
+        a.tile = mode < 2;
+        const size_t fixed = a.tile ? tile_bytes : 0;
+        if (fixed >= cap) continue;
+        for (int v = 1; v <= 2; ++v) {
+            for (int ax = 0; ax < 2; ++ax) {
+                const int L = ax ? H : W;
+                if (ax == 0) {                                              // granules are written whole, one slot apart
+                    a.pitch2[ax] = (L + 7) / 8 * 8;
+                    a.pitch[ax] = (L + E - 1) / E * (E + 1);
+                } else {                                                    // odd: spreads the banks of the turned writes
+                    a.pitch[ax] = (L + v - 1) / v * v | 1;
+                    a.pitch2[ax] = v == 1 ? a.pitch[ax] : (L + v - 1) / v * v + 2;
+                }
+            }
+            auto stage_bytes = [&](int ax, int K) { return (size_t)a.nd * (K * (a.pitch[ax] * sb + (wide ? 0 : a.pitch2[ax] * 2)) + 2 * a.pitch2[ax] * 4); };
+            const int kmax[2] = {(H + 7) / 8 * 8, (W + 7) / 8 * 8};
+            // chunk lengths: 64 B of an image row per request in the horizontal directions if that fits, else 32, else 16;
+            // with each, as many workgroups per CU as the LDS allows
+            for (int seg = 64; seg >= 16; seg /= 2) {
+                for (int wgs = wgs_wanted; wgs >= 1; wgs /= 2) {
+                    const int thr = 1024 / wgs, waves = thr / 64 / a.nd;
+                    if (waves < 1 || fixed >= cap / wgs) continue;
+                    const size_t room = cap / wgs - fixed;
+                    bool ok = true;
+                    for (int ax = 0; ax < 2 && ok; ++ax) {
+                        const int L = ax ? H : W;
+                        int parts = L <= 64 * v ? 1 : (L + 64 * v - 2 * RG_SUB - 1) / (64 * v - 2 * RG_SUB), own = 0;
+                        for (; parts <= waves; ++parts) {
+                            own = ((L + parts - 1) / parts + v - 1) / v * v;
+                            if (parts == 1 || own + 2 * RG_SUB <= 64 * v) break;
+                        }
+                        ok = parts <= waves;
+                        a.parts[ax] = parts; a.own[ax] = own;
+                    }
+                    if (!ok) continue;
+                    auto fits = [&](int ax, int K) {
+                        const int gr = ax ? (K / E) * H : K * ((W + E - 1) / E);
+                        return gr <= thr / a.nd && stage_bytes(ax, K) <= room;
+                    };
+                    int kh = seg / es < 8 ? 8 : seg / es;
+                    if (kh > kmax[1]) kh = kmax[1];
+                    int kv = 8;
+                    if (!fits(1, kh) || !fits(0, kv)) continue;
+                    while (kv + 8 <= kmax[0] && kv + 8 <= 32 && fits(0, kv + 8)) kv += 8;
+                    a.K[0] = kv; a.K[1] = kh;
+                    *threads = thr;
+                    goto found;
+                }
+            }
+            continue;
+        found:
+            size_t top = 0;
+            for (int ax = 0; ax < 2; ++ax) {
+                a.w2_off[ax] = (int)((size_t)a.nd * a.K[ax] * a.pitch[ax] * sb);
+                a.edge_off[ax] = (int)((size_t)a.nd * a.K[ax] * (a.pitch[ax] * sb + (wide ? 0 : a.pitch2[ax] * 2)));
+                const size_t n = stage_bytes(ax, a.K[ax]);
+                if (n > top) top = n;
+            }
+            top = (top + 15) / 16 * 16;
+            a.tile_off = (int)top;
+            if (top + fixed > cap) continue;
+            *out = a; *nv = v; *lds = top + fixed;
+            return true;
+        }
+    }
+    return false;
+}
+
+static bool ragged_fits(const FwdParams& p, int dtype, bool merge_rounds) {
+    RaggedArgs a;
+    int threads, nv;
+    size_t lds;
+    return ragged_plan(p, dtype, merge_rounds, &a, &threads, &nv, &lds);
+}
+bool ragged_applicable(const FwdParams& p, int dtype) { return ragged_fits(p, dtype, false); }
+
+hipError_t launch_fwd_ragged(const FwdParams& p, int dtype, hipStream_t s) {
+    return dtype == 0 ? launch_ragged_f32(p, false, nullptr, s) : dtype == 1 ? launch_ragged_bf16(p, false, nullptr, s) : launch_ragged_f16(p, false, nullptr, s);
+}
+
+namespace {
+
+// Second pass of the backward call: per pixel and direction the sum over the group's channels of e * h of the previous
+// line (gw), glam = x*e and gu = gy*h.  A thread owns 16 bytes of an image row; every tensor, the three taps of h
+// included, is one 16-byte request at element alignment (a tap is the same window one row or one column away).  e comes
+// in fp32: from glam itself in fp32 storage, else its two halves from glam (high) and gu (low).  Every thread reads its
+// own e before it overwrites it.  SL = 4: the four waves of a workgroup take every fourth channel of the same pixels and
+// add their sums in wave order through LDS -- calls have few (image, group) pairs, and one thread walking all channels
+// left four waves per CU waiting on one channel's requests at a time; a channel's requests also go out before the
+// previous channel is stored.  Bound by memory: 16 B per pixel, channel and direction in 16-bit storage beside x and gy.
+template <typename T, int SL>
+__global__ void __launch_bounds__(256) ragged_finish_kernel(BwdParams p, int ndirs) {
+    constexpr int E = 16 / (int)sizeof(T);
+    const int H = p.H, W = p.W, HW = H * W;
+    const int gpr = (W + E - 1) / E;
+    const int npb = H * gpr;
+    const size_t per_dir = (size_t)p.B * p.G * npb;
+    // the workgroups that work on the same pixels in the different directions read the same x and gy: indices 8 apart
+    // go to the same XCD one after the other
+    const unsigned wg = blockIdx.x;
+    int dsel = (int)((wg / 8) % (unsigned)ndirs);
+    const unsigned blk = (wg / (8 * (unsigned)ndirs)) * 8 + (wg % 8);
+    constexpr int GPB = 256 / SL;                              // granules per workgroup
+    const int slice = SL == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / GPB), lane = threadIdx.x % GPB;
+    const size_t want = (size_t)blk * GPB + lane;
+    const bool live = want < per_dir;
+    const size_t rem = live ? want : per_dir - 1;              // spare lanes read the last granule and store nothing
+    const int bg = (int)(rem / npb);
+    const int q = (int)(rem - (size_t)bg * npb);
+    const int row = q / gpr, col = (q - row * gpr) * E;
+    const int off = row * W + col;
+    const int n = min(E, W - col);                             // valid elements
+    int d = 0;
+    for (;; ++d)
+        if ((p.mask >> d) & 1u) { if (dsel == 0) break; --dsel; }
+    const int b = bg / p.G, g = bg - b * p.G;
+    const size_t planes = (size_t)p.B * p.C, groups = (size_t)p.B * p.G;
+    const bool vert = d < 2;
+    const int back = (d & 1) ? 1 : -1;                         // to the previous line of the scan
+    const int S = vert ? H : W, L = vert ? W : H;
+    // windows: own pixels, and per tap; kept inside the tensor (they may reach into neighbouring planes)
+    const int lo = bg == 0 ? 0 : -HW, hi = bg == (int)groups - 1 ? HW - E : 2 * HW - E;
+    const int sh = off - min(max(off, lo), hi);
+    int toff[3], tsh[3];
+    uint32_t tmask[3];                                         // bit e: tap k of element e exists
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int o = off + (vert ? back * W + k - 1 : (k - 1) * W + back);
+        tsh[k] = o - min(max(o, lo), hi);
+        toff[k] = o - tsh[k];
+        tmask[k] = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int r = vert ? row + back : row + k - 1, c = vert ? col + e + k - 1 : col + e + back;
+            const int line = vert ? row : col + e;
+            const bool starts = starts_stretch((d & 1) ? S - 1 - line : line, S, d & 1, p.kchunk);
+            if (r >= 0 && r < H && c >= 0 && c < W && e < n && !starts) tmask[k] |= 1u << e;
+        }
+    }
+    const bool moved = __any(sh != 0 || tsh[0] != 0 || tsh[1] != 0 || tsh[2] != 0);
+    const size_t plane0 = ((size_t)b * p.C + (size_t)g * p.cpg) * HW;
+    const T* X = (const T*)p.x + plane0 + (off - sh);
+    const T* GY = (const T*)p.gy + plane0 + (off - sh);
+    const T* HS = (const T*)p.hs + (size_t)d * planes * HW + plane0;
+    T* GL = (T*)p.glam + (size_t)d * planes * HW + plane0;
+    T* GU = (T*)p.gu + (size_t)d * planes * HW + plane0;
+    float acc[3][E];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[k][e] = 0.f;
+
+    u32x4 eh, el = {0, 0, 0, 0}, xv, gv, hc, t0, t1, t2;
+    auto request = [&](int ci, u32x4& eh_, u32x4& el_, u32x4& xv_, u32x4& gv_, u32x4& hc_, u32x4& t0_, u32x4& t1_, u32x4& t2_) {
+        const size_t po = (size_t)ci * HW;
+        eh_ = rg_load((const T*)GL + po + (off - sh));
+        if constexpr (sizeof(T) == 2) el_ = rg_load((const T*)GU + po + (off - sh));
+        xv_ = rg_load(X + po); gv_ = rg_load(GY + po); hc_ = rg_load(HS + po + (off - sh));
+        t0_ = rg_load(HS + po + toff[0]); t1_ = rg_load(HS + po + toff[1]); t2_ = rg_load(HS + po + toff[2]);
+    };
+    request(slice < p.cpg ? slice : 0, eh, el, xv, gv, hc, t0, t1, t2);
+    for (int ci = slice; ci < p.cpg; ci += SL) {
+        const size_t po = (size_t)ci * HW;
+        // the next channel's values before this one's are stored
+        u32x4 eh_n, el_n = {0, 0, 0, 0}, xv_n, gv_n, hc_n, t0_n, t1_n, t2_n;
+        const bool more = ci + SL < p.cpg;
+        if (more) request(ci + SL, eh_n, el_n, xv_n, gv_n, hc_n, t0_n, t1_n, t2_n);
+        if (moved) {
+            eh = rg_realign<T>(eh, sh); el = rg_realign<T>(el, sh); xv = rg_realign<T>(xv, sh); gv = rg_realign<T>(gv, sh); hc = rg_realign<T>(hc, sh);
+            t0 = rg_realign<T>(t0, tsh[0]); t1 = rg_realign<T>(t1, tsh[1]); t2 = rg_realign<T>(t2, tsh[2]);
+        }
+        float gl[E], gu[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            float ev;
+            if constexpr (sizeof(T) == 4) ev = __uint_as_float(eh[e]);
+            else ev = __uint_as_float((e & 1) ? __builtin_amdgcn_perm(eh[e >> 1], el[e >> 1], 0x07060302u) : __builtin_amdgcn_perm(eh[e >> 1], el[e >> 1], 0x05040100u));
+            acc[0][e] = fmaf(((tmask[0] >> e) & 1u) ? ev : 0.f, ((tmask[0] >> e) & 1u) ? rg_elem<T>(t0, e) : 0.f, acc[0][e]);
+            acc[1][e] = fmaf(((tmask[1] >> e) & 1u) ? ev : 0.f, ((tmask[1] >> e) & 1u) ? rg_elem<T>(t1, e) : 0.f, acc[1][e]);
+            acc[2][e] = fmaf(((tmask[2] >> e) & 1u) ? ev : 0.f, ((tmask[2] >> e) & 1u) ? rg_elem<T>(t2, e) : 0.f, acc[2][e]);
+            gl[e] = rg_elem<T>(xv, e) * ev;
+            gu[e] = rg_elem<T>(gv, e) * rg_elem<T>(hc, e);
+        }
+        u32x4 vl, vu;
+        if constexpr (sizeof(T) == 4) {
+            vl = u32x4{__float_as_uint(gl[0]), __float_as_uint(gl[1]), __float_as_uint(gl[2]), __float_as_uint(gl[3])};
+            vu = u32x4{__float_as_uint(gu[0]), __float_as_uint(gu[1]), __float_as_uint(gu[2]), __float_as_uint(gu[3])};
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { vl[i] = pack_word<T>(gl[2 * i], gl[2 * i + 1]); vu[i] = pack_word<T>(gu[2 * i], gu[2 * i + 1]); }
+        }
+        if (!live) {
+        } else if (n == E) {
+            rg_store(GL + po + off, vl);
+            rg_store(GU + po + off, vu);
+        } else {
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (e < n) { rg_store_bits(GL + po + off + e, rg_bits<T>(vl, e)); rg_store_bits(GU + po + off + e, rg_bits<T>(vu, e)); }
+        }
+        if (more) { eh = eh_n; el = el_n; xv = xv_n; gv = gv_n; hc = hc_n; t0 = t0_n; t1 = t1_n; t2 = t2_n; }
+    }
+    if constexpr (SL > 1) {
+        __shared__ float red[SL - 1][3 * E][GPB];
+        if (slice > 0) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int e = 0; e < E; ++e) red[slice - 1][k * E + e][lane] = acc[k][e];
+        }
+        __syncthreads();
+        if (slice > 0) return;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+#pragma unroll
+                for (int i = 0; i < SL - 1; ++i) acc[k][e] += red[i][k * E + e][lane];
+            }
+    }
+    if (!live) return;
+    if (p.logits) {
+        // the sum over the group's channels goes through the softmax of its pixel once; logits that are never read stay
+        // out, with a gradient of exactly 0
+        const T* Z = (const T*)p.w + ((p.shared ? (size_t)0 : (size_t)d * groups) + bg) * 3 * HW;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int line = vert ? row : col + e, pos = vert ? col + e : row;
+            const bool unread = e >= n || starts_stretch((d & 1) ? S - 1 - line : line, S, d & 1, p.kchunk);
+            float z0 = 0.f, z1 = 0.f, z2 = 0.f;
+            if (!unread) { z0 = ldf(Z + off + e); z1 = ldf(Z + HW + off + e); z2 = ldf(Z + 2 * (size_t)HW + off + e); }
+            softmax3(z0, z1, z2, pos == 0, pos == L - 1);
+            softmax3_grad(acc[0][e], acc[1][e], acc[2][e], z0, z1, z2);
+            if (unread) { acc[0][e] = 0.f; acc[1][e] = 0.f; acc[2][e] = 0.f; }
+        }
+    }
+    T* GW = (T*)p.gw + ((size_t)d * groups + bg) * 3 * HW + off;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        u32x4 v;
+        if constexpr (sizeof(T) == 4) v = u32x4{__float_as_uint(acc[k][0]), __float_as_uint(acc[k][1]), __float_as_uint(acc[k][2]), __float_as_uint(acc[k][3])};
+        else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = pack_word<T>(acc[k][2 * i], acc[k][2 * i + 1]);
+        }
+        if (n == E) rg_store(GW + (size_t)k * HW, v);
+        else {
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (e < n) rg_store_bits(GW + (size_t)k * HW + e, rg_bits<T>(v, e));
+        }
+    }
+}
+
+FwdParams ragged_sweep_params(const BwdParams& p) {
+    FwdParams f = {};
+    f.x = p.gy; f.w = p.w; f.lam = p.u; f.u = p.lam; f.y = p.gx; f.hs = p.glam;
+    f.B = p.B; f.C = p.C; f.H = p.H; f.W = p.W; f.G = p.G; f.cpg = p.cpg;
+    f.mask = p.mask; f.shared = p.shared; f.kchunk = p.kchunk; f.logits = p.logits; f.xt = nullptr;
+    return f;
+}
+
+// channels of a group over the waves of a workgroup where there are that many
+int ragged_slices(const BwdParams& p) { return p.cpg >= 4 ? 4 : 1; }
+unsigned long long ragged_finish_blocks(const BwdParams& p, int dtype) {
+    const int E = dtype == 0 ? 4 : 8;
+    const unsigned long long per_dir = (unsigned long long)p.B * p.G * p.H * ((p.W + E - 1) / E);
+    int ndirs = 0;
+    for (int d = 0; d < 4; ++d) ndirs += (p.mask >> d) & 1u;
+    const unsigned long long gpb = 256 / ragged_slices(p);
+    return ((per_dir + gpb - 1) / gpb + 7) / 8 * 8 * ndirs;         // per direction: a multiple of 8 workgroups
+}
+
+}  // namespace
+
+bool ragged_bwd_applicable(const BwdParams& p, int dtype) {
+    return ragged_fits(ragged_sweep_params(p), dtype, true) && ragged_finish_blocks(p, dtype) <= 0x7fffffffull;
+}
+
+// The two passes of the backward call on any map: the reverse sweep (merged gx, e per direction in fp32), then the sums
+// over the channels.
+hipError_t launch_bwd_ragged(const BwdParams& p, int dtype, hipStream_t s) {
+    const FwdParams f = ragged_sweep_params(p);
+    hipError_t e = dtype == 0 ? launch_ragged_f32(f, true, nullptr, s) : dtype == 1 ? launch_ragged_bf16(f, true, p.gu, s) : launch_ragged_f16(f, true, p.gu, s);
+    if (e != hipSuccess) return e;
+    int ndirs = 0;
+    for (int d = 0; d < 4; ++d) ndirs += (p.mask >> d) & 1u;
+    const dim3 grid((unsigned)ragged_finish_blocks(p, dtype)), block(256);
+    const bool sliced = ragged_slices(p) > 1;
+    void (*k)(BwdParams, int) = dtype == 0 ? (sliced ? ragged_finish_kernel<float, 4> : ragged_finish_kernel<float, 1>)
+                              : dtype == 1 ? (sliced ? ragged_finish_kernel<bf16_t, 4> : ragged_finish_kernel<bf16_t, 1>)
+                                           : (sliced ? ragged_finish_kernel<f16_t, 4> : ragged_finish_kernel<f16_t, 1>);
+    hipLaunchKernelGGL(k, grid, block, 0, s, p, ndirs);
+    return hipGetLastError();
+}
+
+}  // namespace gspn

@@ -1,0 +1,88 @@
+"""Maps of any size on the kernels that walk them in chunks of lines (the "generic" plan's fast form): forward, forward with
+h_save and the backward call against the fp64 oracle, and against the line-by-line kernels over random shapes.  Sizes sit
+where the launch shape changes: granules of 8 / 4 elements and their tails, rows narrower than a granule, lines of one and
+of several waves (64 / 65, 192 / 193 positions), two and four positions per lane (from 193 and 385 up), planes beyond the
+LDS tile, the last chunk of a scan, the middle of the map where the chunks of both directions cross."""
+import numpy as np
+import pytest
+
+from test_gpu_local import check_local
+from test_gpu_logits import check_logits
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 2, 1, 17, 1), (1, 2, 17, 1, 2), (2, 2, 5, 5, 1), (1, 4, 3, 67, 2), (2, 3, 7, 9, 3), (1, 2, 25, 31, 1),
+          (1, 2, 64, 65, 1), (1, 2, 65, 63, 2), (1, 6, 50, 83, 2), (2, 2, 100, 167, 1), (1, 2, 167, 100, 2),
+          (1, 1, 30, 193, 1), (1, 1, 193, 30, 1), (1, 1, 385, 21, 1), (1, 1, 20, 391, 1), (1, 1, 450, 12, 1),
+          (1, 1, 11, 905, 1), (1, 1, 905, 9, 1), (1, 2, 210, 230, 1)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_global_scan(shape, dtype):
+    check_local(shape + (dtype,), 1 << 14)
+
+
+@pytest.mark.parametrize("shape,kchunk,mask", [((1, 2, 25, 31, 1), 1, 15), ((1, 4, 50, 83, 2), 3, 15), ((2, 2, 65, 63, 1), 24, 15),
+                                               ((1, 2, 100, 167, 2), 8, 5), ((1, 2, 17, 193, 1), 16, 10), ((1, 1, 211, 201, 1), 50, 15)],
+                         ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_local_stretches_and_direction_masks(shape, kchunk, mask, dtype):
+    check_local(shape + (dtype,), kchunk, mask=mask, poison_starts=dtype != "f16")
+
+
+@pytest.mark.parametrize("shape,kchunk,mask", [((1, 3, 25, 31, 3), None, 15), ((1, 4, 50, 83, 2), 7, 15), ((1, 2, 100, 167, 1), None, 15),
+                                               ((1, 2, 65, 193, 2), 24, 15), ((1, 2, 31, 77, 2), None, 9), ((1, 1, 205, 230, 1), None, 15)],
+                         ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_weights_as_logits(shape, kchunk, mask, dtype):
+    check_logits(shape + (dtype,), kchunk=kchunk, mask=mask, poison=dtype != "f16")
+
+
+@pytest.mark.parametrize("seed", [31, 32])
+def test_against_the_line_by_line_kernels(seed, monkeypatch):
+    """Random ragged shapes; both sides hold the state, e and the merged output in fp32 where the plane fits the LDS, so
+    they are at most two storage roundings apart (bf16: 2 * 2^-8 of the value; elsewhere one rounding per direction)."""
+    import torch
+    import paper_2512_07884_amd as G
+    from paper_2512_07884_amd import binding
+    from test_gpu_differential import _run, _rel
+    G.binding = binding
+    rng = np.random.default_rng(seed)
+    for it in range(14):
+        dtype = ["bf16", "f32", "f16"][int(rng.integers(0, 3))]
+        H, W = int(2 ** rng.uniform(1, 8.3)), int(2 ** rng.uniform(1, 8.3)) | 1
+        if H * W < 16:
+            H = 16
+        cpg, Gr, B = int(rng.choice([1, 2, 3, 8])), int(rng.integers(1, 4)), int(rng.integers(1, 3))
+        C = cpg * Gr
+        mask = int(rng.integers(1, 16)) if rng.random() < 0.3 else 15
+        kchunk = int(rng.integers(1, max(H, W))) if rng.random() < 0.35 else 0
+        logits = bool(rng.random() < 0.3)
+        td = {"bf16": torch.bfloat16, "f32": torch.float32, "f16": torch.float16}[dtype]
+        g = torch.Generator(device="cuda"); g.manual_seed(1000 * seed + it)
+        z = torch.randn((4, B, Gr, 3, H, W), generator=g, device="cuda")
+        if logits:
+            w = z.to(td)
+        else:
+            z[:2, :, :, 0, :, 0] = -1e30; z[:2, :, :, 2, :, -1] = -1e30; z[2:, :, :, 0, 0, :] = -1e30; z[2:, :, :, 2, -1, :] = -1e30
+            w = torch.softmax(z.double(), dim=3).to(td)
+        inp = {"x": torch.randn((B, C, H, W), generator=g, device="cuda").to(td), "w": w,
+               "lam": torch.rand((4, B, C, H, W), generator=g, device="cuda").to(td),
+               "u": torch.rand((4, B, C, H, W), generator=g, device="cuda").to(td),
+               "gy": torch.randn((B, C, H, W), generator=g, device="cuda").to(td)}
+        monkeypatch.delenv("GSPN_FORCE_GENERIC", raising=False)
+        fast = _run(G, inp, Gr, mask, kchunk, logits)
+        again = _run(G, inp, Gr, mask, kchunk, logits)
+        monkeypatch.setenv("GSPN_FORCE_GENERIC", "1")
+        ref = _run(G, inp, Gr, mask, kchunk, logits)
+        monkeypatch.delenv("GSPN_FORCE_GENERIC", raising=False)
+        tol = {"bf16": 2e-2, "f16": 2.5e-3, "f32": 2e-5}[dtype]
+        case = (seed, it, B, C, H, W, Gr, dtype, mask, kchunk, logits)
+        for n in fast:
+            a, b = fast[n].float(), ref[n].float()
+            na, nb = torch.isnan(a), torch.isnan(b)
+            assert torch.equal(na, nb), (case, n, "slots of unmasked directions differ")
+            e = _rel(torch.where(na, torch.zeros_like(a), a), torch.where(nb, torch.zeros_like(b), b))
+            assert e <= tol, (case, n, e)
+            assert torch.equal(fast[n].view(torch.uint8), again[n].view(torch.uint8)), (case, n, "not the same twice")
