@@ -220,7 +220,9 @@ int gspn_proxy_project_bwd(const void* gout, const void* in, const void* P, void
 #define GSPN_PROXY_STATIC_MAX_FLOATS (1 << 20)
 int gspn_proxy_project_bwd_static(const void* gout, const void* in, const void* P, void* gin, float* gP,
                                   int B, int K, int M, int H, int W, int dtype, void* stream);
-/* "mfma" or "fma": which kernel gspn_proxy_project runs for these arguments ("invalid" for bad ones). */
+/* "mfma": matrix-core kernels with whole 16-byte requests; "fma": every other call -- fp32 storage and K not a multiple of 8
+ * on plain FMA kernels, 16-bit images whose H*W is not a multiple of 8 (from 8 pixels up) on the matrix-core kernels with
+ * requests at element alignment ("invalid" for bad arguments). */
 const char* gspn_proxy_plan(int B, int K, int M, int H, int W, int dtype);
 
 /* Name of the kernel family the forward / backward call would dispatch to for

@@ -13,8 +13,12 @@
 // lanes 32-63 the second), 16 B = 8 consecutive pixels (a wave reads whole 512 B row segments), and regroups them in registers
 // with byte permutes into eight k-packed B operands, one per pixel of its eight.  Eight MFMAs per k-step then give
 // each lane, per output row it holds, eight consecutive pixels: the result leaves as 16 B stores of whole segments.
-// Shapes the MFMA path does not take (fp32 storage, K or N not multiples of 8) run a plain FMA kernel.
-#include "gspn_tile_common.hpp"
+// Where that leaves too few waves (1152 -> 144 channels on two 64x64 images: 160 waves of 72 dependent k-steps) the four
+// waves of a workgroup take every fourth k-step of a narrower tile (128 pixels) and add their sums through LDS in wave order.
+// N not a multiple of 8: the same kernels with requests at element alignment; the last lane of a row takes its last eight
+// (four) pixels, some of them a second time (same sum, same bytes stored).
+// What the MFMA path does not take (fp32 storage, K not a multiple of 8, fewer than 8 pixels) runs a plain FMA kernel.
+#include "gspn_unaligned.hpp"
 
 namespace gspn {
 
@@ -37,49 +41,83 @@ template <typename T> __device__ __forceinline__ f32x16_t mfma_k16(const u32x4& 
     else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
+// NB bytes (16 or 8) of a row at p: ANY = p is aligned to its element only
+template <typename T, int NB, bool ANY> __device__ __forceinline__ void ld_row(const T* p, uint32_t* r) {
+    if constexpr (NB == 16) {
+        u32x4 v;
+        if constexpr (ANY) v = rg_load(p); else v = *(const u32x4*)p;
+        r[0] = v[0]; r[1] = v[1]; r[2] = v[2]; r[3] = v[3];
+    } else {
+        typedef uint32_t any8 __attribute__((ext_vector_type(2), aligned(2)));
+        u32x2 v;
+        if constexpr (ANY) v = *(const any8*)p; else v = *(const u32x2*)p;
+        r[0] = v.x; r[1] = v.y;
+    }
+}
+template <typename T, int NB, bool ANY> __device__ __forceinline__ void st_row(T* p, const uint32_t* r) {
+    if constexpr (NB == 16) {
+        const u32x4 v = {r[0], r[1], r[2], r[3]};
+        if constexpr (ANY) rg_store(p, v); else *(u32x4*)p = v;
+    } else {
+        typedef uint32_t any8 __attribute__((ext_vector_type(2), aligned(2)));
+        const u32x2 v = {r[0], r[1]};
+        if constexpr (ANY) *(any8*)p = v; else *(u32x2*)p = v;
+    }
+}
+
+// one 16x16 step over 32 k values (the small tiles of the weight gradient)
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+template <typename T> __device__ __forceinline__ f32x4_t mfma16_k32(const u32x4& a, const u32x4& b, const f32x4_t& c) {
+    if constexpr (__is_same(T, f16_t)) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
 // KS = k values per MFMA: 8 (v_mfma_f32_32x32x8_bf16_1k) or 16 (v_mfma_f32_32x32x16_bf16, K a multiple of 16).
 // A lane feeds KS/2 consecutive k: lanes 0-31 the first half of the k-step, lanes 32-63 the second.
 // PT: the matrix is applied transposed, out[b][m][n] = sum_k P[k][m] * in[b][k][n] with P stored [K][M] (the gradient of
 // the projection w.r.t. its input): a lane then gathers its KS/2 values of P with 2-byte loads a row apart (P is small
 // and stays in cache).
-template <typename T, int KS, bool PT = false>
+// SPLIT = 1: a wave owns 32 rows x 256 pixels.  SPLIT = 4: a workgroup owns 32 rows x 128 pixels, its waves every fourth
+// k-step (1152 -> 144 on two 64x64 images 58 -> 18 us).  ANY: rows of `in` / `out` start at any element.
+template <typename T, int KS, bool PT, int SPLIT, bool ANY>
 __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ in, const T* __restrict__ P,
                                                          T* __restrict__ out, int B, int K, int M, int N,
                                                          int ntiles, int mtiles) {
     constexpr int KL = KS / 2;                                 // k-rows per lane and k-step
+    constexpr int PX = SPLIT == 1 ? 8 : 4;                     // pixels per lane
+    constexpr int NB = PX * 2;
+    constexpr int DEPTH = SPLIT == 1 ? 1 : 3;                  // k-steps requested ahead
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    // work item -> (image, pixel tile, row tile), row tile fastest: the waves of a workgroup take the row tiles of
-    // one pixel tile (they read the same `in`, which then comes out of L1) or, with a single row tile,
-    // neighbouring pixel tiles
-    const long item = (long)blockIdx.x * 4 + wave;
+    // work item -> (image, pixel tile, row tile), row tile fastest: the waves of a workgroup (SPLIT = 4: neighbouring
+    // workgroups) take the row tiles of one pixel tile (they read the same `in`, which then comes out of the caches) or,
+    // with a single row tile, neighbouring pixel tiles
+    const long item = SPLIT == 1 ? (long)blockIdx.x * 4 + wave : (long)xcd_contiguous_item(blockIdx.x, gridDim.x);
     const long per_image = (long)ntiles * mtiles;
-    if (item >= (long)B * per_image) return;
+    if (item >= (long)B * per_image) return;                   // (whole waves; whole workgroups where the waves meet)
     const int b = (int)(item / per_image);
     const int rem = (int)(item - (long)b * per_image);
     const int nt = rem / mtiles, mt = rem - nt * mtiles;
     const int jl = lane & 31, kh = lane >> 5;                  // pixel group of the lane, which half of the k-step
-    const int n_lane = nt * 256 + jl * 8;                      // first of the lane's eight pixels
-    const bool n_ok = n_lane < N;                              // N is a multiple of 8: all eight or none
+    const int n_raw = nt * (32 * PX) + jl * PX;                // first of the lane's pixels
+    const bool n_ok = n_raw < N;
+    const int n_lane = n_ok ? min(n_raw, N - PX) : 0;          // a row's last lane: its last PX pixels
     const int m_lane = mt * 32 + jl;                           // row of P this lane feeds as the A operand
     const bool m_ok = m_lane < M;
 
-    const rsrc_t inb = make_rsrc(in + (size_t)b * K * N);
+    const T* src = in + (size_t)b * K * N + n_lane;
     const rsrc_t pb = make_rsrc(P);
-    f32x16_t acc[8];
+    f32x16_t acc[PX];
 #pragma unroll
-    for (int v = 0; v < 8; ++v)
+    for (int v = 0; v < PX; ++v)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[v][r] = 0.f;
 
-    struct Step { u32x4 q[KL]; uint32_t pa[KL / 2]; };         // the lane's k-rows of `in`; P[m_lane][its k values]
+    struct Step { uint32_t q[KL][NB / 4]; uint32_t pa[KL / 2]; };         // the lane's k-rows of `in`; P[m_lane][its k values]
     auto fetch = [&](int k0, Step& t) {
         const int kr = k0 + KL * kh;
 #pragma unroll
-        for (int kk = 0; kk < KL; ++kk) {
-            t.q[kk] = u32x4{0, 0, 0, 0};
-            if (n_ok) t.q[kk] = __builtin_amdgcn_raw_buffer_load_b128(inb, (uint32_t)(((size_t)(kr + kk) * N + n_lane) * 2), 0, 0);
-        }
+        for (int kk = 0; kk < KL; ++kk) ld_row<T, NB, ANY>(src + (size_t)(kr + kk) * N, t.q[kk]);      // (spare lanes: pixel 0)
 #pragma unroll
         for (int i = 0; i < KL / 2; ++i) t.pa[i] = 0;
         if (m_ok && PT) {
@@ -97,8 +135,8 @@ __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ i
     };
     auto multiply = [&](const Step& t) {
 #pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            // pixel v of the lane's eight, its k values packed in pairs: element v sits in word v/2, half v%2
+        for (int v = 0; v < PX; ++v) {
+            // pixel v of the lane's, its k values packed in pairs: element v sits in word v/2, half v%2
             const uint32_t sel = (v & 1) ? 0x07060302u : 0x05040100u;
             uint32_t bb[KL / 2];
 #pragma unroll
@@ -112,27 +150,70 @@ __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ i
             }
         }
     };
-    // the operands of the next k-step are requested before the current one is multiplied (past the end the last
+    // the operands of the next k-steps are requested before the current one is multiplied (past the end the last
     // step is requested again: redundant, in bounds, never multiplied)
-    Step cur, nxt;
     const int last = K - KS;
-    fetch(0, cur);
-    for (int k0 = 0; k0 < K; k0 += KS) {
-        fetch(min(k0 + KS, last), nxt);
-        multiply(cur);
-        cur = nxt;
+    const int k_first = SPLIT == 1 ? 0 : wave * KS;
+    constexpr int HOP = KS * SPLIT;
+    if constexpr (DEPTH == 1) {
+        Step cur, nxt;
+        fetch(0, cur);
+        for (int k0 = 0; k0 < K; k0 += KS) {
+            fetch(min(k0 + KS, last), nxt);
+            multiply(cur);
+            cur = nxt;
+        }
+    } else {
+        Step s0, s1, s2;
+        fetch(min(k_first, last), s0);
+        fetch(min(k_first + HOP, last), s1);
+        for (int k0 = k_first; k0 < K; k0 += 3 * HOP) {
+            fetch(min(k0 + 2 * HOP, last), s2);
+            multiply(s0);
+            fetch(min(k0 + 3 * HOP, last), s0);
+            if (k0 + HOP < K) multiply(s1);
+            fetch(min(k0 + 4 * HOP, last), s1);
+            if (k0 + 2 * HOP < K) multiply(s2);
+        }
     }
 
     // accumulator register r of a lane: output row 8*(r/4) + 4*(lane/32) + r%4 of the tile, column = the lane's pixel
-    if (!n_ok) return;
-    const rsrc_t ob = make_rsrc(out + (size_t)b * M * N);
+    T* dst = out + (size_t)b * M * N + n_lane;
+    if constexpr (SPLIT == 1) {
+        if (!n_ok) return;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int m = mt * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
-        if (m < M) {
-            const u32x4 o = {pack_word<T>(acc[0][r], acc[1][r]), pack_word<T>(acc[2][r], acc[3][r]),
-                             pack_word<T>(acc[4][r], acc[5][r]), pack_word<T>(acc[6][r], acc[7][r])};
-            st_b128(ob, (uint32_t)(((size_t)m * N + n_lane) * 2), o);
+        for (int r = 0; r < 16; ++r) {
+            const int m = mt * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
+            if (m < M) {
+                const uint32_t o[4] = {pack_word<T>(acc[0][r], acc[1][r]), pack_word<T>(acc[2][r], acc[3][r]),
+                                       pack_word<T>(acc[4][r], acc[5][r]), pack_word<T>(acc[6][r], acc[7][r])};
+                st_row<T, NB, ANY>(dst + (size_t)m * N, o);
+            }
+        }
+    } else {
+        __shared__ float red[SPLIT][16][PX][64];
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int v = 0; v < PX; ++v) red[wave][r][v][lane] = acc[v][r];
+        __syncthreads();
+        if (!n_ok) return;
+        // each wave adds and stores a quarter of the rows
+#pragma unroll
+        for (int i = 0; i < 16 / SPLIT; ++i) {
+            const int r = wave * (16 / SPLIT) + i;
+            const int m = mt * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
+            if (m < M) {
+                float t[PX];
+#pragma unroll
+                for (int v = 0; v < PX; ++v) {
+                    t[v] = red[0][r][v][lane];
+#pragma unroll
+                    for (int w = 1; w < SPLIT; ++w) t[v] += red[w][r][v][lane];
+                }
+                const uint32_t o[2] = {pack_word<T>(t[0], t[1]), pack_word<T>(t[2], t[3])};
+                st_row<T, NB, ANY>(dst + (size_t)m * N, o);
+            }
         }
     }
 }
@@ -165,7 +246,10 @@ __global__ void __launch_bounds__(256) proxy_fma_kernel(const T* __restrict__ in
 // (image, 32 x 32 tile of gP); its NW waves take interleaved 16-pixel steps of n and add their accumulators through
 // LDS in wave order; the per-image sums go to the caller's workspace and a small kernel adds the images in order, so the
 // result does not depend on scheduling.  NW = 8 where four waves per tile would leave the chip short of loads in flight.
-template <typename T, int NW>
+// KT = 2: a tile of 32 x 64, whose rows of gout feed two products (operand rows read from the caches: 96 per 2048 elements
+// of gP against 128), where the call has enough tiles.  ANY: rows start at any element; N any: the step that crosses the end
+// of the rows takes the last eight pixels and moves them down, zeros behind them.
+template <typename T, int NW, int KT, bool ANY>
 __global__ void __launch_bounds__(64 * NW) proxy_gradw_mfma_kernel(const T* __restrict__ gout, const T* __restrict__ in,
                                                                float* __restrict__ partial, int K, int M, int N,
                                                                int mtiles, int ktiles) {
@@ -177,40 +261,121 @@ __global__ void __launch_bounds__(64 * NW) proxy_gradw_mfma_kernel(const T* __re
     const int rem = blockIdx.x - b * per_image;
     const int mt = rem / ktiles, kt = rem - mt * ktiles;
     const int jl = lane & 31, nh = lane >> 5;                  // row of the operand this lane feeds; which 8 of the 16 pixels
-    const int m_lane = mt * 32 + jl, k_lane = kt * 32 + jl;
-    const bool m_ok = m_lane < M, k_ok = k_lane < K;
-    const rsrc_t gb = make_rsrc(gout + ((size_t)b * M + mt * 32) * N);      // the tile's 32 rows of gout / of in
-    const rsrc_t ib = make_rsrc(in + ((size_t)b * K + kt * 32) * N);
-    const uint32_t row_off = (uint32_t)((size_t)jl * N * 2);
-    f32x16_t acc;
+    const int m_lane = mt * 32 + jl;
+    // rows past the end are read as the last row (their sums are not stored)
+    const T* ga = gout + ((size_t)b * M + min(m_lane, M - 1)) * N;
+    const T* ib[KT];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    // four 16-pixel steps per trip: their eight loads are requested together (N is a multiple of 16; steps past the end
-    // load nothing and multiply zeros)
-    for (int n0 = wave * 16; n0 < N; n0 += 64 * NW) {
-        u32x4 av[4], bv[4];
+    for (int t = 0; t < KT; ++t) ib[t] = in + ((size_t)b * K + min(kt * 32 * KT + 32 * t + jl, K - 1)) * N;
+    f32x16_t acc[KT];
+#pragma unroll
+    for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    // four neighbouring 16-pixel steps per trip: their loads are requested together and cover whole 128-byte lines of the rows
+    // (steps past the end load nothing and multiply zeros)
+    for (int n0 = wave * 64; n0 < N; n0 += 64 * NW) {
+        u32x4 av[4], bv[KT][4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int n = n0 + 16 * NW * q;
-            const uint32_t off = row_off + (uint32_t)((n + 8 * nh) * 2);
-            av[q] = u32x4{0, 0, 0, 0}; bv[q] = u32x4{0, 0, 0, 0};
-            if (m_ok && n < N) av[q] = __builtin_amdgcn_raw_buffer_load_b128(gb, off, 0, 0);
-            if (k_ok && n < N) bv[q] = __builtin_amdgcn_raw_buffer_load_b128(ib, off, 0, 0);
+            const int n = n0 + 16 * q + 8 * nh;
+            av[q] = u32x4{0, 0, 0, 0};
+#pragma unroll
+            for (int t = 0; t < KT; ++t) bv[t][q] = u32x4{0, 0, 0, 0};
+            if (n < N) {
+                const int nl = ANY ? min(n, N - 8) : n;
+                ld_row<T, 16, ANY>(ga + nl, (uint32_t*)&av[q]);
+#pragma unroll
+                for (int t = 0; t < KT; ++t) ld_row<T, 16, ANY>(ib[t] + nl, (uint32_t*)&bv[t][q]);
+            }
+        }
+        if (ANY && n0 + 64 > N) {                              // the end of the rows (a uniform branch)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int n = n0 + 16 * q + 8 * nh;
+                const int sh = n < N ? max(n - (N - 8), 0) : 0;
+                av[q] = rg_realign<T>(av[q], sh);
+#pragma unroll
+                for (int t = 0; t < KT; ++t) bv[t][q] = rg_realign<T>(bv[t][q], sh);
+            }
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            acc = mfma_k16<T>(av[q], bv[q], acc);
+#pragma unroll
+            for (int t = 0; t < KT; ++t) acc[t] = mfma_k16<T>(av[q], bv[t][q], acc[t]);
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r];
+    for (int t = 0; t < KT; ++t) {
+        if (t > 0) __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[t][r];
+        __syncthreads();
+        // accumulator register r of a lane: row 8*(r/4) + 4*(lane/32) + r%4 of the tile (m), column lane%32 (k)
+        for (int idx = threadIdx.x; idx < 16 * 64; idx += 64 * NW) {
+            const int r = idx >> 6, l = idx & 63;
+            float v = red[0][r][l];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) v += red[w][r][l];
+            const int m = mt * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3), k = kt * 32 * KT + 32 * t + (l & 31);
+            if (m < M && k < K) partial[((size_t)b * M + m) * K + k] = v;
+        }
+    }
+}
+
+// The same in tiles of 16 x 16 (v_mfma_f32_16x16x32: 32 pixels per step, lane l feeds row l % 16 and pixels 8 * (l / 16) ..),
+// sixteen waves each, for calls whose 32 x 32 tiles are fewer than a quarter of the CUs: a tile's rows are read by one CU,
+// whose request rate is then what bounds the call (24 <- 96 channels on two 78x117 images: 6 tiles, 44 us -> 24 tiles, 19 us).
+template <typename T, bool ANY>
+__global__ void __launch_bounds__(1024) proxy_gradw_small_kernel(const T* __restrict__ gout, const T* __restrict__ in,
+                                                                 float* __restrict__ partial, int K, int M, int N,
+                                                                 int mtiles, int ktiles) {
+    constexpr int NW = 16;
+    __shared__ float red[NW][4][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int per_image = mtiles * ktiles;
+    const int b = blockIdx.x / per_image;
+    const int rem = blockIdx.x - b * per_image;
+    const int mt = rem / ktiles, kt = rem - mt * ktiles;
+    const int jl = lane & 15, nq = lane >> 4;
+    // rows past the end are read as the last row (their sums are not stored)
+    const T* ga = gout + ((size_t)b * M + min(mt * 16 + jl, M - 1)) * N;
+    const T* ib = in + ((size_t)b * K + min(kt * 16 + jl, K - 1)) * N;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (int n0 = wave * 128; n0 < N; n0 += 128 * NW) {
+        u32x4 av[4], bv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int n = n0 + 32 * q + 8 * nq;
+            av[q] = u32x4{0, 0, 0, 0}; bv[q] = u32x4{0, 0, 0, 0};
+            if (n < N) {
+                const int nl = ANY ? min(n, N - 8) : n;
+                ld_row<T, 16, ANY>(ga + nl, (uint32_t*)&av[q]);
+                ld_row<T, 16, ANY>(ib + nl, (uint32_t*)&bv[q]);
+            }
+        }
+        if (ANY && n0 + 128 > N) {                             // the end of the rows (a uniform branch)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int n = n0 + 32 * q + 8 * nq;
+                const int sh = n < N ? max(n - (N - 8), 0) : 0;
+                av[q] = rg_realign<T>(av[q], sh);
+                bv[q] = rg_realign<T>(bv[q], sh);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc = mfma16_k32<T>(av[q], bv[q], acc);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wave][r][lane] = acc[r];
     __syncthreads();
-    // accumulator register r of a lane: row 8*(r/4) + 4*(lane/32) + r%4 of the tile (m), column lane%32 (k)
-    for (int idx = threadIdx.x; idx < 16 * 64; idx += 64 * NW) {
-        const int r = idx >> 6, l = idx & 63;
+    // accumulator register r of a lane: row 4*(lane/16) + r of the tile (m), column lane%16 (k)
+    if (threadIdx.x < 256) {
+        const int r = threadIdx.x >> 6, l = threadIdx.x & 63;
         float v = red[0][r][l];
 #pragma unroll
         for (int w = 1; w < NW; ++w) v += red[w][r][l];
-        const int m = mt * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3), k = kt * 32 + (l & 31);
+        const int m = mt * 16 + 4 * (l >> 4) + r, k = kt * 16 + (l & 15);
         if (m < M && k < K) partial[((size_t)b * M + m) * K + k] = v;
     }
 }
@@ -268,10 +433,31 @@ __global__ void __launch_bounds__(256) proxy_gradw_sum_kernel(const float* __res
 
 }  // namespace
 
+// the plan name: whole 16-byte requests in every row
 bool proxy_mfma_applicable(int B, int K, int M, int N, int dtype) {
     if (dtype == 0 || K % 8 || N % 8) return false;
     // 32-bit byte offsets inside one image of `in` / `out` and inside P
     return (size_t)K * N * 2 < (1ull << 31) && (size_t)M * N * 2 < (1ull << 31) && (size_t)M * K * 2 < (1ull << 31);
+}
+// rows of any length from eight pixels up run on the matrix cores too, with requests at element alignment
+// (24 <- 96 channels on two 78x117 images, FMA kernels -> these: forward 165 -> 11, input gradient 141 -> 11, weight gradient
+// 492 -> 19 us)
+static bool proxy_mfma_any(int K, int M, int N, int dtype) {
+    return dtype != 0 && K % 8 == 0 && N >= 8 && (size_t)M * K * 2 < (1ull << 31);
+}
+
+template <typename T, int KS, bool PT, int SPLIT>
+static hipError_t launch_project_mfma(const void* in, const void* P, void* out, int B, int K, int M, int N, hipStream_t s) {
+    constexpr int tile = SPLIT == 1 ? 256 : 128;
+    const int ntiles = (N + tile - 1) / tile, mtiles = (M + 31) / 32;
+    const long items = (long)B * ntiles * mtiles, blocks = SPLIT == 1 ? (items + 3) / 4 : items;
+    if (blocks > 0x7fffffffl) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), block(256);
+    if (N % 8 == 0)
+        hipLaunchKernelGGL((proxy_mfma_kernel<T, KS, PT, SPLIT, false>), grid, block, 0, s, (const T*)in, (const T*)P, (T*)out, B, K, M, N, ntiles, mtiles);
+    else
+        hipLaunchKernelGGL((proxy_mfma_kernel<T, KS, PT, SPLIT, true>), grid, block, 0, s, (const T*)in, (const T*)P, (T*)out, B, K, M, N, ntiles, mtiles);
+    return hipGetLastError();
 }
 
 // out = P in (PT = false) or P^T in (PT = true: the gradient w.r.t. the projection's input) in storage type T
@@ -279,15 +465,13 @@ template <typename T, bool PT>
 static hipError_t launch_project_as(const void* in, const void* P, void* out, int B, int K, int M, int N, bool mfma, hipStream_t s) {
     if constexpr (sizeof(T) == 2) {
         if (mfma) {
-            const int ntiles = (N + 255) / 256, mtiles = (M + 31) / 32;
-            const long items = (long)B * ntiles * mtiles;
-            if ((items + 3) / 4 > 0x7fffffffl) return hipErrorInvalidValue;
-            const dim3 grid((unsigned)((items + 3) / 4)), block(256);
-            if (K % 16 == 0)
-                hipLaunchKernelGGL((proxy_mfma_kernel<T, 16, PT>), grid, block, 0, s, (const T*)in, (const T*)P, (T*)out, B, K, M, N, ntiles, mtiles);
-            else
-                hipLaunchKernelGGL((proxy_mfma_kernel<T, 8, PT>), grid, block, 0, s, (const T*)in, (const T*)P, (T*)out, B, K, M, N, ntiles, mtiles);
-            return hipGetLastError();
+            // the waves of a workgroup share the k-steps where one wave per tile would leave the chip with fewer than four
+            // waves per CU and a chain of sixteen and more steps (two 64x64 images, 1152 -> 144: 58 -> 18 us; with 9 steps,
+            // 144 -> 1152, sharing them costs more than it saves: 14 -> 22 us)
+            const long waves = (long)B * ((N + 255) / 256) * ((M + 31) / 32);
+            const bool split = waves < 1024 && K >= 16 * (K % 16 == 0 ? 16 : 8);
+            if (K % 16 == 0) return split ? launch_project_mfma<T, 16, PT, 4>(in, P, out, B, K, M, N, s) : launch_project_mfma<T, 16, PT, 1>(in, P, out, B, K, M, N, s);
+            return split ? launch_project_mfma<T, 8, PT, 4>(in, P, out, B, K, M, N, s) : launch_project_mfma<T, 8, PT, 1>(in, P, out, B, K, M, N, s);
         }
     }
     const long threads = (long)B * N;
@@ -299,7 +483,7 @@ static hipError_t launch_project_as(const void* in, const void* P, void* out, in
 
 hipError_t launch_proxy_project(const void* in, const void* P, void* out, int B, int K, int M, int N, int dtype,
                                 hipStream_t s) {
-    const bool mfma = proxy_mfma_applicable(B, K, M, N, dtype);
+    const bool mfma = proxy_mfma_any(K, M, N, dtype);
     if (dtype == 0) return launch_project_as<float, false>(in, P, out, B, K, M, N, false, s);
     if (dtype == 1) return launch_project_as<bf16_t, false>(in, P, out, B, K, M, N, mfma, s);
     return launch_project_as<f16_t, false>(in, P, out, B, K, M, N, mfma, s);
@@ -308,19 +492,33 @@ hipError_t launch_proxy_project(const void* in, const void* P, void* out, int B,
 // per-image sums of gout in^T into `partial` (B*M*K floats), storage type T
 template <typename T>
 static hipError_t launch_gradw_as(const void* gout, const void* in, float* partial, int B, int K, int M, int N, hipStream_t s) {
-    const bool mfma = sizeof(T) == 2 && N % 16 == 0 && (size_t)N * 2 * 32 < (1ull << 31);
-    const int ktiles = (K + 31) / 32, mtiles = mfma ? (M + 31) / 32 : (M + 7) / 8;
+    const bool mfma = sizeof(T) == 2 && N >= 8;
+    if constexpr (sizeof(T) == 2) {
+        if (mfma && (long)B * ((M + 31) / 32) * ((K + 31) / 32) < 64 && N >= 512) {
+            const int mt = (M + 15) / 16, kt = (K + 15) / 16;
+            void (*k)(const T*, const T*, float*, int, int, int, int, int) = N % 8 ? proxy_gradw_small_kernel<T, true> : proxy_gradw_small_kernel<T, false>;
+            hipLaunchKernelGGL(k, dim3((unsigned)((long)B * mt * kt)), dim3(1024), 0, s, (const T*)gout, (const T*)in, partial, K, M, N, mt, kt);
+            return hipGetLastError();
+        }
+    }
+    const int mtiles = mfma ? (M + 31) / 32 : (M + 7) / 8;
+    // 32 x 64 tiles from one per CU on (fewer, larger tiles would leave CUs idle)
+    const bool pair = mfma && (long)B * mtiles * ((K + 31) / 32) >= 256;
+    const int ktiles = pair ? (K + 63) / 64 : (K + 31) / 32;
     const long blocks = (long)B * mtiles * ktiles;
     if (blocks > 0x7fffffffl) return hipErrorInvalidValue;
     const bool wide = blocks * 4 < 2048;     // eight waves per tile while four would leave a compute unit under eight
     if constexpr (sizeof(T) == 2) {
-        if (mfma && wide)
-            hipLaunchKernelGGL((proxy_gradw_mfma_kernel<T, 8>), dim3((unsigned)blocks), dim3(512), 0, s, (const T*)gout, (const T*)in,
-                               partial, K, M, N, mtiles, ktiles);
-        else if (mfma)
-            hipLaunchKernelGGL((proxy_gradw_mfma_kernel<T, 4>), dim3((unsigned)blocks), dim3(256), 0, s, (const T*)gout, (const T*)in,
-                               partial, K, M, N, mtiles, ktiles);
-        if (mfma) return hipGetLastError();
+        if (mfma) {
+            const bool any = N % 8 != 0;
+            void (*k)(const T*, const T*, float*, int, int, int, int, int) =
+                pair ? (wide ? (any ? proxy_gradw_mfma_kernel<T, 8, 2, true> : proxy_gradw_mfma_kernel<T, 8, 2, false>)
+                             : (any ? proxy_gradw_mfma_kernel<T, 4, 2, true> : proxy_gradw_mfma_kernel<T, 4, 2, false>))
+                     : (wide ? (any ? proxy_gradw_mfma_kernel<T, 8, 1, true> : proxy_gradw_mfma_kernel<T, 8, 1, false>)
+                             : (any ? proxy_gradw_mfma_kernel<T, 4, 1, true> : proxy_gradw_mfma_kernel<T, 4, 1, false>));
+            hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(wide ? 512 : 256), 0, s, (const T*)gout, (const T*)in, partial, K, M, N, mtiles, ktiles);
+            return hipGetLastError();
+        }
     }
     hipLaunchKernelGGL(proxy_gradw_fma_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, s, (const T*)gout, (const T*)in,
                        partial, K, M, N, mtiles, ktiles);
@@ -333,7 +531,7 @@ hipError_t launch_proxy_project_bwd(const void* gout, const void* in, const void
                                     int B, int K, int M, int N, int dtype, hipStream_t s) {
     if (gin) {
         // the forward kernels with the matrix read transposed: K output channels, contraction over the M channels of gout
-        const bool mfma = proxy_mfma_applicable(B, M, K, N, dtype);
+        const bool mfma = proxy_mfma_any(M, K, N, dtype);
         const hipError_t e = dtype == 0 ? launch_project_as<float, true>(gout, P, gin, B, M, K, N, false, s)
                            : dtype == 1 ? launch_project_as<bf16_t, true>(gout, P, gin, B, M, K, N, mfma, s)
                                         : launch_project_as<f16_t, true>(gout, P, gin, B, M, K, N, mfma, s);

@@ -20,7 +20,7 @@
 // What bounds it: the LDS instructions and the vector ALU of the staging and of the scan, close to the memory time
 // on 16-bit maps; measured figures are at the choice of the launch shape (plan_ragged).
 #pragma once
-#include "gspn_tile_common.hpp"
+#include "gspn_unaligned.hpp"
 
 namespace gspn {
 
@@ -41,18 +41,6 @@ bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* o
 
 namespace {
 
-template <typename T> struct RgVec {
-    typedef uint32_t type __attribute__((ext_vector_type(4), aligned(2)));     // 16 bytes at element alignment
-};
-template <> struct RgVec<float> {
-    typedef uint32_t type __attribute__((ext_vector_type(4), aligned(4)));
-};
-template <typename T> __device__ __forceinline__ u32x4 rg_load(const T* p) {
-    return *(const typename RgVec<T>::type*)p;
-}
-template <typename T> __device__ __forceinline__ void rg_store(T* p, u32x4 v) {
-    *(typename RgVec<T>::type*)p = v;
-}
 // element e (compile-time) of a granule in storage bits / widened
 template <typename T> __device__ __forceinline__ uint32_t rg_bits(u32x4 v, int e) {
     if constexpr (sizeof(T) == 4) return v[e];
@@ -66,26 +54,6 @@ template <typename T> __device__ __forceinline__ void rg_store_bits(T* p, uint32
     if constexpr (sizeof(T) == 4) *(uint32_t*)p = bits;
     else *(uint16_t*)p = (uint16_t)bits;
 }
-// A granule whose 16-byte window was moved into the tensor by s elements (first or last granule of a tensor only):
-// element e of the granule is at index e + s of what was loaded.  Elements outside the tensor are never used.
-template <typename T> __device__ __forceinline__ u32x4 rg_realign(u32x4 v, int s) {
-#pragma unroll 1
-    for (int i = 0; i < 16 / (int)sizeof(T) - 1; ++i) {
-        u32x4 r = v, l = v;
-        if constexpr (sizeof(T) == 4) {
-            r = u32x4{v[1], v[2], v[3], 0u};
-            l = u32x4{0u, v[0], v[1], v[2]};
-        } else {
-            r = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
-            l = u32x4{v[0] << 16, (v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16)};
-        }
-        const bool right = s > i, left = -s > i;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = right ? r[k] : (left ? l[k] : v[k]);
-    }
-    return v;
-}
-
 // One pass over the plane: one direction, or both directions of an axis at once.
 template <typename T, int MODE, bool LOGITS, int NV, bool HORZ>
 struct RaggedPass {

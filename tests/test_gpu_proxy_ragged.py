@@ -1,0 +1,47 @@
+"""Proxy projections on images whose pixel count is not a multiple of 8 (requests at element alignment, last pixels taken
+twice), with the k-steps of a tile shared by the waves of a workgroup or not, and the weight gradient in single and double
+tiles: against the fp64 oracle, and bit-for-bit copies with a selection matrix."""
+import numpy as np
+import pytest
+
+from gpu_util import TOL, rel_inf_err
+from oracle import gspn_oracle as O
+from paper_2512_07884_amd import workloads as WL
+from test_gpu_proxy import run_project, run_project_bwd
+
+pytestmark = pytest.mark.gpu
+
+# N = 9, 15, 63, 127, 129, 255, 257, 7020; K in whole and half 16-value steps, fewer steps than waves, ragged row tiles; the
+# larger ones have enough tiles for a wave per tile (forward) and for double tiles (weight gradient)
+SHAPES = [(1, 64, 40, 3, 3), (2, 96, 8, 3, 5), (2, 96, 8, 7, 9), (1, 72, 33, 1, 127), (3, 40, 70, 3, 43), (1, 1152, 144, 5, 51),
+          (1, 144, 1152, 1, 257), (1, 96, 24, 90, 78), (9, 200, 130, 11, 13), (64, 24, 96, 33, 31), (2, 8, 96, 17, 19), (2, 96, 24, 23, 23), (1, 40, 33, 16, 40)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_projection_and_gradients(shape, dtype):
+    B, K, M, H, W = shape
+    rng = np.random.default_rng([29, K, M, H])
+    x = WL.to_storage(rng.standard_normal((B, K, H, W)), dtype)
+    P = WL.to_storage(rng.standard_normal((M, K)) / np.sqrt(K), dtype)
+    g = WL.to_storage(rng.standard_normal((B, M, H, W)), dtype)
+    xf, Pf, gf = (WL.storage_to_f64(a, dtype) for a in (x, P, g))
+    assert rel_inf_err(run_project(x, P, dtype), O.proxy_project(xf, Pf)) <= TOL[dtype]
+    gin_ref, gP_ref = O.proxy_project_bwd(gf, xf, Pf)
+    gin, gP = run_project_bwd(g, x, P, dtype)
+    assert rel_inf_err(gin, gin_ref) <= TOL[dtype], rel_inf_err(gin, gin_ref)
+    assert rel_inf_err(gP, gP_ref) <= 1e-5, rel_inf_err(gP, gP_ref)       # accumulated and returned in fp32
+    gin2, gP2 = run_project_bwd(g, x, P, dtype)
+    assert np.array_equal(gin, gin2) and np.array_equal(gP, gP2)
+
+
+@pytest.mark.parametrize("K,H,W", [(64, 16, 24), (1152, 16, 24), (64, 13, 7), (72, 11, 13), (1152, 5, 29)])
+def test_selection_matrix_copies(K, H, W):
+    rng = np.random.default_rng(31)
+    B, M = 2, 40
+    x = WL.to_storage(rng.standard_normal((B, K, H, W)), "bf16")
+    pick = rng.permutation(K)[:M]
+    P = np.zeros((M, K))
+    P[np.arange(M), pick] = 1.0
+    got = run_project(x, WL.to_storage(P, "bf16"), "bf16")
+    assert np.array_equal(got, WL.storage_to_f64(x, "bf16")[:, pick])
