@@ -35,15 +35,17 @@ bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* o
         a.tile = mode < 2;
         const size_t fixed = a.tile ? tile_bytes : 0;
         if (fixed >= cap) continue;
-        for (int v = 1; v <= 2; ++v) {
+        // positions per lane: a line in one wave (no meetings within a chunk) up to 192 positions, beyond that two, and four
+        // where the scanning waves would otherwise leave too few for the loads
+        for (int v = longest <= 64 ? 1 : longest <= 128 ? 2 : longest <= 192 ? 3 : longest <= 448 ? 2 : 4; v; v = 0) {
             for (int ax = 0; ax < 2; ++ax) {
-                const int L = ax ? H : W;
+                const int L = ((ax ? H : W) + v - 1) / v * v;
                 if (ax == 0) {                                              // granules are written whole, one slot apart
                     a.pitch2[ax] = (L + 7) / 8 * 8;
-                    a.pitch[ax] = (L + E - 1) / E * (E + 1);
+                    a.pitch[ax] = (L + E - 1) / E * (E + 1) + v;        // v spare slots at the end of a line
                 } else {                                                    // odd: spreads the banks of the turned writes
-                    a.pitch[ax] = (L + v - 1) / v * v | 1;
-                    a.pitch2[ax] = v == 1 ? a.pitch[ax] : (L + v - 1) / v * v + 2;
+                    a.pitch[ax] = (L + v) | 1;
+                    a.pitch2[ax] = v % 2 ? L | 1 : L + 2;
                 }
             }
             auto stage_bytes = [&](int ax, int K) { return (size_t)a.nd * (K * (a.pitch[ax] * sb + (wide ? 0 : a.pitch2[ax] * 2)) + 2 * a.pitch2[ax] * 4); };
@@ -53,23 +55,23 @@ bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* o
             for (int seg = 64; seg >= 16; seg /= 2) {
                 for (int wgs = wgs_wanted; wgs >= 1; wgs /= 2) {
                     const int thr = 1024 / wgs, waves = thr / 64 / a.nd;
-                    if (waves < 1 || fixed >= cap / wgs) continue;
+                    if (waves < 2 || fixed >= cap / wgs) continue;
                     const size_t room = cap / wgs - fixed;
                     bool ok = true;
                     for (int ax = 0; ax < 2 && ok; ++ax) {
                         const int L = ax ? H : W;
                         int parts = L <= 64 * v ? 1 : (L + 64 * v - 2 * RG_SUB - 1) / (64 * v - 2 * RG_SUB), own = 0;
-                        for (; parts <= waves; ++parts) {
+                        for (; parts < waves; ++parts) {
                             own = ((L + parts - 1) / parts + v - 1) / v * v;
                             if (parts == 1 || own + 2 * RG_SUB <= 64 * v) break;
                         }
-                        ok = parts <= waves;
+                        ok = parts < waves;                                  // at least one wave loads
                         a.parts[ax] = parts; a.own[ax] = own;
                     }
                     if (!ok) continue;
                     auto fits = [&](int ax, int K) {
                         const int gr = ax ? (K / E) * H : K * ((W + E - 1) / E);
-                        return gr <= thr / a.nd && stage_bytes(ax, K) <= room;
+                        return gr <= RG_ROUNDS * (waves - a.parts[ax]) * 64 && stage_bytes(ax, K) <= room;
                     };
                     int kh = seg / es < 8 ? 8 : seg / es;
                     if (kh > kmax[1]) kh = kmax[1];

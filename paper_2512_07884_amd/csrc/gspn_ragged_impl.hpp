@@ -25,6 +25,7 @@
 namespace gspn {
 
 constexpr int RG_FWD = 0, RG_SAVE = 1, RG_BWD = 2;
+constexpr int RG_ROUNDS = 2;     // granules of a chunk per loading thread, at most
 constexpr int RG_SUB = 8;        // scan steps between two meetings of the waves = positions a part shares with each neighbour
 
 struct RaggedArgs {
@@ -54,6 +55,10 @@ template <typename T> __device__ __forceinline__ void rg_store_bits(T* p, uint32
     if constexpr (sizeof(T) == 4) *(uint32_t*)p = bits;
     else *(uint16_t*)p = (uint16_t)bits;
 }
+// LDS by byte address (the pointer form costs an addition of the array's base per access)
+template <typename V> __device__ __forceinline__ V lds_get(uint32_t addr) { return *(const __attribute__((address_space(3))) V*)addr; }
+template <typename V> __device__ __forceinline__ void lds_set(uint32_t addr, V v) { *(__attribute__((address_space(3))) V*)addr = v; }
+
 // One pass over the plane: one direction, or both directions of an axis at once.
 template <typename T, int MODE, bool LOGITS, int NV, bool HORZ>
 struct RaggedPass {
@@ -76,7 +81,7 @@ struct RaggedPass {
     bool first;                  // global merge: y is overwritten
     char* stA; char* stW2; float* edge; float* tile;
 
-    u32x4 bx, bl, bu, b0, b1, b2, by;     // this thread's granule: x, lam, weights of the next chunk; u and y of the current one
+    struct Regs { u32x4 x, l, u, w0, w1, w2, y; };       // a granule: x, lam, weights of the next chunk; u and y of the current one
 
     __device__ __forceinline__ RaggedPass(const RaggedArgs& args, char* l) : a(args), lds(l) {}
 
@@ -86,9 +91,9 @@ struct RaggedPass {
     static __device__ __forceinline__ int line_slot(int pos) { return HORZ ? pos : pos + pos / E; }
     // this thread's granule of chunk k: image row and first column (a multiple of E), pixel offset, LDS slot of its
     // element 0 and the step to the next, the number of elements inside the row, the shifts of its windows
-    __device__ __forceinline__ Gran gran(int k) const {
+    __device__ __forceinline__ Gran gran(int r, int k) const {
         Gran g;
-        const int q = tid;
+        const int q = tid + r * nthr;
         if constexpr (HORZ) {
             const int gpr = K / E;
             const int row = q / gpr, gi = q - row * gpr;
@@ -124,36 +129,31 @@ struct RaggedPass {
     // reverse sweep: a line takes the weights of the line swept before it
     __device__ __forceinline__ int wshift() const { return BWD ? (rev ? 1 : -1) * (HORZ ? 1 : W) : 0; }
 
-    __device__ __forceinline__ void load(int k) {
-        const Gran g = gran(k);
+    __device__ __forceinline__ void load(int k, int r, Regs& q) const {
+        const Gran g = gran(r, k);
         if (!g.on) return;
         const int o = g.off - g.sh;
-        bx = rg_load(X + o);
-        bl = rg_load(LAM + o);
+        q.x = rg_load(X + o);
+        q.l = rg_load(LAM + o);
         const int ow = g.off + wshift() - g.shw;
-        b0 = rg_load(W0 + ow);
-        b1 = rg_load(W0 + HW + ow);
-        b2 = rg_load(W0 + 2 * (size_t)HW + ow);
+        q.w0 = rg_load(W0 + ow);
+        q.w1 = rg_load(W0 + HW + ow);
+        q.w2 = rg_load(W0 + 2 * (size_t)HW + ow);
     }
     // what finish() of the chunk needs: requested with the chunk's scan
-    __device__ __forceinline__ void load_late(int k) {
-        const Gran g = gran(k);
+    __device__ __forceinline__ void load_late(int k, int r, Regs& q) const {
+        const Gran g = gran(r, k);
         if (!g.on) return;
-        bu = rg_load(U + (g.off - g.sh));
-        if (!a.tile && !first) by = rg_load((const T*)Y + (g.off - g.sh));
-    }
-    // The requests of an iteration are spread over the scan's blocks of lines: issued all at once they hold every wave at
-    // the memory pipe before the first line (25 B per clock and CU), and the scan then runs with the pipe idle.
-    __device__ __forceinline__ void request(int k, int piece) {
-        if (piece == 0) load_late(k);
-        if (piece == 1 && k + 1 < nchunks) load(k + 1);
+        q.u = rg_load(U + (g.off - g.sh));
+        if (!a.tile && !first) q.y = rg_load((const T*)Y + (g.off - g.sh));
     }
 
     // registers of the chunk -> LDS
-    __device__ __forceinline__ void stage(int k) {
-        const Gran g = gran(k);
+    __device__ __forceinline__ void stage(int k, int r, const Regs& in) const {
+        const Gran g = gran(r, k);
         if (!g.on) return;
-        u32x4 x = bx, l = bl, w0 = b0, w1 = b1, w2 = b2;
+        __builtin_amdgcn_sched_barrier(0);
+        u32x4 x = in.x, l = in.l, w0 = in.w0, w1 = in.w1, w2 = in.w2;
         if (__any(g.sh != 0 || g.shw != 0)) {        // first / last granule of a tensor
             x = rg_realign<T>(x, g.sh); l = rg_realign<T>(l, g.sh);
             w0 = rg_realign<T>(w0, g.shw); w1 = rg_realign<T>(w1, g.shw); w2 = rg_realign<T>(w2, g.shw);
@@ -188,6 +188,7 @@ struct RaggedPass {
         if constexpr (WIDE) {
 #pragma unroll
             for (int e = 0; e < E; ++e) {
+                if constexpr (sizeof(T) == 2) __builtin_amdgcn_sched_barrier(0);        // element by element: registers
                 const bool o0 = HORZ ? row_first : (e == 0 && g.col == 0);
                 const bool o2 = HORZ ? row_last : (g.col + e == W - 1);
                 float f0 = rg_elem<T>(w0, e), f1 = rg_elem<T>(w1, e), f2 = rg_elem<T>(w2, e);
@@ -239,10 +240,11 @@ struct RaggedPass {
     }
 
     // h of the chunk from LDS: merged output, and h_save (e of the reverse sweep)
-    __device__ __forceinline__ void finish(int k) {
-        const Gran g = gran(k);
+    __device__ __forceinline__ void finish(int k, int r, const Regs& in) const {
+        const Gran g = gran(r, k);
         if (!g.on) return;
-        u32x4 u = bu, yv = by;
+        __builtin_amdgcn_sched_barrier(0);
+        u32x4 u = in.u, yv = in.y;
         if (__any(g.sh != 0)) {
             u = rg_realign<T>(u, g.sh);
             if (!a.tile && !first) yv = rg_realign<T>(yv, g.sh);
@@ -308,90 +310,124 @@ struct RaggedPass {
         }
     }
 
-    // the scan of nsub * 8 lines of the chunk; h: state of this lane's positions, pos: the first of them
-    __device__ __forceinline__ void scan(int k, int nsub, float (&h)[NV], int& parity) {
+    // The scan of nsub * 8 lines of the chunk by a scanning wave; h: state of this lane's positions.  The LDS reads of HL
+    // lines are issued while the HL lines before them are computed: one wave per SIMD scans, and nothing else hides their
+    // latency.  MEET: the line is shared with other waves, which exchange the last line every 8 steps (a line's h then goes
+    // to LDS after the meeting, when no neighbour reads lam*x there any more).
+    template <bool MEET>
+    __device__ __forceinline__ void scan(int nsub, float (&h)[NV], int& parity, int& until) const {
+        constexpr int HL = WIDE ? (NV == 1 ? 4 : NV == 2 ? 2 : 1) : (NV <= 2 ? 4 : 2);      // what the registers hold twice
+        constexpr int NB = RG_SUB / HL;
+        constexpr int NW2 = WIDE ? 1 : (NV % 2 ? NV : NV / 2);
         const int lane = threadIdx.x & 63;
-        const bool meet = parts > 1;
-        if (part >= parts) {
-            for (int s = 0; s < nsub; ++s) { request(k, s); if (meet) lds_barrier(); }
-            if (nsub < 2) request(k, 1);
-            parity ^= nsub & 1;
-            return;
-        }
-        const int pos = part * a.own[HORZ] - (meet ? RG_SUB : 0) + lane * NV;
+        const int pos = part * a.own[HORZ] - (MEET ? RG_SUB : 0) + lane * NV;
         const int own_end = min(L, (part + 1) * a.own[HORZ]);
         const bool mine = pos >= part * a.own[HORZ] && pos < own_end;      // own[] and pos are multiples of NV
+        // lanes without a position use the NV spare slots at the end of the lines (their state is kept at 0)
         const int pc = min(max(pos, 0), (L - 1) / NV * NV);
+        const bool spare = !MEET && pos >= L;
+        const int first_slot = spare ? pitch - NV : line_slot(pc);
         bool valid[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) valid[v] = pos + v >= 0 && pos + v < L;
-        const char* pa = stA + (size_t)line_slot(pc) * SB;
-        const char* pw = stW2 + (size_t)pc * 2;
-        for (int s = 0; s < nsub; ++s) {
-            request(k, s);
-            __builtin_amdgcn_sched_barrier(0);
-            float hb[RG_SUB][NV];                       // lam*x of the block's lines, then their h
-            uint32_t wa[RG_SUB][NV][WIDE ? 3 : 1], wb[RG_SUB][WIDE ? 1 : (NV + 1) / 2];
-            // all the block's LDS reads first: one latency per block (per half with two positions per lane, for registers)
+        int dv[NV];                                     // bytes from the lane's first slot to that of position v
 #pragma unroll
-            for (int half = 0; half < (NV == 2 ? 2 : 1); ++half) {
-            constexpr int HL = NV == 2 ? RG_SUB / 2 : RG_SUB;
+        for (int v = 0; v < NV; ++v) dv[v] = (NV == 3 && !HORZ && !spare) ? (line_slot(pc + v) - line_slot(pc)) * SB : v * SB;
+        struct Lines { float a[HL][NV]; uint32_t w[HL][NV][WIDE ? 3 : 1], w2[HL][NW2]; };
+        // byte offsets in LDS of the next line to read and of the next line whose h is stored: running sums, one addition per
+        // line (left to itself the compiler keeps an address per line of the block in registers and adds to each)
+        const uint32_t line_a = (uint32_t)(pitch * SB), line_w = (uint32_t)(pitch2 * 2);
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+        uint32_t ra = lds0 + (uint32_t)(stA - lds) + (uint32_t)(first_slot * SB), rw = lds0 + (uint32_t)(stW2 - lds) + (uint32_t)(pc * 2), rh = ra;
+        auto read = [&](Lines& q) {
 #pragma unroll
-            for (int jj = 0; jj < HL; ++jj) {
-                const int j = half * HL + jj;
+            for (int j = 0; j < HL; ++j) {
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
                     if constexpr (WIDE) {
-                        const u32x4 q = *(const u32x4*)(pa + (size_t)(j * pitch + v) * 16);
-                        hb[j][v] = __uint_as_float(q[0]); wa[j][v][0] = q[1]; wa[j][v][1] = q[2]; wa[j][v][2] = q[3];
+                        const u32x4 t = lds_get<u32x4>(ra + dv[v]);
+                        q.a[j][v] = __uint_as_float(t[0]); q.w[j][v][0] = t[1]; q.w[j][v][1] = t[2]; q.w[j][v][2] = t[3];
                     } else {
-                        const u32x2 q = *(const u32x2*)(pa + (size_t)(j * pitch + v) * 8);
-                        hb[j][v] = __uint_as_float(q[0]); wa[j][v][0] = q[1];
+                        const u32x2 t = lds_get<u32x2>(ra + dv[v]);
+                        q.a[j][v] = __uint_as_float(t[0]); q.w[j][v][0] = t[1];
                     }
                 }
+                ra += line_a;
+                asm volatile("" : "+v"(ra));
                 if constexpr (!WIDE) {
-                    if constexpr (NV == 1) wb[j][0] = *(const uint16_t*)(pw + (size_t)(j * pitch2) * 2);
-                    else {
 #pragma unroll
-                        for (int v = 0; v < NV; v += 2) wb[j][v / 2] = *(const uint32_t*)(pw + (size_t)(j * pitch2 + v) * 2);
+                    for (int i = 0; i < NW2; ++i) {
+                        if constexpr (NV % 2) q.w2[j][i] = lds_get<uint16_t>(rw + 2 * i);
+                        else q.w2[j][i] = lds_get<uint32_t>(rw + 4 * i);
                     }
+                    rw += line_w;
+                    asm volatile("" : "+v"(rw));
                 }
             }
-            __builtin_amdgcn_sched_barrier(0);
+        };
+        float hout[NV];                                           // h of the line, for LDS
+        auto line = [&](const Lines& q, int j) {
+            // a stretch starts with the next line: nothing is carried into it, whatever the state holds (the weights there
+            // are 0 already); a mask, not a branch: a wave alone on its SIMD pays some 16 clocks for each
+            const bool keep = --until != 0;
+            until = keep ? until : a.p.kchunk;
+            float av[NV], w0[NV], w1[NV], w2[NV];
 #pragma unroll
-            for (int jj = 0; jj < HL; ++jj) {
-                const int j = half * HL + jj;
-                float av[NV], w0[NV], w1[NV], w2[NV];
+            for (int v = 0; v < NV; ++v) {
+                av[v] = q.a[j][v];
+                if constexpr (WIDE) { w0[v] = __uint_as_float(q.w[j][v][0]); w1[v] = __uint_as_float(q.w[j][v][1]); w2[v] = __uint_as_float(q.w[j][v][2]); }
+                else { w0[v] = word_lo<T>(q.w[j][v][0]); w1[v] = word_hi<T>(q.w[j][v][0]); w2[v] = NV % 2 ? word_lo<T>(q.w2[j][v % NW2]) : (v & 1) ? word_hi<T>(q.w2[j][v / 2]) : word_lo<T>(q.w2[j][v / 2]); }
+            }
+            float hn[NV];
+            if constexpr (BWD) {
+                float q0[NV], q2[NV];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) { q0[v] = valid[v] ? w0[v] * h[v] : 0.f; q2[v] = valid[v] ? w2[v] * h[v] : 0.f; }
+                const float lin = from_lane_below(q2[NV - 1]), rin = from_lane_above(q0[0]);
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
-                    av[v] = hb[j][v];
-                    if constexpr (WIDE) { w0[v] = __uint_as_float(wa[j][v][0]); w1[v] = __uint_as_float(wa[j][v][1]); w2[v] = __uint_as_float(wa[j][v][2]); }
-                    else { w0[v] = word_lo<T>(wa[j][v][0]); w1[v] = word_hi<T>(wa[j][v][0]); w2[v] = (v & 1) ? word_hi<T>(wb[j][v / 2]) : word_lo<T>(wb[j][v / 2]); }
+                    const float lf = v == 0 ? lin : q2[v - 1], rt = v == NV - 1 ? rin : q0[v + 1];
+                    hn[v] = fmaf(w1[v], h[v], av[v]) + (lf + rt);
                 }
-                float hn[NV];
-                if constexpr (BWD) {
-                    float q0[NV], q2[NV];
+            } else {
+                const float lin = from_lane_below(h[NV - 1]), rin = from_lane_above(h[0]);
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) { q0[v] = valid[v] ? w0[v] * h[v] : 0.f; q2[v] = valid[v] ? w2[v] * h[v] : 0.f; }
-                    const float lin = from_lane_below(q2[NV - 1]), rin = from_lane_above(q0[0]);
+                for (int v = 0; v < NV; ++v) {
+                    const float lf = v == 0 ? lin : h[v - 1], rt = v == NV - 1 ? rin : h[v + 1];
+                    hn[v] = fmaf(w0[v], lf, fmaf(w1[v], h[v], fmaf(w2[v], rt, av[v])));
+                }
+            }
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        const float lf = v == 0 ? lin : q2[v - 1], rt = v == NV - 1 ? rin : q0[v + 1];
-                        hn[v] = fmaf(w1[v], h[v], av[v]) + (lf + rt);
-                    }
-                } else {
-                    const float lin = from_lane_below(h[NV - 1]), rin = from_lane_above(h[0]);
+            for (int v = 0; v < NV; ++v) { hout[v] = hn[v]; h[v] = (valid[v] && keep) ? hn[v] : 0.f; }
+        };
+        auto put = [&](const float (&hv)[NV]) {                   // h of the next line
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        const float lf = v == 0 ? lin : h[v - 1], rt = v == NV - 1 ? rin : h[v + 1];
-                        hn[v] = fmaf(w0[v], lf, fmaf(w1[v], h[v], fmaf(w2[v], rt, av[v])));
+            for (int v = 0; v < NV; ++v) lds_set<float>(rh + dv[v], hv[v]);
+            rh += line_a;
+            asm volatile("" : "+v"(rh));
+        };
+        Lines buf[2];
+        read(buf[0]);
+        for (int s = 0; s < nsub; ++s) {
+            float hb[MEET ? RG_SUB : 1][NV];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                static_assert(NB % 2 == 0, "the two line sets alternate");
+                if (i + 1 < NB || s + 1 < nsub) read(buf[(i + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < HL; ++j) {
+                    line(buf[i & 1], j);
+                    if constexpr (MEET) {
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) hb[i * HL + j][v] = hout[v];
+                    } else {
+                        put(hout);
                     }
                 }
-#pragma unroll
-                for (int v = 0; v < NV; ++v) { h[v] = valid[v] ? hn[v] : 0.f; hb[j][v] = h[v]; }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            }
-            if (meet) {
+            if constexpr (MEET) {
                 float* el = edge + (parity ? pitch2 : 0);
                 if (mine) {
 #pragma unroll
@@ -401,17 +437,14 @@ struct RaggedPass {
 #pragma unroll
                 for (int v = 0; v < NV; ++v) { const float t = el[pc + v]; h[v] = valid[v] ? t : 0.f; }
                 parity ^= 1;
-            }
-            if (mine) {
+                if (mine) {
 #pragma unroll
-                for (int j = 0; j < RG_SUB; ++j)
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) *(float*)(pa + (size_t)(j * pitch + v) * SB) = hb[j][v];
+                    for (int j = 0; j < RG_SUB; ++j) put(hb[j]);
+                } else {
+                    rh += RG_SUB * line_a;
+                }
             }
-            pa += (size_t)RG_SUB * pitch * SB;
-            pw += (size_t)RG_SUB * pitch2 * 2;
         }
-        if (nsub < 2) request(k, 1);
     }
 
     __device__ __forceinline__ void run(int d_first, int dcount_, bool first_) {
@@ -423,13 +456,13 @@ struct RaggedPass {
         const int per = dcount == 2 ? nwaves / 2 : nwaves;       // waves of a direction
         dsel = w >= per ? 1 : 0;
         part = w - dsel * per;
-        nthr = per * 64;
-        tid = threadIdx.x - dsel * nthr;
         d = d_first + dsel;
         rev = BWD ? !(d & 1) : (d & 1);
         H = p.H; W = p.W; HW = H * W;
         S = HORZ ? (W + E - 1) / E * E : H; L = HORZ ? H : W;
         K = a.K[ax]; pitch = a.pitch[ax]; pitch2 = a.pitch2[ax]; parts = a.parts[ax];
+        nthr = (per - parts) * 64;                               // the first `parts` waves of a direction scan, the others load
+        tid = (int)threadIdx.x - (dsel * per + parts) * 64;
         const size_t planes = (size_t)p.B * p.C, groups = (size_t)p.B * p.G;
         const size_t pc = (size_t)plane * HW;
         const size_t slot_c = p.shared ? 0 : (size_t)d * planes * HW;
@@ -448,27 +481,61 @@ struct RaggedPass {
         tile = (float*)(lds + a.tile_off);
 
         nchunks = (S + K - 1) / K;
-        float h[NV];
+        auto subs = [&](int k) { return (min(K, S - k * K) + RG_SUB - 1) / RG_SUB; };
+        // both directions add to the same rows / columns of the tile while their chunks cross
+        auto cross = [&](int k) { return dcount == 2 && 2 * (k + 1) * K > S && 2 * k * K < S; };
+        if (part < parts) {
+            __builtin_amdgcn_s_setprio(3);                       // the chain the others wait for
+            float h[NV];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) h[v] = 0.f;
-        int parity = 0;
-        load(0);
-        stage(0);
-        lds_barrier();
-        for (int k = 0; k < nchunks; ++k) {
-            scan(k, (min(K, S - k * K) + RG_SUB - 1) / RG_SUB, h, parity);
+            for (int v = 0; v < NV; ++v) h[v] = 0.f;
+            int parity = 0;
+            // scan steps to the next stretch: cuts lie before image lines 0, kchunk, 2 * kchunk, ..
+            int until = 1 << 30;
+            if (a.p.kchunk > 0) until = rev && S % a.p.kchunk ? S % a.p.kchunk : a.p.kchunk;
             lds_barrier();
-            // both directions add to the same rows / columns of the tile while their chunks cross
-            const bool cross = dcount == 2 && 2 * (k + 1) * K > S && 2 * k * K < S;
-            if (cross) {
-                if (dsel == 0) finish(k);
+            for (int k = 0; k < nchunks; ++k) {
+                if (NV % 2 == 0 && parts > 1) scan<NV % 2 == 0>(subs(k), h, parity, until);      // (lines of one or three positions per lane are one wave's)
+                else scan<false>(subs(k), h, parity, until);
                 lds_barrier();
-                if (dsel == 1) finish(k);
-            } else {
-                finish(k);
+                if (cross(k)) lds_barrier();
+                lds_barrier();
             }
-            if (k + 1 < nchunks) stage(k + 1);
+            __builtin_amdgcn_s_setprio(0);
+        } else {
+            Regs q[RG_ROUNDS];
+            const int gr = HORZ ? (K / E) * H : K * ((W + E - 1) / E);
+            const bool two = gr > nthr;                         // a second granule per thread
+            load(0, 0, q[0]);
+            if (two) load(0, 1, q[1]);
+            stage(0, 0, q[0]);
+            if (two) stage(0, 1, q[1]);
             lds_barrier();
+            for (int k = 0; k < nchunks; ++k) {
+                load_late(k, 0, q[0]);
+                if (two) load_late(k, 1, q[1]);
+                if (k + 1 < nchunks) {
+                    load(k + 1, 0, q[0]);
+                    if (two) load(k + 1, 1, q[1]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (parts > 1) for (int s = subs(k); s > 0; --s) lds_barrier();
+                lds_barrier();
+                if (cross(k)) {
+                    if (dsel == 1) lds_barrier();
+                    finish(k, 0, q[0]);
+                    if (two) finish(k, 1, q[1]);
+                    if (dsel == 0) lds_barrier();
+                } else {
+                    finish(k, 0, q[0]);
+                    if (two) finish(k, 1, q[1]);
+                }
+                if (k + 1 < nchunks) {
+                    stage(k + 1, 0, q[0]);
+                    if (two) stage(k + 1, 1, q[1]);
+                }
+                lds_barrier();
+            }
         }
     }
 };
@@ -536,7 +603,8 @@ __global__ void __launch_bounds__(1024) ragged_kernel(RaggedArgs a) {
 template <typename T, int MODE, bool LOGITS>
 hipError_t launch_ragged_one(const RaggedArgs& a, int threads, int nv, size_t lds, hipStream_t s) {
     const dim3 grid((unsigned)((size_t)a.p.B * a.p.C)), block(threads);
-    void (*k)(RaggedArgs) = nv == 1 ? ragged_kernel<T, MODE, LOGITS, 1> : ragged_kernel<T, MODE, LOGITS, 2>;
+    void (*k)(RaggedArgs) = nv == 1 ? ragged_kernel<T, MODE, LOGITS, 1> : nv == 2 ? ragged_kernel<T, MODE, LOGITS, 2>
+                                    : nv == 3 ? ragged_kernel<T, MODE, LOGITS, 3> : ragged_kernel<T, MODE, LOGITS, 4>;
     const hipError_t e = allow_dynamic_lds((const void*)k, 160 * 1024);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, grid, block, lds, s, a);

@@ -86,3 +86,32 @@ def test_against_the_line_by_line_kernels(seed, monkeypatch):
             e = _rel(torch.where(na, torch.zeros_like(a), a), torch.where(nb, torch.zeros_like(b), b))
             assert e <= tol, (case, n, e)
             assert torch.equal(fast[n].view(torch.uint8), again[n].view(torch.uint8)), (case, n, "not the same twice")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,kchunk", [((1, 2, 29, 41, 1), 8), ((1, 2, 100, 167, 2), 24), ((1, 1, 30, 205, 1), 7)],
+                         ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+def test_what_is_not_finite_stays_in_its_stretch(shape, kchunk, dtype, monkeypatch):
+    """A NaN and an infinity in x and gy: the same elements of every output are finite as on the line-by-line kernels, which
+    read nothing across a cut."""
+    import torch
+    import paper_2512_07884_amd as G
+    from paper_2512_07884_amd import binding
+    from test_gpu_differential import _run
+    G.binding = binding
+    B, C, H, W, Gr = shape
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda"); g.manual_seed(5)
+    w = torch.softmax(torch.randn((4, B, Gr, 3, H, W), generator=g, device="cuda"), dim=3).to(td)
+    inp = {"x": torch.randn((B, C, H, W), generator=g, device="cuda").to(td), "w": w,
+           "lam": torch.rand((4, B, C, H, W), generator=g, device="cuda").to(td),
+           "u": torch.rand((4, B, C, H, W), generator=g, device="cuda").to(td),
+           "gy": torch.randn((B, C, H, W), generator=g, device="cuda").to(td)}
+    inp["x"][0, 0, H // 2, W // 2] = float("nan"); inp["x"][0, 0, 0, W - 1] = float("inf")
+    inp["gy"][0, C - 1, H - 1, 0] = float("nan"); inp["gy"][0, C - 1, H // 3, W // 3] = float("-inf")
+    fast = _run(G, inp, Gr, 15, kchunk, False)
+    monkeypatch.setenv("GSPN_FORCE_GENERIC", "1")
+    ref = _run(G, inp, Gr, 15, kchunk, False)
+    monkeypatch.delenv("GSPN_FORCE_GENERIC", raising=False)
+    for n in fast:
+        assert torch.equal(torch.isfinite(fast[n].float()), torch.isfinite(ref[n].float())), n
