@@ -378,23 +378,28 @@ struct RaggedPass {
                 if constexpr (WIDE) { w0[v] = __uint_as_float(q.w[j][v][0]); w1[v] = __uint_as_float(q.w[j][v][1]); w2[v] = __uint_as_float(q.w[j][v][2]); }
                 else { w0[v] = word_lo<T>(q.w[j][v][0]); w1[v] = word_hi<T>(q.w[j][v][0]); w2[v] = NV % 2 ? word_lo<T>(q.w2[j][v % NW2]) : (v & 1) ? word_hi<T>(q.w2[j][v / 2]) : word_lo<T>(q.w2[j][v / 2]); }
             }
+            // one chain of FMAs per position in the line-by-line kernels' order -- own tap, the neighbour before, the neighbour
+            // after -- so that the states are theirs bit for bit (products of the reverse sweep summed in pairs instead: glam of
+            // fp32 maps 9 % further from 64 bits in the mean, up to 2.4 times)
             float hn[NV];
             if constexpr (BWD) {
-                float q0[NV], q2[NV];
+                // (a lane's positions beyond the line come after those inside, or are all of its positions: their taps are read as 0)
 #pragma unroll
-                for (int v = 0; v < NV; ++v) { q0[v] = valid[v] ? w0[v] * h[v] : 0.f; q2[v] = valid[v] ? w2[v] * h[v] : 0.f; }
-                const float lin = from_lane_below(q2[NV - 1]), rin = from_lane_above(q0[0]);
+                for (int v = 0; v < NV; ++v) hn[v] = fmaf(w1[v], h[v], av[v]);
+                const float lt = from_lane_below(valid[NV - 1] ? w2[NV - 1] : 0.f), lh = from_lane_below(h[NV - 1]);
 #pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const float lf = v == 0 ? lin : q2[v - 1], rt = v == NV - 1 ? rin : q0[v + 1];
-                    hn[v] = fmaf(w1[v], h[v], av[v]) + (lf + rt);
-                }
+                for (int v = 0; v < NV; ++v) hn[v] = fmaf(v == 0 ? lt : w2[v - 1], v == 0 ? lh : h[v - 1], hn[v]);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) w0[v] = valid[v] ? w0[v] : 0.f;
+                const float rt = from_lane_above(w0[0]), rh_ = from_lane_above(h[0]);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) hn[v] = fmaf(v == NV - 1 ? rt : w0[v + 1], v == NV - 1 ? rh_ : h[v + 1], hn[v]);
             } else {
                 const float lin = from_lane_below(h[NV - 1]), rin = from_lane_above(h[0]);
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
                     const float lf = v == 0 ? lin : h[v - 1], rt = v == NV - 1 ? rin : h[v + 1];
-                    hn[v] = fmaf(w0[v], lf, fmaf(w1[v], h[v], fmaf(w2[v], rt, av[v])));
+                    hn[v] = fmaf(w2[v], rt, fmaf(w0[v], lf, fmaf(w1[v], h[v], av[v])));
                 }
             }
 #pragma unroll
