@@ -78,8 +78,9 @@ template <typename T> __device__ __forceinline__ f32x4_t mfma16_k32(const u32x4&
 // the projection w.r.t. its input): a lane then gathers its KS/2 values of P with 2-byte loads a row apart (P is small
 // and stays in cache).
 // SPLIT = 1: a wave owns 32 rows x 256 pixels.  SPLIT = 4: a workgroup owns 32 rows x 128 pixels, its waves every fourth
-// k-step (1152 -> 144 on two 64x64 images 58 -> 18 us).  ANY: rows of `in` / `out` start at any element.
-template <typename T, int KS, bool PT, int SPLIT, bool ANY>
+// k-step (1152 -> 144 on two 64x64 images 58 -> 18 us).  ANY: rows of `in` / `out` start at any element.  BUF: buffer
+// requests and stores with 32-bit offsets; lanes beyond the row request nothing.
+template <typename T, int KS, bool PT, int SPLIT, bool ANY, bool BUF>
 __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ in, const T* __restrict__ P,
                                                          T* __restrict__ out, int B, int K, int M, int N,
                                                          int ntiles, int mtiles) {
@@ -105,7 +106,9 @@ __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ i
     const int m_lane = mt * 32 + jl;                           // row of P this lane feeds as the A operand
     const bool m_ok = m_lane < M;
 
+    static_assert(!BUF || (SPLIT == 1 && !ANY), "buffer requests: whole rows, a wave per tile");
     const T* src = in + (size_t)b * K * N + n_lane;
+    const rsrc_t inb = make_rsrc(in + (size_t)b * K * N), ob = make_rsrc(out + (size_t)b * M * N);
     const rsrc_t pb = make_rsrc(P);
     f32x16_t acc[PX];
 #pragma unroll
@@ -117,7 +120,15 @@ __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ i
     auto fetch = [&](int k0, Step& t) {
         const int kr = k0 + KL * kh;
 #pragma unroll
-        for (int kk = 0; kk < KL; ++kk) ld_row<T, NB, ANY>(src + (size_t)(kr + kk) * N, t.q[kk]);      // (spare lanes: pixel 0)
+        for (int kk = 0; kk < KL; ++kk) {
+            if constexpr (BUF) {
+                u32x4 v = {0, 0, 0, 0};
+                if (n_ok) v = __builtin_amdgcn_raw_buffer_load_b128(inb, (uint32_t)(((size_t)(kr + kk) * N + n_lane) * 2), 0, 0);
+                t.q[kk][0] = v.x; t.q[kk][1] = v.y; t.q[kk][2] = v.z; t.q[kk][3] = v.w;
+            } else {
+                ld_row<T, NB, ANY>(src + (size_t)(kr + kk) * N, t.q[kk]);      // (spare lanes: pixel 0)
+            }
+        }
 #pragma unroll
         for (int i = 0; i < KL / 2; ++i) t.pa[i] = 0;
         if (m_ok && PT) {
@@ -187,7 +198,8 @@ __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ i
             if (m < M) {
                 const uint32_t o[4] = {pack_word<T>(acc[0][r], acc[1][r]), pack_word<T>(acc[2][r], acc[3][r]),
                                        pack_word<T>(acc[4][r], acc[5][r]), pack_word<T>(acc[6][r], acc[7][r])};
-                st_row<T, NB, ANY>(dst + (size_t)m * N, o);
+                if constexpr (BUF) st_b128(ob, (uint32_t)(((size_t)m * N + n_lane) * 2), u32x4{o[0], o[1], o[2], o[3]});
+                else st_row<T, NB, ANY>(dst + (size_t)m * N, o);
             }
         }
     } else {
@@ -452,11 +464,18 @@ static hipError_t launch_project_mfma(const void* in, const void* P, void* out, 
     const int ntiles = (N + tile - 1) / tile, mtiles = (M + 31) / 32;
     const long items = (long)B * ntiles * mtiles, blocks = SPLIT == 1 ? (items + 3) / 4 : items;
     if (blocks > 0x7fffffffl) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(256);
-    if (N % 8 == 0)
-        hipLaunchKernelGGL((proxy_mfma_kernel<T, KS, PT, SPLIT, false>), grid, block, 0, s, (const T*)in, (const T*)P, (T*)out, B, K, M, N, ntiles, mtiles);
-    else
-        hipLaunchKernelGGL((proxy_mfma_kernel<T, KS, PT, SPLIT, true>), grid, block, 0, s, (const T*)in, (const T*)P, (T*)out, B, K, M, N, ntiles, mtiles);
+    void (*k)(const T*, const T*, T*, int, int, int, int, int, int);
+    if (N % 8 != 0) k = proxy_mfma_kernel<T, KS, PT, SPLIT, true, false>;
+    else k = proxy_mfma_kernel<T, KS, PT, SPLIT, false, false>;
+    if constexpr (SPLIT == 1) {
+        // Whole rows: buffer requests for P^T (with global ones 18 -> 20 us at 24 -> 1152 channels on two 128x128 images), for
+        // steps of 8 (8 -> 1152 there 14.6 -> 15.8) and for chains of 24 and more steps (384 -> 288 on 32 images 56x56: 56.5 ->
+        // 59.0); global ones for the other forward calls (288 -> 1152 on four 64x64 images 36.4 -> 31.4, 192 -> 144 on eight
+        // 56x56 13.5 -> 10.1) and where an image's offsets pass 32 bits.
+        const bool fits = (size_t)K * N * 2 < (1ull << 31) && (size_t)M * N * 2 < (1ull << 31);
+        if (N % 8 == 0 && fits && (PT || KS == 8 || K >= 24 * KS)) k = proxy_mfma_kernel<T, KS, PT, 1, false, true>;
+    }
+    hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, s, (const T*)in, (const T*)P, (T*)out, B, K, M, N, ntiles, mtiles);
     return hipGetLastError();
 }
 
@@ -465,11 +484,15 @@ template <typename T, bool PT>
 static hipError_t launch_project_as(const void* in, const void* P, void* out, int B, int K, int M, int N, bool mfma, hipStream_t s) {
     if constexpr (sizeof(T) == 2) {
         if (mfma) {
-            // the waves of a workgroup share the k-steps where one wave per tile would leave the chip with fewer than four
-            // waves per CU and a chain of sixteen and more steps (two 64x64 images, 1152 -> 144: 58 -> 18 us; with 9 steps,
-            // 144 -> 1152, sharing them costs more than it saves: 14 -> 22 us)
+            // The waves of a workgroup share the k-steps where one wave per tile would leave the chip short of waves and the
+            // chain is long: the longer the chain, the more waves that takes.  Measured, plain -> shared: 1152 -> 144 on two
+            // 64x64 images (160 waves, 72 steps) 58 -> 18 us; 288 -> 384 on eight 28x28 (384 waves, 18 steps) 15.0 -> 11.4; 384
+            // -> 24 on eight 128x128 (512 waves, 24 steps) 30.7 -> 23.7; 1152 -> 288 on four 64x64 (576, 72) 61 -> 45.  Beyond
+            // the lines sharing loses: 288 -> 768 on 32 images 14x14 (768, 18) 16.7 -> 22.7; 288 -> 768 on one 96x96 (864, 18)
+            // 19 -> 25; 768 -> 96 on 32 images 64x64 (1536, 48) 56 -> 65; 144 -> 192 on eight 56x56 (624, 9) 11 -> 15.
             const long waves = (long)B * ((N + 255) / 256) * ((M + 31) / 32);
-            const bool split = waves < 1024 && K >= 16 * (K % 16 == 0 ? 16 : 8);
+            const int steps = K / (K % 16 == 0 ? 16 : 8);
+            const bool split = (waves <= 448 && steps >= 16) || (waves <= 640 && steps >= 24) || (waves < 1024 && steps >= 48);
             if (K % 16 == 0) return split ? launch_project_mfma<T, 16, PT, 4>(in, P, out, B, K, M, N, s) : launch_project_mfma<T, 16, PT, 1>(in, P, out, B, K, M, N, s);
             return split ? launch_project_mfma<T, 8, PT, 4>(in, P, out, B, K, M, N, s) : launch_project_mfma<T, 8, PT, 1>(in, P, out, B, K, M, N, s);
         }

@@ -35,6 +35,16 @@ def test_projection_and_gradients(shape, dtype):
     assert np.array_equal(gin, gin2) and np.array_equal(gP, gP2)
 
 
+# Whole rows at the lines of the dispatch: k-steps shared by the waves up to 448 waves from 16 steps on, up to 640 from 24 and
+# up to 1023 from 48 (either side of each); buffer requests for P^T, for steps of 8 and for chains of 24 steps on more waves
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", [(14, 256, 1024, 3, 8), (15, 256, 1024, 3, 8), (3, 240, 40, 5, 8), (20, 384, 1024, 2, 4), (21, 384, 1024, 2, 4),
+                                   (31, 768, 1024, 1, 8), (32, 768, 1024, 1, 8), (5, 136, 40, 9, 8), (2, 1024, 24, 16, 33)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_whole_rows_at_the_lines_of_the_dispatch(shape, dtype):
+    test_projection_and_gradients(shape, dtype)
+
+
 @pytest.mark.parametrize("K,H,W", [(64, 16, 24), (1152, 16, 24), (64, 13, 7), (72, 11, 13), (1152, 5, 29)])
 def test_selection_matrix_copies(K, H, W):
     rng = np.random.default_rng(31)
