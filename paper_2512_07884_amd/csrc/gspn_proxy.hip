@@ -259,8 +259,10 @@ __global__ void __launch_bounds__(256) proxy_fma_kernel(const T* __restrict__ in
 // LDS in wave order; the per-image sums go to the caller's workspace and a small kernel adds the images in order, so the
 // result does not depend on scheduling.  NW = 8 where four waves per tile would leave the chip short of loads in flight.
 // KT = 2: a tile of 32 x 64, whose rows of gout feed two products (operand rows read from the caches: 96 per 2048 elements
-// of gP against 128), where the call has enough tiles.  ANY: rows start at any element; N any: the step that crosses the end
-// of the rows takes the last eight pixels and moves them down, zeros behind them.
+// of gP against 128).  Whole rows: buffer requests, rows past the end request nothing.  ANY: rows start at any element; a
+// wave takes four neighbouring steps (whole 128-byte lines of the rows) and the step that crosses the end of the rows takes
+// the last eight pixels and moves them down, zeros behind them.  (Neighbouring steps and global requests on whole rows were
+// measured slower: 1152 -> 288 on four 96x96 images 171 -> 185 us.)
 template <typename T, int NW, int KT, bool ANY>
 __global__ void __launch_bounds__(64 * NW) proxy_gradw_mfma_kernel(const T* __restrict__ gout, const T* __restrict__ in,
                                                                float* __restrict__ partial, int K, int M, int N,
@@ -273,32 +275,41 @@ __global__ void __launch_bounds__(64 * NW) proxy_gradw_mfma_kernel(const T* __re
     const int rem = blockIdx.x - b * per_image;
     const int mt = rem / ktiles, kt = rem - mt * ktiles;
     const int jl = lane & 31, nh = lane >> 5;                  // row of the operand this lane feeds; which 8 of the 16 pixels
-    const int m_lane = mt * 32 + jl;
-    // rows past the end are read as the last row (their sums are not stored)
+    const int m_lane = mt * 32 + jl, k_lane = kt * 32 * KT + jl;
+    const rsrc_t gb = make_rsrc(gout + ((size_t)b * M + mt * 32) * N);           // the tile's rows of gout / of in
+    const rsrc_t xb = make_rsrc(in + ((size_t)b * K + kt * 32 * KT) * N);
+    const uint32_t row_off = (uint32_t)((size_t)jl * N * 2);
+    // (ANY: rows past the end are read as the last row, their sums are not stored)
     const T* ga = gout + ((size_t)b * M + min(m_lane, M - 1)) * N;
     const T* ib[KT];
 #pragma unroll
-    for (int t = 0; t < KT; ++t) ib[t] = in + ((size_t)b * K + min(kt * 32 * KT + 32 * t + jl, K - 1)) * N;
+    for (int t = 0; t < KT; ++t) ib[t] = in + ((size_t)b * K + min(k_lane + 32 * t, K - 1)) * N;
     f32x16_t acc[KT];
 #pragma unroll
     for (int t = 0; t < KT; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-    // four neighbouring 16-pixel steps per trip: their loads are requested together and cover whole 128-byte lines of the rows
-    // (steps past the end load nothing and multiply zeros)
-    for (int n0 = wave * 64; n0 < N; n0 += 64 * NW) {
+    // four 16-pixel steps per trip: their loads are requested together (steps past the end load nothing and multiply zeros)
+    constexpr int HOP = ANY ? 16 : 16 * NW;
+    for (int n0 = wave * (ANY ? 64 : 16); n0 < N; n0 += 64 * NW) {
         u32x4 av[4], bv[KT][4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int n = n0 + 16 * q + 8 * nh;
+            const int n = n0 + HOP * q + 8 * nh;
             av[q] = u32x4{0, 0, 0, 0};
 #pragma unroll
             for (int t = 0; t < KT; ++t) bv[t][q] = u32x4{0, 0, 0, 0};
-            if (n < N) {
-                const int nl = ANY ? min(n, N - 8) : n;
-                ld_row<T, 16, ANY>(ga + nl, (uint32_t*)&av[q]);
+            if constexpr (!ANY) {
+                const uint32_t off = row_off + (uint32_t)(n * 2);
+                if (m_lane < M && n < N) av[q] = __builtin_amdgcn_raw_buffer_load_b128(gb, off, 0, 0);
 #pragma unroll
-                for (int t = 0; t < KT; ++t) ld_row<T, 16, ANY>(ib[t] + nl, (uint32_t*)&bv[t][q]);
+                for (int t = 0; t < KT; ++t)
+                    if (k_lane + 32 * t < K && n < N) bv[t][q] = __builtin_amdgcn_raw_buffer_load_b128(xb, off + (uint32_t)(64 * t) * (uint32_t)N, 0, 0);
+            } else if (n < N) {
+                const int nl = min(n, N - 8);
+                ld_row<T, 16, true>(ga + nl, (uint32_t*)&av[q]);
+#pragma unroll
+                for (int t = 0; t < KT; ++t) ld_row<T, 16, true>(ib[t] + nl, (uint32_t*)&bv[t][q]);
             }
         }
         if (ANY && n0 + 64 > N) {                              // the end of the rows (a uniform branch)
@@ -516,29 +527,38 @@ hipError_t launch_proxy_project(const void* in, const void* P, void* out, int B,
 template <typename T>
 static hipError_t launch_gradw_as(const void* gout, const void* in, float* partial, int B, int K, int M, int N, hipStream_t s) {
     const bool mfma = sizeof(T) == 2 && N >= 8;
+    const int mtiles = mfma ? (M + 31) / 32 : (M + 7) / 8;
+    int ktiles = (K + 31) / 32;
+    const long tiles = (long)B * mtiles * ktiles;
     if constexpr (sizeof(T) == 2) {
-        if (mfma && (long)B * ((M + 31) / 32) * ((K + 31) / 32) < 64 && N >= 512) {
+        // 16 x 16 tiles where 32 x 32 ones are fewer than a quarter of the CUs and the rows are long (two images, 32 x 32 -> 16 x
+        // 16: 8 <- 96 channels on 96x96 26.8 -> 17.0 us; below 4096 pixels no gain in the mean and up to 7 % lost: 48 <- 96 on
+        // 56x56 16.1 -> 17.2.  Rows at any element: 0.94 of the time in the mean from 1024 pixels on)
+        if (mfma && tiles < 64 && N >= (N % 8 ? 1024 : 4096)) {
             const int mt = (M + 15) / 16, kt = (K + 15) / 16;
             void (*k)(const T*, const T*, float*, int, int, int, int, int) = N % 8 ? proxy_gradw_small_kernel<T, true> : proxy_gradw_small_kernel<T, false>;
             hipLaunchKernelGGL(k, dim3((unsigned)((long)B * mt * kt)), dim3(1024), 0, s, (const T*)gout, (const T*)in, partial, K, M, N, mt, kt);
             return hipGetLastError();
         }
     }
-    const int mtiles = mfma ? (M + 31) / 32 : (M + 7) / 8;
-    // 32 x 64 tiles from one per CU on (fewer, larger tiles would leave CUs idle)
-    const bool pair = mfma && (long)B * mtiles * ((K + 31) / 32) >= 256;
-    const int ktiles = pair ? (K + 63) / 64 : (K + 31) / 32;
+    // 32 x 64 tiles where rows are long, both sides have two tiles to share and the workgroups come out even: all of them at once
+    // instead of a second, partly empty, turn of single tiles, or enough of them (single -> double: 1152 x 144 on two 64x64
+    // images, 360 tiles, 34.5 -> 30.4 us; 96 x 384 on sixteen, 576 tiles, 61 -> 51; 288 x 1152 on four, 1296 tiles, 107 -> 77;
+    // but 144 x 768 on four, 480 tiles in 288 pairs, 37 -> 51; one row tile, 1152 x 8 on sixteen 56x56, 31 -> 35; short rows,
+    // 96 x 768 on 32 images 16x16, 16.2 -> 18.9)
+    const long pairs = (long)B * mtiles * ((ktiles + 1) / 2);
+    const bool pair = mfma && N >= 2048 && mtiles > 1 && ktiles > 1 && tiles > 256 && (pairs <= 256 || tiles >= 576);
+    if (pair) ktiles = (K + 63) / 64;
     const long blocks = (long)B * mtiles * ktiles;
     if (blocks > 0x7fffffffl) return hipErrorInvalidValue;
-    const bool wide = blocks * 4 < 2048;     // eight waves per tile while four would leave a compute unit under eight
+    const bool wide = pair || blocks * 4 < 2048;     // eight waves per tile while four would leave a compute unit under eight
     if constexpr (sizeof(T) == 2) {
         if (mfma) {
-            const bool any = N % 8 != 0;
+            const bool any = N % 8 != 0 || (size_t)N * 2 * 64 >= (1ull << 31);         // (whole rows: 32-bit offsets within a tile's rows)
             void (*k)(const T*, const T*, float*, int, int, int, int, int) =
-                pair ? (wide ? (any ? proxy_gradw_mfma_kernel<T, 8, 2, true> : proxy_gradw_mfma_kernel<T, 8, 2, false>)
-                             : (any ? proxy_gradw_mfma_kernel<T, 4, 2, true> : proxy_gradw_mfma_kernel<T, 4, 2, false>))
-                     : (wide ? (any ? proxy_gradw_mfma_kernel<T, 8, 1, true> : proxy_gradw_mfma_kernel<T, 8, 1, false>)
-                             : (any ? proxy_gradw_mfma_kernel<T, 4, 1, true> : proxy_gradw_mfma_kernel<T, 4, 1, false>));
+                pair ? (any ? proxy_gradw_mfma_kernel<T, 8, 2, true> : proxy_gradw_mfma_kernel<T, 8, 2, false>)
+              : wide ? (any ? proxy_gradw_mfma_kernel<T, 8, 1, true> : proxy_gradw_mfma_kernel<T, 8, 1, false>)
+                     : (any ? proxy_gradw_mfma_kernel<T, 4, 1, true> : proxy_gradw_mfma_kernel<T, 4, 1, false>);
             hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(wide ? 512 : 256), 0, s, (const T*)gout, (const T*)in, partial, K, M, N, mtiles, ktiles);
             return hipGetLastError();
         }

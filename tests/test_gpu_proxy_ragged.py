@@ -45,6 +45,17 @@ def test_whole_rows_at_the_lines_of_the_dispatch(shape, dtype):
     test_projection_and_gradients(shape, dtype)
 
 
+# The weight gradient at the lines of its dispatch: 16 x 16 tiles from 4096 pixels on (1024 where rows start anywhere), 32 x 64
+# tiles with ragged rows and columns in one turn of workgroups and in several, the same sizes just short of 2048 pixels, whole
+# rows of half a 16-pixel step
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", [(1, 56, 40, 64, 64), (1, 56, 40, 64, 63), (1, 56, 40, 25, 41), (1, 56, 40, 31, 33), (9, 104, 232, 8, 256),
+                                   (9, 104, 232, 8, 255), (9, 104, 232, 7, 293), (18, 72, 232, 16, 129), (2, 40, 24, 3, 8)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_weight_gradient_at_the_lines_of_the_dispatch(shape, dtype):
+    test_projection_and_gradients(shape, dtype)
+
+
 @pytest.mark.parametrize("K,H,W", [(64, 16, 24), (1152, 16, 24), (64, 13, 7), (72, 11, 13), (1152, 5, 29)])
 def test_selection_matrix_copies(K, H, W):
     rng = np.random.default_rng(31)
