@@ -196,6 +196,8 @@ hipError_t launch_fwd_ragged(const FwdParams& p, int dtype, hipStream_t s);
 bool ragged_applicable(const FwdParams& p, int dtype);
 hipError_t launch_bwd_ragged(const BwdParams& p, int dtype, hipStream_t s);
 bool ragged_bwd_applicable(const BwdParams& p, int dtype);
+int ragged_fwd_threads(const FwdParams& p, int dtype);        // threads per workgroup, 0: not taken
+int ragged_bwd_threads(const BwdParams& p, int dtype);
 hipError_t launch_fwd_tile(const FwdParams& p, int dtype, hipStream_t s);
 bool fwd_tile_applicable(const FwdParams& p, int dtype);
 hipError_t launch_fwd_plane(const FwdParams& p, int dtype, hipStream_t s);

@@ -128,3 +128,17 @@ const char* bwd_plan_name(const BwdParams& p, int dtype) {
 }
 
 }  // namespace gspn
+
+// For the tests, not part of the ABI: threads per workgroup of the any-size kernel for a call whose plan is "generic" (both its
+// kernels have that name), 0 where the line-by-line kernels take it or the plan is another.  kchunk 0: the global scan.
+extern "C" int gspn_any_size_threads(int B, int C, int H, int W, int G, int kchunk, int logits, unsigned mask, int dtype, int backward) {
+    using namespace gspn;
+    if (backward) {
+        BwdParams p = {};
+        p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
+        return choose_bwd(p, dtype) == BWD_GENERIC && !knobs().force_generic ? ragged_bwd_threads(p, dtype) : 0;
+    }
+    FwdParams p = {};
+    p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
+    return choose_fwd(p, dtype) == FWD_GENERIC && !knobs().force_generic ? ragged_fwd_threads(p, dtype) : 0;
+}

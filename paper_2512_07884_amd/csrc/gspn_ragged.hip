@@ -102,13 +102,29 @@ bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* o
     return false;
 }
 
-static bool ragged_fits(const FwdParams& p, int dtype, bool merge_rounds) {
+// threads per workgroup of a call, 0 where no launch shape fits
+static int ragged_threads(const FwdParams& p, int dtype, bool merge_rounds) {
     RaggedArgs a;
     int threads, nv;
     size_t lds;
-    return ragged_plan(p, dtype, merge_rounds, &a, &threads, &nv, &lds);
+    return ragged_plan(p, dtype, merge_rounds, &a, &threads, &nv, &lds) ? threads : 0;
 }
-bool ragged_applicable(const FwdParams& p, int dtype) { return ragged_fits(p, dtype, false); }
+static int lines_walked(unsigned mask, int H, int W) {
+    return (int)((mask & 1u) + ((mask >> 1) & 1u)) * H + (int)(((mask >> 2) & 1u) + ((mask >> 3) & 1u)) * W;
+}
+
+// Calls of few scan steps, and of many planes of a few pixels, stay with the line-by-line kernels: a pass here loads, turns and
+// scans eight lines whatever there are, and its LDS lets a CU hold eight planes at most where theirs holds up to 32.  Measured on
+// 1500 random calls of up to 900 steps, line by line -> here: 1712 planes 3x251, top to bottom only, 12 -> 45 us; 35488 planes
+// 82x4, left to right, 73 -> 188; 5215 planes 4x7, three directions, 20 -> 42; 4128 planes 18x1, all four, 30 -> 43; 18160
+// planes 6x11, all four, 128 -> 134.
+// Beyond the lines: 664 planes 16x301, top to bottom, 40 -> 29; 4314 planes 124x17, right to left, 225 -> 67.
+int ragged_fwd_threads(const FwdParams& p, int dtype) {
+    const long long steps = lines_walked(p.mask, p.H, p.W), HW = (long long)p.H * p.W, planes = (long long)p.B * p.C;
+    if (steps <= 12 || steps * HW <= 480 || (steps * HW <= 1000 && planes > 2048) || (steps * HW <= 3400 && planes * HW > 100000)) return 0;
+    return ragged_threads(p, dtype, false);
+}
+bool ragged_applicable(const FwdParams& p, int dtype) { return ragged_fwd_threads(p, dtype) != 0; }
 
 hipError_t launch_fwd_ragged(const FwdParams& p, int dtype, hipStream_t s) {
     return dtype == 0 ? launch_ragged_f32(p, false, nullptr, s) : dtype == 1 ? launch_ragged_bf16(p, false, nullptr, s) : launch_ragged_f16(p, false, nullptr, s);
@@ -309,9 +325,16 @@ unsigned long long ragged_finish_blocks(const BwdParams& p, int dtype) {
 
 }  // namespace
 
-bool ragged_bwd_applicable(const BwdParams& p, int dtype) {
-    return ragged_fits(ragged_sweep_params(p), dtype, true) && ragged_finish_blocks(p, dtype) <= 0x7fffffffull;
+// As for the forward call, with two launches here; line by line a workgroup takes a whole weight group, so more channels per
+// group draw the line nearer.  Line by line -> here: 1712 planes 3x251, 16 per group, top to bottom, 39 -> 70 us; 35488 planes
+// 82x4, left to right, 148 -> 284; 5215 planes 4x7, one per group, three directions, 44 -> 60.  Beyond the lines: 107 planes
+// 14x95, one per group, top to bottom, 21 -> 18; 16 planes 11x5, 16 per group, three directions, logits, 253 -> 37.
+int ragged_bwd_threads(const BwdParams& p, int dtype) {
+    const long long steps = lines_walked(p.mask, p.H, p.W), HW = (long long)p.H * p.W, groups = (long long)p.B * p.G;
+    if (steps <= 2 || (steps <= 4 && p.cpg <= 16) || (steps <= 10 && p.cpg <= 2) || (steps * HW <= 520 && groups > 512)) return 0;
+    return ragged_finish_blocks(p, dtype) <= 0x7fffffffull ? ragged_threads(ragged_sweep_params(p), dtype, true) : 0;
 }
+bool ragged_bwd_applicable(const BwdParams& p, int dtype) { return ragged_bwd_threads(p, dtype) != 0; }
 
 // The two passes of the backward call on any map: the reverse sweep (merged gx, e per direction in fp32), then the sums
 // over the channels.

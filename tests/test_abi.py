@@ -191,3 +191,21 @@ def test_binding_refuses_cpu_tensors_and_missing_library(monkeypatch):
     monkeypatch.setattr(binding, "lib_path", lambda: "/nonexistent/libgspn.so")
     with pytest.raises(ImportError):
         binding.load_library()
+
+
+def test_short_scans_and_tiny_planes_stay_line_by_line(lib):
+    """Of the calls with the plan "generic": few scan steps, or many planes of a few pixels, run line by line (no threads of
+    the any-size kernel); the other side of each line does not."""
+    f = lambda B, C, H, W, G, mask, dtype, backward: lib.gspn_any_size_threads(B, C, H, W, G, 0, 0, ctypes.c_uint(mask), dtype, backward)
+    for dtype in (0, 1, 2):
+        assert f(1, 1712, 3, 251, 107, 1, dtype, 0) == 0 and f(1, 1712, 3, 251, 107, 1, dtype, 1) == 0
+        assert f(1, 64, 12, 101, 8, 1, dtype, 0) == 0 and f(1, 64, 13, 101, 8, 1, dtype, 0) > 0
+        assert f(1, 64, 100, 6, 4, 12, dtype, 0) == 0 and f(1, 64, 100, 7, 4, 12, dtype, 0) > 0
+        assert f(1, 10, 1, 17, 10, 4, dtype, 0) == 0 and f(1, 10, 1, 23, 10, 4, dtype, 0) > 0           # 17 and 23 steps
+        assert f(1, 3704, 1, 27, 8, 15, dtype, 0) == 0 and f(1, 3703, 1, 27, 8, 15, dtype, 0) > 0        # 56 steps, 100 008 and 99 981 pixels
+        assert f(1, 2049, 18, 1, 2049, 15, dtype, 0) == 0 and f(1, 2048, 18, 1, 2048, 15, dtype, 0) > 0
+        assert f(1, 5000, 25, 31, 8, 15, dtype, 0) > 0 and f(1, 5000, 25, 31, 8, 15, dtype, 1) > 0
+        assert f(1, 64, 2, 101, 1, 1, dtype, 1) == 0 and f(1, 64, 3, 101, 1, 1, dtype, 1) > 0
+        assert f(1, 64, 4, 101, 4, 1, dtype, 1) == 0 and f(1, 64, 5, 101, 4, 1, dtype, 1) > 0
+        assert f(1, 64, 10, 101, 32, 1, dtype, 1) == 0 and f(1, 64, 11, 101, 32, 1, dtype, 1) > 0
+        assert f(1, 513, 17, 1, 513, 1, dtype, 1) == 0 and f(1, 512, 17, 1, 512, 1, dtype, 1) > 0
