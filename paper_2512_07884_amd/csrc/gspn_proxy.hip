@@ -493,6 +493,18 @@ static hipError_t launch_project_mfma(const void* in, const void* P, void* out, 
 // out = P in (PT = false) or P^T in (PT = true: the gradient w.r.t. the projection's input) in storage type T
 template <typename T, bool PT>
 static hipError_t launch_project_as(const void* in, const void* P, void* out, int B, int K, int M, int N, bool mfma, hipStream_t s) {
+    // a launch counts its threads in 32 bits (what is beyond is cut off without an error): very many images go in several
+    const unsigned long long image = mfma ? 64ull * ((N + 255) / 256) * ((M + 31) / 32) : (unsigned long long)N;
+    const unsigned long long most = ((1ull << 32) - 512) / image;
+    if ((unsigned long long)B > most) {
+        if (most < 1) return hipErrorInvalidValue;
+        for (long b0 = 0; b0 < B; b0 += (long)most) {
+            const int n = (int)(B - b0 < (long)most ? B - b0 : (long)most);
+            const hipError_t e = launch_project_as<T, PT>((const T*)in + (size_t)b0 * K * N, P, (T*)out + (size_t)b0 * M * N, n, K, M, N, mfma, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     if constexpr (sizeof(T) == 2) {
         if (mfma) {
             // The waves of a workgroup share the k-steps where one wave per tile would leave the chip short of waves and the

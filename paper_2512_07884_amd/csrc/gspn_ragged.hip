@@ -102,12 +102,14 @@ bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* o
     return false;
 }
 
-// threads per workgroup of a call, 0 where no launch shape fits
+// threads per workgroup of a call, 0 where no launch shape fits.  A launch counts its threads in 32 bits -- what is beyond is
+// cut off without an error -- so a call of too many planes is left to the line-by-line kernels, which loop over them.
 static int ragged_threads(const FwdParams& p, int dtype, bool merge_rounds) {
     RaggedArgs a;
     int threads, nv;
     size_t lds;
-    return ragged_plan(p, dtype, merge_rounds, &a, &threads, &nv, &lds) ? threads : 0;
+    if (!ragged_plan(p, dtype, merge_rounds, &a, &threads, &nv, &lds)) return 0;
+    return (unsigned long long)p.B * p.C * threads < (1ull << 32) ? threads : 0;
 }
 static int lines_walked(unsigned mask, int H, int W) {
     return (int)((mask & 1u) + ((mask >> 1) & 1u)) * H + (int)(((mask >> 2) & 1u) + ((mask >> 3) & 1u)) * W;
@@ -332,7 +334,7 @@ unsigned long long ragged_finish_blocks(const BwdParams& p, int dtype) {
 int ragged_bwd_threads(const BwdParams& p, int dtype) {
     const long long steps = lines_walked(p.mask, p.H, p.W), HW = (long long)p.H * p.W, groups = (long long)p.B * p.G;
     if (steps <= 2 || (steps <= 4 && p.cpg <= 16) || (steps <= 10 && p.cpg <= 2) || (steps * HW <= 520 && groups > 512)) return 0;
-    return ragged_finish_blocks(p, dtype) <= 0x7fffffffull ? ragged_threads(ragged_sweep_params(p), dtype, true) : 0;
+    return ragged_finish_blocks(p, dtype) * 256 < (1ull << 32) ? ragged_threads(ragged_sweep_params(p), dtype, true) : 0;
 }
 bool ragged_bwd_applicable(const BwdParams& p, int dtype) { return ragged_bwd_threads(p, dtype) != 0; }
 

@@ -209,3 +209,14 @@ def test_short_scans_and_tiny_planes_stay_line_by_line(lib):
         assert f(1, 64, 4, 101, 4, 1, dtype, 1) == 0 and f(1, 64, 5, 101, 4, 1, dtype, 1) > 0
         assert f(1, 64, 10, 101, 32, 1, dtype, 1) == 0 and f(1, 64, 11, 101, 32, 1, dtype, 1) > 0
         assert f(1, 513, 17, 1, 513, 1, dtype, 1) == 0 and f(1, 512, 17, 1, 512, 1, dtype, 1) > 0
+
+
+def test_more_planes_than_a_launch_counts_threads_for_go_line_by_line(lib):
+    """A launch holds fewer than 2^32 threads; the any-size kernel takes one workgroup per plane."""
+    f = lambda C, H, W, dtype, backward: lib.gspn_any_size_threads(1, C, H, W, 1, 0, 0, ctypes.c_uint(15), dtype, backward)
+    for dtype, H, W in ((1, 9, 11), (2, 17, 17), (0, 17, 19)):
+        for backward in (0, 1):
+            t = f(5000, H, W, dtype, backward)
+            assert t in (128, 256, 512, 1024)
+            most = ((1 << 32) - 1) // t
+            assert f(most, H, W, dtype, backward) == t and f(most + 1, H, W, dtype, backward) == 0
