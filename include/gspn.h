@@ -191,9 +191,9 @@ unsigned long long gspn_unfused_workspace_bytes(int B, int C, int H, int W);
  * axis that takes x from C channels to C_proxy before the scan, and the learned 1x1 projection back to C after it:
  *     out[b][m][h][w] = sum_k P[m][k] * in[b][k][h][w]
  *   in  [B,K,H,W]   P [M,K] row-major   out [B,M,H,W]   (down: K = C, M = C_proxy; up: K = C_proxy, M = C)
- * The scan in the proxy space is an ordinary gspn_scan_fwd on [B,C_proxy,H,W].  16-bit storage (bf16, fp16) with K and H*W
- * multiples of 8 runs on the matrix cores (fp32 accumulation, one rounding per output); other shapes and fp32
- * storage run a plain FMA kernel.  Pointers, stream and errors as for the scan calls. */
+ * The scan in the proxy space is an ordinary gspn_scan_fwd on [B,C_proxy,H,W].  16-bit storage (bf16, fp16) with K a
+ * multiple of 8 and at least 8 pixels runs on the matrix cores (fp32 accumulation, one rounding per output); other shapes
+ * and fp32 storage run a plain FMA kernel.  Pointers, stream and errors as for the scan calls. */
 int gspn_proxy_project(const void* in, const void* P, void* out, int B, int K, int M, int H, int W, int dtype,
                        void* stream);
 /* Gradients of gspn_proxy_project for a scalar loss L, given gout = dL/dout (chain rule on the sum above):
@@ -204,8 +204,8 @@ int gspn_proxy_project(const void* in, const void* P, void* out, int B, int K, i
  *   gP      out [M,K] in fp32 whatever the storage type, or NULL (not computed; at least one of gin, gP is required)
  *   partial workspace of the caller's, B*M*K floats, required with gP (NULL otherwise): it receives the per-image
  *           sums, which a second small kernel adds in image order -- no atomics, the result is bitwise repeatable.
- * The library still allocates nothing.  16-bit storage runs on the matrix cores when M (for gin) and H*W (both; for gP
- * a multiple of 16) allow, as in the forward call; other shapes and fp32 storage run plain FMA kernels. */
+ * The library still allocates nothing.  16-bit storage with at least 8 pixels runs on the matrix cores (for gin
+ * where M is a multiple of 8); other shapes and fp32 storage run plain FMA kernels. */
 int gspn_proxy_project_bwd(const void* gout, const void* in, const void* P, void* gin, float* gP, float* partial,
                            int B, int K, int M, int H, int W, int dtype, void* stream);
 /* gspn_proxy_project_bwd for callers that cannot allocate device memory and have no workspace to pass: code
@@ -220,9 +220,7 @@ int gspn_proxy_project_bwd(const void* gout, const void* in, const void* P, void
 #define GSPN_PROXY_STATIC_MAX_FLOATS (1 << 20)
 int gspn_proxy_project_bwd_static(const void* gout, const void* in, const void* P, void* gin, float* gP,
                                   int B, int K, int M, int H, int W, int dtype, void* stream);
-/* "mfma": matrix-core kernels with whole 16-byte requests; "fma": every other call -- fp32 storage and K not a multiple of 8
- * on plain FMA kernels, 16-bit images whose H*W is not a multiple of 8 (from 8 pixels up) on the matrix-core kernels with
- * requests at element alignment ("invalid" for bad arguments). */
+/* "mfma" or "fma": which kernel gspn_proxy_project runs for these arguments ("invalid" for bad ones). */
 const char* gspn_proxy_plan(int B, int K, int M, int H, int W, int dtype);
 
 /* Name of the kernel family the forward / backward call would dispatch to for

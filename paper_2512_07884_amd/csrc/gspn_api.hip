@@ -263,7 +263,7 @@ int gspn_proxy_project_bwd_static(const void* gout, const void* in, const void* 
 const char* gspn_proxy_plan(int B, int K, int M, int H, int W, int dtype) {
     if (B < 1 || K < 1 || M < 1 || H < 1 || W < 1 || (dtype != GSPN_F32 && dtype != GSPN_BF16 && dtype != GSPN_F16)) return "invalid";
     if (H > GSPN_MAX_LINE || W > GSPN_MAX_LINE || (long long)H * W >= (1ll << 31)) return "invalid";
-    return proxy_mfma_applicable(B, K, M, H * W, dtype) ? "mfma" : "fma";
+    return proxy_mfma_applicable(K, M, H * W, dtype) ? "mfma" : "fma";
 }
 
 const char* gspn_status_string(int status) {

@@ -456,16 +456,10 @@ __global__ void __launch_bounds__(256) proxy_gradw_sum_kernel(const float* __res
 
 }  // namespace
 
-// the plan name: whole 16-byte requests in every row
-bool proxy_mfma_applicable(int B, int K, int M, int N, int dtype) {
-    if (dtype == 0 || K % 8 || N % 8) return false;
-    // 32-bit byte offsets inside one image of `in` / `out` and inside P
-    return (size_t)K * N * 2 < (1ull << 31) && (size_t)M * N * 2 < (1ull << 31) && (size_t)M * K * 2 < (1ull << 31);
-}
-// rows of any length from eight pixels up run on the matrix cores too, with requests at element alignment
-// (24 <- 96 channels on two 78x117 images, FMA kernels -> these: forward 165 -> 11, input gradient 141 -> 11, weight gradient
-// 492 -> 19 us)
-static bool proxy_mfma_any(int K, int M, int N, int dtype) {
+// 16-bit rows of any length from eight pixels up (those that are not a multiple of eight with requests at element alignment:
+// 24 <- 96 channels on two 78x117 images, FMA kernels -> these: forward 165 -> 11, input gradient 141 -> 11, weight gradient
+// 492 -> 19 us); 32-bit byte offsets inside P
+bool proxy_mfma_applicable(int K, int M, int N, int dtype) {
     return dtype != 0 && K % 8 == 0 && N >= 8 && (size_t)M * K * 2 < (1ull << 31);
 }
 
@@ -529,7 +523,7 @@ static hipError_t launch_project_as(const void* in, const void* P, void* out, in
 
 hipError_t launch_proxy_project(const void* in, const void* P, void* out, int B, int K, int M, int N, int dtype,
                                 hipStream_t s) {
-    const bool mfma = proxy_mfma_any(K, M, N, dtype);
+    const bool mfma = proxy_mfma_applicable(K, M, N, dtype);
     if (dtype == 0) return launch_project_as<float, false>(in, P, out, B, K, M, N, false, s);
     if (dtype == 1) return launch_project_as<bf16_t, false>(in, P, out, B, K, M, N, mfma, s);
     return launch_project_as<f16_t, false>(in, P, out, B, K, M, N, mfma, s);
@@ -586,7 +580,7 @@ hipError_t launch_proxy_project_bwd(const void* gout, const void* in, const void
                                     int B, int K, int M, int N, int dtype, hipStream_t s) {
     if (gin) {
         // the forward kernels with the matrix read transposed: K output channels, contraction over the M channels of gout
-        const bool mfma = proxy_mfma_any(M, K, N, dtype);
+        const bool mfma = proxy_mfma_applicable(M, K, N, dtype);
         const hipError_t e = dtype == 0 ? launch_project_as<float, true>(gout, P, gin, B, M, K, N, false, s)
                            : dtype == 1 ? launch_project_as<bf16_t, true>(gout, P, gin, B, M, K, N, mfma, s)
                                         : launch_project_as<f16_t, true>(gout, P, gin, B, M, K, N, mfma, s);

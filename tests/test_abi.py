@@ -220,3 +220,12 @@ def test_more_planes_than_a_launch_counts_threads_for_go_line_by_line(lib):
             assert t in (128, 256, 512, 1024)
             most = ((1 << 32) - 1) // t
             assert f(most, H, W, dtype, backward) == t and f(most + 1, H, W, dtype, backward) == 0
+
+
+def test_proxy_plan_names_the_kernel_that_runs(lib):
+    plan = lambda *a: lib.gspn_proxy_plan(*a).decode()
+    for dtype in (1, 2):
+        assert plan(2, 96, 24, 78, 117, dtype) == "mfma" and plan(1, 96, 8, 3, 3, dtype) == "mfma"      # rows that start at any element
+        assert plan(1, 96, 8, 1, 7, dtype) == "fma" and plan(1, 12, 8, 8, 8, dtype) == "fma"             # under 8 pixels; K
+        assert plan(1, 96, 8, 16384, 16384, dtype) == "mfma"                                             # an image beyond 2^31 bytes
+    assert plan(2, 96, 24, 78, 117, 0) == "fma"
