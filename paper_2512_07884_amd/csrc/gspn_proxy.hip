@@ -474,11 +474,11 @@ static hipError_t launch_project_mfma(const void* in, const void* P, void* out, 
     else k = proxy_mfma_kernel<T, KS, PT, SPLIT, false, false>;
     if constexpr (SPLIT == 1) {
         // Whole rows: buffer requests for P^T (with global ones 18 -> 20 us at 24 -> 1152 channels on two 128x128 images), for
-        // steps of 8 (8 -> 1152 there 14.6 -> 15.8) and for chains of 24 and more steps (384 -> 288 on 32 images 56x56: 56.5 ->
-        // 59.0); global ones for the other forward calls (288 -> 1152 on four 64x64 images 36.4 -> 31.4, 192 -> 144 on eight
-        // 56x56 13.5 -> 10.1) and where an image's offsets pass 32 bits.
+        // steps of 8 (8 -> 1152 there 14.6 -> 15.8) and from four waves per CU on (from memory: 144 -> 192 on 64 images 28x28
+        // 21.1 -> 22.3, 288 -> 768 on 64 of 32x32 84 -> 88).  With fewer waves the lanes' own addresses serve better (144 -> 192
+        // on eight 64x64 images 17.0 -> 14.8, 288 -> 1152 on two 56x56 24.8 -> 20.6), and they reach images beyond 2^31 bytes.
         const bool fits = (size_t)K * N * 2 < (1ull << 31) && (size_t)M * N * 2 < (1ull << 31);
-        if (N % 8 == 0 && fits && (PT || KS == 8 || K >= 24 * KS)) k = proxy_mfma_kernel<T, KS, PT, 1, false, true>;
+        if (N % 8 == 0 && fits && (PT || KS == 8 || items >= 1024)) k = proxy_mfma_kernel<T, KS, PT, 1, false, true>;
     }
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, s, (const T*)in, (const T*)P, (T*)out, B, K, M, N, ntiles, mtiles);
     return hipGetLastError();
@@ -503,13 +503,14 @@ static hipError_t launch_project_as(const void* in, const void* P, void* out, in
         if (mfma) {
             // The waves of a workgroup share the k-steps where one wave per tile would leave the chip short of waves and the
             // chain is long: the longer the chain, the more waves that takes.  Measured, plain -> shared: 1152 -> 144 on two
-            // 64x64 images (160 waves, 72 steps) 58 -> 18 us; 288 -> 384 on eight 28x28 (384 waves, 18 steps) 15.0 -> 11.4; 384
-            // -> 24 on eight 128x128 (512 waves, 24 steps) 30.7 -> 23.7; 1152 -> 288 on four 64x64 (576, 72) 61 -> 45.  Beyond
-            // the lines sharing loses: 288 -> 768 on 32 images 14x14 (768, 18) 16.7 -> 22.7; 288 -> 768 on one 96x96 (864, 18)
-            // 19 -> 25; 768 -> 96 on 32 images 64x64 (1536, 48) 56 -> 65; 144 -> 192 on eight 56x56 (624, 9) 11 -> 15.
+            // 64x64 images (160 waves, 72 steps) 58 -> 18 us; 288 -> 384 on eight 28x28 (384 waves, 18 steps) 15.0 -> 11.4;
+            // 1152 -> 288 on four 64x64 (576, 72) 61 -> 45.  Beyond the lines sharing loses: 384 -> 24 on eight 128x128 (512,
+            // 24) from memory 42 -> 46; 288 -> 768 on 32 images 14x14 (768, 18) 16.7 -> 22.7; 768 -> 8 on 64 images 56x56 (832,
+            // 48) from memory 118 -> 122; 768 -> 96 on 32 images 64x64 (1536, 48) 56 -> 65; 144 -> 192 on eight 56x56 (624, 9)
+            // 11 -> 15.
             const long waves = (long)B * ((N + 255) / 256) * ((M + 31) / 32);
             const int steps = K / (K % 16 == 0 ? 16 : 8);
-            const bool split = (waves <= 448 && steps >= 16) || (waves <= 640 && steps >= 24) || (waves < 1024 && steps >= 48);
+            const bool split = (waves <= 448 && steps >= 16) || (waves <= 768 && steps >= 48);
             if (K % 16 == 0) return split ? launch_project_mfma<T, 16, PT, 4>(in, P, out, B, K, M, N, s) : launch_project_mfma<T, 16, PT, 1>(in, P, out, B, K, M, N, s);
             return split ? launch_project_mfma<T, 8, PT, 4>(in, P, out, B, K, M, N, s) : launch_project_mfma<T, 8, PT, 1>(in, P, out, B, K, M, N, s);
         }

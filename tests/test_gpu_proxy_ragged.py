@@ -35,11 +35,11 @@ def test_projection_and_gradients(shape, dtype):
     assert np.array_equal(gin, gin2) and np.array_equal(gP, gP2)
 
 
-# Whole rows at the lines of the dispatch: k-steps shared by the waves up to 448 waves from 16 steps on, up to 640 from 24 and
-# up to 1023 from 48 (either side of each); buffer requests for P^T, for steps of 8 and for chains of 24 steps on more waves
+# Whole rows at the lines of the dispatch: k-steps shared by the waves up to 448 waves from 16 steps on and up to 768 from 48;
+# buffer requests for P^T, for steps of 8 and from 1024 waves on (either side of each)
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("shape", [(14, 256, 1024, 3, 8), (15, 256, 1024, 3, 8), (3, 240, 40, 5, 8), (20, 384, 1024, 2, 4), (21, 384, 1024, 2, 4),
-                                   (31, 768, 1024, 1, 8), (32, 768, 1024, 1, 8), (5, 136, 40, 9, 8), (2, 1024, 24, 16, 33)],
+@pytest.mark.parametrize("shape", [(14, 256, 1024, 3, 8), (15, 256, 1024, 3, 8), (3, 240, 40, 5, 8), (24, 768, 1024, 1, 8), (25, 768, 1024, 1, 8),
+                                   (31, 48, 1024, 1, 8), (32, 48, 1024, 1, 8), (5, 136, 40, 9, 8), (2, 1024, 24, 16, 33)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_whole_rows_at_the_lines_of_the_dispatch(shape, dtype):
     test_projection_and_gradients(shape, dtype)
