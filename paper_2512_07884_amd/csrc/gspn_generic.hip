@@ -10,9 +10,10 @@
 // else in place in global memory -- so no atomics and no zero-fill are needed and
 // the summation order is fixed.
 //
-// This is the fallback for shapes no other kernel takes (lines beyond the reach of gspn_ragged*.hip, planes of fewer than
-// 16 pixels, the transposed layout off the tile kernel) and the reference the fast kernels are compared with; it makes no
-// attempt at coalescing the horizontal directions.
+// This is the fallback for calls no other kernel takes: what gspn_ragged*.hip has no launch shape for (long lines, 16-bit
+// forward planes whose fp32 tile leaves no room for a chunk), its short scans and tiny planes, planes of fewer than 16 pixels,
+// more planes than a launch counts threads for, and the transposed layout off the tile kernel.  It is also the reference the
+// fast kernels are compared with; it makes no attempt at coalescing the horizontal directions.
 #include "gspn_common.hpp"
 
 namespace gspn {

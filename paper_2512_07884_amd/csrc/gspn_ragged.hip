@@ -26,9 +26,9 @@ bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* o
     // The line-by-line kernel sums the four directions of a 16-bit plane in an fp32 LDS tile where its two line buffers leave
     // room; a merge in global memory rounds once per direction, so it is taken only where that kernel would do so too.
     const bool must_tile = dtype != 0 && !merge_rounds && (size_t)H * W * 4 + 2 * (size_t)longest * 4 <= cap;
-    // workgroups a CU is to hold: as many as the call has for it, up to 8; sixteen waves per CU (128 registers) in any case
+    // workgroups a CU is to hold: as many as the call has for it, up to 4; sixteen waves per CU (128 registers) in any case
     int wgs_wanted = 1;
-    while (wgs_wanted < 8 && (size_t)wgs_wanted * 256 < planes) wgs_wanted *= 2;
+    while (wgs_wanted < 4 && (size_t)wgs_wanted * 256 < planes) wgs_wanted *= 2;
 
     for (int mode = 0; mode < (must_tile ? 2 : 3); ++mode) {     // tile and both directions; tile and one; y in global memory
         a.nd = mode == 0 ? 2 : 1;
@@ -37,67 +37,66 @@ bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* o
         if (fixed >= cap) continue;
         // positions per lane: a line in one wave (no meetings within a chunk) up to 192 positions, beyond that two, and four
         // where the scanning waves would otherwise leave too few for the loads
-        for (int v = longest <= 64 ? 1 : longest <= 128 ? 2 : longest <= 192 ? 3 : longest <= 448 ? 2 : 4; v; v = 0) {
-            for (int ax = 0; ax < 2; ++ax) {
-                const int L = ((ax ? H : W) + v - 1) / v * v;
-                if (ax == 0) {                                              // granules are written whole, one slot apart
-                    a.pitch2[ax] = (L + 7) / 8 * 8;
-                    a.pitch[ax] = (L + E - 1) / E * (E + 1) + v;        // v spare slots at the end of a line
-                } else {                                                    // odd: spreads the banks of the turned writes
-                    a.pitch[ax] = (L + v) | 1;
-                    a.pitch2[ax] = v % 2 ? L | 1 : L + 2;
-                }
+        const int v = longest <= 64 ? 1 : longest <= 128 ? 2 : longest <= 192 ? 3 : longest <= 448 ? 2 : 4;
+        for (int ax = 0; ax < 2; ++ax) {
+            const int L = ((ax ? H : W) + v - 1) / v * v;
+            if (ax == 0) {                                              // granules are written whole, one slot apart
+                a.pitch2[ax] = (L + 7) / 8 * 8;
+                a.pitch[ax] = (L + E - 1) / E * (E + 1) + v;        // v spare slots at the end of a line
+            } else {                                                    // odd: spreads the banks of the turned writes
+                a.pitch[ax] = (L + v) | 1;
+                a.pitch2[ax] = v % 2 ? L | 1 : L + 2;
             }
-            auto stage_bytes = [&](int ax, int K) { return (size_t)a.nd * (K * (a.pitch[ax] * sb + (wide ? 0 : a.pitch2[ax] * 2)) + 2 * a.pitch2[ax] * 4); };
-            const int kmax[2] = {(H + 7) / 8 * 8, (W + 7) / 8 * 8};
-            // chunk lengths: 64 B of an image row per request in the horizontal directions if that fits, else 32, else 16;
-            // with each, as many workgroups per CU as the LDS allows
-            for (int seg = 64; seg >= 16; seg /= 2) {
-                for (int wgs = wgs_wanted; wgs >= 1; wgs /= 2) {
-                    const int thr = 1024 / wgs, waves = thr / 64 / a.nd;
-                    if (waves < 2 || fixed >= cap / wgs) continue;
-                    const size_t room = cap / wgs - fixed;
-                    bool ok = true;
-                    for (int ax = 0; ax < 2 && ok; ++ax) {
-                        const int L = ax ? H : W;
-                        int parts = L <= 64 * v ? 1 : (L + 64 * v - 2 * RG_SUB - 1) / (64 * v - 2 * RG_SUB), own = 0;
-                        for (; parts < waves; ++parts) {
-                            own = ((L + parts - 1) / parts + v - 1) / v * v;
-                            if (parts == 1 || own + 2 * RG_SUB <= 64 * v) break;
-                        }
-                        ok = parts < waves;                                  // at least one wave loads
-                        a.parts[ax] = parts; a.own[ax] = own;
-                    }
-                    if (!ok) continue;
-                    auto fits = [&](int ax, int K) {
-                        const int gr = ax ? (K / E) * H : K * ((W + E - 1) / E);
-                        return gr <= RG_ROUNDS * (waves - a.parts[ax]) * 64 && stage_bytes(ax, K) <= room;
-                    };
-                    int kh = seg / es < 8 ? 8 : seg / es;
-                    if (kh > kmax[1]) kh = kmax[1];
-                    int kv = 8;
-                    if (!fits(1, kh) || !fits(0, kv)) continue;
-                    while (kv + 8 <= kmax[0] && kv + 8 <= 32 && fits(0, kv + 8)) kv += 8;
-                    a.K[0] = kv; a.K[1] = kh;
-                    *threads = thr;
-                    goto found;
-                }
-            }
-            continue;
-        found:
-            size_t top = 0;
-            for (int ax = 0; ax < 2; ++ax) {
-                a.w2_off[ax] = (int)((size_t)a.nd * a.K[ax] * a.pitch[ax] * sb);
-                a.edge_off[ax] = (int)((size_t)a.nd * a.K[ax] * (a.pitch[ax] * sb + (wide ? 0 : a.pitch2[ax] * 2)));
-                const size_t n = stage_bytes(ax, a.K[ax]);
-                if (n > top) top = n;
-            }
-            top = (top + 15) / 16 * 16;
-            a.tile_off = (int)top;
-            if (top + fixed > cap) continue;
-            *out = a; *nv = v; *lds = top + fixed;
-            return true;
         }
+        auto stage_bytes = [&](int ax, int K) { return (size_t)a.nd * (K * (a.pitch[ax] * sb + (wide ? 0 : a.pitch2[ax] * 2)) + 2 * a.pitch2[ax] * 4); };
+        const int kmax[2] = {(H + 7) / 8 * 8, (W + 7) / 8 * 8};
+        // chunk lengths: 64 B of an image row per request in the horizontal directions if that fits, else 32, else 16;
+        // with each, as many workgroups per CU as the LDS allows
+        for (int seg = 64; seg >= 16; seg /= 2) {
+            for (int wgs = wgs_wanted; wgs >= 1; wgs /= 2) {
+                const int thr = 1024 / wgs, waves = thr / 64 / a.nd;
+                if (waves < 2 || fixed >= cap / wgs) continue;
+                const size_t room = cap / wgs - fixed;
+                bool ok = true;
+                for (int ax = 0; ax < 2 && ok; ++ax) {
+                    const int L = ax ? H : W;
+                    int parts = L <= 64 * v ? 1 : (L + 64 * v - 2 * RG_SUB - 1) / (64 * v - 2 * RG_SUB), own = 0;
+                    for (; parts < waves; ++parts) {
+                        own = ((L + parts - 1) / parts + v - 1) / v * v;
+                        if (parts == 1 || own + 2 * RG_SUB <= 64 * v) break;
+                    }
+                    ok = parts < waves;                                  // at least one wave loads
+                    a.parts[ax] = parts; a.own[ax] = own;
+                }
+                if (!ok) continue;
+                auto fits = [&](int ax, int K) {
+                    const int gr = ax ? (K / E) * H : K * ((W + E - 1) / E);
+                    return gr <= RG_ROUNDS * (waves - a.parts[ax]) * 64 && stage_bytes(ax, K) <= room;
+                };
+                int kh = seg / es < 8 ? 8 : seg / es;
+                if (kh > kmax[1]) kh = kmax[1];
+                int kv = 8;
+                if (!fits(1, kh) || !fits(0, kv)) continue;
+                while (kv + 8 <= kmax[0] && kv + 8 <= 32 && fits(0, kv + 8)) kv += 8;
+                a.K[0] = kv; a.K[1] = kh;
+                *threads = thr;
+                goto found;
+            }
+        }
+        continue;
+    found:
+        size_t top = 0;
+        for (int ax = 0; ax < 2; ++ax) {
+            a.w2_off[ax] = (int)((size_t)a.nd * a.K[ax] * a.pitch[ax] * sb);
+            a.edge_off[ax] = (int)((size_t)a.nd * a.K[ax] * (a.pitch[ax] * sb + (wide ? 0 : a.pitch2[ax] * 2)));
+            const size_t n = stage_bytes(ax, a.K[ax]);
+            if (n > top) top = n;
+        }
+        top = (top + 15) / 16 * 16;
+        a.tile_off = (int)top;
+        if (top + fixed > cap) continue;
+        *out = a; *nv = v; *lds = top + fixed;
+        return true;
     }
     return false;
 }
@@ -116,7 +115,7 @@ static int lines_walked(unsigned mask, int H, int W) {
 }
 
 // Calls of few scan steps, and of many planes of a few pixels, stay with the line-by-line kernels: a pass here loads, turns and
-// scans eight lines whatever there are, and its LDS lets a CU hold eight planes at most where theirs holds up to 32.  Measured on
+// scans eight lines whatever there are, and a CU holds four planes at most where theirs holds up to 32.  Measured on
 // 1500 random calls of up to 900 steps, line by line -> here: 1712 planes 3x251, top to bottom only, 12 -> 45 us; 35488 planes
 // 82x4, left to right, 73 -> 188; 5215 planes 4x7, three directions, 20 -> 42; 4128 planes 18x1, all four, 30 -> 43; 18160
 // planes 6x11, all four, 128 -> 134.

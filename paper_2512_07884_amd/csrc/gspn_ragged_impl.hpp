@@ -1,9 +1,12 @@
-// Scan kernel for maps of any height and width: odd sides, rows that start at any element, lines of up to 1792 positions.
+// Scan kernel for maps of any height and width: odd sides, rows that start at any element.  Lines of up to 768 positions in fp32
+// storage and 1280 in 16-bit storage (1072 with logits): a chunk of eight lines is at most two granules per loading thread.
+// 16-bit forward calls whose merged output the line-by-line kernels sum in fp32 on chip keep the fp32 tile: with it the LDS
+// ends at 900 positions on narrow maps (687 with logits) and has no room for planes of about 33 700 (30 000) to 40 500 pixels.
 // Forward, forward with h_save, and the reverse sweep of the backward call; global scan, GSPN-local, weights as logits.
 //
 // One workgroup owns one (image, channel) plane.  A direction is walked in chunks of K scan lines that pass through LDS:
-//   load    every thread holds one granule of a chunk (16 B of one image row: x, lam, u and the three weights) in
-//           registers, requested a whole chunk ahead.  16-byte requests at element alignment: rows of an odd width start
+//   load    a loading thread holds one or two granules of a chunk (16 B of one image row: x, lam, u and the three weights)
+//           in registers, requested a whole chunk ahead.  16-byte requests at element alignment: rows of an odd width start
 //           anywhere, and the memory pipe takes them, so no width needs a narrower path;
 //   stage   lam*x in fp32 and the weights (taps outside the line and lines without a predecessor zeroed, logits
 //           normalised in fp32) go to LDS as [scan line][position]: a vertical scan's granules along a line, a horizontal
@@ -17,8 +20,9 @@
 // Both directions of an axis run at once where the tile fits, half of the waves each; where their chunks cross in the
 // middle of the map the second waits for the first, so the order of every sum is fixed.
 //
-// What bounds it: the LDS instructions and the vector ALU of the staging and of the scan, close to the memory time
-// on 16-bit maps; measured figures are at the choice of the launch shape (plan_ragged).
+// What bounds it: the chain of the scanning wave -- one per direction of a plane, and the LDS holds one plane of 100x167 -- and
+// the LDS traffic of staging behind it.  2 x 256 channels 100x167 in bf16: 122 us forward (1.5 TB/s of its 0.18 GB; line by
+// line 968), 130 with h_save, 303 backward; the LDS index unit is active in 32 % of a CU's busy cycles, 14 % bank conflicts.
 #pragma once
 #include "gspn_unaligned.hpp"
 
@@ -490,7 +494,7 @@ struct RaggedPass {
         // both directions add to the same rows / columns of the tile while their chunks cross
         auto cross = [&](int k) { return dcount == 2 && 2 * (k + 1) * K > S && 2 * k * K < S; };
         if (part < parts) {
-            __builtin_amdgcn_s_setprio(3);                       // the chain the others wait for
+            __builtin_amdgcn_s_setprio(3);       // the chain the others wait for (a few per cent either way: 2048 planes 25x31 33.7 -> 32.4 us, 768 of 50x83 63.3 -> 64.7)
             float h[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) h[v] = 0.f;
