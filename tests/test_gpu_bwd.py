@@ -231,8 +231,8 @@ def test_backward_generic_kernel_bf16(monkeypatch):
 
 @pytest.mark.parametrize("shape", [(2, 24, 57, 57, 2), (1, 64, 33, 70, 1), (1, 8, 1, 56, 2)], ids=lambda s: "x".join(map(str, s)))
 def test_backward_generic_kernel_bf16_large_groups(shape):
-    """Odd widths (and single rows) run the generic kernels; the sum of gw over the 12 / 64 channels of a group is taken
-    in fp32 and rounded once, so the bf16 tolerance holds at any group size."""
+    """Odd widths (and single rows) have the plan "generic"; the sum of gw over the 12 / 64 channels of a group is taken
+    in fp32 and rounded once, so the bf16 tolerance holds at any group size (line by line: test_gpu_line_by_line)."""
     import paper_2512_07884_amd as G
     B, C, H, W, Gr = shape
     assert G.gspn_bwd_plan(B, C, H, W, Gr, 15, 1, 0) == "generic", shape

@@ -1,6 +1,6 @@
 """Seeded random shapes, masks, stretch lengths and call forms: what the fast kernels return (plane, tile, stream,
 two-pass backward) against what the generic kernels return for the same device tensors.  The generic kernels are held
-against the oracle elsewhere (test_gpu_fwd / test_gpu_bwd / test_gpu_local / test_gpu_logits with GSPN_FORCE_GENERIC);
+against the oracle elsewhere (test_gpu_line_by_line, and test_gpu_fwd / test_gpu_bwd, with GSPN_FORCE_GENERIC);
 this test spreads over many more shapes than the oracle could check in the same time."""
 import numpy as np
 import pytest

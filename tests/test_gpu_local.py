@@ -102,8 +102,7 @@ def test_local_scans_on_the_plane_kernels(shape, kchunk, monkeypatch):
 
 # larger maps: forward plane kernel with the backward tile kernel (lines of 33..64 positions), the tile kernels'
 # horizontal variants (whole rows, 64 B and 16 B bursts, rows split over waves), the stream kernel, per-channel
-# and shared weights, and ragged shapes on the generic kernels (whose bf16 gw is summed in storage precision
-# channel by channel: small groups there)
+# and shared weights, and ragged shapes with the plan "generic" (the any-size kernel; line by line in test_gpu_line_by_line)
 @pytest.mark.parametrize("shape,kchunk,plans", [
     ((2, 8, 56, 56, 2, "bf16"), 14, ("plane", "tile")), ((1, 8, 64, 64, 8, "bf16"), 10, ("plane", "tile")),
     ((1, 6, 40, 24, 3, "bf16"), 16, ("plane", "twopass")), ((2, 8, 56, 56, 2, "f32"), 9, ("tile", "tile")),

@@ -1,8 +1,12 @@
 """Maps of any size on the kernels that walk them in chunks of lines (the "generic" plan's fast form): forward, forward with
 h_save and the backward call against the fp64 oracle, and against the line-by-line kernels over random shapes.  Sizes sit
-where the launch shape changes: granules of 8 / 4 elements and their tails, rows narrower than a granule, lines of one and
-of several waves (64 / 65, 192 / 193 positions), two and four positions per lane (from 193 and 385 up), planes beyond the
-LDS tile, the last chunk of a scan, the middle of the map where the chunks of both directions cross."""
+where the launch shape changes: granules of 8 / 4 elements and their tails, rows narrower than a granule, lines of one wave
+(one position per lane up to 64, two up to 128, three up to 192) and of several (two positions per lane from 193, four from
+449 up), the longest lines, planes beyond the LDS tile, the last chunk of a scan, the middle of the map where the chunks of
+both directions cross, 1024, 512 and 256 threads (from 257 and 513 planes).  Each call is asked which kernel it runs: the plan
+name "generic" is also the line-by-line kernels'."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -14,12 +18,24 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(1, 2, 1, 17, 1), (1, 2, 17, 1, 2), (2, 2, 5, 5, 1), (1, 4, 3, 67, 2), (2, 3, 7, 9, 3), (1, 2, 25, 31, 1),
           (1, 2, 64, 65, 1), (1, 2, 65, 63, 2), (1, 6, 50, 83, 2), (2, 2, 100, 167, 1), (1, 2, 167, 100, 2),
           (1, 1, 30, 193, 1), (1, 1, 193, 30, 1), (1, 1, 385, 21, 1), (1, 1, 20, 391, 1), (1, 1, 450, 12, 1),
-          (1, 1, 11, 905, 1), (1, 1, 905, 9, 1), (1, 2, 210, 230, 1)]
+          (1, 1, 11, 905, 1), (1, 1, 905, 9, 1), (1, 2, 210, 230, 1), (1, 1, 11, 767, 1), (1, 1, 767, 9, 1), (1, 1, 449, 451, 1),
+          (3, 96, 25, 31, 8), (5, 120, 17, 21, 8)]
+
+
+def threads(shape, dtype, kchunk=0, logits=False, mask=15):
+    """Threads per workgroup of the any-size kernel in the forward and the backward call, 0 where another kernel takes it."""
+    from paper_2512_07884_amd import binding
+    B, C, H, W, Gr = shape
+    f = binding.load_library().gspn_any_size_threads
+    return tuple(f(B, C, H, W, Gr, kchunk, int(logits), ctypes.c_uint(mask), {"f32": 0, "bf16": 1, "f16": 2}[dtype], b) for b in (0, 1))
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_global_scan(shape, dtype):
+    # (fp32 lines beyond 768 positions have no launch shape and run line by line: kept as a test of the hand-over)
+    want = 0 if dtype == "f32" and 905 in shape else 1024 if shape[0] * shape[1] <= 256 else 512 if shape[0] * shape[1] <= 512 else 256
+    assert threads(shape, dtype) == (want, want)
     check_local(shape + (dtype,), 1 << 14)
 
 
@@ -28,14 +44,17 @@ def test_global_scan(shape, dtype):
                          ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 def test_local_stretches_and_direction_masks(shape, kchunk, mask, dtype):
+    assert min(threads(shape, dtype, kchunk, False, mask)) > 0
     check_local(shape + (dtype,), kchunk, mask=mask, poison_starts=dtype != "f16")
 
 
 @pytest.mark.parametrize("shape,kchunk,mask", [((1, 3, 25, 31, 3), None, 15), ((1, 4, 50, 83, 2), 7, 15), ((1, 2, 100, 167, 1), None, 15),
-                                               ((1, 2, 65, 193, 2), 24, 15), ((1, 2, 31, 77, 2), None, 9), ((1, 1, 205, 230, 1), None, 15)],
+                                               ((1, 2, 65, 193, 2), 24, 15), ((1, 2, 31, 77, 2), None, 9), ((1, 1, 205, 230, 1), None, 15),
+                                               ((1, 2, 21, 501, 1), None, 15), ((1, 2, 501, 21, 2), 24, 15), ((3, 96, 25, 31, 8), None, 15)],
                          ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 def test_weights_as_logits(shape, kchunk, mask, dtype):
+    assert min(threads(shape, dtype, kchunk or 0, True, mask)) > 0
     check_logits(shape + (dtype,), kchunk=kchunk, mask=mask, poison=dtype != "f16")
 
 
@@ -49,6 +68,7 @@ def test_against_the_line_by_line_kernels(seed, monkeypatch):
     from test_gpu_differential import _run, _rel
     G.binding = binding
     rng = np.random.default_rng(seed)
+    on_any_size = 0
     for it in range(14):
         dtype = ["bf16", "f32", "f16"][int(rng.integers(0, 3))]
         H, W = int(2 ** rng.uniform(1, 8.3)), int(2 ** rng.uniform(1, 8.3)) | 1
@@ -59,6 +79,7 @@ def test_against_the_line_by_line_kernels(seed, monkeypatch):
         mask = int(rng.integers(1, 16)) if rng.random() < 0.3 else 15
         kchunk = int(rng.integers(1, max(H, W))) if rng.random() < 0.35 else 0
         logits = bool(rng.random() < 0.3)
+        on_any_size += sum(t > 0 for t in threads((B, C, H, W, Gr), dtype, kchunk, logits, mask))
         td = {"bf16": torch.bfloat16, "f32": torch.float32, "f16": torch.float16}[dtype]
         g = torch.Generator(device="cuda"); g.manual_seed(1000 * seed + it)
         z = torch.randn((4, B, Gr, 3, H, W), generator=g, device="cuda")
@@ -86,6 +107,7 @@ def test_against_the_line_by_line_kernels(seed, monkeypatch):
             e = _rel(torch.where(na, torch.zeros_like(a), a), torch.where(nb, torch.zeros_like(b), b))
             assert e <= tol, (case, n, e)
             assert torch.equal(fast[n].view(torch.uint8), again[n].view(torch.uint8)), (case, n, "not the same twice")
+    assert on_any_size >= 14, "most of the calls are to run the kernel under test"
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -109,6 +131,7 @@ def test_what_is_not_finite_stays_in_its_stretch(shape, kchunk, dtype, monkeypat
            "gy": torch.randn((B, C, H, W), generator=g, device="cuda").to(td)}
     inp["x"][0, 0, H // 2, W // 2] = float("nan"); inp["x"][0, 0, 0, W - 1] = float("inf")
     inp["gy"][0, C - 1, H - 1, 0] = float("nan"); inp["gy"][0, C - 1, H // 3, W // 3] = float("-inf")
+    assert min(threads(shape, dtype, kchunk)) > 0
     fast = _run(G, inp, Gr, 15, kchunk, False)
     monkeypatch.setenv("GSPN_FORCE_GENERIC", "1")
     ref = _run(G, inp, Gr, 15, kchunk, False)
@@ -139,6 +162,7 @@ def test_states_are_those_of_the_line_by_line_kernels(shape, kchunk, mask, logit
            "lam": torch.rand((4, B, C, H, W), generator=g, device="cuda").to(td),
            "u": torch.rand((4, B, C, H, W), generator=g, device="cuda").to(td),
            "gy": torch.randn((B, C, H, W), generator=g, device="cuda").to(td)}
+    assert min(threads(shape, dtype, kchunk, logits, mask)) > 0
     fast = _run(G, inp, Gr, mask, kchunk, logits)
     monkeypatch.setenv("GSPN_FORCE_GENERIC", "1")
     ref = _run(G, inp, Gr, mask, kchunk, logits)
