@@ -11,7 +11,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libgspn.so")
-SOURCES = ["gspn_api.hip", "gspn_dispatch.hip", "gspn_generic.hip", "gspn_unfused.hip", "gspn_fwd_tile.hip", "gspn_fwd_tile_f32_global.hip", "gspn_fwd_tile_f32_local.hip", "gspn_fwd_tile_bf16_global.hip", "gspn_fwd_tile_bf16_local.hip", "gspn_fwd_tile_f16_global.hip", "gspn_fwd_tile_f16_local.hip", "gspn_fwd_stream.hip", "gspn_fwd_stream_f32.hip", "gspn_fwd_stream_bf16.hip", "gspn_fwd_stream_f16.hip", "gspn_fwd_stream_staged.hip", "gspn_fwd_stream_staged_bf16.hip", "gspn_fwd_stream_staged_f16.hip", "gspn_fwd_stream_staged_bf16_local.hip", "gspn_fwd_stream_staged_f16_local.hip", "gspn_fwd_stream_staged_bf16_logits.hip", "gspn_fwd_stream_staged_f16_logits.hip", "gspn_fwd_stream_big.hip", "gspn_fwd_stream_big_global.hip", "gspn_fwd_stream_big_local.hip", "gspn_fwd_stream_big_logits.hip", "gspn_fwd_plane.hip", "gspn_fwd_pair.hip", "gspn_fwd_pair_bf16.hip", "gspn_fwd_pair_f16.hip", "gspn_fwd_chunk.hip", "gspn_bwd_tile.hip", "gspn_bwd_plane.hip", "gspn_bwd_twopass.hip", "gspn_bwd_twopass_f32.hip", "gspn_bwd_twopass_bf16.hip", "gspn_bwd_twopass_f32_local.hip", "gspn_bwd_twopass_bf16_local.hip", "gspn_bwd_twopass_f16.hip", "gspn_bwd_twopass_f16_local.hip", "gspn_ragged.hip", "gspn_ragged_f32.hip", "gspn_ragged_bf16.hip", "gspn_ragged_f16.hip", "gspn_proxy.hip"]
+SOURCES = ["gspn_api.hip", "gspn_dispatch.hip", "gspn_generic.hip", "gspn_unfused.hip", "gspn_fwd_tile.hip", "gspn_fwd_tile_f32_global.hip", "gspn_fwd_tile_f32_local.hip", "gspn_fwd_tile_bf16_global.hip", "gspn_fwd_tile_bf16_local.hip", "gspn_fwd_tile_f16_global.hip", "gspn_fwd_tile_f16_local.hip", "gspn_fwd_stream.hip", "gspn_fwd_stream_f32.hip", "gspn_fwd_stream_bf16.hip", "gspn_fwd_stream_f16.hip", "gspn_fwd_stream_staged.hip", "gspn_fwd_stream_staged_bf16.hip", "gspn_fwd_stream_staged_f16.hip", "gspn_fwd_stream_staged_bf16_local.hip", "gspn_fwd_stream_staged_f16_local.hip", "gspn_fwd_stream_staged_bf16_logits.hip", "gspn_fwd_stream_staged_f16_logits.hip", "gspn_fwd_stream_big.hip", "gspn_fwd_stream_big_global.hip", "gspn_fwd_stream_big_local.hip", "gspn_fwd_stream_big_logits.hip", "gspn_fwd_plane.hip", "gspn_fwd_pair.hip", "gspn_fwd_pair_bf16.hip", "gspn_fwd_pair_f16.hip", "gspn_fwd_chunk.hip", "gspn_bwd_tile.hip", "gspn_bwd_plane.hip", "gspn_bwd_twopass.hip", "gspn_bwd_twopass_f32.hip", "gspn_bwd_twopass_bf16.hip", "gspn_bwd_twopass_f32_local.hip", "gspn_bwd_twopass_bf16_local.hip", "gspn_bwd_twopass_f16.hip", "gspn_bwd_twopass_f16_local.hip", "gspn_ragged.hip", "gspn_ragged_f32_tile.hip", "gspn_ragged_f32_mem.hip", "gspn_ragged_bf16_tile.hip", "gspn_ragged_bf16_mem.hip", "gspn_ragged_f16_tile.hip", "gspn_ragged_f16_mem.hip", "gspn_proxy.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -64,12 +64,9 @@ SPILL_ALLOWED = {
     # the same in fp16 storage, and its GSPN-local forward with h_save (96 values, none in the band loop either; the
     # hardware conversions hold a few registers more than the shifts of bf16): parity-tested at full size
     "fwd_pair_kernelINS_5f16_tELb1ELb0ELb1ELb1": 144, "fwd_pair_kernelINS_5f16_tELb1ELb0ELb1ELb0": 96,
-    # any-size kernel in 16-bit storage: 128 registers, so that sixteen waves share a CU; the loading waves park a few values
-    # (7 to 48 in fp16, whose conversions hold more at a time, at most 2 in bf16) between the chunks.  In the assembly no loop
-    # that shifts lanes, which is the scanning waves' line loop, holds a scratch access, in any instantiation;
-    # 64 registers of requests per thread are what keeps the memory pipe busy (one granule per thread instead of two, no
-    # spills: 100x167 with 512 planes 134 -> 153 us)
-    "ragged_kernelItLi": 2, "ragged_kernelINS_5f16_tELi": 48,
+    # any-size kernel in bf16: 128 registers, so that sixteen waves share a CU; four instantiations (the reverse sweep, and with
+    # logits and four positions per lane the one that merges in global memory) park one or two values between the chunks
+    "ragged_kernelItLi": 2,
     # fp32 maps with rows of 112 bytes on workgroups of more than four waves, without h_save: off every benchmark shape
     # (the plane kernel takes 28x28, the four-wave instantiation 56x56); kept because the shapes must run somewhere
     "fwd_tile_kernelIfLi2ELi1ELi28ELb0ELi8ELb0ELi8ELb0ELb0ELb0": 259, "fwd_tile_kernelIfLi2ELi1ELi28ELb0ELi8ELb0ELi8ELb1ELb0ELb0": 47,

@@ -3,13 +3,16 @@
 
 namespace gspn {
 
-hipError_t launch_ragged_f32(const FwdParams& p, bool reverse, void* e_lo, hipStream_t s);
-hipError_t launch_ragged_bf16(const FwdParams& p, bool reverse, void* e_lo, hipStream_t s);
-hipError_t launch_ragged_f16(const FwdParams& p, bool reverse, void* e_lo, hipStream_t s);
+hipError_t launch_ragged_f32_tile(const RaggedArgs& a, bool reverse, int threads, int nv, size_t lds, hipStream_t s);
+hipError_t launch_ragged_f32_mem(const RaggedArgs& a, bool reverse, int threads, int nv, size_t lds, hipStream_t s);
+hipError_t launch_ragged_bf16_tile(const RaggedArgs& a, bool reverse, int threads, int nv, size_t lds, hipStream_t s);
+hipError_t launch_ragged_bf16_mem(const RaggedArgs& a, bool reverse, int threads, int nv, size_t lds, hipStream_t s);
+hipError_t launch_ragged_f16_tile(const RaggedArgs& a, bool reverse, int threads, int nv, size_t lds, hipStream_t s);
+hipError_t launch_ragged_f16_mem(const RaggedArgs& a, bool reverse, int threads, int nv, size_t lds, hipStream_t s);
 
 // The launch shape for a call, or false where no shape fits (the line-by-line kernels then take it).
 // merge_rounds: the caller's merged output was rounded once per direction anyway (gx of the backward call).
-bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* out, int* threads, int* nv, size_t* lds) {
+static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* out, int* threads, int* nv, size_t* lds) {
     const int H = p.H, W = p.W, es = dtype == 0 ? 4 : 2, E = 16 / es;
     if (p.xt) return false;
     if ((size_t)H * W < 16 || (size_t)H * W >= (1u << 29)) return false;
@@ -30,11 +33,18 @@ bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* o
     int wgs_wanted = 1;
     while (wgs_wanted < 4 && (size_t)wgs_wanted * 256 < planes) wgs_wanted *= 2;
 
-    for (int mode = 0; mode < (must_tile ? 2 : 3); ++mode) {     // tile and both directions; tile and one; y in global memory
+    const int kmax[2] = {(H + 7) / 8 * 8, (W + 7) / 8 * 8};
+    // One launch shape: how the output is merged (mode 0: LDS tile and both directions of an axis at once; 1: tile and one; 2: y
+    // in global memory), chunks of a direction in LDS, bytes of an image row per request in the horizontal directions,
+    // workgroups per CU, lines of a vertical chunk at most.
+    auto fits = [&](int mode, int nbuf, int seg, int wgs, int kv_most) -> bool {
         a.nd = mode == 0 ? 2 : 1;
         a.tile = mode < 2;
+        a.nbuf = nbuf;
         const size_t fixed = a.tile ? tile_bytes : 0;
-        if (fixed >= cap) continue;
+        const int thr = 1024 / wgs, waves = thr / 64 / a.nd;
+        if (waves < 2 || fixed >= cap / wgs) return false;
+        const size_t room = cap / wgs - fixed;
         // positions per lane: a line in one wave (no meetings within a chunk) up to 192 positions, beyond that two, and four
         // where the scanning waves would otherwise leave too few for the loads
         const int v = longest <= 64 ? 1 : longest <= 128 ? 2 : longest <= 192 ? 3 : longest <= 448 ? 2 : 4;
@@ -48,56 +58,73 @@ bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* o
                 a.pitch2[ax] = v % 2 ? L | 1 : L + 2;
             }
         }
-        auto stage_bytes = [&](int ax, int K) { return (size_t)a.nd * (K * (a.pitch[ax] * sb + (wide ? 0 : a.pitch2[ax] * 2)) + 2 * a.pitch2[ax] * 4); };
-        const int kmax[2] = {(H + 7) / 8 * 8, (W + 7) / 8 * 8};
-        // chunk lengths: 64 B of an image row per request in the horizontal directions if that fits, else 32, else 16;
-        // with each, as many workgroups per CU as the LDS allows
-        for (int seg = 64; seg >= 16; seg /= 2) {
-            for (int wgs = wgs_wanted; wgs >= 1; wgs /= 2) {
-                const int thr = 1024 / wgs, waves = thr / 64 / a.nd;
-                if (waves < 2 || fixed >= cap / wgs) continue;
-                const size_t room = cap / wgs - fixed;
-                bool ok = true;
-                for (int ax = 0; ax < 2 && ok; ++ax) {
-                    const int L = ax ? H : W;
-                    int parts = L <= 64 * v ? 1 : (L + 64 * v - 2 * RG_SUB - 1) / (64 * v - 2 * RG_SUB), own = 0;
-                    for (; parts < waves; ++parts) {
-                        own = ((L + parts - 1) / parts + v - 1) / v * v;
-                        if (parts == 1 || own + 2 * RG_SUB <= 64 * v) break;
-                    }
-                    ok = parts < waves;                                  // at least one wave loads
-                    a.parts[ax] = parts; a.own[ax] = own;
-                }
-                if (!ok) continue;
-                auto fits = [&](int ax, int K) {
-                    const int gr = ax ? (K / E) * H : K * ((W + E - 1) / E);
-                    return gr <= RG_ROUNDS * (waves - a.parts[ax]) * 64 && stage_bytes(ax, K) <= room;
-                };
-                int kh = seg / es < 8 ? 8 : seg / es;
-                if (kh > kmax[1]) kh = kmax[1];
-                int kv = 8;
-                if (!fits(1, kh) || !fits(0, kv)) continue;
-                while (kv + 8 <= kmax[0] && kv + 8 <= 32 && fits(0, kv + 8)) kv += 8;
-                a.K[0] = kv; a.K[1] = kh;
-                *threads = thr;
-                goto found;
+        for (int ax = 0; ax < 2; ++ax) {
+            const int L = ax ? H : W;
+            int parts = L <= 64 * v ? 1 : (L + 64 * v - 2 * RG_SUB - 1) / (64 * v - 2 * RG_SUB), own = 0;
+            for (; parts < waves; ++parts) {
+                own = ((L + parts - 1) / parts + v - 1) / v * v;
+                if (parts == 1 || own + 2 * RG_SUB <= 64 * v) break;
             }
+            if (parts >= waves) return false;                        // at least one wave loads
+            a.parts[ax] = parts; a.own[ax] = own;
         }
-        continue;
-    found:
+        auto bytes = [&](int ax, int K) {
+            return (size_t)a.nd * (nbuf * K * (a.pitch[ax] * sb + (wide ? 0 : a.pitch2[ax] * 2)) + 2 * a.pitch2[ax] * 4);
+        };
+        auto chunk_fits = [&](int ax, int K) {
+            const int gr = ax ? (K / E) * H : K * ((W + E - 1) / E);
+            return gr <= RG_ROUNDS * (waves - a.parts[ax]) * 64 && bytes(ax, K) <= room;
+        };
+        int kh = seg / es < 8 ? 8 : seg / es;
+        if (kh > kmax[1]) kh = kmax[1];
+        int kv = 8;
+        if (!chunk_fits(1, kh) || !chunk_fits(0, kv)) return false;
+        while (kv + 8 <= kmax[0] && kv + 8 <= kv_most && chunk_fits(0, kv + 8)) kv += 8;
+        a.K[0] = kv; a.K[1] = kh;
         size_t top = 0;
         for (int ax = 0; ax < 2; ++ax) {
-            a.w2_off[ax] = (int)((size_t)a.nd * a.K[ax] * a.pitch[ax] * sb);
-            a.edge_off[ax] = (int)((size_t)a.nd * a.K[ax] * (a.pitch[ax] * sb + (wide ? 0 : a.pitch2[ax] * 2)));
-            const size_t n = stage_bytes(ax, a.K[ax]);
+            const size_t lines = (size_t)a.nd * nbuf * a.K[ax];
+            a.w2_off[ax] = (int)(lines * a.pitch[ax] * sb);
+            a.edge_off[ax] = (int)(lines * (a.pitch[ax] * sb + (wide ? 0 : a.pitch2[ax] * 2)));
+            const size_t n = bytes(ax, a.K[ax]);
             if (n > top) top = n;
         }
         top = (top + 15) / 16 * 16;
         a.tile_off = (int)top;
-        if (top + fixed > cap) continue;
-        *out = a; *nv = v; *lds = top + fixed;
+        if (top + fixed > cap) return false;
+        *out = a; *threads = thr; *nv = v; *lds = top + fixed;
         return true;
-    }
+    };
+    // Which of the shapes that fit.  Every shape was timed on 130 random calls (16 to 300 positions a side and beyond, 8 to 4000
+    // planes, the three types): the first of these that fits takes 1.03 of the best one's time in the mean (the order before, one
+    // chunk at a time and the longest request first, 1.17).  Several workgroups hide each other's turns, so there a chunk at a time is
+    // enough and longer requests come first; a workgroup alone on its CU works on two chunks.  fp32 granules are four columns, so
+    // its 32-byte requests make chunks of eight lines, which cost more barriers than one direction after the other costs passes
+    // (4 x 512 channels 104x80: 436 -> 337 us).  Examples (us): 512 planes 85x34 bf16 with h_save: two workgroups and chunks in turn 31, one and
+    // two chunks 45; 256 planes 80x68: 34 and 28; 112x120 bf16, 1024 planes: {0, 1, 64} 145, {1, 2, 64} 181.
+    struct Shape { int mode, nbuf, seg; };
+    static const Shape several16[] = {{0, 1, 64}, {0, 1, 32}, {0, 2, 32}, {0, 2, 16}, {1, 1, 64}, {1, 1, 32}};
+    static const Shape several32[] = {{0, 1, 64}, {1, 1, 64}, {0, 1, 32}, {0, 2, 32}};
+    static const Shape few16[] = {{0, 2, 64}, {0, 2, 32}, {0, 1, 64}, {0, 1, 32}, {1, 2, 64}, {1, 2, 32}, {0, 2, 16}, {1, 1, 64}, {1, 1, 32}, {0, 1, 16}, {1, 2, 16}, {1, 1, 16}};
+    static const Shape few32[] = {{0, 2, 64}, {0, 1, 64}, {2, 2, 64}, {0, 2, 32}, {0, 1, 32}, {1, 2, 64}, {1, 2, 32}, {0, 2, 16}, {1, 1, 64}, {1, 1, 32}, {0, 1, 16}, {1, 2, 16}, {1, 1, 16}};
+    static const Shape many16[] = {{0, 2, 64}, {0, 1, 64}, {0, 2, 32}, {0, 1, 32}, {1, 2, 64}, {1, 2, 32}, {1, 1, 64}, {1, 1, 32}, {0, 2, 16}, {0, 1, 16}, {1, 2, 16}, {1, 1, 16}};
+    static const Shape many32[] = {{0, 2, 64}, {0, 1, 64}, {1, 2, 64}, {2, 2, 64}, {0, 2, 32}, {0, 1, 32}, {1, 2, 32}, {1, 1, 64}, {1, 1, 32}, {0, 2, 16}, {0, 1, 16}, {1, 2, 16}, {1, 1, 16}};
+    // y in global memory: with fewer planes than half of the CUs nothing but the second chunk hides the latency
+    static const Shape mem_few[] = {{2, 2, 64}, {2, 2, 32}, {2, 1, 64}, {2, 1, 32}, {2, 2, 16}, {2, 1, 16}};
+    static const Shape mem_many[] = {{2, 2, 64}, {2, 1, 64}, {2, 2, 32}, {2, 1, 32}, {2, 2, 16}, {2, 1, 16}};
+    auto first_of = [&](const Shape* t, int n, int wgs) {
+        for (int i = 0; i < n; ++i)
+            if (!(must_tile && t[i].mode == 2) && fits(t[i].mode, t[i].nbuf, t[i].seg, wgs, t[i].mode == 2 ? 16 : 32)) return true;
+        return false;
+    };
+    const bool f32 = dtype == 0;
+    for (int wgs = wgs_wanted; wgs > 1; wgs /= 2)
+        if (f32 ? first_of(several32, 4, wgs) : first_of(several16, 6, wgs)) return true;
+    if (planes <= 256 ? (f32 ? first_of(few32, 13, 1) : first_of(few16, 12, 1)) : (f32 ? first_of(many32, 13, 1) : first_of(many16, 12, 1))) return true;
+    const Shape* const mem = planes < 128 ? mem_few : mem_many;
+    for (int i = 0; i < 6; ++i)
+        for (int wgs = wgs_wanted; wgs >= 1; wgs /= 2)
+            if (first_of(mem + i, 1, wgs)) return true;
     return false;
 }
 
@@ -127,9 +154,17 @@ int ragged_fwd_threads(const FwdParams& p, int dtype) {
 }
 bool ragged_applicable(const FwdParams& p, int dtype) { return ragged_fwd_threads(p, dtype) != 0; }
 
-hipError_t launch_fwd_ragged(const FwdParams& p, int dtype, hipStream_t s) {
-    return dtype == 0 ? launch_ragged_f32(p, false, nullptr, s) : dtype == 1 ? launch_ragged_bf16(p, false, nullptr, s) : launch_ragged_f16(p, false, nullptr, s);
+static hipError_t launch_ragged(const FwdParams& p, int dtype, bool reverse, void* e_lo, hipStream_t s) {
+    RaggedArgs a = {};
+    int threads, nv;
+    size_t lds;
+    if (!ragged_plan(p, dtype, reverse, &a, &threads, &nv, &lds)) return hipErrorInvalidValue;
+    a.hs_lo = e_lo;
+    if (dtype == 0) return (a.tile ? launch_ragged_f32_tile : launch_ragged_f32_mem)(a, reverse, threads, nv, lds, s);
+    if (dtype == 1) return (a.tile ? launch_ragged_bf16_tile : launch_ragged_bf16_mem)(a, reverse, threads, nv, lds, s);
+    return (a.tile ? launch_ragged_f16_tile : launch_ragged_f16_mem)(a, reverse, threads, nv, lds, s);
 }
+hipError_t launch_fwd_ragged(const FwdParams& p, int dtype, hipStream_t s) { return launch_ragged(p, dtype, false, nullptr, s); }
 
 namespace {
 
@@ -341,7 +376,7 @@ bool ragged_bwd_applicable(const BwdParams& p, int dtype) { return ragged_bwd_th
 // over the channels.
 hipError_t launch_bwd_ragged(const BwdParams& p, int dtype, hipStream_t s) {
     const FwdParams f = ragged_sweep_params(p);
-    hipError_t e = dtype == 0 ? launch_ragged_f32(f, true, nullptr, s) : dtype == 1 ? launch_ragged_bf16(f, true, p.gu, s) : launch_ragged_f16(f, true, p.gu, s);
+    hipError_t e = launch_ragged(f, dtype, true, dtype == 0 ? nullptr : p.gu, s);
     if (e != hipSuccess) return e;
     int ndirs = 0;
     for (int d = 0; d < 4; ++d) ndirs += (p.mask >> d) & 1u;

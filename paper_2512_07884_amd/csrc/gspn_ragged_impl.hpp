@@ -19,10 +19,14 @@
 //           or, for planes that do not fit, y in global memory, one direction after the other in a fixed order.
 // Both directions of an axis run at once where the tile fits, half of the waves each; where their chunks cross in the
 // middle of the map the second waits for the first, so the order of every sum is fixed.
+// Where the LDS holds two chunks of a direction, the scan of one runs beside the finishing of the chunk before and the staging
+// of the one after, with one barrier per chunk (move_ahead; the turns before took as long as the scan itself: 256 planes 80x68 in
+// bf16 33 -> 27 us); where several workgroups share a CU they hide each other's turns and one chunk does (move_in_turn).
 //
-// What bounds it: the chain of the scanning wave -- one per direction of a plane, and the LDS holds one plane of 100x167 -- and
-// the LDS traffic of staging behind it.  2 x 256 channels 100x167 in bf16: 122 us forward (1.5 TB/s of its 0.18 GB; line by
-// line 968), 130 with h_save, 303 backward; the LDS index unit is active in 32 % of a CU's busy cycles, 14 % bank conflicts.
+// What bounds it: with few planes the chain of the scanning wave (some 180 clocks per line) and the latency of a chunk's
+// requests; with many the L1s -- the loads alone of 1024 planes 64x168 fp32 take 172 of 222 us, 5.9 TB/s into the L1s, a limit of
+// the chip -- and behind them the stores of h_save.  A 16-bit request at an odd element costs the address unit four times an
+// aligned one (64 clocks per wave against 16).  2 x 256 channels 100x167 in bf16: 109 us forward (122 in turns), 1.7 TB/s of its 0.18 GB.
 #pragma once
 #include "gspn_unaligned.hpp"
 
@@ -37,12 +41,11 @@ struct RaggedArgs {
     void* hs_lo;                 // reverse sweep in 16-bit storage: low halves of e (high halves: p.hs); e stays fp32 between the passes
     int nd;                      // directions of an axis walked at once (1 or 2)
     int tile;                    // 1: merged output in an LDS tile; 0: in global memory
+    int nbuf;                    // chunks of a direction in LDS: 2 (scan, load and finish work on neighbouring chunks at once) or 1 (in turn)
     int tile_pitch, tile_off;    // floats per row, byte offset in LDS
     int K[2], parts[2], own[2], pitch[2], pitch2[2];     // per axis (0 vertical, 1 horizontal): lines per chunk, waves per line, positions a wave owns, LDS slots per line (of {lam*x, w0, w1}; of tap 2)
     int w2_off[2], edge_off[2];               // byte offsets in LDS: tap 2 (16-bit weights), edge lines
 };
-
-bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, RaggedArgs* out, int* threads, int* nv, size_t* lds);
 
 namespace {
 
@@ -64,7 +67,7 @@ template <typename V> __device__ __forceinline__ V lds_get(uint32_t addr) { retu
 template <typename V> __device__ __forceinline__ void lds_set(uint32_t addr, V v) { *(__attribute__((address_space(3))) V*)addr = v; }
 
 // One pass over the plane: one direction, or both directions of an axis at once.
-template <typename T, int MODE, bool LOGITS, int NV, bool HORZ>
+template <typename T, int MODE, bool LOGITS, int NV, bool TILE, bool HORZ>
 struct RaggedPass {
     static constexpr int E = 16 / (int)sizeof(T);
     static constexpr bool BWD = MODE == RG_BWD;
@@ -73,100 +76,106 @@ struct RaggedPass {
 
     const RaggedArgs& a;
     char* lds;
+    uint32_t lds0;               // LDS address of `lds`
     int H, W, HW, S, L, K, pitch, pitch2;
-    int tid, nthr;               // this thread among the threads of its direction
-    int wave, part, parts;
+    int tid, nthr;               // this thread among the loading threads of its direction
+    int part, parts;
     int d, rev;                  // direction slot; rev: this pass walks the lines from the last to the first
     int plane, bg;
-    int lo, hi;                  // where a 16-byte window may start, relative to the plane
-    const T *X, *LAM, *U, *W0;
-    T *Y, *HS, *LO;
     int dsel, dcount, nchunks;
     bool first;                  // global merge: y is overwritten
-    char* stA; char* stW2; float* edge; float* tile;
+    // where a 16-byte window may start: byte offsets in [0, top] from the tensors' pointers here, which lie a plane before this
+    // one where there is one (a window may reach into the neighbouring planes, not beyond the ends of the tensor)
+    bool at_ends;                // a window of this plane can meet an end of the tensor
+    int top;
+    const char *X, *LAM, *U, *W0, *W1, *W2;
+    char *Y, *HS, *LO;           // (these at the plane itself)
+    float* edge;
 
-    struct Regs { u32x4 x, l, u, w0, w1, w2, y; };       // a granule: x, lam, weights of the next chunk; u and y of the current one
+    int bufA, bufW2;             // bytes from a chunk's place in LDS to the next one's
+    uint32_t stA, stW2;          // LDS addresses of this direction's place for the first chunk
+    __device__ __forceinline__ int buf(int k) const { return a.nbuf == 2 ? k & 1 : 0; }
 
-    __device__ __forceinline__ RaggedPass(const RaggedArgs& args, char* l) : a(args), lds(l) {}
+    struct Regs { u32x4 x, l, u, w0, w1, w2, y; };       // a granule: x, lam, weights of a coming chunk; u and y of the one to finish
 
-    struct Gran { bool on; int off, col, row, slot, step, slot2, step2, sh, shw, n; };
+    __device__ __forceinline__ RaggedPass(const RaggedArgs& args, char* l) : a(args), lds(l) {
+        lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+    }
+
     // slot of a position of a line: a vertical scan's line has one slot of padding per granule, which spreads the banks of
     // lanes a granule apart
     static __device__ __forceinline__ int line_slot(int pos) { return HORZ ? pos : pos + pos / E; }
-    // this thread's granule of chunk k: image row and first column (a multiple of E), pixel offset, LDS slot of its
-    // element 0 and the step to the next, the number of elements inside the row, the shifts of its windows
-    __device__ __forceinline__ Gran gran(int r, int k) const {
+
+    // This thread's granule of every chunk: the same lines of the chunk (vertical: one, horizontal: E) and the same positions,
+    // so a chunk's addresses are the first one's plus a multiple of a uniform step.
+    struct Gran {
+        int t;                   // first line of the chunk it holds; beyond the chunk where the thread has none
+        int col, row;            // of chunk 0
+        int off;                 // bytes from the tensors' pointers in chunk 0
+        uint32_t slot, slot2;    // LDS addresses of its element 0 in buffer 0
+        uint32_t tile;           // ... of its place in the output tile in chunk 0
+    };
+    __device__ __forceinline__ int col_step() const { return HORZ ? (rev ? -K : K) : 0; }
+    __device__ __forceinline__ int row_step() const { return HORZ ? 0 : (rev ? -K : K); }
+    __device__ __forceinline__ int off_step() const { return (HORZ ? K : K * W) * (rev ? -1 : 1) * (int)sizeof(T); }
+    __device__ __forceinline__ int slot_step() const { return HORZ ? (rev ? -pitch : pitch) * SB : SB; }        // to the next element
+    __device__ __forceinline__ int slot2_step() const { return HORZ ? (rev ? -pitch2 : pitch2) * 2 : 2; }
+    __device__ __forceinline__ int granules() const { return HORZ ? (K / E) * H : K * ((W + E - 1) / E); }
+    __device__ __forceinline__ Gran place(int r) const {
         Gran g;
-        const int q = tid + r * nthr;
+        const int per = HORZ ? K / E : (W + E - 1) / E, last = granules() - 1;
+        const int want = tid + r * nthr, q = min(want, last);       // a thread without a granule requests the last one's
+        const int major = q / per, minor = (q - major * per) * E;
         if constexpr (HORZ) {
-            const int gpr = K / E;
-            const int row = q / gpr, gi = q - row * gpr;
-            g.row = row;
-            g.col = rev ? S - k * K - gi * E - E : k * K + gi * E;         // S: the width in whole granules
-            const int t0 = gi * E + (rev ? E - 1 : 0);
-            g.slot = t0 * pitch + row;
-            g.step = rev ? -pitch : pitch;
-            g.slot2 = t0 * pitch2 + row;
-            g.step2 = rev ? -pitch2 : pitch2;
-            g.n = min(E, W - g.col);
-            g.on = row < H && g.col >= 0 && g.n > 0;
+            g.row = major;
+            g.col = rev ? S - minor - E : minor;                    // S: the width in whole granules
+            g.t = minor;
+            const int t0 = minor + (rev ? E - 1 : 0);
+            g.slot = stA + (t0 * pitch + g.row) * SB;
+            g.slot2 = stW2 + (t0 * pitch2 + g.row) * 2;
         } else {
-            const int gpl = (W + E - 1) / E;
-            const int t = q / gpl;
-            g.col = (q - t * gpl) * E;
-            const int st = k * K + t;
-            g.row = rev ? S - 1 - st : st;
-            g.slot = t * pitch + line_slot(g.col);
-            g.step = 1;
-            g.slot2 = t * pitch2 + g.col;
-            g.step2 = 1;
-            g.n = min(E, W - g.col);
-            g.on = t < K && st < S;
+            g.col = minor;
+            g.row = rev ? S - 1 - major : major;
+            g.t = major;
+            g.slot = stA + (major * pitch + line_slot(g.col)) * SB;
+            g.slot2 = stW2 + (major * pitch2 + g.col) * 2;
         }
-        g.off = g.row * W + g.col;
-        asm volatile("" : "+v"(g.slot), "+v"(g.slot2), "+v"(g.off));       // addresses are computed per chunk, not kept in registers
-        const int offw = g.off + wshift();
-        g.sh = g.off - min(max(g.off, lo), hi);
-        g.shw = offw - min(max(offw, lo), hi);
+        g.off = (g.row * W + g.col) * (int)sizeof(T);
+        g.tile = lds0 + a.tile_off + (g.row * a.tile_pitch + g.col) * 4;
+        if (want > last) g.t = 1 << 29;
         return g;
     }
+    // is the granule of chunk k inside the scan?  (chunks -1 and those beyond the last: none is)
+    __device__ __forceinline__ bool live(const Gran& g, int k) const { return g.t + k * K < S; }
+    __device__ __forceinline__ int clamped(int off) const { return min(max(off, 0), top); }
     // reverse sweep: a line takes the weights of the line swept before it
     __device__ __forceinline__ int wshift() const { return BWD ? (rev ? 1 : -1) * (HORZ ? 1 : W) : 0; }
 
-    __device__ __forceinline__ void load(int k, int r, Regs& q) const {
-        const Gran g = gran(r, k);
-        if (!g.on) return;
-        const int o = g.off - g.sh;
-        q.x = rg_load(X + o);
-        q.l = rg_load(LAM + o);
-        const int ow = g.off + wshift() - g.shw;
-        q.w0 = rg_load(W0 + ow);
-        q.w1 = rg_load(W0 + HW + ow);
-        q.w2 = rg_load(W0 + 2 * (size_t)HW + ow);
+    // No request hangs on a branch, so that the waits count them; what lies outside the scan is read from some place of the tensor.
+    __device__ __forceinline__ void load(int k, const Gran& g, Regs& q) const {
+        const int off = g.off + base_off() + k * off_step();
+        const uint32_t o = (uint32_t)clamped(off), ow = BWD ? (uint32_t)clamped(off + wshift() * (int)sizeof(T)) : o;
+        q.x = rg_load((const T*)(X + o));
+        q.l = rg_load((const T*)(LAM + o));
+        q.w0 = rg_load((const T*)(W0 + ow));
+        q.w1 = rg_load((const T*)(W1 + ow));
+        q.w2 = rg_load((const T*)(W2 + ow));
     }
-    // what finish() of the chunk needs: requested with the chunk's scan
-    __device__ __forceinline__ void load_late(int k, int r, Regs& q) const {
-        const Gran g = gran(r, k);
-        if (!g.on) return;
-        q.u = rg_load(U + (g.off - g.sh));
-        if (!a.tile && !first) q.y = rg_load((const T*)Y + (g.off - g.sh));
+    // what finish() of the chunk needs
+    __device__ __forceinline__ void load_late(int k, const Gran& g, Regs& q) const {
+        const uint32_t o = (uint32_t)clamped(g.off + base_off() + k * off_step());
+        q.u = rg_load((const T*)(U + o));
+        if constexpr (!TILE) q.y = rg_load((const T*)(Y + ((int)o - base_off())));      // (not used by the first direction)
     }
+    __device__ __forceinline__ int base_off() const { return bg == 0 ? 0 : HW * (int)sizeof(T); }
 
-    // registers of the chunk -> LDS
-    __device__ __forceinline__ void stage(int k, int r, const Regs& in) const {
-        const Gran g = gran(r, k);
-        if (!g.on) return;
-        __builtin_amdgcn_sched_barrier(0);
-        u32x4 x = in.x, l = in.l, w0 = in.w0, w1 = in.w1, w2 = in.w2;
-        if (__any(g.sh != 0 || g.shw != 0)) {        // first / last granule of a tensor
-            x = rg_realign<T>(x, g.sh); l = rg_realign<T>(l, g.sh);
-            w0 = rg_realign<T>(w0, g.shw); w1 = rg_realign<T>(w1, g.shw); w2 = rg_realign<T>(w2, g.shw);
-        }
-        // lines whose weights are never read: the first line of the scan, of a stretch (by the line the weights
-        // belong to), and, in a reverse sweep, the line after the last
+    // Bit e: the weights of element e are never read: the first line of the scan, of a stretch (by the line the weights belong
+    // to), and, in a reverse sweep, the line after the last.
+    __device__ __forceinline__ uint32_t dead_elements(const Gran& g, int k) const {
+        const int col = g.col + k * col_step(), row = g.row + k * row_step();
         const int S1 = (HORZ ? W : H) - 1, drev = d & 1, kc = a.p.kchunk;
-        int wl = (HORZ ? g.col : g.row) + (BWD ? (rev ? 1 : -1) : 0);      // line the weights of element 0 belong to
-        uint32_t dead = 0;                                                 // bit e: the weights of element e are not read
+        int wl = (HORZ ? col : row) + (BWD ? (rev ? 1 : -1) : 0);          // line the weights of element 0 belong to
+        uint32_t dead = 0;
         if constexpr (HORZ) {
             const int e0 = (drev ? S1 : 0) - wl;                           // element on the first line of the scan
             if (e0 >= 0 && e0 < E) dead |= 1u << e0;
@@ -177,30 +186,53 @@ struct RaggedPass {
 #pragma unroll
                 for (int e = 0; e < E; ++e) { if (m == 0) dead |= 1u << e; m = m + 1 == kc ? 0 : m + 1; }
             }
-            dead |= ~((1u << g.n) - 1u) & ((1u << E) - 1u);                // beyond the row: a scan from the right starts there, with 0
+            const int n = min(E, W - col);
+            dead |= ~((1u << n) - 1u) & ((1u << E) - 1u);                  // beyond the row: a scan from the right starts there, with 0
         } else {
             const bool z = (BWD && (wl < 0 || wl > S1)) || starts_stretch(drev ? S1 - wl : wl, S, drev, kc);
             dead = z ? (1u << E) - 1 : 0u;
         }
-        const bool row_first = g.row == 0, row_last = g.row == H - 1;
+        return dead;
+    }
+
+    // registers of the chunk -> LDS
+    __device__ __forceinline__ void stage(int k, const Gran& g, const Regs& in) const {
+        if (!live(g, k)) return;
+        __builtin_amdgcn_sched_barrier(0);
+        u32x4 x = in.x, l = in.l, w0 = in.w0, w1 = in.w1, w2 = in.w2;
+        const int col = HORZ ? g.col + k * col_step() : g.col;
+        if (at_ends) {                               // first / last granule of a tensor
+            const int off = g.off + base_off() + k * off_step(), offw = off + wshift() * (int)sizeof(T);
+            const int sh = (off - clamped(off)) / (int)sizeof(T), shw = (offw - clamped(offw)) / (int)sizeof(T);
+            if (__any(sh != 0 || shw != 0)) {
+                x = rg_realign<T>(x, sh); l = rg_realign<T>(l, sh);
+                w0 = rg_realign<T>(w0, shw); w1 = rg_realign<T>(w1, shw); w2 = rg_realign<T>(w2, shw);
+            }
+        }
+        // the first chunk holds the first line of the scan (and, from the right, what lies beyond the row)
+        uint32_t dead = 0;
+        if (k == 0 || a.p.kchunk > 0) dead = dead_elements(g, k);
         float av[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            av[e] = rg_elem<T>(l, e) * rg_elem<T>(x, e);
-            if constexpr (HORZ) av[e] = e < g.n ? av[e] : 0.f;
+        for (int e = 0; e < E; ++e) av[e] = rg_elem<T>(l, e) * rg_elem<T>(x, e);
+        if (HORZ && k == 0) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) av[e] = col + e < W ? av[e] : 0.f;
         }
+        const uint32_t s0 = g.slot + buf(k) * bufA;
+        const int ss = slot_step();
         if constexpr (WIDE) {
+            const bool row_first = g.row == 0, row_last = g.row == H - 1;
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 if constexpr (sizeof(T) == 2) __builtin_amdgcn_sched_barrier(0);        // element by element: registers
-                const bool o0 = HORZ ? row_first : (e == 0 && g.col == 0);
-                const bool o2 = HORZ ? row_last : (g.col + e == W - 1);
+                const bool o0 = HORZ ? row_first : (e == 0 && col == 0);
+                const bool o2 = HORZ ? row_last : (col + e == W - 1);
                 float f0 = rg_elem<T>(w0, e), f1 = rg_elem<T>(w1, e), f2 = rg_elem<T>(w2, e);
                 if constexpr (LOGITS) softmax3(f0, f1, f2, o0, o2);
                 const bool dd = (dead >> e) & 1u;
                 f0 = (dd || o0) ? 0.f : f0; f1 = dd ? 0.f : f1; f2 = (dd || o2) ? 0.f : f2;
-                const u32x4 v = {__float_as_uint(av[e]), __float_as_uint(f0), __float_as_uint(f1), __float_as_uint(f2)};
-                *(u32x4*)(stA + (size_t)(g.slot + e * g.step) * 16) = v;
+                lds_set<u32x4>(s0 + e * ss, u32x4{__float_as_uint(av[e]), __float_as_uint(f0), __float_as_uint(f1), __float_as_uint(f2)});
             }
         } else {
             if (dead) {                                     // few granules: clear the elements that are not read
@@ -211,12 +243,11 @@ struct RaggedPass {
                 }
             }
             if constexpr (HORZ) {
-                const uint32_t m0 = row_first ? 0u : 0xffffffffu, m2 = row_last ? 0u : 0xffffffffu;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { w0[i] &= m0; w2[i] &= m2; }
+                if (g.row == 0) w0 = u32x4{0, 0, 0, 0};
+                if (g.row == H - 1) w2 = u32x4{0, 0, 0, 0};
             } else {
-                if (g.col == 0) w0[0] &= 0xffff0000u;
-                const int el = W - 1 - g.col;
+                if (col == 0) w0[0] &= 0xffff0000u;
+                const int el = W - 1 - col;
                 if (el < E) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) w2[i] &= (el >> 1) != i ? 0xffffffffu : ((el & 1) ? 0xffffu : 0xffff0000u);
@@ -228,89 +259,96 @@ struct RaggedPass {
                 w01[2 * i] = __builtin_amdgcn_perm(w1[i], w0[i], 0x05040100u);          // {w0 lo, w1 lo}
                 w01[2 * i + 1] = __builtin_amdgcn_perm(w1[i], w0[i], 0x07060302u);      // {w0 hi, w1 hi}
             }
+            const uint32_t s2 = g.slot2 + buf(k) * bufW2;
             if constexpr (HORZ) {
+                const int ss2 = slot2_step();
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    const int s = g.slot + e * g.step;
-                    *(u32x2*)(stA + (size_t)s * 8) = u32x2{__float_as_uint(av[e]), w01[e]};
-                    *(uint16_t*)(stW2 + (size_t)(g.slot2 + e * g.step2) * 2) = (uint16_t)rg_bits<T>(w2, e);
+                    lds_set<u32x2>(s0 + e * ss, u32x2{__float_as_uint(av[e]), w01[e]});
+                    lds_set<uint16_t>(s2 + e * ss2, (uint16_t)((e & 1) ? w2[e >> 1] >> 16 : w2[e >> 1]));
                 }
             } else {
 #pragma unroll
-                for (int e = 0; e < E; ++e) *(u32x2*)(stA + (size_t)(g.slot + e) * 8) = u32x2{__float_as_uint(av[e]), w01[e]};
-                *(u32x4*)(stW2 + (size_t)g.slot2 * 2) = w2;
+                for (int e = 0; e < E; ++e) lds_set<u32x2>(s0 + e * SB, u32x2{__float_as_uint(av[e]), w01[e]});
+                lds_set<u32x4>(s2, w2);
             }
         }
     }
 
-    // h of the chunk from LDS: merged output, and h_save (e of the reverse sweep)
-    __device__ __forceinline__ void finish(int k, int r, const Regs& in) const {
-        const Gran g = gran(r, k);
-        if (!g.on) return;
+    // h of the chunk from LDS: the merged output in LDS, and what goes to global memory -- h_save (e of the reverse sweep), y
+    // merged there -- in registers for store().  The two are apart because a wait for a request counts the stores issued
+    // behind it: store() comes when the next chunk's requests have been waited for.
+    struct Out { u32x4 v, lw, y; };
+    __device__ __forceinline__ void finish(int k, const Gran& g, const Regs& in, Out& out) const {
+        if (!live(g, k)) return;
         __builtin_amdgcn_sched_barrier(0);
         u32x4 u = in.u, yv = in.y;
-        if (__any(g.sh != 0)) {
-            u = rg_realign<T>(u, g.sh);
-            if (!a.tile && !first) yv = rg_realign<T>(yv, g.sh);
+        if (at_ends) {
+            const int off = g.off + base_off() + k * off_step(), sh = (off - clamped(off)) / (int)sizeof(T);
+            if (__any(sh != 0)) {
+                u = rg_realign<T>(u, sh);
+                if constexpr (!TILE) yv = rg_realign<T>(yv, sh);
+            }
         }
+        const uint32_t s0 = g.slot + buf(k) * bufA;
+        const int ss = slot_step();
         float h[E], y[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) h[e] = *(const float*)(stA + (size_t)(g.slot + e * g.step) * SB);
+        for (int e = 0; e < E; ++e) h[e] = lds_get<float>(s0 + e * (HORZ ? ss : SB));
 #pragma unroll
         for (int e = 0; e < E; ++e) y[e] = rg_elem<T>(u, e) * h[e];
-        const bool full = g.n == E;
         if constexpr (MODE != RG_FWD) {
-            u32x4 v, lw;
             if constexpr (sizeof(T) == 4) {
-                v = u32x4{__float_as_uint(h[0]), __float_as_uint(h[1]), __float_as_uint(h[2]), __float_as_uint(h[3])};
+                out.v = u32x4{__float_as_uint(h[0]), __float_as_uint(h[1]), __float_as_uint(h[2]), __float_as_uint(h[3])};
             } else if constexpr (BWD) {                  // e as two 16-bit halves of its fp32 word
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    v[i] = __builtin_amdgcn_perm(__float_as_uint(h[2 * i + 1]), __float_as_uint(h[2 * i]), 0x07060302u);
-                    lw[i] = __builtin_amdgcn_perm(__float_as_uint(h[2 * i + 1]), __float_as_uint(h[2 * i]), 0x05040100u);
+                    out.v[i] = __builtin_amdgcn_perm(__float_as_uint(h[2 * i + 1]), __float_as_uint(h[2 * i]), 0x07060302u);
+                    out.lw[i] = __builtin_amdgcn_perm(__float_as_uint(h[2 * i + 1]), __float_as_uint(h[2 * i]), 0x05040100u);
                 }
             } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = pack_word<T>(h[2 * i], h[2 * i + 1]);
-            }
-            if (full) {
-                rg_store(HS + g.off, v);
-                if constexpr (BWD && sizeof(T) == 2) rg_store(LO + g.off, lw);
-            } else {
-#pragma unroll
-                for (int e = 0; e < E; ++e)
-                    if (e < g.n) {
-                        rg_store_bits(HS + g.off + e, rg_bits<T>(v, e));
-                        if constexpr (BWD && sizeof(T) == 2) rg_store_bits(LO + g.off + e, rg_bits<T>(lw, e));
-                    }
+                for (int i = 0; i < 4; ++i) out.v[i] = pack_word<T>(h[2 * i], h[2 * i + 1]);
             }
         }
-        if (a.tile) {
-            float* tp = tile + g.row * a.tile_pitch + g.col;
+        if constexpr (TILE) {
+            const uint32_t tp = g.tile + (uint32_t)(k * (HORZ ? col_step() : row_step() * a.tile_pitch) * 4);
             // the tile's rows are whole granules: what lies beyond the image row is never read
+            typedef float f32x4 __attribute__((ext_vector_type(4)));
+            f32x4 t[E / 4];
 #pragma unroll
-            for (int i = 0; i < E / 4; ++i) {
-                float4 t = ((float4*)tp)[i];
-                t.x += y[4 * i]; t.y += y[4 * i + 1]; t.z += y[4 * i + 2]; t.w += y[4 * i + 3];
-                ((float4*)tp)[i] = t;
-            }
+            for (int i = 0; i < E / 4; ++i) t[i] = lds_get<f32x4>(tp + 16 * i);
+#pragma unroll
+            for (int i = 0; i < E / 4; ++i) lds_set<f32x4>(tp + 16 * i, f32x4{t[i][0] + y[4 * i], t[i][1] + y[4 * i + 1], t[i][2] + y[4 * i + 2], t[i][3] + y[4 * i + 3]});
         } else {
             if (!first) {
 #pragma unroll
                 for (int e = 0; e < E; ++e) y[e] += rg_elem<T>(yv, e);
             }
-            u32x4 v;
-            if constexpr (sizeof(T) == 4) v = u32x4{__float_as_uint(y[0]), __float_as_uint(y[1]), __float_as_uint(y[2]), __float_as_uint(y[3])};
+            if constexpr (sizeof(T) == 4) out.y = u32x4{__float_as_uint(y[0]), __float_as_uint(y[1]), __float_as_uint(y[2]), __float_as_uint(y[3])};
             else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = pack_word<T>(y[2 * i], y[2 * i + 1]);
+                for (int i = 0; i < 4; ++i) out.y[i] = pack_word<T>(y[2 * i], y[2 * i + 1]);
             }
-            if (full) rg_store(Y + g.off, v);
-            else {
+        }
+    }
+    __device__ __forceinline__ void store(int k, const Gran& g, const Out& out) const {
+        if constexpr (MODE == RG_FWD && TILE) return;
+        if (!live(g, k)) return;
+        const int n = W - (HORZ ? g.col + k * col_step() : g.col);           // elements inside the row
+        const uint32_t off = (uint32_t)(g.off + k * off_step());
+        if (n >= E) {
+            if constexpr (MODE != RG_FWD) rg_store((T*)(HS + off), out.v);
+            if constexpr (BWD && sizeof(T) == 2) rg_store((T*)(LO + off), out.lw);
+            if constexpr (!TILE) rg_store((T*)(Y + off), out.y);
+        } else {
 #pragma unroll
-                for (int e = 0; e < E; ++e)
-                    if (e < g.n) rg_store_bits(Y + g.off + e, rg_bits<T>(v, e));
-            }
+            for (int e = 0; e < E; ++e)
+                if (e < n) {
+                    if constexpr (MODE != RG_FWD) rg_store_bits((T*)(HS + off) + e, rg_bits<T>(out.v, e));
+                    if constexpr (BWD && sizeof(T) == 2) rg_store_bits((T*)(LO + off) + e, rg_bits<T>(out.lw, e));
+                    if constexpr (!TILE) rg_store_bits((T*)(Y + off) + e, rg_bits<T>(out.y, e));
+                }
         }
     }
 
@@ -318,9 +356,9 @@ struct RaggedPass {
     // lines are issued while the HL lines before them are computed: one wave per SIMD scans, and nothing else hides their
     // latency.  MEET: the line is shared with other waves, which exchange the last line every 8 steps (a line's h then goes
     // to LDS after the meeting, when no neighbour reads lam*x there any more).
-    template <bool MEET>
-    __device__ __forceinline__ void scan(int nsub, float (&h)[NV], int& parity, int& until) const {
-        constexpr int HL = WIDE ? (NV == 1 ? 4 : NV == 2 ? 2 : 1) : (NV <= 2 ? 4 : 2);      // what the registers hold twice
+    template <bool MEET, bool LOCAL>
+    __device__ __forceinline__ void scan(int k, int nsub, float (&h)[NV], int& parity, int& until) const {
+        constexpr int HL = WIDE ? (NV == 1 ? 4 : NV <= 3 ? 2 : 1) : (NV <= 2 ? 4 : 2);      // what the registers hold twice
         constexpr int NB = RG_SUB / HL;
         constexpr int NW2 = WIDE ? 1 : (NV % 2 ? NV : NV / 2);
         const int lane = threadIdx.x & 63;
@@ -341,8 +379,7 @@ struct RaggedPass {
         // byte offsets in LDS of the next line to read and of the next line whose h is stored: running sums, one addition per
         // line (left to itself the compiler keeps an address per line of the block in registers and adds to each)
         const uint32_t line_a = (uint32_t)(pitch * SB), line_w = (uint32_t)(pitch2 * 2);
-        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-        uint32_t ra = lds0 + (uint32_t)(stA - lds) + (uint32_t)(first_slot * SB), rw = lds0 + (uint32_t)(stW2 - lds) + (uint32_t)(pc * 2), rh = ra;
+        uint32_t ra = stA + buf(k) * bufA + (uint32_t)(first_slot * SB), rw = stW2 + buf(k) * bufW2 + (uint32_t)(pc * 2), rh = ra;
         auto read = [&](Lines& q) {
 #pragma unroll
             for (int j = 0; j < HL; ++j) {
@@ -369,43 +406,68 @@ struct RaggedPass {
                 }
             }
         };
-        float hout[NV];                                           // h of the line, for LDS
-        auto line = [&](const Lines& q, int j) {
-            // a stretch starts with the next line: nothing is carried into it, whatever the state holds (the weights there
-            // are 0 already); a mask, not a branch: a wave alone on its SIMD pays some 16 clocks for each
-            const bool keep = --until != 0;
-            until = keep ? until : a.p.kchunk;
-            float av[NV], w0[NV], w1[NV], w2[NV];
+        // A line's operands in fp32, unpacked in three parts while the line before it is computed: an instruction that waits for
+        // the one before it costs a lone wave twice its issue, and the chain of a line alone leaves every second slot empty.
+        struct Taps { float a[NV], w0[NV], w1[NV], w2[NV], lt, rt; };
+        auto unpack = [&](const Lines& q, int j, Taps& t, int what) {
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
-                av[v] = q.a[j][v];
-                if constexpr (WIDE) { w0[v] = __uint_as_float(q.w[j][v][0]); w1[v] = __uint_as_float(q.w[j][v][1]); w2[v] = __uint_as_float(q.w[j][v][2]); }
-                else { w0[v] = word_lo<T>(q.w[j][v][0]); w1[v] = word_hi<T>(q.w[j][v][0]); w2[v] = NV % 2 ? word_lo<T>(q.w2[j][v % NW2]) : (v & 1) ? word_hi<T>(q.w2[j][v / 2]) : word_lo<T>(q.w2[j][v / 2]); }
+                if constexpr (WIDE) {
+                    if (what == 0) { t.a[v] = q.a[j][v]; t.w1[v] = __uint_as_float(q.w[j][v][1]); }
+                    if (what == 1) t.w0[v] = __uint_as_float(q.w[j][v][0]);
+                    if (what == 2) t.w2[v] = __uint_as_float(q.w[j][v][2]);
+                } else {
+                    if (what == 0) { t.a[v] = q.a[j][v]; t.w1[v] = word_hi<T>(q.w[j][v][0]); }
+                    if (what == 1) t.w0[v] = word_lo<T>(q.w[j][v][0]);
+                    if (what == 2) t.w2[v] = NV % 2 ? word_lo<T>(q.w2[j][v % NW2]) : (v & 1) ? word_hi<T>(q.w2[j][v / 2]) : word_lo<T>(q.w2[j][v / 2]);
+                }
+            }
+            if constexpr (BWD) {
+                // the taps that reach this lane's positions from its neighbours' (a lane's positions beyond the line come after
+                // those inside, or are all of its positions: their taps are read as 0)
+                if (what == 1) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) t.w0[v] = valid[v] ? t.w0[v] : 0.f;
+                    t.rt = from_lane_above(t.w0[0]);
+                }
+                if (what == 2) t.lt = from_lane_below(valid[NV - 1] ? t.w2[NV - 1] : 0.f);
+            }
+        };
+        float hout[NV];                                           // h of the line, for LDS
+        auto line = [&](const Taps& t, const Lines& qn, int jn, Taps& tn) {
+            // a stretch starts with the next line: nothing is carried into it, whatever the state holds (the weights there
+            // are 0 already); a mask, not a branch: a wave alone on its SIMD pays some 16 clocks for each
+            bool keep = true;
+            if constexpr (LOCAL) {
+                keep = --until != 0;
+                until = keep ? until : a.p.kchunk;
             }
             // one chain of FMAs per position in the line-by-line kernels' order -- own tap, the neighbour before, the neighbour
             // after -- so that the states are theirs bit for bit (products of the reverse sweep summed in pairs instead: glam of
             // fp32 maps 9 % further from 64 bits in the mean, up to 2.4 times)
             float hn[NV];
-            if constexpr (BWD) {
-                // (a lane's positions beyond the line come after those inside, or are all of its positions: their taps are read as 0)
+            const float lin = from_lane_below(h[NV - 1]), rin = from_lane_above(h[0]);
 #pragma unroll
-                for (int v = 0; v < NV; ++v) hn[v] = fmaf(w1[v], h[v], av[v]);
-                const float lt = from_lane_below(valid[NV - 1] ? w2[NV - 1] : 0.f), lh = from_lane_below(h[NV - 1]);
+            for (int v = 0; v < NV; ++v) hn[v] = fmaf(t.w1[v], h[v], t.a[v]);
+            __builtin_amdgcn_sched_barrier(0);
+            unpack(qn, jn, tn, 0);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int v = 0; v < NV; ++v) hn[v] = fmaf(v == 0 ? lt : w2[v - 1], v == 0 ? lh : h[v - 1], hn[v]);
-#pragma unroll
-                for (int v = 0; v < NV; ++v) w0[v] = valid[v] ? w0[v] : 0.f;
-                const float rt = from_lane_above(w0[0]), rh_ = from_lane_above(h[0]);
-#pragma unroll
-                for (int v = 0; v < NV; ++v) hn[v] = fmaf(v == NV - 1 ? rt : w0[v + 1], v == NV - 1 ? rh_ : h[v + 1], hn[v]);
-            } else {
-                const float lin = from_lane_below(h[NV - 1]), rin = from_lane_above(h[0]);
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const float lf = v == 0 ? lin : h[v - 1], rt = v == NV - 1 ? rin : h[v + 1];
-                    hn[v] = fmaf(w2[v], rt, fmaf(w0[v], lf, fmaf(w1[v], h[v], av[v])));
-                }
+            for (int v = 0; v < NV; ++v) {
+                const float w = BWD ? (v == 0 ? t.lt : t.w2[v > 0 ? v - 1 : 0]) : t.w0[v];
+                hn[v] = fmaf(w, v == 0 ? lin : h[v > 0 ? v - 1 : 0], hn[v]);
             }
+            __builtin_amdgcn_sched_barrier(0);
+            unpack(qn, jn, tn, 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const float w = BWD ? (v == NV - 1 ? t.rt : t.w0[v < NV - 1 ? v + 1 : v]) : t.w2[v];
+                hn[v] = fmaf(w, v == NV - 1 ? rin : h[v < NV - 1 ? v + 1 : v], hn[v]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            unpack(qn, jn, tn, 2);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int v = 0; v < NV; ++v) { hout[v] = hn[v]; h[v] = (valid[v] && keep) ? hn[v] : 0.f; }
         };
@@ -416,17 +478,22 @@ struct RaggedPass {
             asm volatile("" : "+v"(rh));
         };
         Lines buf[2];
+        Taps taps[2];
         read(buf[0]);
+        read(buf[1]);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) unpack(buf[0], 0, taps[0], i);
         for (int s = 0; s < nsub; ++s) {
             float hb[MEET ? RG_SUB : 1][NV];
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
                 static_assert(NB % 2 == 0, "the two line sets alternate");
-                if (i + 1 < NB || s + 1 < nsub) read(buf[(i + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int j = 0; j < HL; ++j) {
-                    line(buf[i & 1], j);
+                    // (after the last line of the chunk what is unpacked next is never used)
+                    constexpr int odd = HL & 1;
+                    const int at = odd ? (i * HL + j) & 1 : j & 1;
+                    line(taps[at], buf[(j + 1 < HL ? i : i + 1) & 1], (j + 1) % HL, taps[at ^ 1]);
                     if constexpr (MEET) {
 #pragma unroll
                         for (int v = 0; v < NV; ++v) hb[i * HL + j][v] = hout[v];
@@ -434,6 +501,8 @@ struct RaggedPass {
                         put(hout);
                     }
                 }
+                __builtin_amdgcn_sched_barrier(0);
+                if (i + 2 < NB || s + 1 < nsub) read(buf[i & 1]);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (MEET) {
@@ -476,80 +545,167 @@ struct RaggedPass {
         const size_t pc = (size_t)plane * HW;
         const size_t slot_c = p.shared ? 0 : (size_t)d * planes * HW;
         const size_t slot_w = p.shared ? 0 : (size_t)d * groups * 3 * HW;
-        X = (const T*)p.x + pc; LAM = (const T*)p.lam + slot_c + pc; U = (const T*)p.u + slot_c + pc;
-        W0 = (const T*)p.w + slot_w + (size_t)bg * 3 * HW;
-        Y = (T*)p.y + pc;
-        HS = MODE != RG_FWD ? (T*)p.hs + (size_t)d * planes * HW + pc : nullptr;
-        LO = (BWD && sizeof(T) == 2) ? (T*)a.hs_lo + (size_t)d * planes * HW + pc : nullptr;
-        // a window may reach into the neighbouring planes of the tensor, not beyond its ends
-        lo = bg == 0 ? 0 : -HW;
-        hi = bg == (int)groups - 1 ? HW - E : 2 * HW - E;
-        stA = lds + (size_t)dsel * K * pitch * SB;
-        stW2 = lds + a.w2_off[ax] + (size_t)dsel * K * pitch2 * 2;
+        const size_t back = bg == 0 ? 0 : (size_t)HW;             // the neighbouring plane a window may reach into
+        X = (const char*)((const T*)p.x + pc - back);
+        LAM = (const char*)((const T*)p.lam + slot_c + pc - back);
+        U = (const char*)((const T*)p.u + slot_c + pc - back);
+        W0 = (const char*)((const T*)p.w + slot_w + (size_t)bg * 3 * HW - back);
+        W1 = W0 + (size_t)HW * sizeof(T);
+        W2 = W1 + (size_t)HW * sizeof(T);
+        Y = (char*)((T*)p.y + pc);
+        HS = MODE != RG_FWD ? (char*)((T*)p.hs + (size_t)d * planes * HW + pc) : nullptr;
+        LO = (BWD && sizeof(T) == 2) ? (char*)((T*)a.hs_lo + (size_t)d * planes * HW + pc) : nullptr;
+        at_ends = bg == 0 || bg == (int)groups - 1;
+        top = ((int)back + (bg == (int)groups - 1 ? HW : 2 * HW) - E) * (int)sizeof(T);
+        bufA = a.nd * K * pitch * SB; bufW2 = a.nd * K * pitch2 * 2;
+        stA = lds0 + dsel * K * pitch * SB;
+        stW2 = lds0 + a.w2_off[ax] + dsel * K * pitch2 * 2;
         edge = (float*)(lds + a.edge_off[ax]) + dsel * 2 * pitch2;
-        tile = (float*)(lds + a.tile_off);
 
         nchunks = (S + K - 1) / K;
-        auto subs = [&](int k) { return (min(K, S - k * K) + RG_SUB - 1) / RG_SUB; };
-        // both directions add to the same rows / columns of the tile while their chunks cross
-        auto cross = [&](int k) { return dcount == 2 && 2 * (k + 1) * K > S && 2 * k * K < S; };
         if (part < parts) {
             __builtin_amdgcn_s_setprio(3);       // the chain the others wait for (a few per cent either way: 2048 planes 25x31 33.7 -> 32.4 us, 768 of 50x83 63.3 -> 64.7)
-            float h[NV];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) h[v] = 0.f;
-            int parity = 0;
-            // scan steps to the next stretch: cuts lie before image lines 0, kchunk, 2 * kchunk, ..
-            int until = 1 << 30;
-            if (a.p.kchunk > 0) until = rev && S % a.p.kchunk ? S % a.p.kchunk : a.p.kchunk;
-            lds_barrier();
-            for (int k = 0; k < nchunks; ++k) {
-                if (NV % 2 == 0 && parts > 1) scan<NV % 2 == 0>(subs(k), h, parity, until);      // (lines of one or three positions per lane are one wave's)
-                else scan<false>(subs(k), h, parity, until);
-                lds_barrier();
-                if (cross(k)) lds_barrier();
-                lds_barrier();
-            }
+            if (a.p.kchunk > 0) scan_all<true>();
+            else scan_all<false>();
             __builtin_amdgcn_s_setprio(0);
         } else {
-            Regs q[RG_ROUNDS];
-            const int gr = HORZ ? (K / E) * H : K * ((W + E - 1) / E);
-            const bool two = gr > nthr;                         // a second granule per thread
-            load(0, 0, q[0]);
-            if (two) load(0, 1, q[1]);
-            stage(0, 0, q[0]);
-            if (two) stage(0, 1, q[1]);
-            lds_barrier();
-            for (int k = 0; k < nchunks; ++k) {
-                load_late(k, 0, q[0]);
-                if (two) load_late(k, 1, q[1]);
-                if (k + 1 < nchunks) {
-                    load(k + 1, 0, q[0]);
-                    if (two) load(k + 1, 1, q[1]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                if (parts > 1) for (int s = subs(k); s > 0; --s) lds_barrier();
-                lds_barrier();
-                if (cross(k)) {
-                    if (dsel == 1) lds_barrier();
-                    finish(k, 0, q[0]);
-                    if (two) finish(k, 1, q[1]);
-                    if (dsel == 0) lds_barrier();
-                } else {
-                    finish(k, 0, q[0]);
-                    if (two) finish(k, 1, q[1]);
-                }
-                if (k + 1 < nchunks) {
-                    stage(k + 1, 0, q[0]);
-                    if (two) stage(k + 1, 1, q[1]);
-                }
-                lds_barrier();
+            if (__builtin_amdgcn_readfirstlane(tid) >= granules()) { stand_by(); return; }      // (the same for the whole wave)
+            const bool two = granules() > nthr;                     // granules of a chunk per thread
+            if (a.nbuf == 2) {
+                if (two) move_ahead<2>(); else move_ahead<1>();
+            } else {
+                if (two) move_in_turn<2>(); else move_in_turn<1>();
             }
+        }
+    }
+
+    __device__ __forceinline__ int subs(int k) const { return (min(K, S - k * K) + RG_SUB - 1) / RG_SUB; }
+    // both directions add to the same rows / columns of the tile while their chunks cross
+    __device__ __forceinline__ bool cross(int k) const { return dcount == 2 && 2 * (k + 1) * K > S && 2 * k * K < S; }
+
+    // A scanning wave's part of a pass: the barriers below are the ones of move_ahead / move_in_turn.
+    template <bool LOCAL>
+    __device__ __forceinline__ void scan_all() {
+        float h[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) h[v] = 0.f;
+        int parity = 0;
+        // scan steps to the next stretch: cuts lie before image lines 0, kchunk, 2 * kchunk, ..
+        int until = 1 << 30;
+        if (LOCAL) until = rev && S % a.p.kchunk ? S % a.p.kchunk : a.p.kchunk;
+        const bool ahead = a.nbuf == 2;
+        lds_barrier();
+        for (int k = 0; k < nchunks; ++k) {
+            if (NV % 2 == 0 && parts > 1) scan<NV % 2 == 0, LOCAL>(k, subs(k), h, parity, until);      // (lines of one or three positions per lane are one wave's)
+            else scan<false, LOCAL>(k, subs(k), h, parity, until);
+            if (ahead) {
+                if (k > 0 && cross(k - 1)) lds_barrier();
+            } else {
+                lds_barrier();
+                if (cross(k)) lds_barrier();
+            }
+            lds_barrier();
+        }
+        if (ahead) {
+            if (cross(nchunks - 1)) lds_barrier();
+            lds_barrier();
+        }
+    }
+
+    // A loading wave without a granule: the barriers of the others.
+    __device__ __forceinline__ void stand_by() const {
+        lds_barrier();
+        for (int k = 0; k <= nchunks; ++k) {
+            const int meetings = parts > 1 && k < nchunks ? subs(k) : 0;
+            int n = a.nbuf == 2 ? meetings + (k > 0 && cross(k - 1) ? 2 : 1) : k < nchunks ? meetings + (cross(k) ? 3 : 2) : 0;
+            for (; n > 0; --n) lds_barrier();
+        }
+    }
+
+    // A loading wave's part with two chunks in LDS: while chunk k is scanned, chunk k - 1 is finished, chunk k + 1 takes its
+    // place and the requests of chunk k + 2 go out.  A thread reads and writes its own granules' places there, so nothing but
+    // the end of the scan is waited for.  R: granules of a chunk per thread.
+    template <int R>
+    __device__ __forceinline__ void move_ahead() {
+        Regs q[R];
+        Gran g[R];
+        Out out[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) g[r] = place(r);
+#pragma unroll
+        for (int r = 0; r < R; ++r) load(0, g[r], q[r]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) stage(0, g[r], q[r]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) load(1, g[r], q[r]);
+        lds_barrier();
+        for (int k = 0; k <= nchunks; ++k) {
+            const bool crossing = k > 0 && cross(k - 1);
+            int meetings = parts > 1 && k < nchunks ? subs(k) : 0;
+            if (crossing && dsel == 1) lds_barrier();
+            if (k > 0) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) finish(k - 1, g[r], q[r], out[r]);
+            }
+            if (crossing && dsel == 0) lds_barrier();
+            if (meetings > 1) { lds_barrier(); --meetings; }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < R; ++r) load_late(k, g[r], q[r]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < R; ++r) stage(k + 1, g[r], q[r]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (k > 0) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) store(k - 1, g[r], out[r]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < R; ++r) load(k + 2, g[r], q[r]);
+            __builtin_amdgcn_sched_barrier(0);
+            for (; meetings > 0; --meetings) lds_barrier();
+            lds_barrier();
+        }
+    }
+
+    // ... and with one: scan and loads take turns
+    template <int R>
+    __device__ __forceinline__ void move_in_turn() {
+        Regs q[R];
+        Gran g[R];
+        Out out[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) g[r] = place(r);
+#pragma unroll
+        for (int r = 0; r < R; ++r) load(0, g[r], q[r]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) stage(0, g[r], q[r]);
+        lds_barrier();
+        for (int k = 0; k < nchunks; ++k) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) load_late(k, g[r], q[r]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) load(k + 1, g[r], q[r]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (parts > 1) for (int s = subs(k); s > 0; --s) lds_barrier();
+            lds_barrier();
+            if (cross(k) && dsel == 1) lds_barrier();
+#pragma unroll
+            for (int r = 0; r < R; ++r) finish(k, g[r], q[r], out[r]);
+            if (cross(k) && dsel == 0) lds_barrier();
+#pragma unroll
+            for (int r = 0; r < R; ++r) stage(k + 1, g[r], q[r]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < R; ++r) store(k, g[r], out[r]);
+            lds_barrier();
         }
     }
 };
 
-template <typename T, int MODE, bool LOGITS, int NV>
+template <typename T, int MODE, bool LOGITS, int NV, bool TILE>
 __global__ void __launch_bounds__(1024) ragged_kernel(RaggedArgs a) {
     extern __shared__ __attribute__((aligned(16))) char rg_lds[];
     constexpr int E = 16 / (int)sizeof(T);
@@ -558,30 +714,30 @@ __global__ void __launch_bounds__(1024) ragged_kernel(RaggedArgs a) {
     const int b = plane / p.C, c = plane - b * p.C;
     const int bg = b * p.G + c / p.cpg;
     float* tile = (float*)(rg_lds + a.tile_off);
-    if (a.tile) {
+    if constexpr (TILE) {
         for (int i = threadIdx.x; i < p.H * a.tile_pitch; i += blockDim.x) tile[i] = 0.f;
         // (visible after the first barrier of the first pass)
     }
     bool first = true;
     {
-        RaggedPass<T, MODE, LOGITS, NV, false> v(a, rg_lds);
+        RaggedPass<T, MODE, LOGITS, NV, TILE, false> v(a, rg_lds);
         v.plane = plane; v.bg = bg;
         const int m = p.mask & 3;
         if (m == 3 && a.nd == 2) { v.run(0, 2, first); first = false; }
         else
             for (int i = 0; i < 2; ++i)
-                if ((m >> i) & 1) { v.run(i, 1, first); if (!a.tile) __syncthreads(); first = false; }
+                if ((m >> i) & 1) { v.run(i, 1, first); if constexpr (!TILE) __syncthreads(); first = false; }
     }
     {
-        RaggedPass<T, MODE, LOGITS, NV, true> v(a, rg_lds);
+        RaggedPass<T, MODE, LOGITS, NV, TILE, true> v(a, rg_lds);
         v.plane = plane; v.bg = bg;
         const int m = (p.mask >> 2) & 3;
         if (m == 3 && a.nd == 2) v.run(2, 2, first);
         else
             for (int i = 0; i < 2; ++i)
-                if ((m >> i) & 1) { v.run(2 + i, 1, first); if (!a.tile) __syncthreads(); first = false; }
+                if ((m >> i) & 1) { v.run(2 + i, 1, first); if constexpr (!TILE) __syncthreads(); first = false; }
     }
-    if (a.tile) {
+    if constexpr (TILE) {
         T* Y = (T*)p.y + (size_t)plane * p.H * p.W;
         const int gpr = (p.W + E - 1) / E;
         for (int q = threadIdx.x; q < p.H * gpr; q += blockDim.x) {
@@ -609,27 +765,22 @@ __global__ void __launch_bounds__(1024) ragged_kernel(RaggedArgs a) {
     }
 }
 
-template <typename T, int MODE, bool LOGITS>
+template <typename T, int MODE, bool LOGITS, bool TILE>
 hipError_t launch_ragged_one(const RaggedArgs& a, int threads, int nv, size_t lds, hipStream_t s) {
     const dim3 grid((unsigned)((size_t)a.p.B * a.p.C)), block(threads);
-    void (*k)(RaggedArgs) = nv == 1 ? ragged_kernel<T, MODE, LOGITS, 1> : nv == 2 ? ragged_kernel<T, MODE, LOGITS, 2>
-                                    : nv == 3 ? ragged_kernel<T, MODE, LOGITS, 3> : ragged_kernel<T, MODE, LOGITS, 4>;
+    void (*k)(RaggedArgs) = nv == 1 ? ragged_kernel<T, MODE, LOGITS, 1, TILE> : nv == 2 ? ragged_kernel<T, MODE, LOGITS, 2, TILE>
+                                    : nv == 3 ? ragged_kernel<T, MODE, LOGITS, 3, TILE> : ragged_kernel<T, MODE, LOGITS, 4, TILE>;
     const hipError_t e = allow_dynamic_lds((const void*)k, 160 * 1024);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, grid, block, lds, s, a);
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_ragged_type(const FwdParams& p, int dtype, bool reverse, void* e_lo, hipStream_t s) {
-    RaggedArgs a = {};
-    int threads, nv;
-    size_t lds;
-    if (!ragged_plan(p, dtype, reverse, &a, &threads, &nv, &lds)) return hipErrorInvalidValue;
-    a.hs_lo = e_lo;
-    if (reverse) return p.logits ? launch_ragged_one<T, RG_BWD, true>(a, threads, nv, lds, s) : launch_ragged_one<T, RG_BWD, false>(a, threads, nv, lds, s);
-    if (p.hs) return p.logits ? launch_ragged_one<T, RG_SAVE, true>(a, threads, nv, lds, s) : launch_ragged_one<T, RG_SAVE, false>(a, threads, nv, lds, s);
-    return p.logits ? launch_ragged_one<T, RG_FWD, true>(a, threads, nv, lds, s) : launch_ragged_one<T, RG_FWD, false>(a, threads, nv, lds, s);
+template <typename T, bool TILE>
+hipError_t launch_ragged_type(const RaggedArgs& a, bool reverse, int threads, int nv, size_t lds, hipStream_t s) {
+    if (reverse) return a.p.logits ? launch_ragged_one<T, RG_BWD, true, TILE>(a, threads, nv, lds, s) : launch_ragged_one<T, RG_BWD, false, TILE>(a, threads, nv, lds, s);
+    if (a.p.hs) return a.p.logits ? launch_ragged_one<T, RG_SAVE, true, TILE>(a, threads, nv, lds, s) : launch_ragged_one<T, RG_SAVE, false, TILE>(a, threads, nv, lds, s);
+    return a.p.logits ? launch_ragged_one<T, RG_FWD, true, TILE>(a, threads, nv, lds, s) : launch_ragged_one<T, RG_FWD, false, TILE>(a, threads, nv, lds, s);
 }
 
 }  // namespace
