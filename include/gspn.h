@@ -237,6 +237,8 @@ const char* gspn_proxy_plan(int B, int K, int M, int H, int W, int dtype);
  * storage e passes through storage precision between the two), "generic" (any shape);
  * static string, never NULL.  Host only.
  *
+ * (The name is the family whose limits the call meets.  Among the calls of the "plane" and "tile" families, and in the first
+ * pass of "twopass", those with too few planes or lines for that family's own kernel run the any-size kernel of "generic".)
  * Environment variables for tests (results are the same whichever kernel runs, up to the rounding of
  * the storage type).  They are read once per process, by the first call that dispatches; a process
  * that changes them afterwards calls gspn_reload_env():

@@ -64,9 +64,9 @@ SPILL_ALLOWED = {
     # the same in fp16 storage, and its GSPN-local forward with h_save (96 values, none in the band loop either; the
     # hardware conversions hold a few registers more than the shifts of bf16): parity-tested at full size
     "fwd_pair_kernelINS_5f16_tELb1ELb0ELb1ELb1": 144, "fwd_pair_kernelINS_5f16_tELb1ELb0ELb1ELb0": 96,
-    # any-size kernel in bf16: 128 registers, so that sixteen waves share a CU; four instantiations (the reverse sweep, and with
-    # logits and four positions per lane the one that merges in global memory) park one or two values between the chunks
-    "ragged_kernelItLi": 2,
+    # any-size kernel, reverse sweep in 16-bit storage: 128 registers, so that sixteen waves share a CU; what the loading waves park
+    # (at most 14 values in bf16, 8 in fp16) lies between the chunks, none in the line loops
+    "ragged_kernelItLi2": 14, "ragged_kernelINS_5f16_tELi2": 8,
     # fp32 maps with rows of 112 bytes on workgroups of more than four waves, without h_save: off every benchmark shape
     # (the plane kernel takes 28x28, the four-wave instantiation 56x56); kept because the shapes must run somewhere
     "fwd_tile_kernelIfLi2ELi1ELi28ELb0ELi8ELb0ELi8ELb0ELb0ELb0": 259, "fwd_tile_kernelIfLi2ELi1ELi28ELb0ELi8ELb0ELi8ELb1ELb0ELb0": 47,

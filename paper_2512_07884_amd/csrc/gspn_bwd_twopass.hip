@@ -252,6 +252,10 @@ hipError_t launch_bwd_twopass(const BwdParams& p, int dtype, hipStream_t s) {
     hipError_t e;
     if (chunk_kernels_enabled() && reverse_sweep_chunk_applicable(f, dtype)) {
         e = launch_reverse_sweep_chunk(f, dtype, s);
+    } else if (reverse_sweep_plane_applicable(f, dtype) ? any_size_before_plane(f) && reverse_sweep_ragged_applicable(f, dtype)
+                                                         : !(pair_kernels_enabled() && reverse_sweep_pair_applicable(f, dtype)) && fwd_tile_applicable(f, dtype) &&
+                                                               any_size_before_tile(f) && reverse_sweep_ragged_applicable(f, dtype)) {
+        e = launch_reverse_sweep_ragged(f, dtype, s);
     } else if (reverse_sweep_plane_applicable(f, dtype)) {
         e = launch_reverse_sweep_plane(f, dtype, s);
     } else if (pair_kernels_enabled() && reverse_sweep_pair_applicable(f, dtype)) {

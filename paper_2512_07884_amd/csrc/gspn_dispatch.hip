@@ -46,6 +46,33 @@ bool chunk_kernels_enabled() { return !knobs().fwd_no_chunk; }
 bool stream_two_channels_enabled() { return !knobs().stream_one_channel; }
 bool stream_two_channels_forced() { return knobs().stream_two_channels; }
 
+// Calls of the "plane" and "tile" families (what gspn_fwd_plan / gspn_bwd_plan answer) that the any-size kernel runs faster: GPU time
+// of graph replays on 520 random calls of the three types, forward and with h_save; family's own kernel -> any size, us.
+// Plane: its kernel deals several channels to a workgroup and walks the directions one after the other, so a call of few planes
+// leaves CUs idle; up to 1024 planes (512 with logits) of more than 196 pixels 0.67 of its time in the mean, 1.05 at most: 512
+// planes 44x44 bf16 31 -> 23, 256 planes 30x30 fp16 34 -> 16.  Beyond the lines: 768 planes 46x18 with logits 23 -> 29, 1728 planes
+// 20x20 19 -> 22, 96 planes 11x11 12.8 -> 13.6.
+bool any_size_before_plane(const FwdParams& p) {
+    const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
+    return !knobs().fwd_no_plane && planes >= 64 && planes <= (p.logits ? 512 : 1024) && HW > 196;
+}
+// Tile: the waves that scan load for themselves there; 0.68 of its kernel's time in the mean: 1024 planes 80x112 bf16 with h_save
+// 172 -> 143, 32 planes 64x80 with stretches 42 -> 22.  It keeps rows of 96 and 128 elements in calls of 1024 planes and more
+// (requests of whole 64-byte sectors: 128x128 fp32 241 -> 268, 104x96 fp16 112 -> 125) and planes of more than 20 000 pixels, whose
+// output tile leaves no room for two chunks (512 planes 240x96 fp32 204 -> 236).
+bool any_size_before_tile(const FwdParams& p) {
+    const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
+    return !knobs().fwd_no_plane && planes >= 32 && HW <= 20000 && !(planes >= 1024 && (p.W == 96 || p.W == 128));
+}
+// Backward: the single-launch kernels hold a weight group's channels in one workgroup, the any-size kernel a plane, with a second
+// pass over the channels.  Plane, more than 256 pixels (per-channel weights: up to 2048 planes): 0.2 to 0.9 of its time (512 planes
+// 28x30 fp32 with logits 175 -> 51; 16x16 with 48 channels per group 55 -> 60).  Tile: 0.17 (768 planes 43x44 with logits 631 -> 88).
+static bool any_size_before_bwd_plane(const BwdParams& p) {
+    const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
+    return planes >= 64 && HW > 256 && (p.cpg > 1 || planes <= 2048);
+}
+static bool any_size_before_bwd_tile(const BwdParams& p) { return (size_t)p.B * p.C >= 32; }
+
 static FwdPlan choose_fwd(const FwdParams& p, int dtype) {
     const Knobs k = knobs();
     if (k.force_generic) return FWD_GENERIC;
@@ -83,7 +110,10 @@ static BwdPlan choose_bwd(const BwdParams& p, int dtype) {
 }
 
 hipError_t launch_fwd(const FwdParams& p, int dtype, hipStream_t s) {
-    switch (choose_fwd(p, dtype)) {
+    const FwdPlan plan = choose_fwd(p, dtype);
+    if (((plan == FWD_PLANE && any_size_before_plane(p)) || (plan == FWD_TILE && any_size_before_tile(p))) && ragged_applicable(p, dtype))
+        return launch_fwd_ragged(p, dtype, s);
+    switch (plan) {
         case FWD_TILE: return launch_fwd_tile(p, dtype, s);
         case FWD_STREAM: return launch_fwd_stream(p, dtype, s);
         case FWD_PLANE: return launch_fwd_plane(p, dtype, s);
@@ -97,7 +127,12 @@ hipError_t launch_fwd(const FwdParams& p, int dtype, hipStream_t s) {
 }
 
 hipError_t launch_bwd(const BwdParams& p, int dtype, hipStream_t s) {
-    switch (choose_bwd(p, dtype)) {
+    const BwdPlan plan = choose_bwd(p, dtype);
+    const Knobs k = knobs();
+    if (((plan == BWD_PLANE && any_size_before_bwd_plane(p)) || (plan == BWD_TILE && any_size_before_bwd_tile(p))) &&
+        !k.bwd_no_plane && !k.bwd_no_twopass && ragged_bwd_applicable(p, dtype))
+        return launch_bwd_ragged(p, dtype, s);
+    switch (plan) {
         case BWD_TILE: return launch_bwd_tile(p, dtype, s);
         case BWD_PLANE: return launch_bwd_plane(p, dtype, s);
         case BWD_TWOPASS: return launch_bwd_twopass(p, dtype, s);

@@ -109,9 +109,11 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
     static const Shape few32[] = {{0, 2, 64}, {0, 1, 64}, {2, 2, 64}, {0, 2, 32}, {0, 1, 32}, {1, 2, 64}, {1, 2, 32}, {0, 2, 16}, {1, 1, 64}, {1, 1, 32}, {0, 1, 16}, {1, 2, 16}, {1, 1, 16}};
     static const Shape many16[] = {{0, 2, 64}, {0, 1, 64}, {0, 2, 32}, {0, 1, 32}, {1, 2, 64}, {1, 2, 32}, {1, 1, 64}, {1, 1, 32}, {0, 2, 16}, {0, 1, 16}, {1, 2, 16}, {1, 1, 16}};
     static const Shape many32[] = {{0, 2, 64}, {0, 1, 64}, {1, 2, 64}, {2, 2, 64}, {0, 2, 32}, {0, 1, 32}, {1, 2, 32}, {1, 1, 64}, {1, 1, 32}, {0, 2, 16}, {0, 1, 16}, {1, 2, 16}, {1, 1, 16}};
-    // y in global memory: with fewer planes than half of the CUs nothing but the second chunk hides the latency
+    // y in global memory: with fewer planes than half of the CUs nothing but the second chunk hides the latency; with more, 16-bit
+    // maps run faster a chunk at a time (128 planes 320x320 bf16 290, with two chunks 320; 226x207 172 and 187)
     static const Shape mem_few[] = {{2, 2, 64}, {2, 2, 32}, {2, 1, 64}, {2, 1, 32}, {2, 2, 16}, {2, 1, 16}};
-    static const Shape mem_many[] = {{2, 2, 64}, {2, 1, 64}, {2, 2, 32}, {2, 1, 32}, {2, 2, 16}, {2, 1, 16}};
+    static const Shape mem_many16[] = {{2, 1, 64}, {2, 2, 64}, {2, 2, 32}, {2, 1, 32}, {2, 2, 16}, {2, 1, 16}};
+    static const Shape mem_many32[] = {{2, 2, 64}, {2, 1, 64}, {2, 2, 32}, {2, 1, 32}, {2, 2, 16}, {2, 1, 16}};
     auto first_of = [&](const Shape* t, int n, int wgs) {
         for (int i = 0; i < n; ++i)
             if (!(must_tile && t[i].mode == 2) && fits(t[i].mode, t[i].nbuf, t[i].seg, wgs, t[i].mode == 2 ? 16 : 32)) return true;
@@ -121,7 +123,7 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
     for (int wgs = wgs_wanted; wgs > 1; wgs /= 2)
         if (f32 ? first_of(several32, 4, wgs) : first_of(several16, 6, wgs)) return true;
     if (planes <= 256 ? (f32 ? first_of(few32, 13, 1) : first_of(few16, 12, 1)) : (f32 ? first_of(many32, 13, 1) : first_of(many16, 12, 1))) return true;
-    const Shape* const mem = planes < 128 ? mem_few : mem_many;
+    const Shape* const mem = planes < 128 ? mem_few : f32 ? mem_many32 : mem_many16;
     for (int i = 0; i < 6; ++i)
         for (int wgs = wgs_wanted; wgs >= 1; wgs /= 2)
             if (first_of(mem + i, 1, wgs)) return true;
@@ -154,17 +156,21 @@ int ragged_fwd_threads(const FwdParams& p, int dtype) {
 }
 bool ragged_applicable(const FwdParams& p, int dtype) { return ragged_fwd_threads(p, dtype) != 0; }
 
-static hipError_t launch_ragged(const FwdParams& p, int dtype, bool reverse, void* e_lo, hipStream_t s) {
+static hipError_t launch_ragged(const FwdParams& p, int dtype, bool reverse, bool merge_rounds, void* e_lo, hipStream_t s) {
     RaggedArgs a = {};
     int threads, nv;
     size_t lds;
-    if (!ragged_plan(p, dtype, reverse, &a, &threads, &nv, &lds)) return hipErrorInvalidValue;
+    if (!ragged_plan(p, dtype, merge_rounds, &a, &threads, &nv, &lds)) return hipErrorInvalidValue;
     a.hs_lo = e_lo;
     if (dtype == 0) return (a.tile ? launch_ragged_f32_tile : launch_ragged_f32_mem)(a, reverse, threads, nv, lds, s);
     if (dtype == 1) return (a.tile ? launch_ragged_bf16_tile : launch_ragged_bf16_mem)(a, reverse, threads, nv, lds, s);
     return (a.tile ? launch_ragged_f16_tile : launch_ragged_f16_mem)(a, reverse, threads, nv, lds, s);
 }
-hipError_t launch_fwd_ragged(const FwdParams& p, int dtype, hipStream_t s) { return launch_ragged(p, dtype, false, nullptr, s); }
+hipError_t launch_fwd_ragged(const FwdParams& p, int dtype, hipStream_t s) { return launch_ragged(p, dtype, false, false, nullptr, s); }
+
+// The first pass of the two-pass backward call: e rounded to storage, and gx merged, as the other kernels of that pass do.
+bool reverse_sweep_ragged_applicable(const FwdParams& p, int dtype) { return ragged_threads(p, dtype, false) != 0; }
+hipError_t launch_reverse_sweep_ragged(const FwdParams& p, int dtype, hipStream_t s) { return launch_ragged(p, dtype, true, false, nullptr, s); }
 
 namespace {
 
@@ -376,7 +382,7 @@ bool ragged_bwd_applicable(const BwdParams& p, int dtype) { return ragged_bwd_th
 // over the channels.
 hipError_t launch_bwd_ragged(const BwdParams& p, int dtype, hipStream_t s) {
     const FwdParams f = ragged_sweep_params(p);
-    hipError_t e = launch_ragged(f, dtype, true, dtype == 0 ? nullptr : p.gu, s);
+    hipError_t e = launch_ragged(f, dtype, true, true, dtype == 0 ? nullptr : p.gu, s);
     if (e != hipSuccess) return e;
     int ndirs = 0;
     for (int d = 0; d < 4; ++d) ndirs += (p.mask >> d) & 1u;

@@ -38,7 +38,7 @@ constexpr int RG_SUB = 8;        // scan steps between two meetings of the waves
 
 struct RaggedArgs {
     FwdParams p;
-    void* hs_lo;                 // reverse sweep in 16-bit storage: low halves of e (high halves: p.hs); e stays fp32 between the passes
+    void* hs_lo;                 // reverse sweep in 16-bit storage: low halves of e (high halves: p.hs), which stays fp32 between the passes; null: e is rounded
     int nd;                      // directions of an axis walked at once (1 or 2)
     int tile;                    // 1: merged output in an LDS tile; 0: in global memory
     int nbuf;                    // chunks of a direction in LDS: 2 (scan, load and finish work on neighbouring chunks at once) or 1 (in turn)
@@ -300,7 +300,7 @@ struct RaggedPass {
         if constexpr (MODE != RG_FWD) {
             if constexpr (sizeof(T) == 4) {
                 out.v = u32x4{__float_as_uint(h[0]), __float_as_uint(h[1]), __float_as_uint(h[2]), __float_as_uint(h[3])};
-            } else if constexpr (BWD) {                  // e as two 16-bit halves of its fp32 word
+            } else if (BWD && a.hs_lo) {                 // e as two 16-bit halves of its fp32 word
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     out.v[i] = __builtin_amdgcn_perm(__float_as_uint(h[2 * i + 1]), __float_as_uint(h[2 * i]), 0x07060302u);
@@ -339,14 +339,14 @@ struct RaggedPass {
         const uint32_t off = (uint32_t)(g.off + k * off_step());
         if (n >= E) {
             if constexpr (MODE != RG_FWD) rg_store((T*)(HS + off), out.v);
-            if constexpr (BWD && sizeof(T) == 2) rg_store((T*)(LO + off), out.lw);
+            if constexpr (BWD && sizeof(T) == 2) { if (a.hs_lo) rg_store((T*)(LO + off), out.lw); }
             if constexpr (!TILE) rg_store((T*)(Y + off), out.y);
         } else {
 #pragma unroll
             for (int e = 0; e < E; ++e)
                 if (e < n) {
                     if constexpr (MODE != RG_FWD) rg_store_bits((T*)(HS + off) + e, rg_bits<T>(out.v, e));
-                    if constexpr (BWD && sizeof(T) == 2) rg_store_bits((T*)(LO + off) + e, rg_bits<T>(out.lw, e));
+                    if constexpr (BWD && sizeof(T) == 2) { if (a.hs_lo) rg_store_bits((T*)(LO + off) + e, rg_bits<T>(out.lw, e)); }
                     if constexpr (!TILE) rg_store_bits((T*)(Y + off) + e, rg_bits<T>(out.y, e));
                 }
         }
