@@ -46,8 +46,10 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
         if (waves < 2 || fixed >= cap / wgs) return false;
         const size_t room = cap / wgs - fixed;
         // positions per lane: a line in one wave (no meetings within a chunk) up to 192 positions, beyond that two, and four
-        // where the scanning waves would otherwise leave too few for the loads
-        const int v = longest <= 64 ? 1 : longest <= 128 ? 2 : longest <= 192 ? 3 : longest <= 448 ? 2 : 4;
+        // where the scanning waves would otherwise leave too few for the loads.  With y in global memory the LDS has room for long
+        // chunks, and four positions of one wave beat two of two or three that meet up to 256 (128 planes 226x207 bf16 180 -> 131
+        // us, 512 planes 256x192 352 -> 332); with the tile the chunks are short and they do not (128 planes 23x251 38 -> 51).
+        const int v = longest <= 64 ? 1 : longest <= 128 ? 2 : longest <= 192 ? 3 : longest <= (a.tile ? 0 : 256) ? 4 : longest <= 448 ? 2 : 4;
         for (int ax = 0; ax < 2; ++ax) {
             const int L = ((ax ? H : W) + v - 1) / v * v;
             if (ax == 0) {                                              // granules are written whole, one slot apart
@@ -109,11 +111,10 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
     static const Shape few32[] = {{0, 2, 64}, {0, 1, 64}, {2, 2, 64}, {0, 2, 32}, {0, 1, 32}, {1, 2, 64}, {1, 2, 32}, {0, 2, 16}, {1, 1, 64}, {1, 1, 32}, {0, 1, 16}, {1, 2, 16}, {1, 1, 16}};
     static const Shape many16[] = {{0, 2, 64}, {0, 1, 64}, {0, 2, 32}, {0, 1, 32}, {1, 2, 64}, {1, 2, 32}, {1, 1, 64}, {1, 1, 32}, {0, 2, 16}, {0, 1, 16}, {1, 2, 16}, {1, 1, 16}};
     static const Shape many32[] = {{0, 2, 64}, {0, 1, 64}, {1, 2, 64}, {2, 2, 64}, {0, 2, 32}, {0, 1, 32}, {1, 2, 32}, {1, 1, 64}, {1, 1, 32}, {0, 2, 16}, {0, 1, 16}, {1, 2, 16}, {1, 1, 16}};
-    // y in global memory: with fewer planes than half of the CUs nothing but the second chunk hides the latency; with more, 16-bit
-    // maps run faster a chunk at a time (128 planes 320x320 bf16 290, with two chunks 320; 226x207 172 and 187)
+    // y in global memory: with fewer planes than half of the CUs nothing but the second chunk hides the latency; with more,
+    // 64 bytes of a row per request count for more (128 planes 320x320 bf16: one chunk and 64 bytes 290, two and 32 bytes 320)
     static const Shape mem_few[] = {{2, 2, 64}, {2, 2, 32}, {2, 1, 64}, {2, 1, 32}, {2, 2, 16}, {2, 1, 16}};
-    static const Shape mem_many16[] = {{2, 1, 64}, {2, 2, 64}, {2, 2, 32}, {2, 1, 32}, {2, 2, 16}, {2, 1, 16}};
-    static const Shape mem_many32[] = {{2, 2, 64}, {2, 1, 64}, {2, 2, 32}, {2, 1, 32}, {2, 2, 16}, {2, 1, 16}};
+    static const Shape mem_many[] = {{2, 2, 64}, {2, 1, 64}, {2, 2, 32}, {2, 1, 32}, {2, 2, 16}, {2, 1, 16}};
     auto first_of = [&](const Shape* t, int n, int wgs) {
         for (int i = 0; i < n; ++i)
             if (!(must_tile && t[i].mode == 2) && fits(t[i].mode, t[i].nbuf, t[i].seg, wgs, t[i].mode == 2 ? 16 : 32)) return true;
@@ -123,7 +124,7 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
     for (int wgs = wgs_wanted; wgs > 1; wgs /= 2)
         if (f32 ? first_of(several32, 4, wgs) : first_of(several16, 6, wgs)) return true;
     if (planes <= 256 ? (f32 ? first_of(few32, 13, 1) : first_of(few16, 12, 1)) : (f32 ? first_of(many32, 13, 1) : first_of(many16, 12, 1))) return true;
-    const Shape* const mem = planes < 128 ? mem_few : f32 ? mem_many32 : mem_many16;
+    const Shape* const mem = planes < 128 ? mem_few : mem_many;
     for (int i = 0; i < 6; ++i)
         for (int wgs = wgs_wanted; wgs >= 1; wgs /= 2)
             if (first_of(mem + i, 1, wgs)) return true;
