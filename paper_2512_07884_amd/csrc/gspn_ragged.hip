@@ -175,54 +175,61 @@ hipError_t launch_reverse_sweep_ragged(const FwdParams& p, int dtype, hipStream_
 
 namespace {
 
+// A granule moved by one element: element e - 1 (BACK) or e + 1, from the lane before or after across the granule's ends.
+template <typename T, bool BACK> __device__ __forceinline__ u32x4 next_element(u32x4 v) {
+    const uint32_t below = __float_as_uint(from_lane_below(__uint_as_float(v[3]))), above = __float_as_uint(from_lane_above(__uint_as_float(v[0])));
+    if constexpr (sizeof(T) == 4) return BACK ? u32x4{below, v[0], v[1], v[2]} : u32x4{v[1], v[2], v[3], above};
+    else if constexpr (BACK) return u32x4{__builtin_amdgcn_alignbit(v[0], below, 16), __builtin_amdgcn_alignbit(v[1], v[0], 16), __builtin_amdgcn_alignbit(v[2], v[1], 16), __builtin_amdgcn_alignbit(v[3], v[2], 16)};
+    else return u32x4{__builtin_amdgcn_alignbit(v[1], v[0], 16), __builtin_amdgcn_alignbit(v[2], v[1], 16), __builtin_amdgcn_alignbit(v[3], v[2], 16), __builtin_amdgcn_alignbit(above, v[3], 16)};
+}
+
 // Second pass of the backward call: per pixel and direction the sum over the group's channels of e * h of the previous
-// line (gw), glam = x*e and gu = gy*h.  A thread owns 16 bytes of an image row; every tensor, the three taps of h
-// included, is one 16-byte request at element alignment (a tap is the same window one row or one column away).  e comes
+// line (gw), glam = x*e and gu = gy*h.  A thread owns 16 bytes of an image row.  The states of a tap one column away are the
+// same granule's, moved by an element (next_element), not a request of their own: lanes hold consecutive granules, and the first
+// and last lane of a wave hold their neighbours' for that and nothing else.  A 16-bit request one element off takes the address
+// unit four times as long as an aligned one, and there were two or three of eight: backward call of 1024 planes 80x136 bf16 352 ->
+// 323 us, of 384 planes 65x191 with logits 124 -> 114.  e comes
 // in fp32: from glam itself in fp32 storage, else its two halves from glam (high) and gu (low).  Every thread reads its
 // own e before it overwrites it.  SL = 4: the four waves of a workgroup take every fourth channel of the same pixels and
 // add their sums in wave order through LDS -- calls have few (image, group) pairs, and one thread walking all channels
 // left four waves per CU waiting on one channel's requests at a time; a channel's requests also go out before the
 // previous channel is stored.  Bound by memory: 16 B per pixel, channel and direction in 16-bit storage beside x and gy.
-template <typename T, int SL>
-__global__ void __launch_bounds__(256) ragged_finish_kernel(BwdParams p, int ndirs) {
+constexpr int RG_LIVE = 62;                                    // granules of a wave: all lanes but the first and the last
+template <typename T, int SL, bool VERT>
+__device__ __forceinline__ void ragged_finish(const BwdParams& p, int d, unsigned blk, float (*red)[3 * 16 / (int)sizeof(T)][64]) {
     constexpr int E = 16 / (int)sizeof(T);
     const int H = p.H, W = p.W, HW = H * W;
     const int gpr = (W + E - 1) / E;
     const int npb = H * gpr;
     const size_t per_dir = (size_t)p.B * p.G * npb;
-    // the workgroups that work on the same pixels in the different directions read the same x and gy: indices 8 apart
-    // go to the same XCD one after the other
-    const unsigned wg = blockIdx.x;
-    int dsel = (int)((wg / 8) % (unsigned)ndirs);
-    const unsigned blk = (wg / (8 * (unsigned)ndirs)) * 8 + (wg % 8);
-    constexpr int GPB = 256 / SL;                              // granules per workgroup
-    const int slice = SL == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / GPB), lane = threadIdx.x % GPB;
-    const size_t want = (size_t)blk * GPB + lane;
-    const bool live = want < per_dir;
-    const size_t rem = live ? want : per_dir - 1;              // spare lanes read the last granule and store nothing
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, slice = SL == 1 ? 0 : wave;
+    const long long want = (long long)(SL == 1 ? blk * 4 + wave : blk) * RG_LIVE + lane - 1;
+    const bool live = lane > 0 && lane <= RG_LIVE && want < (long long)per_dir;
+    const size_t rem = (size_t)min(max(want, 0ll), (long long)per_dir - 1);   // spare lanes read some granule and store nothing
     const int bg = (int)(rem / npb);
     const int q = (int)(rem - (size_t)bg * npb);
     const int row = q / gpr, col = (q - row * gpr) * E;
     const int off = row * W + col;
     const int n = min(E, W - col);                             // valid elements
-    int d = 0;
-    for (;; ++d)
-        if ((p.mask >> d) & 1u) { if (dsel == 0) break; --dsel; }
     const int b = bg / p.G, g = bg - b * p.G;
     const size_t planes = (size_t)p.B * p.C, groups = (size_t)p.B * p.G;
-    const bool vert = d < 2;
+    constexpr bool vert = VERT;
     const int back = (d & 1) ? 1 : -1;                         // to the previous line of the scan
     const int S = vert ? H : W, L = vert ? W : H;
     // windows: own pixels, and per tap; kept inside the tensor (they may reach into neighbouring planes)
     const int lo = bg == 0 ? 0 : -HW, hi = bg == (int)groups - 1 ? HW - E : 2 * HW - E;
     const int sh = off - min(max(off, lo), hi);
-    int toff[3], tsh[3];
+    // of a vertical scan the row the states come from, of a horizontal one the rows above and below (its own is hc)
+    int toff[2], tsh[2];
     uint32_t tmask[3];                                         // bit e: tap k of element e exists
 #pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int o = off + (vert ? back * W : i == 0 ? -W : W);
+        tsh[i] = o - min(max(o, lo), hi);
+        toff[i] = o - tsh[i];
+    }
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const int o = off + (vert ? back * W + k - 1 : (k - 1) * W + back);
-        tsh[k] = o - min(max(o, lo), hi);
-        toff[k] = o - tsh[k];
         tmask[k] = 0;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -232,7 +239,7 @@ __global__ void __launch_bounds__(256) ragged_finish_kernel(BwdParams p, int ndi
             if (r >= 0 && r < H && c >= 0 && c < W && e < n && !starts) tmask[k] |= 1u << e;
         }
     }
-    const bool moved = __any(sh != 0 || tsh[0] != 0 || tsh[1] != 0 || tsh[2] != 0);
+    const bool moved = __any(sh != 0 || tsh[0] != 0 || tsh[1] != 0);
     const size_t plane0 = ((size_t)b * p.C + (size_t)g * p.cpg) * HW;
     const T* X = (const T*)p.x + plane0 + (off - sh);
     const T* GY = (const T*)p.gy + plane0 + (off - sh);
@@ -245,24 +252,33 @@ __global__ void __launch_bounds__(256) ragged_finish_kernel(BwdParams p, int ndi
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[k][e] = 0.f;
 
-    u32x4 eh, el = {0, 0, 0, 0}, xv, gv, hc, t0, t1, t2;
-    auto request = [&](int ci, u32x4& eh_, u32x4& el_, u32x4& xv_, u32x4& gv_, u32x4& hc_, u32x4& t0_, u32x4& t1_, u32x4& t2_) {
+    u32x4 eh, el = {0, 0, 0, 0}, xv, gv, hc, ta, tb = {0, 0, 0, 0};
+    auto request = [&](int ci, u32x4& eh_, u32x4& el_, u32x4& xv_, u32x4& gv_, u32x4& hc_, u32x4& ta_, u32x4& tb_) {
         const size_t po = (size_t)ci * HW;
         eh_ = rg_load((const T*)GL + po + (off - sh));
         if constexpr (sizeof(T) == 2) el_ = rg_load((const T*)GU + po + (off - sh));
         xv_ = rg_load(X + po); gv_ = rg_load(GY + po); hc_ = rg_load(HS + po + (off - sh));
-        t0_ = rg_load(HS + po + toff[0]); t1_ = rg_load(HS + po + toff[1]); t2_ = rg_load(HS + po + toff[2]);
+        ta_ = rg_load(HS + po + toff[0]);
+        if constexpr (!VERT) tb_ = rg_load(HS + po + toff[1]);
     };
-    request(slice < p.cpg ? slice : 0, eh, el, xv, gv, hc, t0, t1, t2);
+    request(slice < p.cpg ? slice : 0, eh, el, xv, gv, hc, ta, tb);
     for (int ci = slice; ci < p.cpg; ci += SL) {
         const size_t po = (size_t)ci * HW;
         // the next channel's values before this one's are stored
-        u32x4 eh_n, el_n = {0, 0, 0, 0}, xv_n, gv_n, hc_n, t0_n, t1_n, t2_n;
+        u32x4 eh_n, el_n = {0, 0, 0, 0}, xv_n, gv_n, hc_n, ta_n, tb_n = {0, 0, 0, 0};
         const bool more = ci + SL < p.cpg;
-        if (more) request(ci + SL, eh_n, el_n, xv_n, gv_n, hc_n, t0_n, t1_n, t2_n);
+        if (more) request(ci + SL, eh_n, el_n, xv_n, gv_n, hc_n, ta_n, tb_n);
         if (moved) {
             eh = rg_realign<T>(eh, sh); el = rg_realign<T>(el, sh); xv = rg_realign<T>(xv, sh); gv = rg_realign<T>(gv, sh); hc = rg_realign<T>(hc, sh);
-            t0 = rg_realign<T>(t0, tsh[0]); t1 = rg_realign<T>(t1, tsh[1]); t2 = rg_realign<T>(t2, tsh[2]);
+            ta = rg_realign<T>(ta, tsh[0]); tb = rg_realign<T>(tb, tsh[1]);
+        }
+        u32x4 t0, t1, t2;
+        if constexpr (VERT) {
+            t0 = next_element<T, true>(ta); t1 = ta; t2 = next_element<T, false>(ta);
+        } else if (d & 1) {
+            t0 = next_element<T, false>(ta); t1 = next_element<T, false>(hc); t2 = next_element<T, false>(tb);
+        } else {
+            t0 = next_element<T, true>(ta); t1 = next_element<T, true>(hc); t2 = next_element<T, true>(tb);
         }
         float gl[E], gu[E];
 #pragma unroll
@@ -293,10 +309,9 @@ __global__ void __launch_bounds__(256) ragged_finish_kernel(BwdParams p, int ndi
             for (int e = 0; e < E; ++e)
                 if (e < n) { rg_store_bits(GL + po + off + e, rg_bits<T>(vl, e)); rg_store_bits(GU + po + off + e, rg_bits<T>(vu, e)); }
         }
-        if (more) { eh = eh_n; el = el_n; xv = xv_n; gv = gv_n; hc = hc_n; t0 = t0_n; t1 = t1_n; t2 = t2_n; }
+        if (more) { eh = eh_n; el = el_n; xv = xv_n; gv = gv_n; hc = hc_n; ta = ta_n; tb = tb_n; }
     }
     if constexpr (SL > 1) {
-        __shared__ float red[SL - 1][3 * E][GPB];
         if (slice > 0) {
 #pragma unroll
             for (int k = 0; k < 3; ++k)
@@ -347,6 +362,21 @@ __global__ void __launch_bounds__(256) ragged_finish_kernel(BwdParams p, int ndi
     }
 }
 
+template <typename T, int SL>
+__global__ void __launch_bounds__(256) ragged_finish_kernel(BwdParams p, int ndirs) {
+    __shared__ float red[SL > 1 ? SL - 1 : 1][3 * 16 / (int)sizeof(T)][64];
+    // the workgroups that work on the same pixels in the different directions read the same x and gy: indices 8 apart
+    // go to the same XCD one after the other
+    const unsigned wg = blockIdx.x;
+    int dsel = (int)((wg / 8) % (unsigned)ndirs);
+    const unsigned blk = (wg / (8 * (unsigned)ndirs)) * 8 + (wg % 8);
+    int d = 0;
+    for (;; ++d)
+        if ((p.mask >> d) & 1u) { if (dsel == 0) break; --dsel; }
+    if (d < 2) ragged_finish<T, SL, true>(p, d, blk, red);
+    else ragged_finish<T, SL, false>(p, d, blk, red);
+}
+
 FwdParams ragged_sweep_params(const BwdParams& p) {
     FwdParams f = {};
     f.x = p.gy; f.w = p.w; f.lam = p.u; f.u = p.lam; f.y = p.gx; f.hs = p.glam;
@@ -362,7 +392,7 @@ unsigned long long ragged_finish_blocks(const BwdParams& p, int dtype) {
     const unsigned long long per_dir = (unsigned long long)p.B * p.G * p.H * ((p.W + E - 1) / E);
     int ndirs = 0;
     for (int d = 0; d < 4; ++d) ndirs += (p.mask >> d) & 1u;
-    const unsigned long long gpb = 256 / ragged_slices(p);
+    const unsigned long long gpb = ragged_slices(p) > 1 ? RG_LIVE : 4 * RG_LIVE;
     return ((per_dir + gpb - 1) / gpb + 7) / 8 * 8 * ndirs;         // per direction: a multiple of 8 workgroups
 }
 
