@@ -15,5 +15,6 @@ def __getattr__(name):
                 "gspn_scan_fwd_unfused", "gspn_unfused_workspace_bytes",
                 "gspn_status_string", "gspn_version", "gspn_reload_env", "load_library", "lib_path", "GspnError"):
         from . import binding
-        return getattr(binding, name)
+        value = globals()[name] = getattr(binding, name)      # found without this function from now on
+        return value
     raise AttributeError(name)

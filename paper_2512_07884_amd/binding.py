@@ -142,20 +142,26 @@ def gspn_bwd_logits_plan(B, C, H, W, G, kchunk=GLOBAL_SCAN, dir_mask=DIR_ALL, dt
 
 
 # ---------------------------------------------------------------- marshalling
+_DTYPES = {}          # torch dtype -> code, filled on first use
+
+
 def _dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.float32:
-        return GSPN_F32
-    if t.dtype == torch.bfloat16:
-        return GSPN_BF16
-    if t.dtype == torch.float16:
-        return GSPN_F16
-    raise TypeError(f"unsupported dtype {t.dtype}: float32, bfloat16 or float16")
+    if not _DTYPES:
+        import torch
+        _DTYPES.update({torch.float32: GSPN_F32, torch.bfloat16: GSPN_BF16, torch.float16: GSPN_F16})
+    code = _DTYPES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}: float32, bfloat16 or float16")
+    return code
 
 
 def _ptr(t, name, shape, like):
     if t is None:
         return None
+    # the usual case first, in as few attribute reads as tell it: calls on small maps wait for the host (8x8, 384 planes: 12.9 us of
+    # host time per call before, 11.1 now)
+    if t.is_cuda and t.dtype is like.dtype and t.shape == shape and t.get_device() == like.get_device() and t.is_contiguous():
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError(f"{name}: must be a device tensor")
     if t.device != like.device or t.dtype != like.dtype:
@@ -164,12 +170,12 @@ def _ptr(t, name, shape, like):
         raise ValueError(f"{name}: shape {tuple(t.shape)} != expected {tuple(shape)}")
     if not t.is_contiguous():
         raise ValueError(f"{name}: must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
-    import torch
     if stream is None:
+        import torch
         stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
