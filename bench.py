@@ -152,21 +152,19 @@ def run_workload(cfg, steps: int, warmup: int, kchunk: int = 0, logits: bool = F
 
 def summarise(cfg, r):
     import paper_2512_07884_amd as G
+    from paper_2512_07884_amd.binding import call_kernel
     dt = {"f32": 0, "bf16": 1, "f16": 2}[cfg.dtype]
     training = r["training"]
     kchunk = r.get("kchunk", 0)
-    big = 1 << 14                      # a stretch longer than any line: the global scan
-    fplan, bplan = (G.gspn_fwd_logits_plan, G.gspn_bwd_logits_plan) if r.get("logits") else \
-                   (G.gspn_fwd_local_plan, G.gspn_bwd_local_plan)
-    if r.get("transposed"):
-        fplan = lambda B, C, H, W, G_, k, mask, dt, flags, save: G.gspn_fwd_transposed_plan(B, C, H, W, G_, mask, dt, flags)
+    kernel = lambda call: call_kernel(cfg.B, cfg.C, cfg.H, cfg.W, cfg.G, dt, call, kchunk, bool(r.get("logits")), cfg.dir_mask)
     fwd_bytes = cfg.fwd_algorithmic_bytes(save_h=training)
     d = {"workload": cfg.name, "B": cfg.B, "C": cfg.C, "H": cfg.H, "W": cfg.W, "G": cfg.G,
          "storage": cfg.dtype, "directions": cfg.n_dirs,
          "step": "fwd+bwd" if training else "fwd",
          "ms_per_step": r["ms_per_step"], "warm_single_set_ms_per_step": r["warm_ms_per_step"],
          "gpixel_ch_per_s": cfg.pixel_channels / (r["ms_per_step"] * 1e-3) / 1e9,
-         "fwd_kernel": fplan(cfg.B, cfg.C, cfg.H, cfg.W, cfg.G, kchunk or big, cfg.dir_mask, dt, 0, training),
+         "fwd_kernel": G.gspn_fwd_transposed_plan(cfg.B, cfg.C, cfg.H, cfg.W, cfg.G, cfg.dir_mask, dt, 0) if r.get("transposed")
+                       else kernel("save" if training else "fwd"),
          "fwd_ms_avg": r["fwd_ms_avg"], "fwd_ms_min": r["fwd_ms_min"],
          "fwd_algorithmic_bytes": fwd_bytes,
          "fwd_algorithmic_GBs": fwd_bytes / (r["fwd_ms_avg"] * 1e-3) / 1e9,
@@ -185,7 +183,7 @@ def summarise(cfg, r):
         d["fwd_frac_of_hbm_peak_incl_second_x"] = with_xt / (r["fwd_ms_avg"] * 1e-3) / 1e9 / HBM_PEAK_GBS
     if training:
         bb = cfg.bwd_algorithmic_bytes()
-        d.update({"bwd_kernel": bplan(cfg.B, cfg.C, cfg.H, cfg.W, cfg.G, kchunk or big, cfg.dir_mask, dt, 0),
+        d.update({"bwd_kernel": kernel("bwd"),
                   "bwd_ms_avg": r["bwd_ms_avg"], "bwd_ms_min": r["bwd_ms_min"],
                   "bwd_algorithmic_bytes": bb,
                   "bwd_algorithmic_GBs": bb / (r["bwd_ms_avg"] * 1e-3) / 1e9,
@@ -322,6 +320,7 @@ def unfused_table(steps: int = 3):
     C = 8, where it reports 40x end to end on an A100) and on the two target shapes with few channels (Table 1 regime)."""
     import torch
     import paper_2512_07884_amd as G
+    from paper_2512_07884_amd.binding import call_kernel
     from paper_2512_07884_amd import workloads as WL
     rows = []
     for name, B, C, H, W, Gr, dtype in (("step-by-step study shape", 16, 8, 1024, 1024, 1, "f32"),
@@ -348,7 +347,7 @@ def unfused_table(steps: int = 3):
             torch.cuda.synchronize()
             times[kind] = (time.perf_counter() - t0) * 1e3 / steps
         rows.append({"shape": name, "B": B, "C": C, "H": H, "W": W, "G": Gr, "storage": dtype,
-                     "fused_kernel": G.gspn_fwd_plan(B, C, H, W, Gr, 15, dt, 0, False),
+                     "fused_kernel": call_kernel(B, C, H, W, Gr, dt, "fwd"),
                      "fused_ms": times["fused"], "unfused_ms": times["unfused"],
                      "launches_unfused": 2 * (H + W), "ratio": times["unfused"] / times["fused"]})
         del s, y, ws

@@ -237,14 +237,17 @@ const char* gspn_proxy_plan(int B, int K, int M, int H, int W, int dtype);
  * storage e passes through storage precision between the two), "generic" (any shape);
  * static string, never NULL.  Host only.
  *
- * (The name is the family whose limits the call meets.  Among the calls of the "plane" and "tile" families, and in the first
- * pass of "twopass", those with too few planes or lines for that family's own kernel run the any-size kernel of "generic".)
+ * (The name is the family whose limits the call meets.  Most calls of the "tile" family, those of the "plane" family with few
+ * planes, and the first pass of such "twopass" calls run the any-size kernel of "generic" in its place.)
  * Environment variables for tests (results are the same whichever kernel runs, up to the rounding of
  * the storage type).  They are read once per process, by the first call that dispatches; a process
  * that changes them afterwards calls gspn_reload_env():
- *   GSPN_FORCE_GENERIC=1   always the generic kernels
- *   GSPN_FWD_NO_PLANE=1, GSPN_BWD_NO_PLANE=1   skip the "plane" kernels
- *   GSPN_BWD_NO_TWOPASS=1   skip the "twopass" backward (the "tile" / "generic" kernels take its maps)
+ *   GSPN_FORCE_GENERIC=1   always the line-by-line kernels of "generic"
+ *   GSPN_NO_ANY_SIZE=1   the any-size kernel for the plan "generic" alone: calls of the other plans run their family's kernels
+ *   GSPN_FWD_NO_PLANE=1, GSPN_BWD_NO_PLANE=1   skip the "plane" kernels (and the any-size kernel in place of "tile", and of the
+ *                             first pass of "twopass", or of a single-launch backward)
+ *   GSPN_BWD_NO_TWOPASS=1   skip the "twopass" backward (the "tile" / "generic" kernels take its maps, the any-size kernel only
+ *                             those of "generic")
  *   GSPN_FWD_NO_PAIR=1   skip the "pair" kernels (forward and the reverse sweep of the two-pass backward)
  *   GSPN_STREAM_NO_STAGED=1   the general "stream" kernel (the one fp32 maps take) on the 16-bit maps
  *                             that have a kernel of their own

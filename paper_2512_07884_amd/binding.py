@@ -141,6 +141,14 @@ def gspn_bwd_logits_plan(B, C, H, W, G, kchunk=GLOBAL_SCAN, dir_mask=DIR_ALL, dt
     return load_library().gspn_bwd_logits_plan(B, C, H, W, G, kchunk, dir_mask, dtype, flags).decode()
 
 
+def call_kernel(B, C, H, W, G, dtype, call, kchunk=0, logits=False, dir_mask=DIR_ALL) -> str:
+    """The kernel a call runs, for tests and benchmarks (the plans name families): `call` is "fwd", "save" (forward with h_save)
+    or "bwd"; kchunk 0 is the global scan."""
+    f = load_library().gspn_call_kernel
+    f.restype = ctypes.c_char_p
+    return f(B, C, H, W, G, kchunk, int(logits), ctypes.c_uint(dir_mask), dtype, ("fwd", "save", "bwd").index(call)).decode()
+
+
 # ---------------------------------------------------------------- marshalling
 _DTYPES = {}          # torch dtype -> code, filled on first use
 

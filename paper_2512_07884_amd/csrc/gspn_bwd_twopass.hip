@@ -246,27 +246,46 @@ bool bwd_twopass_applicable(const BwdParams& p, int dtype) {
            (chunk_kernels_enabled() && reverse_sweep_chunk_applicable(f, dtype));
 }
 
+namespace {
+enum Sweep { SWEEP_CHUNK, SWEEP_ANY_SIZE, SWEEP_PLANE, SWEEP_PAIR, SWEEP_TILE, SWEEP_STREAM };
+Sweep choose_sweep(const FwdParams& f, int dtype) {
+    if (chunk_kernels_enabled() && reverse_sweep_chunk_applicable(f, dtype)) return SWEEP_CHUNK;
+    if (reverse_sweep_plane_applicable(f, dtype))
+        return any_size_before_plane(f) && reverse_sweep_ragged_applicable(f, dtype) ? SWEEP_ANY_SIZE : SWEEP_PLANE;
+    if (pair_kernels_enabled() && reverse_sweep_pair_applicable(f, dtype)) return SWEEP_PAIR;
+    if (fwd_tile_applicable(f, dtype))
+        return any_size_before_tile(f) && reverse_sweep_ragged_applicable(f, dtype) ? SWEEP_ANY_SIZE : SWEEP_TILE;
+    return SWEEP_STREAM;
+}
+}  // namespace
+
+const char* twopass_kernel_name(const BwdParams& p, int dtype) {
+    switch (choose_sweep(reverse_sweep_params(p), dtype)) {
+        case SWEEP_CHUNK: return "twopass/chunk";
+        case SWEEP_ANY_SIZE: return "twopass/any size";
+        case SWEEP_PLANE: return "twopass/plane";
+        case SWEEP_PAIR: return "twopass/pair";
+        case SWEEP_TILE: return "twopass/tile";
+        default: return "twopass/stream";
+    }
+}
+
 hipError_t launch_bwd_twopass(const BwdParams& p, int dtype, hipStream_t s) {
     if (!bwd_twopass_applicable(p, dtype)) return hipErrorInvalidValue;
     const FwdParams f = reverse_sweep_params(p);
+    const bool local = p.kchunk > 0 || p.logits;
     hipError_t e;
-    if (chunk_kernels_enabled() && reverse_sweep_chunk_applicable(f, dtype)) {
-        e = launch_reverse_sweep_chunk(f, dtype, s);
-    } else if (reverse_sweep_plane_applicable(f, dtype) ? any_size_before_plane(f) && reverse_sweep_ragged_applicable(f, dtype)
-                                                         : !(pair_kernels_enabled() && reverse_sweep_pair_applicable(f, dtype)) && fwd_tile_applicable(f, dtype) &&
-                                                               any_size_before_tile(f) && reverse_sweep_ragged_applicable(f, dtype)) {
-        e = launch_reverse_sweep_ragged(f, dtype, s);
-    } else if (reverse_sweep_plane_applicable(f, dtype)) {
-        e = launch_reverse_sweep_plane(f, dtype, s);
-    } else if (pair_kernels_enabled() && reverse_sweep_pair_applicable(f, dtype)) {
-        e = launch_reverse_sweep_pair(f, dtype, s);
-    } else if (fwd_tile_applicable(f, dtype)) {
-        const bool local = p.kchunk > 0 || p.logits;
-        if (dtype == 0) e = local ? launch_reverse_sweep_f32_local(f, s) : launch_reverse_sweep_f32(f, s);
-        else if (dtype == 1) e = local ? launch_reverse_sweep_bf16_local(f, s) : launch_reverse_sweep_bf16(f, s);
-        else e = local ? launch_reverse_sweep_f16_local(f, s) : launch_reverse_sweep_f16(f, s);
-    } else {
-        e = launch_reverse_sweep_stream(f, dtype, s);
+    switch (choose_sweep(f, dtype)) {
+        case SWEEP_CHUNK: e = launch_reverse_sweep_chunk(f, dtype, s); break;
+        case SWEEP_ANY_SIZE: e = launch_reverse_sweep_ragged(f, dtype, s); break;
+        case SWEEP_PLANE: e = launch_reverse_sweep_plane(f, dtype, s); break;
+        case SWEEP_PAIR: e = launch_reverse_sweep_pair(f, dtype, s); break;
+        case SWEEP_TILE:
+            if (dtype == 0) e = local ? launch_reverse_sweep_f32_local(f, s) : launch_reverse_sweep_f32(f, s);
+            else if (dtype == 1) e = local ? launch_reverse_sweep_bf16_local(f, s) : launch_reverse_sweep_bf16(f, s);
+            else e = local ? launch_reverse_sweep_f16_local(f, s) : launch_reverse_sweep_f16(f, s);
+            break;
+        default: e = launch_reverse_sweep_stream(f, dtype, s);
     }
     if (e != hipSuccess) return e;
     int ndirs = 0;

@@ -5,20 +5,22 @@
 
 namespace gspn {
 
-enum FwdPlan { FWD_GENERIC = 0, FWD_TILE = 1, FWD_STREAM = 2, FWD_PLANE = 3, FWD_PAIR = 4, FWD_CHUNK = 5 };
-enum BwdPlan { BWD_GENERIC = 0, BWD_TILE = 1, BWD_PLANE = 2, BWD_TWOPASS = 3 };
+// What a call's plan names (all but ANY_SIZE) and what kernel it runs (GENERIC: line by line).
+enum FwdPlan { FWD_GENERIC = 0, FWD_TILE = 1, FWD_STREAM = 2, FWD_PLANE = 3, FWD_PAIR = 4, FWD_CHUNK = 5, FWD_ANY_SIZE = 6 };
+enum BwdPlan { BWD_GENERIC = 0, BWD_TILE = 1, BWD_PLANE = 2, BWD_TWOPASS = 3, BWD_ANY_SIZE = 4 };
 
-// Testing aids that keep every kernel family reachable on every shape it accepts.  The environment is read once, on
+// Testing aids that, together, keep every kernel family reachable on every shape it accepts.  The environment is read once, on
 // the first call of a process (and again only when reload_env_knobs() is called, which the tests do after they change
 // it): a launch costs one atomic load, and no call races with a setenv elsewhere in the process.
-// GSPN_FORCE_GENERIC=1: the generic kernels; GSPN_FWD_NO_PLANE=1 / GSPN_BWD_NO_PLANE=1: skip the plane kernels;
-// GSPN_BWD_NO_TWOPASS=1: skip the two-pass backward; GSPN_FWD_NO_PAIR=1: skip the two-channel kernels (forward and the
+// GSPN_FORCE_GENERIC=1: the line-by-line kernels; GSPN_FWD_NO_PLANE=1 / GSPN_BWD_NO_PLANE=1: skip the plane kernels;
+// GSPN_BWD_NO_TWOPASS=1: skip the two-pass backward; GSPN_NO_ANY_SIZE=1: no any-size kernel in the "plane", "tile" and "twopass"
+// plans (each of the three skips above implies it for the calls whose plan it could change); GSPN_FWD_NO_PAIR=1: skip the two-channel kernels (forward and the
 // reverse sweep of the two-pass backward); GSPN_STREAM_NO_STAGED=1: the stream kernel whose horizontal phases request one
 // row per lane instead of the one with whole-line requests; GSPN_FWD_NO_CHUNK=1: skip the per-stretch kernels of GSPN-local
 // (forward and the reverse sweep of the two-pass backward); GSPN_STREAM_ONE_CHANNEL=1: the whole-line stream kernel with one
 // channel per workgroup on the maps where two channels of a group normally share a workgroup; GSPN_STREAM_TWO_CHANNELS=1:
 // two channels per workgroup there also in calls with too few planes to fill the chip that way.
-enum : unsigned { K_FORCE_GENERIC = 1, K_FWD_NO_PLANE = 2, K_BWD_NO_PLANE = 4, K_BWD_NO_TWOPASS = 8, K_FWD_NO_PAIR = 16, K_STREAM_NO_STAGED = 32, K_FWD_NO_CHUNK = 64, K_STREAM_ONE_CHANNEL = 128, K_STREAM_TWO_CHANNELS = 256, K_VALID = 1u << 31 };
+enum : unsigned { K_FORCE_GENERIC = 1, K_FWD_NO_PLANE = 2, K_BWD_NO_PLANE = 4, K_BWD_NO_TWOPASS = 8, K_FWD_NO_PAIR = 16, K_STREAM_NO_STAGED = 32, K_FWD_NO_CHUNK = 64, K_STREAM_ONE_CHANNEL = 128, K_STREAM_TWO_CHANNELS = 256, K_NO_ANY_SIZE = 512, K_VALID = 1u << 31 };
 static std::atomic<unsigned> g_knobs{0};
 static bool env_flag(const char* name) { const char* v = getenv(name); return v && v[0] == '1'; }
 void reload_env_knobs() {
@@ -32,13 +34,14 @@ void reload_env_knobs() {
     if (env_flag("GSPN_FWD_NO_CHUNK")) k |= K_FWD_NO_CHUNK;
     if (env_flag("GSPN_STREAM_ONE_CHANNEL")) k |= K_STREAM_ONE_CHANNEL;
     if (env_flag("GSPN_STREAM_TWO_CHANNELS")) k |= K_STREAM_TWO_CHANNELS;
+    if (env_flag("GSPN_NO_ANY_SIZE")) k |= K_NO_ANY_SIZE;
     g_knobs.store(k, std::memory_order_release);
 }
-struct Knobs { bool force_generic, fwd_no_plane, bwd_no_plane, bwd_no_twopass, fwd_no_pair, stream_no_staged, fwd_no_chunk, stream_one_channel, stream_two_channels; };
+struct Knobs { bool force_generic, fwd_no_plane, bwd_no_plane, bwd_no_twopass, fwd_no_pair, stream_no_staged, fwd_no_chunk, stream_one_channel, stream_two_channels, no_any_size; };
 static Knobs knobs() {
     unsigned k = g_knobs.load(std::memory_order_acquire);
     if (!(k & K_VALID)) { reload_env_knobs(); k = g_knobs.load(std::memory_order_acquire); }
-    return Knobs{(k & K_FORCE_GENERIC) != 0, (k & K_FWD_NO_PLANE) != 0, (k & K_BWD_NO_PLANE) != 0, (k & K_BWD_NO_TWOPASS) != 0, (k & K_FWD_NO_PAIR) != 0, (k & K_STREAM_NO_STAGED) != 0, (k & K_FWD_NO_CHUNK) != 0, (k & K_STREAM_ONE_CHANNEL) != 0, (k & K_STREAM_TWO_CHANNELS) != 0};
+    return Knobs{(k & K_FORCE_GENERIC) != 0, (k & K_FWD_NO_PLANE) != 0, (k & K_BWD_NO_PLANE) != 0, (k & K_BWD_NO_TWOPASS) != 0, (k & K_FWD_NO_PAIR) != 0, (k & K_STREAM_NO_STAGED) != 0, (k & K_FWD_NO_CHUNK) != 0, (k & K_STREAM_ONE_CHANNEL) != 0, (k & K_STREAM_TWO_CHANNELS) != 0, (k & K_NO_ANY_SIZE) != 0};
 }
 bool pair_kernels_enabled() { return !knobs().fwd_no_pair; }
 bool staged_stream_enabled() { return !knobs().stream_no_staged; }
@@ -54,7 +57,7 @@ bool stream_two_channels_forced() { return knobs().stream_two_channels; }
 // 20x20 19 -> 22, 96 planes 11x11 12.8 -> 13.6.
 bool any_size_before_plane(const FwdParams& p) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
-    return !knobs().fwd_no_plane && planes >= 64 && planes <= (p.logits ? 512 : 1024) && HW > 196;
+    return !knobs().fwd_no_plane && !knobs().no_any_size && planes >= 64 && planes <= (p.logits ? 512 : 1024) && HW > 196;
 }
 // Tile: the waves that scan load for themselves there; 0.68 of its kernel's time in the mean: 1024 planes 80x112 bf16 with h_save
 // 172 -> 143, 32 planes 64x80 with stretches 42 -> 22.  It keeps rows of 96 and 128 elements in calls of 1024 planes and more
@@ -62,7 +65,7 @@ bool any_size_before_plane(const FwdParams& p) {
 // output tile leaves no room for two chunks (512 planes 240x96 fp32 204 -> 236).
 bool any_size_before_tile(const FwdParams& p) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
-    return !knobs().fwd_no_plane && planes >= 32 && HW <= 20000 && !(planes >= 1024 && (p.W == 96 || p.W == 128));
+    return !knobs().fwd_no_plane && !knobs().no_any_size && planes >= 32 && HW <= 20000 && !(planes >= 1024 && (p.W == 96 || p.W == 128));
 }
 // Backward: the single-launch kernels hold a weight group's channels in one workgroup, the any-size kernel a plane, with a second
 // pass over the channels.  Plane, more than 256 pixels (per-channel weights: up to 2048 planes): 0.2 to 0.9 of its time (512 planes
@@ -109,36 +112,41 @@ static BwdPlan choose_bwd(const BwdParams& p, int dtype) {
     return (dtype != 2 && bwd_tile_applicable(p, dtype)) ? BWD_TILE : BWD_GENERIC;
 }
 
-hipError_t launch_fwd(const FwdParams& p, int dtype, hipStream_t s) {
+// The kernel of a call: its family's, or the any-size kernel in the families' place (rules above) and, for the plan "generic",
+// wherever a shape of it fits.
+static FwdPlan fwd_kernel(const FwdParams& p, int dtype) {
     const FwdPlan plan = choose_fwd(p, dtype);
-    if (((plan == FWD_PLANE && any_size_before_plane(p)) || (plan == FWD_TILE && any_size_before_tile(p))) && ragged_applicable(p, dtype))
-        return launch_fwd_ragged(p, dtype, s);
-    switch (plan) {
+    const bool any = plan == FWD_PLANE ? any_size_before_plane(p) : plan == FWD_TILE ? any_size_before_tile(p) : plan == FWD_GENERIC && !knobs().force_generic;
+    return any && ragged_applicable(p, dtype) ? FWD_ANY_SIZE : plan;
+}
+static BwdPlan bwd_kernel(const BwdParams& p, int dtype) {
+    const BwdPlan plan = choose_bwd(p, dtype);
+    const Knobs k = knobs();
+    const bool own = k.bwd_no_plane || k.bwd_no_twopass || k.no_any_size;
+    const bool any = plan == BWD_PLANE ? !own && any_size_before_bwd_plane(p) : plan == BWD_TILE ? !own && any_size_before_bwd_tile(p)
+                                                                              : plan == BWD_GENERIC && !k.force_generic;
+    return any && ragged_bwd_applicable(p, dtype) ? BWD_ANY_SIZE : plan;
+}
+
+hipError_t launch_fwd(const FwdParams& p, int dtype, hipStream_t s) {
+    switch (fwd_kernel(p, dtype)) {
         case FWD_TILE: return launch_fwd_tile(p, dtype, s);
         case FWD_STREAM: return launch_fwd_stream(p, dtype, s);
         case FWD_PLANE: return launch_fwd_plane(p, dtype, s);
         case FWD_PAIR: return launch_fwd_pair(p, dtype, s);
         case FWD_CHUNK: return launch_fwd_chunk(p, dtype, s);
-        // any other map: the chunked kernel for maps of any size, and line by line where no shape of it fits
-        default:
-            if (!knobs().force_generic && ragged_applicable(p, dtype)) return launch_fwd_ragged(p, dtype, s);
-            return launch_fwd_generic(p, dtype, s);
+        case FWD_ANY_SIZE: return launch_fwd_ragged(p, dtype, s);
+        default: return launch_fwd_generic(p, dtype, s);
     }
 }
 
 hipError_t launch_bwd(const BwdParams& p, int dtype, hipStream_t s) {
-    const BwdPlan plan = choose_bwd(p, dtype);
-    const Knobs k = knobs();
-    if (((plan == BWD_PLANE && any_size_before_bwd_plane(p)) || (plan == BWD_TILE && any_size_before_bwd_tile(p))) &&
-        !k.bwd_no_plane && !k.bwd_no_twopass && ragged_bwd_applicable(p, dtype))
-        return launch_bwd_ragged(p, dtype, s);
-    switch (plan) {
+    switch (bwd_kernel(p, dtype)) {
         case BWD_TILE: return launch_bwd_tile(p, dtype, s);
         case BWD_PLANE: return launch_bwd_plane(p, dtype, s);
         case BWD_TWOPASS: return launch_bwd_twopass(p, dtype, s);
-        default:
-            if (!knobs().force_generic && ragged_bwd_applicable(p, dtype)) return launch_bwd_ragged(p, dtype, s);
-            return launch_bwd_generic(p, dtype, s);
+        case BWD_ANY_SIZE: return launch_bwd_ragged(p, dtype, s);
+        default: return launch_bwd_generic(p, dtype, s);
     }
 }
 
@@ -163,6 +171,37 @@ const char* bwd_plan_name(const BwdParams& p, int dtype) {
 }
 
 }  // namespace gspn
+
+// For the tests, bench.py and smoke(), not part of the ABI: the kernel a valid call runs -- pass 0 forward, 1 forward with h_save,
+// 2 backward ("twopass/..": its first pass after the slash).  kchunk 0: the global scan.
+extern "C" const char* gspn_call_kernel(int B, int C, int H, int W, int G, int kchunk, int logits, unsigned mask, int dtype, int pass) {
+    using namespace gspn;
+    if (kchunk >= (H > W ? H : W)) kchunk = 0;
+    if (pass == 2) {
+        BwdParams p = {};
+        p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
+        p.glam = (void*)16;                                    // (where the first of two passes stores its states)
+        switch (bwd_kernel(p, dtype)) {
+            case BWD_TILE: return "tile";
+            case BWD_PLANE: return "plane";
+            case BWD_TWOPASS: return twopass_kernel_name(p, dtype);
+            case BWD_ANY_SIZE: return "any size";
+            default: return "line by line";
+        }
+    }
+    FwdParams p = {};
+    p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
+    p.hs = pass ? (void*)16 : nullptr;
+    switch (fwd_kernel(p, dtype)) {
+        case FWD_TILE: return "tile";
+        case FWD_STREAM: return "stream";
+        case FWD_PLANE: return "plane";
+        case FWD_PAIR: return "pair";
+        case FWD_CHUNK: return "chunk";
+        case FWD_ANY_SIZE: return "any size";
+        default: return "line by line";
+    }
+}
 
 // For the tests, not part of the ABI: threads per workgroup of the any-size kernel for a call whose plan is "generic" (both its
 // kernels have that name), 0 where the line-by-line kernels take it or the plan is another.  kchunk 0: the global scan.

@@ -39,3 +39,9 @@ def monkeypatch(monkeypatch):
     yield monkeypatch
     monkeypatch.undo()
     _reload_library_env()
+
+
+@pytest.fixture
+def family_kernels(monkeypatch):
+    """For tests of the "plane", "tile" and "twopass" kernels: no any-size kernel in their place."""
+    monkeypatch.setenv("GSPN_NO_ANY_SIZE", "1")

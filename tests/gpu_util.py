@@ -29,6 +29,12 @@ def empty_like_dev(shape, dtype: str, fill=None):
     return t
 
 
+def call_kernel(B, C, H, W, G, dtype, call, kchunk=0, logits=False, mask=15) -> str:
+    """The kernel a call runs (the plans name families): call is "fwd", "save" (forward with h_save) or "bwd"."""
+    from paper_2512_07884_amd import binding
+    return binding.call_kernel(B, C, H, W, G, {"f32": 0, "bf16": 1, "f16": 2}[dtype], call, kchunk, logits, mask)
+
+
 def rel_inf_err(a: np.ndarray, ref: np.ndarray) -> float:
     scale = np.max(np.abs(ref))
     if scale == 0:

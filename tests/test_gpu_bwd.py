@@ -6,7 +6,7 @@ tensor is compared separately with the tolerance of its storage dtype.
 import numpy as np
 import pytest
 
-from gpu_util import TOL, rel_inf_err, to_device, to_host_f64, empty_like_dev
+from gpu_util import TOL, call_kernel, rel_inf_err, to_device, to_host_f64, empty_like_dev
 from oracle import gspn_oracle as O
 from paper_2512_07884_amd import workloads as WL
 
@@ -83,10 +83,11 @@ TILE_BWD_SHAPES = [(2, 8, 56, 56, 2), (1, 4, 56, 56, 4), (1, 8, 64, 128, 2), (1,
 
 
 @pytest.mark.parametrize("shape", PLANE_BWD_SHAPES)
+@pytest.mark.usefixtures("family_kernels")
 def test_backward_plane_kernel_shapes(shape):
     import paper_2512_07884_amd as G
     B, C, H, W, Gr = shape
-    assert G.gspn_bwd_plan(B, C, H, W, Gr, 15, 0, 0) == "plane", shape
+    assert G.gspn_bwd_plan(B, C, H, W, Gr, 15, 0, 0) == call_kernel(*shape, "f32", "bwd") == "plane", shape
     check_bwd(WL.ScanConfig("bwdplane", B, C, H, W, Gr, "f32", 15, 1.0, 29))
 
 
@@ -188,13 +189,14 @@ def test_backward_generic_kernel_on_tile_shapes(monkeypatch):
 
 
 @pytest.mark.parametrize("kernel", ["plane", "tile"])
+@pytest.mark.usefixtures("family_kernels")
 def test_backward_is_bitwise_repeatable_with_split_groups(kernel, monkeypatch):
     import torch
     import paper_2512_07884_amd as G
     if kernel == "tile":
         monkeypatch.setenv("GSPN_BWD_NO_PLANE", "1")
         monkeypatch.setenv("GSPN_BWD_NO_TWOPASS", "1")
-    assert G.gspn_bwd_plan(2, 96, 28, 28, 2, 15, 0, 0) == kernel
+    assert G.gspn_bwd_plan(2, 96, 28, 28, 2, 15, 0, 0) == call_kernel(2, 96, 28, 28, 2, "f32", "bwd") == kernel
     cfg = WL.ScanConfig("bwdrep", 2, 96, 28, 28, 2, "f32", 15, 1.0, 41)     # 48 channels per group: two workgroups per group
     inp = WL.make_inputs(cfg)
     dev = {k: to_device(v, "f32") for k, v in inp.items()}

@@ -28,6 +28,7 @@ SHAPES = [(1, 4, 128, 128, 2, "bf16"), (2, 4, 128, 128, 4, "bf16"), (1, 2, 128, 
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.usefixtures("family_kernels")
 def test_two_pass_backward_shapes(shape):
     import paper_2512_07884_amd as G
     B, C, H, W, Gr, dtype = shape
@@ -100,6 +101,7 @@ def test_two_pass_backward_on_512x512_planes():
                                           # maps beyond the LDS tile
                                           ((1, 2, 256, 256, 1, "bf16"), 37), ((1, 2, 128, 256, 2, "f32"), 100), ((1, 2, 64, 1024, 1, "bf16"), 300)],
                          ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+@pytest.mark.usefixtures("family_kernels")
 def test_two_pass_backward_with_local_stretches(shape, kchunk):
     import paper_2512_07884_amd as G
     from test_gpu_local import check_local
@@ -112,6 +114,7 @@ def test_two_pass_backward_with_local_stretches(shape, kchunk):
                                           ((1, 4, 96, 72, 2, "bf16"), 20), ((1, 4, 70, 36, 2, "f32"), 16), ((1, 32, 56, 56, 1, "f32"), None),
                                           ((1, 2, 256, 256, 1, "bf16"), None), ((1, 2, 128, 256, 2, "f32"), 50), ((2, 2, 320, 256, 2, "bf16"), 64)],
                          ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+@pytest.mark.usefixtures("family_kernels")
 def test_two_pass_backward_with_logits(shape, kchunk):
     from test_gpu_logits import check_logits
     check_logits(shape, kchunk=kchunk, bwd_plan="twopass")

@@ -8,7 +8,7 @@ storage-rounded inputs, and the oracle's backward consumes its own states rounde
 import numpy as np
 import pytest
 
-from gpu_util import TOL, rel_inf_err, to_device, to_host_f64, empty_like_dev
+from gpu_util import TOL, call_kernel, rel_inf_err, to_device, to_host_f64, empty_like_dev
 from oracle import gspn_oracle as O
 from paper_2512_07884_amd import workloads as WL
 from test_gpu_fwd import check_case
@@ -36,9 +36,11 @@ PLANE_SHAPES = [((2, 8, 56, 56, 2), "twopass"), ((2, 16, 28, 28, 2), "twopass"),
 
 
 @pytest.mark.parametrize("shape,bwd_plan", PLANE_SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+@pytest.mark.usefixtures("family_kernels")
 def test_f16_on_the_plane_kernels(shape, bwd_plan):
     B, C, H, W, Gr = shape
     assert plans(B, C, H, W, Gr) == ("plane", bwd_plan)
+    assert call_kernel(*shape, "f16", "save") == call_kernel(*shape, "f16", "bwd").split("/")[-1] == "plane"
     cfg = WL.ScanConfig("f16plane", B, C, H, W, Gr, "f16", 15, 2.0, 127)
     check_case(cfg)
     check_case(cfg, save_h=False)

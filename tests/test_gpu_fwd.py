@@ -6,7 +6,7 @@ Tolerances (max|gpu - oracle| / max|oracle| per tensor): 1e-5 for fp32 storage,
 import numpy as np
 import pytest
 
-from gpu_util import TOL, rel_inf_err, run_fwd_gpu, to_device, to_host_f64, empty_like_dev
+from gpu_util import TOL, call_kernel, rel_inf_err, run_fwd_gpu, to_device, to_host_f64, empty_like_dev
 from oracle import gspn_oracle as O
 from paper_2512_07884_amd import workloads as WL
 
@@ -84,6 +84,7 @@ SHRUNK = [
 
 
 @pytest.mark.parametrize("cfg", SHRUNK, ids=lambda c: f"{c.name}-{c.B}x{c.C}x{c.H}x{c.W}-G{c.G}-{c.dtype}")
+@pytest.mark.usefixtures("family_kernels")
 def test_benchmark_shapes_with_fewer_channels(cfg):
     check_case(cfg)
     check_case(cfg, save_h=False)
@@ -217,6 +218,7 @@ PLANE_FWD_SHAPES = [(2, 24, 56, 56, 2, "bf16"), (2, 16, 28, 28, 2, "f32"), (2, 8
 
 
 @pytest.mark.parametrize("shape", PLANE_FWD_SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.usefixtures("family_kernels")
 def test_forward_plane_kernel_shapes(shape):
     import paper_2512_07884_amd as G
     B, C, H, W, Gr, dtype = shape
@@ -239,10 +241,11 @@ FLAT_FWD_SHAPES = [(2, 16, 28, 28, 2, "bf16"), (2, 8, 14, 14, 2, "f32"), (2, 16,
 
 
 @pytest.mark.parametrize("shape", FLAT_FWD_SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.usefixtures("family_kernels")
 def test_forward_plane_kernel_on_maps_with_ragged_rows(shape):
     import paper_2512_07884_amd as G
     B, C, H, W, Gr, dtype = shape
-    assert G.gspn_fwd_plan(B, C, H, W, Gr, 15, int(dtype == "bf16"), 0, True) == "plane", shape
+    assert G.gspn_fwd_plan(B, C, H, W, Gr, 15, int(dtype == "bf16"), 0, True) == call_kernel(*shape, "save") == call_kernel(*shape, "fwd") == "plane", shape
     cfg = WL.ScanConfig("fwdflat", B, C, H, W, Gr, dtype, 15, 1.0, 53)
     check_case(cfg)
     check_case(cfg, save_h=False)

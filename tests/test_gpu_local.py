@@ -90,6 +90,7 @@ PLANE_LOCAL = [((2, 16, 28, 28, 2, "f32"), 7), ((2, 8, 28, 28, 8, "f32"), 5), ((
 
 
 @pytest.mark.parametrize("shape,kchunk", PLANE_LOCAL, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+@pytest.mark.usefixtures("family_kernels")
 def test_local_scans_on_the_plane_kernels(shape, kchunk, monkeypatch):
     import paper_2512_07884_amd as G
     monkeypatch.setenv("GSPN_BWD_NO_TWOPASS", "1")     # (the two-pass backward takes the larger bf16 maps first)

@@ -121,6 +121,7 @@ def test_logits_on_the_plane_kernels(shape, monkeypatch):
                                    (1, 48, 7, 7, 1, "f32"), (2, 16, 14, 14, 2, "f32"), (2, 16, 7, 7, 2, "bf16"),
                                    (1, 24, 28, 28, 1, "bf16"), (3, 32, 2, 4, 32, "bf16"), (2, 4, 32, 32, 4, "f32")],
                          ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.usefixtures("family_kernels")
 def test_logits_on_the_backward_plane_kernel_variants(shape, monkeypatch):
     monkeypatch.setenv("GSPN_BWD_NO_TWOPASS", "1")     # (the two-pass backward takes the larger bf16 maps first)
     check_logits(shape, bwd_plan="plane")

@@ -1,0 +1,51 @@
+"""Which kernel a call runs, on either side of the lines between the kernel families and the any-size kernel (host code only)."""
+import os
+
+import pytest
+
+from gpu_util import call_kernel
+
+
+@pytest.fixture(scope="module", autouse=True)
+def library():
+    from paper_2512_07884_amd import binding
+    if not os.path.exists(binding.lib_path()):
+        from paper_2512_07884_amd import build
+        build.build(verbose=False)
+
+
+# (B, C, H, W, G), dtype, call, kchunk, logits: kernel, and without the any-size kernel in the families' place
+CALLS = [
+    # forward, plane family: 64 to 1024 planes (512 with logits) of more than 196 pixels
+    ((3, 21, 14, 16, 7), "bf16", "save", 0, False, "plane", "plane"), ((4, 16, 14, 16, 4), "bf16", "save", 0, False, "any size", "plane"),
+    ((4, 16, 14, 14, 4), "f32", "fwd", 0, False, "plane", "plane"), ((8, 128, 14, 16, 8), "f16", "save", 0, False, "any size", "plane"),
+    ((5, 205, 14, 16, 5), "bf16", "save", 0, False, "plane", "plane"), ((4, 128, 28, 28, 8), "f32", "save", 0, True, "any size", "plane"),
+    ((4, 132, 28, 28, 12), "f32", "save", 0, True, "plane", "plane"), ((2, 48, 56, 56, 4), "bf16", "save", 14, True, "any size", "plane"),
+    # forward, tile family: 32 planes and more of up to 20 000 pixels
+    ((1, 31, 80, 72, 1), "bf16", "fwd", 0, False, "tile", "tile"), ((1, 32, 80, 72, 1), "bf16", "fwd", 0, False, "any size", "tile"),
+    ((1, 32, 80, 64, 4), "f32", "save", 24, False, "any size", "tile"), ((1, 32, 156, 128, 2), "f32", "fwd", 0, False, "any size", "tile"),
+    ((1, 32, 240, 96, 2), "f32", "fwd", 0, False, "tile", "tile"),
+    # backward
+    ((3, 20, 28, 28, 10), "f32", "bwd", 0, False, "plane", "plane"), ((4, 16, 28, 28, 4), "f32", "bwd", 0, False, "any size", "plane"),
+    ((4, 16, 16, 16, 4), "f32", "bwd", 0, False, "plane", "plane"), ((32, 192, 28, 28, 192), "f32", "bwd", 0, True, "plane", "plane"),
+    ((2, 64, 32, 32, 64), "f16", "bwd", 0, False, "any size", "plane"),
+    ((2, 24, 56, 56, 2), "f32", "bwd", 0, False, "twopass/any size", "twopass/tile"), ((4, 16, 56, 56, 4), "bf16", "bwd", 0, False, "twopass/any size", "twopass/plane"),
+    ((2, 24, 56, 56, 2), "bf16", "bwd", 0, False, "twopass/plane", "twopass/plane"),
+    ((1, 28, 43, 44, 7), "bf16", "bwd", 0, True, "tile", "tile"), ((1, 32, 43, 44, 8), "bf16", "bwd", 0, True, "any size", "tile"),
+    # elsewhere it takes nothing but the plan "generic"
+    ((2, 1024, 128, 128, 16), "bf16", "fwd", 0, False, "pair", "pair"), ((2, 1024, 128, 128, 16), "f16", "bwd", 0, False, "twopass/pair", "twopass/pair"),
+    ((1, 512, 512, 512, 16), "bf16", "fwd", 0, False, "stream", "stream"), ((1, 512, 512, 512, 16), "bf16", "bwd", 0, False, "twopass/stream", "twopass/stream"),
+    ((1, 32, 128, 128, 4), "f32", "fwd", 32, False, "chunk", "chunk"), ((1, 32, 128, 128, 4), "f32", "bwd", 32, False, "twopass/chunk", "twopass/chunk"),
+    ((4, 192, 50, 83, 8), "f32", "save", 0, False, "any size", "any size"), ((4, 192, 50, 83, 8), "f32", "bwd", 0, False, "any size", "any size"),
+    ((1, 8, 1, 7, 1), "f32", "fwd", 0, False, "line by line", "line by line"), ((1, 2, 1001, 9, 1), "f32", "bwd", 0, False, "line by line", "line by line"),
+]
+
+
+@pytest.mark.parametrize("shape,dtype,call,kchunk,logits,kernel,own", CALLS,
+                         ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s).replace(" ", "-"))
+def test_either_side_of_the_lines(shape, dtype, call, kchunk, logits, kernel, own, monkeypatch):
+    assert call_kernel(*shape, dtype, call, kchunk, logits) == kernel
+    monkeypatch.setenv("GSPN_NO_ANY_SIZE", "1")
+    assert call_kernel(*shape, dtype, call, kchunk, logits) == own
+    monkeypatch.setenv("GSPN_FORCE_GENERIC", "1")
+    assert call_kernel(*shape, dtype, call, kchunk, logits) == "line by line"
