@@ -204,6 +204,7 @@ bool any_size_before_tile(const FwdParams& p);
 const char* twopass_kernel_name(const BwdParams& p, int dtype);      // for gspn_call_kernel
 int ragged_fwd_threads(const FwdParams& p, int dtype);        // threads per workgroup, 0: not taken
 int ragged_bwd_threads(const BwdParams& p, int dtype);
+bool ragged_shape(const FwdParams& p, int dtype, bool merge_rounds, int out[7]);
 hipError_t launch_fwd_tile(const FwdParams& p, int dtype, hipStream_t s);
 bool fwd_tile_applicable(const FwdParams& p, int dtype);
 hipError_t launch_fwd_plane(const FwdParams& p, int dtype, hipStream_t s);

@@ -1,6 +1,7 @@
 // Chooses the kernel family for a call.  Host code only.
 #include "gspn_common.hpp"
 #include <stdlib.h>
+#include <string.h>
 #include <atomic>
 
 namespace gspn {
@@ -201,6 +202,17 @@ extern "C" const char* gspn_call_kernel(int B, int C, int H, int W, int G, int k
         case FWD_ANY_SIZE: return "any size";
         default: return "line by line";
     }
+}
+
+// For the tests, not part of the ABI: the launch shape of the any-size kernel where a call runs it (see ragged_shape), else 0.
+extern "C" int gspn_any_size_shape(int B, int C, int H, int W, int G, int kchunk, int logits, unsigned mask, int dtype, int pass, int* shape) {
+    using namespace gspn;
+    const char* kernel = gspn_call_kernel(B, C, H, W, G, kchunk, logits, mask, dtype, pass);
+    const size_t n = strlen(kernel);
+    if (n < 8 || strcmp(kernel + n - 8, "any size")) return 0;
+    FwdParams p = {};
+    p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
+    return ragged_shape(p, dtype, pass == 2 && n == 8, shape);
 }
 
 // For the tests, not part of the ABI: threads per workgroup of the any-size kernel for a call whose plan is "generic" (both its

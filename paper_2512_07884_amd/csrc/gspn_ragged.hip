@@ -47,9 +47,12 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
         const size_t room = cap / wgs - fixed;
         // positions per lane: a line in one wave (no meetings within a chunk) up to 192 positions, beyond that two, and four
         // where the scanning waves would otherwise leave too few for the loads.  With y in global memory the LDS has room for long
-        // chunks, and four positions of one wave beat two of two or three that meet up to 256 (128 planes 226x207 bf16 180 -> 131
-        // us, 512 planes 256x192 352 -> 332); with the tile the chunks are short and they do not (128 planes 23x251 38 -> 51).
-        const int v = longest <= 64 ? 1 : longest <= 128 ? 2 : longest <= 192 ? 3 : longest <= (a.tile ? 0 : 256) ? 4 : longest <= 448 ? 2 : 4;
+        // chunks, and up to 256 positions four of one wave beat two of two or three that meet, provided that both sides are long,
+        // for the other axis pays for the idle lanes (both widths timed on 440 calls: 0.92 of the time with a shorter side of 129
+        // and more -- 128 planes 226x207 bf16 180 -> 131 us --, 1.06 with 65 to 128, 1.16 below that); with the tile the chunks are
+        // short and they do not (1.16; 128 planes 23x251 38 -> 51).
+        const bool both_long = longest <= 256 && (H < W ? H : W) > 128;
+        const int v = longest <= 64 ? 1 : longest <= 128 ? 2 : longest <= 192 ? 3 : !a.tile && both_long ? 4 : longest <= 448 ? 2 : 4;
         for (int ax = 0; ax < 2; ++ax) {
             const int L = ((ax ? H : W) + v - 1) / v * v;
             if (ax == 0) {                                              // granules are written whole, one slot apart
@@ -121,6 +124,28 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
         return false;
     };
     const bool f32 = dtype == 0;
+    // Narrow maps, the longer side over 128 positions and three times the other: one axis has few lines of that many positions, the
+    // other many short ones, so that the chunks of the first set the LDS.  There requests of 16 and 32 bytes with both directions at
+    // once beat longer ones walked one after the other, above all merged in global memory.  Every shape timed on 2660 calls: the
+    // first of these that fits takes 1.02 of the best one's time in the mean, of the orders above 1.10 and up to 1.8 (64 planes
+    // 233x13 fp32 with h_save: {2, 2, 64} 64, {0, 2, 32} 40 us; 768 planes 508x17 bf16 with h_save: {1, 1, 32} 485, {0, 1, 16} 319).
+    // By planes: up to 256, up to 512, more.  In 16 bits the merge in global memory comes last: it rounds gx once per direction.
+    struct ShapeAt { int mode, nbuf, seg, wgs; };
+    static const ShapeAt narrow16_few[] = {{0, 2, 64, 1}, {0, 2, 32, 1}, {0, 2, 16, 1}, {0, 1, 64, 1}, {0, 1, 16, 1}, {1, 1, 64, 1}, {1, 1, 16, 1}, {2, 2, 64, 1}, {2, 2, 32, 1}, {2, 2, 16, 1}, {2, 1, 64, 1}, {2, 1, 16, 1}};
+    static const ShapeAt narrow16_512[] = {{0, 2, 32, 2}, {0, 2, 16, 2}, {0, 1, 64, 2}, {1, 2, 64, 2}, {0, 1, 32, 2}, {0, 1, 16, 2}, {1, 2, 16, 2}, {1, 1, 64, 2}, {0, 2, 64, 1}, {0, 1, 64, 1}, {1, 1, 16, 2}, {0, 1, 32, 1}, {1, 1, 64, 1}, {0, 1, 16, 1}, {1, 1, 16, 1}, {2, 1, 64, 2}, {2, 1, 64, 1}, {2, 2, 32, 1}, {2, 1, 16, 2}, {2, 1, 16, 1}};
+    static const ShapeAt narrow16_more[] = {{1, 2, 64, 4}, {1, 2, 16, 4}, {1, 1, 64, 4}, {0, 1, 64, 2}, {1, 1, 16, 4}, {0, 1, 32, 2}, {1, 2, 64, 2}, {0, 1, 16, 2}, {1, 2, 16, 2}, {1, 1, 64, 2}, {0, 1, 64, 1}, {1, 1, 16, 2}, {1, 2, 64, 1}, {0, 1, 32, 1}, {0, 1, 16, 1}, {1, 1, 64, 1}, {1, 1, 32, 1}, {1, 1, 16, 1}, {2, 1, 64, 2}, {2, 1, 64, 1}, {2, 2, 32, 1}, {2, 1, 16, 1}};
+    static const ShapeAt narrow32_few[] = {{0, 2, 64, 1}, {0, 2, 32, 1}, {0, 1, 64, 1}, {0, 1, 32, 1}, {1, 2, 64, 1}, {1, 2, 32, 1}, {2, 2, 64, 1}, {2, 2, 32, 1}, {2, 1, 64, 1}, {1, 1, 32, 1}, {2, 1, 32, 1}};
+    static const ShapeAt narrow32_512[] = {{0, 1, 64, 2}, {1, 2, 64, 2}, {1, 1, 64, 2}, {1, 1, 32, 2}, {1, 2, 64, 1}, {0, 1, 32, 1}, {2, 2, 64, 1}, {1, 2, 32, 1}, {2, 1, 64, 1}, {1, 1, 32, 1}, {2, 1, 32, 1}};
+    static const ShapeAt narrow32_more[] = {{1, 1, 64, 4}, {0, 1, 64, 2}, {1, 1, 32, 4}, {0, 2, 64, 1}, {1, 1, 64, 2}, {1, 2, 32, 2}, {1, 1, 32, 2}, {1, 2, 64, 1}, {0, 1, 32, 1}, {2, 2, 64, 1}, {1, 1, 64, 1}, {1, 2, 32, 1}, {2, 1, 64, 1}, {1, 1, 32, 1}, {2, 1, 32, 1}};
+    auto first_at = [&](const auto& table) {
+        for (const ShapeAt& t : table)
+            if (!(must_tile && t.mode == 2) && fits(t.mode, t.nbuf, t.seg, t.wgs, t.mode == 2 ? 16 : 32)) return true;
+        return false;
+    };
+    if (longest > 128 && 3 * (H < W ? H : W) <= longest) {
+        if (f32) return planes <= 256 ? first_at(narrow32_few) : planes <= 512 ? first_at(narrow32_512) : first_at(narrow32_more);
+        return planes <= 256 ? first_at(narrow16_few) : planes <= 512 ? first_at(narrow16_512) : first_at(narrow16_more);
+    }
     for (int wgs = wgs_wanted; wgs > 1; wgs /= 2)
         if (f32 ? first_of(several32, 4, wgs) : first_of(several16, 6, wgs)) return true;
     if (planes <= 256 ? (f32 ? first_of(few32, 13, 1) : first_of(few16, 12, 1)) : (f32 ? first_of(many32, 13, 1) : first_of(many16, 12, 1))) return true;
@@ -139,6 +164,17 @@ static int ragged_threads(const FwdParams& p, int dtype, bool merge_rounds) {
     size_t lds;
     if (!ragged_plan(p, dtype, merge_rounds, &a, &threads, &nv, &lds)) return 0;
     return (unsigned long long)p.B * p.C * threads < (1ull << 32) ? threads : 0;
+}
+// {merge (0: LDS tile and both directions at once, 1: tile and one, 2: global memory), chunks, bytes of a row per request, workgroups
+// per CU, positions per lane, waves per vertical and per horizontal line}: for gspn_any_size_shape
+bool ragged_shape(const FwdParams& p, int dtype, bool merge_rounds, int out[7]) {
+    RaggedArgs a;
+    int threads, nv;
+    size_t lds;
+    if (!ragged_plan(p, dtype, merge_rounds, &a, &threads, &nv, &lds)) return false;
+    const int shape[7] = {a.tile ? 2 - a.nd : 2, a.nbuf, a.K[1] * (dtype == 0 ? 4 : 2), 1024 / threads, nv, a.parts[0], a.parts[1]};
+    for (int i = 0; i < 7; ++i) out[i] = shape[i];
+    return true;
 }
 static int lines_walked(unsigned mask, int H, int W) {
     return (int)((mask & 1u) + ((mask >> 1) & 1u)) * H + (int)(((mask >> 2) & 1u) + ((mask >> 3) & 1u)) * W;

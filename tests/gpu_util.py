@@ -55,3 +55,15 @@ def run_fwd_gpu(inp: dict, cfg, dir_mask=None, save_h=False, flags=0, poison=Tru
     G.gspn_scan_fwd(dev["x"], dev["w"], dev["lam"], dev["u"], y, hs, G=cfg.G, dir_mask=mask, flags=flags)
     torch.cuda.synchronize()
     return (to_host_f64(y), to_host_f64(hs) if save_h else None, dev, y, hs)
+
+
+def any_size_shape(B, C, H, W, G, dtype, call, kchunk=0, logits=False, mask=15):
+    """The launch shape of the any-size kernel in a call that runs it, else None: (merge -- 0: LDS tile, both directions of an axis
+    at once, 1: LDS tile, one after the other, 2: global memory --, chunks of a direction in LDS, bytes of an image row per
+    request, workgroups per CU, positions per lane, waves per vertical line, waves per horizontal line)."""
+    import ctypes
+    from paper_2512_07884_amd import binding
+    out = (ctypes.c_int * 7)()
+    f = binding.load_library().gspn_any_size_shape
+    return tuple(out) if f(B, C, H, W, G, kchunk, int(logits), ctypes.c_uint(mask), {"f32": 0, "bf16": 1, "f16": 2}[dtype],
+                           ("fwd", "save", "bwd").index(call), out) else None

@@ -15,7 +15,10 @@ CALLS = [((1, 2, 9, 11, 1), "bf16", 0, False), ((1, 2, 33, 41, 2), "f32", 0, Fal
          ((1, 2, 160, 144, 1), "f32", 0, False), ((1, 2, 135, 181, 2), "f32", 0, True), ((1, 2, 256, 264, 1), "bf16", 0, False),  # global memory, two chunks
          ((1, 128, 195, 197, 8), "f32", 0, False), ((1, 130, 230, 212, 2), "bf16", 0, False),                                     # global memory, 128 planes and more
          ((3, 96, 85, 34, 8), "bf16", 0, False), ((3, 96, 104, 81, 4), "f32", 0, False), ((3, 96, 64, 150, 8), "f16", 0, True),   # two workgroups per CU
-         ((5, 128, 27, 27, 8), "bf16", 0, False), ((5, 128, 63, 61, 8), "f32", 16, True)]                                        # four
+         ((5, 128, 27, 27, 8), "bf16", 0, False), ((5, 128, 63, 61, 8), "f32", 16, True),                                        # four
+         # narrow maps: short requests, two workgroups per CU with two chunks each, lines of two and three waves
+         ((1, 2, 233, 13, 1), "f32", 0, False), ((1, 4, 19, 211, 1), "f32", 30, True), ((1, 2, 225, 20, 2), "f16", 0, True),
+         ((1, 288, 17, 257, 4), "f16", 0, False), ((1, 520, 258, 17, 8), "bf16", 0, False), ((1, 520, 200, 31, 8), "f32", 0, False)]
 
 
 @pytest.mark.parametrize("mask", [15, 9])

@@ -3,7 +3,7 @@ import os
 
 import pytest
 
-from gpu_util import call_kernel
+from gpu_util import any_size_shape, call_kernel
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -49,3 +49,19 @@ def test_either_side_of_the_lines(shape, dtype, call, kchunk, logits, kernel, ow
     assert call_kernel(*shape, dtype, call, kchunk, logits) == own
     monkeypatch.setenv("GSPN_FORCE_GENERIC", "1")
     assert call_kernel(*shape, dtype, call, kchunk, logits) == "line by line"
+
+
+# Narrow maps (the longer side over 128 positions and three times the other) have orders of launch shapes of their own, in which
+# short requests with both directions at once come before a merge in global memory; four positions per lane there only for lines of
+# up to 256 positions of maps whose shorter side has more than 128.
+@pytest.mark.parametrize("shape,dtype,logits,want", [
+    ((1, 64, 233, 13, 8), "f32", False, (0, 2, 32, 1, 2, 1, 3)), ((1, 1, 288, 39, 1), "f32", False, (0, 1, 32, 1, 2, 1, 3)),
+    ((1, 128, 240, 33, 8), "f32", False, (0, 2, 32, 1, 2, 1, 3)), ((1, 300, 200, 31, 4), "f32", True, (1, 1, 32, 2, 2, 1, 2)),
+    ((1, 600, 19, 211, 4), "f32", False, (0, 2, 64, 1, 2, 2, 1)), ((1, 64, 225, 20, 8), "f16", True, (0, 2, 16, 1, 2, 1, 3)),
+    ((1, 300, 17, 257, 4), "f16", False, (1, 2, 64, 2, 2, 3, 1)), ((1, 768, 258, 17, 8), "bf16", False, (1, 2, 16, 2, 2, 1, 3)),
+    ((1, 16, 129, 43, 8), "bf16", False, (0, 2, 32, 1, 3, 1, 1)), ((1, 16, 129, 44, 8), "f32", False, (0, 2, 64, 1, 3, 1, 1)),
+    ((1, 16, 225, 129, 8), "f32", False, (2, 2, 64, 1, 4, 1, 1)), ((1, 16, 225, 128, 8), "f32", False, (2, 2, 64, 1, 2, 1, 3)),
+    ((1, 16, 257, 129, 8), "f32", False, (2, 2, 64, 1, 2, 2, 3))],
+    ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+def test_launch_shapes_of_narrow_maps(shape, dtype, logits, want):
+    assert any_size_shape(*shape, dtype, "save", 0, logits) == any_size_shape(*shape, dtype, "bwd", 0, logits) == want
