@@ -25,7 +25,7 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
     a.p = p;
     a.tile_pitch = (W + E - 1) / E * E;
     const size_t tile_bytes = (size_t)H * a.tile_pitch * 4;
-    const int longest = H > W ? H : W;
+    const int longest = H > W ? H : W, shortest = H < W ? H : W;
     // The line-by-line kernel sums the four directions of a 16-bit plane in an fp32 LDS tile where its two line buffers leave
     // room; a merge in global memory rounds once per direction, so it is taken only where that kernel would do so too.
     const bool must_tile = dtype != 0 && !merge_rounds && (size_t)H * W * 4 + 2 * (size_t)longest * 4 <= cap;
@@ -51,7 +51,7 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
         // for the other axis pays for the idle lanes (both widths timed on 440 calls: 0.92 of the time with a shorter side of 129
         // and more -- 128 planes 226x207 bf16 180 -> 131 us --, 1.06 with 65 to 128, 1.16 below that); with the tile the chunks are
         // short and they do not (1.16; 128 planes 23x251 38 -> 51).
-        const bool both_long = longest <= 256 && (H < W ? H : W) > 128;
+        const bool both_long = longest <= 256 && shortest > 128;
         const int v = longest <= 64 ? 1 : longest <= 128 ? 2 : longest <= 192 ? 3 : !a.tile && both_long ? 4 : longest <= 448 ? 2 : 4;
         for (int ax = 0; ax < 2; ++ax) {
             const int L = ((ax ? H : W) + v - 1) / v * v;
@@ -129,7 +129,9 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
     // once beat longer ones walked one after the other, above all merged in global memory.  Every shape timed on 2660 calls: the
     // first of these that fits takes 1.02 of the best one's time in the mean, of the orders above 1.10 and up to 1.8 (64 planes
     // 233x13 fp32 with h_save: {2, 2, 64} 64, {0, 2, 32} 40 us; 768 planes 508x17 bf16 with h_save: {1, 1, 32} 485, {0, 1, 16} 319).
-    // By planes: up to 256, up to 512, more.  In 16 bits the merge in global memory comes last: it rounds gx once per direction.
+    // By planes: up to 256, up to 512, more.  In 16 bits the merge in global memory comes last: it rounds gx once per direction; and
+    // where the shorter side is long too (over 48 positions), in calls of more than 64 planes, requests of 16 bytes come after the
+    // longer ones, for the bytes count there (256 planes 240x80 fp16 with h_save 110 -> 85).
     struct ShapeAt { int mode, nbuf, seg, wgs; };
     static const ShapeAt narrow16_few[] = {{0, 2, 64, 1}, {0, 2, 32, 1}, {0, 2, 16, 1}, {0, 1, 64, 1}, {0, 1, 16, 1}, {1, 1, 64, 1}, {1, 1, 16, 1}, {2, 2, 64, 1}, {2, 2, 32, 1}, {2, 2, 16, 1}, {2, 1, 64, 1}, {2, 1, 16, 1}};
     static const ShapeAt narrow16_512[] = {{0, 2, 32, 2}, {0, 2, 16, 2}, {0, 1, 64, 2}, {1, 2, 64, 2}, {0, 1, 32, 2}, {0, 1, 16, 2}, {1, 2, 16, 2}, {1, 1, 64, 2}, {0, 2, 64, 1}, {0, 1, 64, 1}, {1, 1, 16, 2}, {0, 1, 32, 1}, {1, 1, 64, 1}, {0, 1, 16, 1}, {1, 1, 16, 1}, {2, 1, 64, 2}, {2, 1, 64, 1}, {2, 2, 32, 1}, {2, 1, 16, 2}, {2, 1, 16, 1}};
@@ -138,11 +140,12 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
     static const ShapeAt narrow32_512[] = {{0, 1, 64, 2}, {1, 2, 64, 2}, {1, 1, 64, 2}, {1, 1, 32, 2}, {1, 2, 64, 1}, {0, 1, 32, 1}, {2, 2, 64, 1}, {1, 2, 32, 1}, {2, 1, 64, 1}, {1, 1, 32, 1}, {2, 1, 32, 1}};
     static const ShapeAt narrow32_more[] = {{1, 1, 64, 4}, {0, 1, 64, 2}, {1, 1, 32, 4}, {0, 2, 64, 1}, {1, 1, 64, 2}, {1, 2, 32, 2}, {1, 1, 32, 2}, {1, 2, 64, 1}, {0, 1, 32, 1}, {2, 2, 64, 1}, {1, 1, 64, 1}, {1, 2, 32, 1}, {2, 1, 64, 1}, {1, 1, 32, 1}, {2, 1, 32, 1}};
     auto first_at = [&](const auto& table) {
-        for (const ShapeAt& t : table)
-            if (!(must_tile && t.mode == 2) && fits(t.mode, t.nbuf, t.seg, t.wgs, t.mode == 2 ? 16 : 32)) return true;
+        for (int late16 = !f32 && shortest > 48 && planes > 64; late16 >= 0; --late16)
+            for (const ShapeAt& t : table)
+                if (!(late16 && (t.seg == 16 || t.mode == 2)) && !(must_tile && t.mode == 2) && fits(t.mode, t.nbuf, t.seg, t.wgs, t.mode == 2 ? 16 : 32)) return true;
         return false;
     };
-    if (longest > 128 && 3 * (H < W ? H : W) <= longest) {
+    if (longest > 128 && 3 * shortest <= longest) {
         if (f32) return planes <= 256 ? first_at(narrow32_few) : planes <= 512 ? first_at(narrow32_512) : first_at(narrow32_more);
         return planes <= 256 ? first_at(narrow16_few) : planes <= 512 ? first_at(narrow16_512) : first_at(narrow16_more);
     }
