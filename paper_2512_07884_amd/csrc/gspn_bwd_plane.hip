@@ -611,6 +611,19 @@ static PlanePlan plan_plane(const BwdParams& p, int dtype) {
 
 bool bwd_plane_applicable(const BwdParams& p, int dtype) { return plan_plane(p, dtype).ok; }
 
+// A CU holds as many workgroups as the LDS does and at most eight waves (224 registers), the last round of workgroups is as long
+// as the others, and a wave walks its share of the workgroup's channels in turn.
+float bwd_plane_channels_in_flight(const BwdParams& p, int dtype) {
+    const PlanePlan t = plan_plane(p, dtype);
+    if (!t.ok) return 0.f;
+    const size_t groups = (size_t)p.B * (p.C / t.K);
+    size_t resident = PLANE_LDS_BUDGET / t.lds;
+    if (resident > (size_t)(8 / t.nwaves)) resident = 8 / t.nwaves;
+    if (resident < 1) resident = 1;
+    const size_t rounds = (groups + 256 * resident - 1) / (256 * resident), turns = t.K / (t.cpw * t.nwaves);
+    return (float)((double)p.B * p.C / (256.0 * rounds * turns));
+}
+
 template <typename T, int SMAX, int CPW, bool SHARED, bool LOCAL, bool LOGITS>
 static hipError_t launch_plane_k(const BwdPlaneArgs& a, const PlanePlan& t, hipStream_t s) {
     auto k = bwd_plane_kernel<T, SMAX, CPW, SHARED, LOCAL, LOGITS>;

@@ -51,7 +51,8 @@ bool stream_two_channels_enabled() { return !knobs().stream_one_channel; }
 bool stream_two_channels_forced() { return knobs().stream_two_channels; }
 
 // Calls of the "plane" and "tile" families (what gspn_fwd_plan / gspn_bwd_plan answer) that the any-size kernel runs faster: GPU time
-// of graph replays on 520 random calls of the three types, forward and with h_save; family's own kernel -> any size, us.
+// of graph replays on some 8000 random calls of the three types, forward, with h_save and backward; family's own kernel -> any
+// size, us.
 // Plane: its kernel deals several channels to a workgroup and walks the directions one after the other, so a call of few planes
 // leaves CUs idle; up to 1024 planes (512 with logits) of more than 196 pixels 0.67 of its time in the mean, 1.05 at most: 512
 // planes 44x44 bf16 31 -> 23, 256 planes 30x30 fp16 34 -> 16.  Beyond the lines: 768 planes 46x18 with logits 23 -> 29, 1728 planes
@@ -69,11 +70,17 @@ bool any_size_before_tile(const FwdParams& p) {
     return !knobs().fwd_no_plane && !knobs().no_any_size && planes >= 32 && HW <= 20000 && !(planes >= 1024 && (p.W == 96 || p.W == 128));
 }
 // Backward: the single-launch kernels hold a weight group's channels in one workgroup, the any-size kernel a plane, with a second
-// pass over the channels.  Plane, more than 256 pixels (per-channel weights: up to 2048 planes): 0.2 to 0.9 of its time (512 planes
-// 28x30 fp32 with logits 175 -> 51; 16x16 with 48 channels per group 55 -> 60).  Tile: 0.17 (768 planes 43x44 with logits 631 -> 88).
-static bool any_size_before_bwd_plane(const BwdParams& p) {
+// pass over the channels that writes and reads e once more.  Plane, more than 256 pixels (per-channel weights: up to 2048 planes):
+// 0.2 to 0.9 of its time (512 planes 28x30 fp32 with logits 175 -> 51; 16x16 with 48 channels per group 55 -> 60) -- unless the
+// workgroups fill the CUs there: more than 4096 planes, lines of up to 28 positions, no logits, more than 11 channels in flight per CU
+// in the mean of the call (16 are the most).  There it takes 0.83 to 1.03 of the any-size kernel's time on maps of more than 600 pixels (420 where the
+// rows are not whole 16-byte granules), each tensor crossing once: 6144 planes 28x28, 48 per group, 161 -> 194; 7104 planes 26x26, 4
+// per group, 201 -> 260.  Tile: 0.17 (768 planes 43x44 with logits 631 -> 88).
+static bool any_size_before_bwd_plane(const BwdParams& p, int dtype) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
-    return planes >= 64 && HW > 256 && (p.cpg > 1 || planes <= 2048);
+    if (planes < 64 || HW <= 256 || (p.cpg == 1 && planes > 2048)) return false;
+    const bool few_reads = !p.logits && p.H <= 28 && p.W <= 28 && HW > (p.W % 4 ? 420u : 600u);
+    return !(dtype == 0 && p.cpg > 1 && planes > 4096 && few_reads && bwd_plane_channels_in_flight(p, dtype) > 11.f);
 }
 static bool any_size_before_bwd_tile(const BwdParams& p) { return (size_t)p.B * p.C >= 32; }
 
@@ -101,7 +108,8 @@ static BwdPlan choose_bwd(const BwdParams& p, int dtype) {
         // the single-launch plane kernel, except where the two passes were measured faster: bf16 storage, shared
         // weights, lines of more than 16 positions (28x28x192, B = 64, G = 8: 382 -> 270 us; B = 32, G = 4, where a bf16
         // group cannot be split over workgroups: 1401 -> 177 us; 32x32x256 G = 16: 250 -> 73 us; the shorter lines of
-        // the later classifier stages and the fp32 maps run as fast or faster on the plane kernel)
+        // the later classifier stages, and fp32 maps of calls that fill its workgroups, run as fast or faster on the plane kernel;
+        // of the others the any-size kernel takes most: any_size_before_bwd_plane)
         const int m = p.H > p.W ? p.H : p.W;
         if (twopass && dtype != 0 && p.cpg > 1 && m > 16) return BWD_TWOPASS;
         return BWD_PLANE;
@@ -124,7 +132,7 @@ static BwdPlan bwd_kernel(const BwdParams& p, int dtype) {
     const BwdPlan plan = choose_bwd(p, dtype);
     const Knobs k = knobs();
     const bool own = k.bwd_no_plane || k.bwd_no_twopass || k.no_any_size;
-    const bool any = plan == BWD_PLANE ? !own && any_size_before_bwd_plane(p) : plan == BWD_TILE ? !own && any_size_before_bwd_tile(p)
+    const bool any = plan == BWD_PLANE ? !own && any_size_before_bwd_plane(p, dtype) : plan == BWD_TILE ? !own && any_size_before_bwd_tile(p)
                                                                               : plan == BWD_GENERIC && !k.force_generic;
     return any && ragged_bwd_applicable(p, dtype) ? BWD_ANY_SIZE : plan;
 }

@@ -131,7 +131,7 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
     // 233x13 fp32 with h_save: {2, 2, 64} 64, {0, 2, 32} 40 us; 768 planes 508x17 bf16 with h_save: {1, 1, 32} 485, {0, 1, 16} 319).
     // By planes: up to 256, up to 512, more.  In 16 bits the merge in global memory comes last: it rounds gx once per direction; and
     // where the shorter side is long too (over 48 positions), in calls of more than 64 planes, requests of 16 bytes come after the
-    // longer ones, for the bytes count there (256 planes 240x80 fp16 with h_save 110 -> 85).
+    // longer ones, for the bytes count there (256 planes 240x80 fp16 with h_save 110 -> 97).
     struct ShapeAt { int mode, nbuf, seg, wgs; };
     static const ShapeAt narrow16_few[] = {{0, 2, 64, 1}, {0, 2, 32, 1}, {0, 2, 16, 1}, {0, 1, 64, 1}, {0, 1, 16, 1}, {1, 1, 64, 1}, {1, 1, 16, 1}, {2, 2, 64, 1}, {2, 2, 32, 1}, {2, 2, 16, 1}, {2, 1, 64, 1}, {2, 1, 16, 1}};
     static const ShapeAt narrow16_512[] = {{0, 2, 32, 2}, {0, 2, 16, 2}, {0, 1, 64, 2}, {1, 2, 64, 2}, {0, 1, 32, 2}, {0, 1, 16, 2}, {1, 2, 16, 2}, {1, 1, 64, 2}, {0, 2, 64, 1}, {0, 1, 64, 1}, {1, 1, 16, 2}, {0, 1, 32, 1}, {1, 1, 64, 1}, {0, 1, 16, 1}, {1, 1, 16, 1}, {2, 1, 64, 2}, {2, 1, 64, 1}, {2, 2, 32, 1}, {2, 1, 16, 2}, {2, 1, 16, 1}};

@@ -24,14 +24,21 @@ CALLS = [
     # forward, tile family: 32 planes and more of up to 20 000 pixels
     ((1, 31, 80, 72, 1), "bf16", "fwd", 0, False, "tile", "tile"), ((1, 32, 80, 72, 1), "bf16", "fwd", 0, False, "any size", "tile"),
     ((1, 32, 80, 64, 4), "f32", "save", 24, False, "any size", "tile"), ((1, 32, 156, 128, 2), "f32", "fwd", 0, False, "any size", "tile"),
-    ((1, 32, 240, 96, 2), "f32", "fwd", 0, False, "tile", "tile"),
-    # backward
+    ((1, 32, 240, 96, 2), "f32", "fwd", 0, False, "tile", "tile"), ((64, 96, 56, 56, 8), "f32", "fwd", 0, False, "any size", "tile"),
+    # backward, plane family: 64 planes and more of more than 256 pixels (one channel per group: up to 2048 planes)
     ((3, 20, 28, 28, 10), "f32", "bwd", 0, False, "plane", "plane"), ((4, 16, 28, 28, 4), "f32", "bwd", 0, False, "any size", "plane"),
     ((4, 16, 16, 16, 4), "f32", "bwd", 0, False, "plane", "plane"), ((32, 192, 28, 28, 192), "f32", "bwd", 0, True, "plane", "plane"),
     ((2, 64, 32, 32, 64), "f16", "bwd", 0, False, "any size", "plane"),
+    # ... unless its workgroups fill the CUs: the training stage of the classifier, 256 workgroups of half a weight group each
+    ((32, 192, 28, 28, 4), "f32", "bwd", 0, False, "plane", "plane"), ((32, 192, 28, 28, 4), "f32", "bwd", 0, True, "any size", "plane"),
+    ((32, 192, 28, 32, 4), "f32", "bwd", 0, False, "any size", "plane"), ((33, 192, 28, 28, 4), "f32", "bwd", 0, False, "any size", "plane"),
+    ((32, 192, 24, 24, 4), "f32", "bwd", 0, False, "any size", "plane"), ((64, 192, 28, 28, 8), "f32", "bwd", 0, False, "plane", "plane"),
+    ((16, 256, 26, 26, 64), "f32", "bwd", 0, False, "any size", "plane"), ((17, 256, 26, 26, 64), "f32", "bwd", 0, False, "any size", "plane"),
+    ((24, 256, 26, 26, 64), "f32", "bwd", 0, False, "plane", "plane"), ((27, 256, 20, 22, 64), "f32", "bwd", 0, False, "plane", "plane"),
+    # ... tile family, and the first pass of the two
+    ((1, 28, 43, 44, 7), "bf16", "bwd", 0, True, "tile", "tile"), ((1, 32, 43, 44, 8), "bf16", "bwd", 0, True, "any size", "tile"),
     ((2, 24, 56, 56, 2), "f32", "bwd", 0, False, "twopass/any size", "twopass/tile"), ((4, 16, 56, 56, 4), "bf16", "bwd", 0, False, "twopass/any size", "twopass/plane"),
     ((2, 24, 56, 56, 2), "bf16", "bwd", 0, False, "twopass/plane", "twopass/plane"),
-    ((1, 28, 43, 44, 7), "bf16", "bwd", 0, True, "tile", "tile"), ((1, 32, 43, 44, 8), "bf16", "bwd", 0, True, "any size", "tile"),
     # elsewhere it takes nothing but the plan "generic"
     ((2, 1024, 128, 128, 16), "bf16", "fwd", 0, False, "pair", "pair"), ((2, 1024, 128, 128, 16), "f16", "bwd", 0, False, "twopass/pair", "twopass/pair"),
     ((1, 512, 512, 512, 16), "bf16", "fwd", 0, False, "stream", "stream"), ((1, 512, 512, 512, 16), "bf16", "bwd", 0, False, "twopass/stream", "twopass/stream"),
