@@ -254,7 +254,7 @@ Sweep choose_sweep(const FwdParams& f, int dtype) {
         return any_size_before_plane(f) && reverse_sweep_ragged_applicable(f, dtype) ? SWEEP_ANY_SIZE : SWEEP_PLANE;
     if (pair_kernels_enabled() && reverse_sweep_pair_applicable(f, dtype)) return SWEEP_PAIR;
     if (fwd_tile_applicable(f, dtype))
-        return any_size_before_tile(f) && reverse_sweep_ragged_applicable(f, dtype) ? SWEEP_ANY_SIZE : SWEEP_TILE;
+        return any_size_before_tile(f, dtype) && reverse_sweep_ragged_applicable(f, dtype) ? SWEEP_ANY_SIZE : SWEEP_TILE;
     return SWEEP_STREAM;
 }
 }  // namespace

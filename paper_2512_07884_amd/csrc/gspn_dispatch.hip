@@ -61,13 +61,21 @@ bool any_size_before_plane(const FwdParams& p) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
     return !knobs().fwd_no_plane && !knobs().no_any_size && planes >= 64 && planes <= (p.logits ? 512 : 1024) && HW > 196;
 }
-// Tile: the waves that scan load for themselves there; 0.68 of its kernel's time in the mean: 1024 planes 80x112 bf16 with h_save
-// 172 -> 143, 32 planes 64x80 with stretches 42 -> 22.  It keeps rows of 96 and 128 elements in calls of 1024 planes and more
-// (requests of whole 64-byte sectors: 128x128 fp32 241 -> 268, 104x96 fp16 112 -> 125) and planes of more than 20 000 pixels, whose
-// output tile leaves no room for two chunks (512 planes 240x96 fp32 204 -> 236).
-bool any_size_before_tile(const FwdParams& p) {
+// Tile: the waves that scan load for themselves there; 0.75 of its kernel's time in the mean, at any number of planes (timed up to
+// 9000): 1024 planes 80x112 bf16 with h_save 172 -> 143, 32 planes 64x80 with stretches 42 -> 22.  It keeps planes of more than
+// 20 000 pixels, whose output tile leaves no room for two chunks (512 planes 240x96 fp32 204 -> 236), and of 16-bit maps
+//   rows of 224 bytes, up to 64 of them, which it reads in two bursts of 112 bytes per lane: 1.13 of its time in the mean (984 planes
+//   28x112 bf16 25 -> 34); with logits in calls of more than 512 planes (1.16; 0.8 below that, its softmax being the longer chain),
+//   rows of 192 and 256 bytes, which it reads in whole 64-byte sectors, without h_save, in calls of more than 512 planes (of up to 40
+//   rows: 1024 and more), which fill the chip both ways: 1.07 (680 planes 62x128 bf16 51 -> 69).  With the stores of h_save or of the reverse
+//   sweep 0.7 to 0.97, in calls of fewer planes 0.5 to 0.9, rows of 128 bytes 0.7 to 0.8, fp32 0.8.
+bool any_size_before_tile(const FwdParams& p, int dtype) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
-    return !knobs().fwd_no_plane && !knobs().no_any_size && planes >= 32 && HW <= 20000 && !(planes >= 1024 && (p.W == 96 || p.W == 128));
+    if (knobs().fwd_no_plane || knobs().no_any_size || planes < 32 || HW > 20000) return false;
+    const int row_bytes = p.W * 2;                                        // (of a 16-bit map)
+    if (dtype == 0) return true;
+    if (row_bytes == 2 * 112 && p.H <= 64) return p.logits && planes <= 512;
+    return !(!p.hs && row_bytes >= 192 && row_bytes % 64 == 0 && (p.H > 40 ? planes > 512 : planes >= 1024));
 }
 // Backward: the single-launch kernels hold a weight group's channels in one workgroup, the any-size kernel a plane, with a second
 // pass over the channels that writes and reads e once more.  Plane, more than 256 pixels (per-channel weights: up to 2048 planes):
@@ -125,7 +133,7 @@ static BwdPlan choose_bwd(const BwdParams& p, int dtype) {
 // wherever a shape of it fits.
 static FwdPlan fwd_kernel(const FwdParams& p, int dtype) {
     const FwdPlan plan = choose_fwd(p, dtype);
-    const bool any = plan == FWD_PLANE ? any_size_before_plane(p) : plan == FWD_TILE ? any_size_before_tile(p) : plan == FWD_GENERIC && !knobs().force_generic;
+    const bool any = plan == FWD_PLANE ? any_size_before_plane(p) : plan == FWD_TILE ? any_size_before_tile(p, dtype) : plan == FWD_GENERIC && !knobs().force_generic;
     return any && ragged_applicable(p, dtype) ? FWD_ANY_SIZE : plan;
 }
 static BwdPlan bwd_kernel(const BwdParams& p, int dtype) {

@@ -25,6 +25,17 @@ CALLS = [
     ((1, 31, 80, 72, 1), "bf16", "fwd", 0, False, "tile", "tile"), ((1, 32, 80, 72, 1), "bf16", "fwd", 0, False, "any size", "tile"),
     ((1, 32, 80, 64, 4), "f32", "save", 24, False, "any size", "tile"), ((1, 32, 156, 128, 2), "f32", "fwd", 0, False, "any size", "tile"),
     ((1, 32, 240, 96, 2), "f32", "fwd", 0, False, "tile", "tile"), ((64, 96, 56, 56, 8), "f32", "fwd", 0, False, "any size", "tile"),
+    # ... 16-bit rows of 224 bytes, up to 64 of them (with logits: more than 512 planes)
+    ((1, 64, 64, 112, 8), "f16", "fwd", 0, False, "tile", "tile"), ((1, 64, 66, 112, 8), "f16", "fwd", 0, False, "any size", "tile"),
+    ((1, 64, 64, 112, 8), "f32", "fwd", 0, False, "any size", "tile"), ((4, 128, 64, 112, 8), "bf16", "save", 0, True, "any size", "tile"),
+    ((4, 129, 64, 112, 3), "bf16", "save", 0, True, "tile", "tile"), ((4, 128, 64, 112, 8), "bf16", "bwd", 0, False, "twopass/tile", "twopass/tile"),
+    ((4, 128, 64, 112, 8), "bf16", "bwd", 0, True, "twopass/any size", "twopass/tile"),
+    # ... 16-bit rows of 192 and 256 bytes without h_save, more than 512 planes (up to 40 rows: 1024 and more)
+    ((4, 128, 104, 96, 16), "bf16", "fwd", 0, False, "any size", "tile"), ((4, 129, 104, 96, 3), "bf16", "fwd", 0, False, "tile", "tile"),
+    ((4, 129, 104, 96, 3), "bf16", "save", 0, False, "any size", "tile"), ((4, 129, 104, 96, 3), "f32", "fwd", 0, False, "any size", "tile"),
+    ((4, 129, 104, 88, 3), "bf16", "fwd", 0, False, "any size", "tile"), ((4, 129, 104, 64, 3), "bf16", "fwd", 0, False, "any size", "tile"),
+    ((4, 255, 40, 128, 15), "f16", "fwd", 0, False, "any size", "tile"), ((4, 256, 40, 128, 16), "f16", "fwd", 0, False, "tile", "tile"),
+    ((4, 256, 104, 96, 16), "f16", "bwd", 0, False, "twopass/any size", "twopass/tile"),
     # backward, plane family: 64 planes and more of more than 256 pixels (one channel per group: up to 2048 planes)
     ((3, 20, 28, 28, 10), "f32", "bwd", 0, False, "plane", "plane"), ((4, 16, 28, 28, 4), "f32", "bwd", 0, False, "any size", "plane"),
     ((4, 16, 16, 16, 4), "f32", "bwd", 0, False, "plane", "plane"), ((32, 192, 28, 28, 192), "f32", "bwd", 0, True, "plane", "plane"),
