@@ -251,7 +251,7 @@ enum Sweep { SWEEP_CHUNK, SWEEP_ANY_SIZE, SWEEP_PLANE, SWEEP_PAIR, SWEEP_TILE, S
 Sweep choose_sweep(const FwdParams& f, int dtype) {
     if (chunk_kernels_enabled() && reverse_sweep_chunk_applicable(f, dtype)) return SWEEP_CHUNK;
     if (reverse_sweep_plane_applicable(f, dtype))
-        return any_size_before_plane(f) && reverse_sweep_ragged_applicable(f, dtype) ? SWEEP_ANY_SIZE : SWEEP_PLANE;
+        return any_size_before_plane(f, dtype) && reverse_sweep_ragged_applicable(f, dtype) ? SWEEP_ANY_SIZE : SWEEP_PLANE;
     if (pair_kernels_enabled() && reverse_sweep_pair_applicable(f, dtype)) return SWEEP_PAIR;
     if (fwd_tile_applicable(f, dtype))
         return any_size_before_tile(f, dtype) && reverse_sweep_ragged_applicable(f, dtype) ? SWEEP_ANY_SIZE : SWEEP_TILE;

@@ -199,7 +199,7 @@ bool ragged_bwd_applicable(const BwdParams& p, int dtype);
 hipError_t launch_reverse_sweep_ragged(const FwdParams& p, int dtype, hipStream_t s);
 bool reverse_sweep_ragged_applicable(const FwdParams& p, int dtype);
 // gspn_dispatch.hip: the any-size kernel rather than the plane / tile kernel, in forward calls and reverse sweeps alike
-bool any_size_before_plane(const FwdParams& p);
+bool any_size_before_plane(const FwdParams& p, int dtype);
 bool any_size_before_tile(const FwdParams& p, int dtype);
 float bwd_plane_channels_in_flight(const BwdParams& p, int dtype);   // of bwd_plane_applicable calls: per CU, in the mean of the call
 const char* twopass_kernel_name(const BwdParams& p, int dtype);      // for gspn_call_kernel

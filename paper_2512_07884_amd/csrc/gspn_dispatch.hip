@@ -54,12 +54,16 @@ bool stream_two_channels_forced() { return knobs().stream_two_channels; }
 // of graph replays on some 8000 random calls of the three types, forward, with h_save and backward; family's own kernel -> any
 // size, us.
 // Plane: its kernel deals several channels to a workgroup and walks the directions one after the other, so a call of few planes
-// leaves CUs idle; up to 1024 planes (512 with logits) of more than 196 pixels 0.67 of its time in the mean, 1.05 at most: 512
-// planes 44x44 bf16 31 -> 23, 256 planes 30x30 fp16 34 -> 16.  Beyond the lines: 768 planes 46x18 with logits 23 -> 29, 1728 planes
-// 20x20 19 -> 22, 96 planes 11x11 12.8 -> 13.6.
-bool any_size_before_plane(const FwdParams& p) {
+// leaves CUs idle; up to 1024 planes (512 with logits) of more than 196 pixels 0.67 of its time in the mean: 512 planes 44x44 bf16
+// 31 -> 23, 256 planes 30x30 fp16 34 -> 16.  With rows of whole 16-byte granules none of 560 calls ran longer.  fp32 maps of other
+// rows keep the plane kernel, whose workgroups stage them in whole granules all the same, where a weight group has the channels for
+// eight waves (8 and more) and the call more than 512 planes, or more than 128 of up to 330 pixels: 1.1 of its time in the mean, 768
+// planes 20x34 17.4 -> 22.6, 512 planes 12x18 15.1 -> 18.2 (groups of 2 and 4 channels 0.7 to 0.9; 16 bits 0.8).  Beyond the lines:
+// 768 planes 46x18 with logits 23 -> 29, 1728 planes 20x20 19 -> 22, 96 planes 11x11 12.8 -> 13.6.
+bool any_size_before_plane(const FwdParams& p, int dtype) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
-    return !knobs().fwd_no_plane && !knobs().no_any_size && planes >= 64 && planes <= (p.logits ? 512 : 1024) && HW > 196;
+    if (knobs().fwd_no_plane || knobs().no_any_size || planes < 64 || planes > (p.logits ? 512 : 1024) || HW <= 196) return false;
+    return !(dtype == 0 && p.W % 4 != 0 && p.cpg >= 8 && (planes > 512 || (planes > 128 && HW <= 330)));
 }
 // Tile: the waves that scan load for themselves there; 0.75 of its kernel's time in the mean, at any number of planes (timed up to
 // 9000): 1024 planes 80x112 bf16 with h_save 172 -> 143, 32 planes 64x80 with stretches 42 -> 22.  It keeps planes of more than
@@ -133,7 +137,7 @@ static BwdPlan choose_bwd(const BwdParams& p, int dtype) {
 // wherever a shape of it fits.
 static FwdPlan fwd_kernel(const FwdParams& p, int dtype) {
     const FwdPlan plan = choose_fwd(p, dtype);
-    const bool any = plan == FWD_PLANE ? any_size_before_plane(p) : plan == FWD_TILE ? any_size_before_tile(p, dtype) : plan == FWD_GENERIC && !knobs().force_generic;
+    const bool any = plan == FWD_PLANE ? any_size_before_plane(p, dtype) : plan == FWD_TILE ? any_size_before_tile(p, dtype) : plan == FWD_GENERIC && !knobs().force_generic;
     return any && ragged_applicable(p, dtype) ? FWD_ANY_SIZE : plan;
 }
 static BwdPlan bwd_kernel(const BwdParams& p, int dtype) {

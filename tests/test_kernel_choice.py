@@ -21,6 +21,12 @@ CALLS = [
     ((4, 16, 14, 14, 4), "f32", "fwd", 0, False, "plane", "plane"), ((8, 128, 14, 16, 8), "f16", "save", 0, False, "any size", "plane"),
     ((5, 205, 14, 16, 5), "bf16", "save", 0, False, "plane", "plane"), ((4, 128, 28, 28, 8), "f32", "save", 0, True, "any size", "plane"),
     ((4, 132, 28, 28, 12), "f32", "save", 0, True, "plane", "plane"), ((2, 48, 56, 56, 4), "bf16", "save", 14, True, "any size", "plane"),
+    # ... fp32 rows that are not whole granules, eight channels per group and more: up to 512 planes, up to 128 of up to 330 pixels
+    ((4, 128, 20, 34, 16), "f32", "save", 0, False, "any size", "plane"), ((4, 130, 20, 34, 10), "f32", "save", 0, False, "plane", "plane"),
+    ((4, 132, 20, 34, 33), "f32", "save", 0, False, "any size", "plane"), ((4, 136, 20, 36, 17), "f32", "save", 0, False, "any size", "plane"),
+    ((4, 136, 20, 34, 17), "bf16", "save", 0, False, "any size", "plane"), ((2, 64, 18, 18, 8), "f32", "fwd", 0, False, "any size", "plane"),
+    ((2, 72, 18, 18, 9), "f32", "fwd", 0, False, "plane", "plane"), ((2, 72, 15, 22, 9), "f32", "fwd", 0, False, "plane", "plane"),
+    ((2, 72, 19, 18, 9), "f32", "fwd", 0, False, "any size", "plane"), ((2, 264, 18, 30, 33), "f32", "bwd", 0, True, "any size", "plane"),
     # forward, tile family: 32 planes and more of up to 20 000 pixels
     ((1, 31, 80, 72, 1), "bf16", "fwd", 0, False, "tile", "tile"), ((1, 32, 80, 72, 1), "bf16", "fwd", 0, False, "any size", "tile"),
     ((1, 32, 80, 64, 4), "f32", "save", 24, False, "any size", "tile"), ((1, 32, 156, 128, 2), "f32", "fwd", 0, False, "any size", "tile"),
