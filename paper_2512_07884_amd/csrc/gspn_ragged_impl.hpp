@@ -768,8 +768,9 @@ __global__ void __launch_bounds__(1024) ragged_kernel(RaggedArgs a) {
 template <typename T, int MODE, bool LOGITS, bool TILE>
 hipError_t launch_ragged_one(const RaggedArgs& a, int threads, int nv, size_t lds, hipStream_t s) {
     const dim3 grid((unsigned)((size_t)a.p.B * a.p.C)), block(threads);
-    void (*k)(RaggedArgs) = nv == 1 ? ragged_kernel<T, MODE, LOGITS, 1, TILE> : nv == 2 ? ragged_kernel<T, MODE, LOGITS, 2, TILE>
-                                    : nv == 3 ? ragged_kernel<T, MODE, LOGITS, 3, TILE> : ragged_kernel<T, MODE, LOGITS, 4, TILE>;
+    void (*k)(RaggedArgs) = nv == 2 ? ragged_kernel<T, MODE, LOGITS, 2, TILE> : nv == 3 ? ragged_kernel<T, MODE, LOGITS, 3, TILE> : ragged_kernel<T, MODE, LOGITS, 4, TILE>;
+    if constexpr (TILE) { if (nv == 1) k = ragged_kernel<T, MODE, LOGITS, 1, TILE>; }
+    else if (nv == 1) return hipErrorInvalidValue;              // (lines of up to 64 positions: the tile of a plane always fits)
     const hipError_t e = allow_dynamic_lds((const void*)k, 160 * 1024);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, grid, block, lds, s, a);
