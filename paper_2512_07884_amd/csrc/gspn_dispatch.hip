@@ -72,12 +72,15 @@ bool any_size_before_plane(const FwdParams& p, int dtype) {
 //   28x112 bf16 25 -> 34); with logits in calls of more than 512 planes (1.16; 0.8 below that, its softmax being the longer chain),
 //   rows of 192 and 256 bytes, which it reads in whole 64-byte sectors, without h_save, in calls of more than 512 planes (of up to 40
 //   rows: 1024 and more), which fill the chip both ways: 1.07 (680 planes 62x128 bf16 51 -> 69).  With the stores of h_save or of the reverse
-//   sweep 0.7 to 0.97, in calls of fewer planes 0.5 to 0.9, rows of 128 bytes 0.7 to 0.8, fp32 0.8.
+//   sweep 0.7 to 0.97, in calls of fewer planes 0.5 to 0.9, rows of 128 bytes 0.7 to 0.8.
+// In fp32 it keeps the longest rows it takes, 512 bytes, of planes of more than 12 800 pixels, which leave no room for two any-size
+// workgroups on a CU, without h_save, in calls of more than 512 planes: 1.04 (1024 planes 128x128 244 -> 272; with h_save 494 -> 337,
+// planes of fewer rows 0.7 to 0.95, rows of 384 bytes 0.6 to 0.96).
 bool any_size_before_tile(const FwdParams& p, int dtype) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
     if (knobs().fwd_no_plane || knobs().no_any_size || planes < 32 || HW > 20000) return false;
-    const int row_bytes = p.W * 2;                                        // (of a 16-bit map)
-    if (dtype == 0) return true;
+    const int row_bytes = p.W * (dtype == 0 ? 4 : 2);
+    if (dtype == 0) return !(!p.hs && row_bytes >= 512 && HW > 12800 && planes > 512);
     if (row_bytes == 2 * 112 && p.H <= 64) return p.logits && planes <= 512;
     return !(!p.hs && row_bytes >= 192 && row_bytes % 64 == 0 && (p.H > 40 ? planes > 512 : planes >= 1024));
 }

@@ -42,6 +42,10 @@ CALLS = [
     ((4, 129, 104, 88, 3), "bf16", "fwd", 0, False, "any size", "tile"), ((4, 129, 104, 64, 3), "bf16", "fwd", 0, False, "any size", "tile"),
     ((4, 255, 40, 128, 15), "f16", "fwd", 0, False, "any size", "tile"), ((4, 256, 40, 128, 16), "f16", "fwd", 0, False, "tile", "tile"),
     ((4, 256, 104, 96, 16), "f16", "bwd", 0, False, "twopass/any size", "twopass/tile"),
+    # ... fp32 rows of 512 bytes of more than 12 800 pixels without h_save, more than 512 planes
+    ((4, 128, 102, 128, 16), "f32", "fwd", 0, False, "any size", "tile"), ((4, 129, 102, 128, 3), "f32", "fwd", 0, False, "tile", "tile"),
+    ((4, 129, 100, 128, 3), "f32", "fwd", 0, False, "any size", "tile"), ((4, 129, 102, 128, 3), "f32", "save", 0, False, "any size", "tile"),
+    ((4, 129, 138, 96, 3), "f32", "fwd", 0, False, "any size", "tile"),
     # backward, plane family: 64 planes and more of more than 256 pixels (one channel per group: up to 2048 planes)
     ((3, 20, 28, 28, 10), "f32", "bwd", 0, False, "plane", "plane"), ((4, 16, 28, 28, 4), "f32", "bwd", 0, False, "any size", "plane"),
     ((4, 16, 16, 16, 4), "f32", "bwd", 0, False, "plane", "plane"), ((32, 192, 28, 28, 192), "f32", "bwd", 0, True, "plane", "plane"),
