@@ -53,49 +53,65 @@ bool stream_two_channels_forced() { return knobs().stream_two_channels; }
 // Calls of the "plane" and "tile" families (what gspn_fwd_plan / gspn_bwd_plan answer) that the any-size kernel runs faster: GPU time
 // of graph replays on some 8000 random calls of the three types, forward, with h_save and backward; family's own kernel -> any
 // size, us.
+// The any-size kernel walks the two directions of an axis at once, the plane kernels one after the other: calls that walk an axis one
+// way only have lines of their own, drawn on 2300 calls of every mask.
+static bool both_ways(unsigned mask) { return (mask & 3) == 3 || (mask & 12) == 12; }
 // Plane: its kernel deals several channels to a workgroup and walks the directions one after the other, so a call of few planes
 // leaves CUs idle; up to 1024 planes (512 with logits) of more than 196 pixels 0.67 of its time in the mean: 512 planes 44x44 bf16
-// 31 -> 23, 256 planes 30x30 fp16 34 -> 16.  With rows of whole 16-byte granules none of 560 calls ran longer.  fp32 maps of other
+// 28 -> 23, 256 planes 30x30 fp16 24 -> 16.  With rows of whole 16-byte granules none of 560 calls ran longer.  fp32 maps of other
 // rows keep the plane kernel, whose workgroups stage them in whole granules all the same, where a weight group has the channels for
 // eight waves (8 and more) and the call more than 512 planes, or more than 128 of up to 330 pixels: 1.1 of its time in the mean, 768
-// planes 20x34 17.4 -> 22.6, 512 planes 12x18 15.1 -> 18.2 (groups of 2 and 4 channels 0.7 to 0.9; 16 bits 0.8).  Beyond the lines:
-// 768 planes 46x18 with logits 23 -> 29, 1728 planes 20x20 19 -> 22, 96 planes 11x11 12.8 -> 13.6.
+// planes 20x34 17.4 -> 22.6, 512 planes 12x18 15.1 -> 18.2 (groups of 2 and 4 channels 0.7 to 0.9; 16 bits 0.8).  With no axis both ways
+// the other rows' maps of up to 1500 pixels stay there in every type from 4 channels per group and 257 planes on: 1.15 of its time (992
+// planes 28x34 bf16, one direction of each axis, 13.4 -> 19.4; fewer planes, fewer channels or whole granules 0.63 to 1.0).  Beyond the
+// lines: 768 planes 46x18 with logits 23 -> 29, 1728 planes 20x20 19 -> 22, 96 planes 11x11 12.8 -> 13.6.
 bool any_size_before_plane(const FwdParams& p, int dtype) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
     if (knobs().fwd_no_plane || knobs().no_any_size || planes < 64 || planes > (p.logits ? 512 : 1024) || HW <= 196) return false;
+    if (!both_ways(p.mask) && p.W % (dtype == 0 ? 4 : 8) != 0 && p.cpg >= 4 && planes > 256 && HW <= 1500) return false;
     return !(dtype == 0 && p.W % 4 != 0 && p.cpg >= 8 && (planes > 512 || (planes > 128 && HW <= 330)));
 }
 // Tile: the waves that scan load for themselves there; 0.75 of its kernel's time in the mean, at any number of planes (timed up to
-// 9000): 1024 planes 80x112 bf16 with h_save 172 -> 143, 32 planes 64x80 with stretches 42 -> 22.  It keeps planes of more than
-// 20 000 pixels, whose output tile leaves no room for two chunks (512 planes 240x96 fp32 204 -> 236), and of 16-bit maps
+// 9000): 1024 planes 80x112 bf16 with h_save 172 -> 98, 32 planes 64x80 fp32 with h_save and stretches 47 -> 22.  It keeps planes of
+// more than 20 000 pixels, whose output tile leaves no room for two chunks (512 planes 240x96 fp32 204 -> 236), and of 16-bit maps
 //   rows of 224 bytes, up to 64 of them, which it reads in two bursts of 112 bytes per lane: 1.13 of its time in the mean (984 planes
 //   28x112 bf16 25 -> 34); with logits in calls of more than 512 planes (1.16; 0.8 below that, its softmax being the longer chain),
 //   rows of 192 and 256 bytes, which it reads in whole 64-byte sectors, without h_save, in calls of more than 512 planes (of up to 40
-//   rows: 1024 and more), which fill the chip both ways: 1.07 (680 planes 62x128 bf16 51 -> 69).  With the stores of h_save or of the reverse
-//   sweep 0.7 to 0.97, in calls of fewer planes 0.5 to 0.9, rows of 128 bytes 0.7 to 0.8.
+//   rows: 1024 and more), which fill the chip both ways: 1.07 (680 planes 62x128 bf16 51 -> 69).  With the stores of h_save or of the
+//   reverse sweep 0.7 to 0.97, in calls of fewer planes 0.5 to 0.9, rows of 128 bytes 0.7 to 0.8,
+// where the call walks both vertical directions (without one of them 0.95 and 0.6 to 0.9 of its time: 768 planes 120x128 fp16, up and
+// right, 102 -> 81); and it keeps calls of nothing else, whose lines are the rows that it loads: both vertical directions of more than
+// 512 planes 1.17 of its time (2176 planes 128x80 fp16 90 -> 137; 0.7 to 0.9 below), one alone 1.2 with the rows of 192 and 256 bytes
+// of more than 1024 planes (3626 planes 66x96 bf16 110 -> 168; other rows 0.95).
 // In fp32 it keeps the longest rows it takes, 512 bytes, of planes of more than 12 800 pixels, which leave no room for two any-size
 // workgroups on a CU, without h_save, in calls of more than 512 planes: 1.04 (1024 planes 128x128 244 -> 272; with h_save 494 -> 337,
-// planes of fewer rows 0.7 to 0.95, rows of 384 bytes 0.6 to 0.96).
+// planes of fewer rows 0.7 to 0.95, rows of 384 bytes 0.6 to 0.96; vertical directions alone 1.03).
 bool any_size_before_tile(const FwdParams& p, int dtype) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
     if (knobs().fwd_no_plane || knobs().no_any_size || planes < 32 || HW > 20000) return false;
     const int row_bytes = p.W * (dtype == 0 ? 4 : 2);
     if (dtype == 0) return !(!p.hs && row_bytes >= 512 && HW > 12800 && planes > 512);
+    const bool sectors = row_bytes >= 192 && row_bytes % 64 == 0, down_and_up = (p.mask & 3) == 3;
+    if ((p.mask & 12) == 0 && (down_and_up ? planes > 512 : sectors && planes > 1024)) return false;
+    if (!down_and_up) return true;
     if (row_bytes == 2 * 112 && p.H <= 64) return p.logits && planes <= 512;
-    return !(!p.hs && row_bytes >= 192 && row_bytes % 64 == 0 && (p.H > 40 ? planes > 512 : planes >= 1024));
+    return !(!p.hs && sectors && (p.H > 40 ? planes > 512 : planes >= 1024));
 }
 // Backward: the single-launch kernels hold a weight group's channels in one workgroup, the any-size kernel a plane, with a second
 // pass over the channels that writes and reads e once more.  Plane, more than 256 pixels (per-channel weights: up to 2048 planes):
-// 0.2 to 0.9 of its time (512 planes 28x30 fp32 with logits 175 -> 51; 16x16 with 48 channels per group 55 -> 60) -- unless the
-// workgroups fill the CUs there: more than 4096 planes, lines of up to 28 positions, no logits, more than 11 channels in flight per CU
-// in the mean of the call (16 are the most).  There it takes 0.83 to 1.03 of the any-size kernel's time on maps of more than 600 pixels (420 where the
-// rows are not whole 16-byte granules), each tensor crossing once: 6144 planes 28x28, 48 per group, 161 -> 194; 7104 planes 26x26, 4
-// per group, 201 -> 260.  Tile: 0.17 (768 planes 43x44 with logits 631 -> 88).
+// 0.2 to 0.9 of its time (512 planes 28x30 fp32 with logits 295 -> 76; 16x16 with 48 channels per group 55 -> 60) -- unless, in fp32,
+// the plane kernel's workgroups fill the CUs: calls of more than 4096 planes that keep more than 11 channels in flight per CU in the
+// mean of the call (16 are the most), lines of up to 28 positions, no logits.  Each tensor crosses once there, and on maps of more than
+// 600 pixels (420 where the rows are not whole 16-byte granules) it takes 0.83 to 1.03 of the any-size kernel's time: 6144 planes
+// 28x28, 48 per group, 161 against 194; 7104 planes 26x26, 4 per group, with stretches 196 against 260.  Of one direction alone, its
+// three passes over the channels are then one, and it keeps all such calls from 1025 planes on: 1.31 of its time (3808 planes 28x26 29 ->
+// 50; up to 1024 planes 0.97, logits 0.5 to 1.1, two directions 0.7 to 1.05).  Tile: 0.2 (768 planes 43x44 bf16 with logits 427 -> 88).
 static bool any_size_before_bwd_plane(const BwdParams& p, int dtype) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
     if (planes < 64 || HW <= 256 || (p.cpg == 1 && planes > 2048)) return false;
-    const bool few_reads = !p.logits && p.H <= 28 && p.W <= 28 && HW > (p.W % 4 ? 420u : 600u);
-    return !(dtype == 0 && p.cpg > 1 && planes > 4096 && few_reads && bwd_plane_channels_in_flight(p, dtype) > 11.f);
+    if (dtype != 0 || p.logits || p.H > 28 || p.W > 28) return true;
+    if ((p.mask & (p.mask - 1)) == 0 && planes > 1024) return false;
+    return !(p.cpg > 1 && planes > 4096 && HW > (p.W % 4 ? 420u : 600u) && bwd_plane_channels_in_flight(p, dtype) > 11.f);
 }
 static bool any_size_before_bwd_tile(const BwdParams& p) { return (size_t)p.B * p.C >= 32; }
 

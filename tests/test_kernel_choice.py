@@ -79,6 +79,26 @@ def test_either_side_of_the_lines(shape, dtype, call, kchunk, logits, kernel, ow
     assert call_kernel(*shape, dtype, call, kchunk, logits) == "line by line"
 
 
+# Calls that walk no axis both ways (plane family), or the two vertical directions alone (tile family).
+@pytest.mark.parametrize("shape,dtype,call,logits,any_size,own", [
+    ((4, 64, 26, 28, 16), "bf16", "save", False, (1, 2, 5, 10, 15), ()), ((4, 68, 26, 28, 17), "bf16", "save", True, (3, 12, 7, 14, 15), (1, 8, 5, 9)),
+    ((4, 66, 26, 28, 22), "bf16", "fwd", False, (1, 5, 3, 15), ()), ((4, 68, 26, 32, 17), "bf16", "fwd", False, (1, 5, 3, 15), ()),
+    ((4, 68, 26, 28, 17), "f32", "fwd", False, (1, 5, 3, 15), ()), ((4, 68, 26, 30, 34), "f32", "fwd", False, (1, 5, 3, 15), ()),
+    ((4, 68, 26, 30, 17), "f32", "fwd", False, (3, 12, 7, 15), (2, 4, 6, 10)), ((4, 68, 38, 38, 17), "f32", "save", False, (3, 12), (1, 5)),
+    ((4, 68, 40, 38, 17), "f32", "save", False, (1, 5, 3, 12), ()), ((4, 68, 36, 44, 17), "f16", "bwd", False, (1, 5, 3, 15), ()),
+    ((4, 68, 34, 44, 17), "f16", "bwd", False, (3, 11, 15), (1, 5)),
+    ((4, 128, 72, 80, 8), "bf16", "fwd", False, (1, 3, 4, 12, 5, 15), ()), ((4, 129, 72, 80, 3), "bf16", "fwd", True, (1, 2, 4, 12, 5, 7, 15), (3,)),
+    ((8, 128, 20, 112, 16), "f16", "save", False, (1, 4, 12, 5, 14), (3, 7, 15)), ((4, 129, 50, 128, 3), "bf16", "fwd", False, (1, 4, 12, 14), (3, 11, 15)),
+    ((4, 256, 50, 96, 8), "bf16", "save", False, (1, 2, 5, 15), (3,)), ((4, 258, 50, 96, 6), "bf16", "save", False, (5, 7, 15), (1, 2, 3)),
+    ((4, 129, 72, 80, 3), "f16", "bwd", False, (1, 2, 12, 7, 15), (3,)), ((4, 129, 72, 80, 3), "f32", "bwd", False, (1, 3, 12, 15), ()),
+    ((16, 64, 28, 28, 16), "f32", "bwd", False, (1, 5, 3, 15), ()), ((17, 64, 28, 28, 16), "f32", "bwd", False, (5, 10, 3, 15), (1, 8)),
+    ((17, 64, 28, 28, 16), "f32", "bwd", True, (1, 8, 5, 3, 15), ()), ((17, 64, 28, 29, 16), "f32", "bwd", False, (1, 8, 5, 3, 15), ())],
+    ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+def test_lines_by_direction_mask(shape, dtype, call, logits, any_size, own):
+    for mask in any_size + own:
+        assert (call_kernel(*shape, dtype, call, logits=logits, mask=mask).split("/")[-1] == "any size") == (mask in any_size), mask
+
+
 # Narrow maps (the longer side over 128 positions and three times the other) have orders of launch shapes of their own, in which
 # short requests with both directions at once come before a merge in global memory; four positions per lane there only for lines of
 # up to 256 positions of maps whose shorter side has more than 128.
