@@ -49,7 +49,7 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
         // where the scanning waves would otherwise leave too few for the loads.  With y in global memory the LDS has room for long
         // chunks, and up to 256 positions four of one wave beat two of two or three that meet, provided that both sides are long,
         // for the other axis pays for the idle lanes (both widths timed on 440 calls: 0.92 of the time with a shorter side of 129
-        // and more -- 128 planes 226x207 bf16 180 -> 131 us --, 1.06 with 65 to 128, 1.16 below that); with the tile the chunks are
+        // and more -- 128 planes 226x207 bf16 176 -> 134 us --, 1.06 with 65 to 128, 1.16 below that); with the tile the chunks are
         // short and they do not (1.16; 128 planes 23x251 38 -> 51).
         const bool both_long = longest <= 256 && shortest > 128;
         const int v = longest <= 64 ? 1 : longest <= 128 ? 2 : longest <= 192 ? 3 : !a.tile && both_long ? 4 : longest <= 448 ? 2 : 4;
@@ -128,10 +128,10 @@ static bool ragged_plan(const FwdParams& p, int dtype, bool merge_rounds, Ragged
     // other many short ones, so that the chunks of the first set the LDS.  There requests of 16 and 32 bytes with both directions at
     // once beat longer ones walked one after the other, above all merged in global memory.  Every shape timed on 2660 calls: the
     // first of these that fits takes 1.02 of the best one's time in the mean, of the orders above 1.10 and up to 1.8 (64 planes
-    // 233x13 fp32 with h_save: {2, 2, 64} 64, {0, 2, 32} 40 us; 768 planes 508x17 bf16 with h_save: {1, 1, 32} 485, {0, 1, 16} 319).
+    // 233x13 fp32 with h_save: {2, 2, 64} 64, {0, 2, 32} 34 us; 768 planes 508x17 bf16 with h_save: {1, 1, 32} 501, {0, 1, 16} 338).
     // By planes: up to 256, up to 512, more.  In 16 bits the merge in global memory comes last: it rounds gx once per direction; and
     // where the shorter side is long too (over 48 positions), in calls of more than 64 planes, requests of 16 bytes come after the
-    // longer ones, for the bytes count there (256 planes 240x80 fp16 with h_save 110 -> 97).
+    // longer ones, for the bytes count there (256 planes 240x80 fp16 with h_save and stretches 110 -> 97).
     struct ShapeAt { int mode, nbuf, seg, wgs; };
     static const ShapeAt narrow16_few[] = {{0, 2, 64, 1}, {0, 2, 32, 1}, {0, 2, 16, 1}, {0, 1, 64, 1}, {0, 1, 16, 1}, {1, 1, 64, 1}, {1, 1, 16, 1}, {2, 2, 64, 1}, {2, 2, 32, 1}, {2, 2, 16, 1}, {2, 1, 64, 1}, {2, 1, 16, 1}};
     static const ShapeAt narrow16_512[] = {{0, 2, 32, 2}, {0, 2, 16, 2}, {0, 1, 64, 2}, {1, 2, 64, 2}, {0, 1, 32, 2}, {0, 1, 16, 2}, {1, 2, 16, 2}, {1, 1, 64, 2}, {0, 2, 64, 1}, {0, 1, 64, 1}, {1, 1, 16, 2}, {0, 1, 32, 1}, {1, 1, 64, 1}, {0, 1, 16, 1}, {1, 1, 16, 1}, {2, 1, 64, 2}, {2, 1, 64, 1}, {2, 2, 32, 1}, {2, 1, 16, 2}, {2, 1, 16, 1}};

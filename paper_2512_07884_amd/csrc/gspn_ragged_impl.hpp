@@ -1,7 +1,8 @@
 // Scan kernel for maps of any height and width: odd sides, rows that start at any element.  Lines of up to 768 positions in fp32
 // storage and 1280 in 16-bit storage (1072 with logits): a chunk of eight lines is at most two granules per loading thread.
-// 16-bit forward calls whose merged output the line-by-line kernels sum in fp32 on chip keep the fp32 tile: with it the LDS
-// ends at 900 positions on narrow maps (687 with logits) and has no room for planes of about 33 700 (30 000) to 40 500 pixels.
+// 16-bit forward calls whose merged output the line-by-line kernels sum in fp32 on chip keep the fp32 tile: they need room in the 160 KB
+// for the tile (4 bytes per position) and a chunk of eight lines of either axis in one direction (10 bytes per position and line, 16 with
+// logits), which maps of 435x67, 325x101 and 191x191 no longer have (with logits 386x67, 297x101 and 185x185): those run line by line.
 // Forward, forward with h_save, and the reverse sweep of the backward call; global scan, GSPN-local, weights as logits.
 //
 // One workgroup owns one (image, channel) plane.  A direction is walked in chunks of K scan lines that pass through LDS:
@@ -20,13 +21,20 @@
 // Both directions of an axis run at once where the tile fits, half of the waves each; where their chunks cross in the
 // middle of the map the second waits for the first, so the order of every sum is fixed.
 // Where the LDS holds two chunks of a direction, the scan of one runs beside the finishing of the chunk before and the staging
-// of the one after, with one barrier per chunk (move_ahead; the turns before took as long as the scan itself: 256 planes 80x68 in
-// bf16 33 -> 27 us); where several workgroups share a CU they hide each other's turns and one chunk does (move_in_turn).
+// of the one after, with one barrier per chunk (move_ahead, the usual form of calls of up to 256 planes; the turns before took as long
+// as the scan itself: 256 planes 80x68 in bf16 32 -> 26 us).  Where several workgroups share a CU they hide each other's turns and one
+// chunk does (move_in_turn: 768 planes 50x83 and 1024 planes 64x168 in fp32, 288 planes 64x64 with logits), and one has to do where the
+// tile leaves no room for a second that is as long (512 planes 100x167).  What these calls gained at the same time came from addresses
+// as running sums, operands unpacked a line ahead and stores behind the next requests.
 //
-// What bounds it: with few planes the chain of the scanning wave (some 180 clocks per line) and the latency of a chunk's
-// requests; with many the L1s -- the loads alone of 1024 planes 64x168 fp32 take 172 of 222 us, 5.9 TB/s into the L1s, a limit of
-// the chip -- and behind them the stores of h_save.  A 16-bit request at an odd element costs the address unit four times an
-// aligned one (64 clocks per wave against 16).  2 x 256 channels 100x167 in bf16: 109 us forward (122 in turns), 1.7 TB/s of its 0.18 GB.
+// What bounds it, kernel times on buffers in turn.  With many planes the L1s: 1024 planes 64x168 in fp32 162 us for 1.06 GB of requests,
+// 6.5 TB/s, the chip's rate of pulling lines into its L1s; the LDS index unit is active in 38 % of a CU's busy cycles (45 % of them
+// bank conflicts), the vector ALUs issue in 6 %.  With few planes the chain of the scanning wave (some 180 clocks per line) and the latency
+// of a chunk's requests: 256 planes 80x68 in bf16 26 us, 148 lines each.  Neither where one workgroup per CU takes turns: 2 x 256
+// channels 100x167 in bf16 134 us, with logits 174, of which the scans' chains are a quarter (267 lines a plane, two planes per CU);
+// with logits the chunks are 8 and 16 lines, 168 and 200 granules for 448 loading threads a direction, so that about half of the
+// loading waves stand by while the others stage a softmax per element, and scan and loads wait for each other.  A 16-bit request at an
+// odd element costs the address unit four times an aligned one (64 clocks per wave against 16).
 #pragma once
 #include "gspn_unaligned.hpp"
 
