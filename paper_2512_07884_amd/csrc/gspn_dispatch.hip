@@ -79,6 +79,10 @@ bool any_size_before_plane(const FwdParams& p, int dtype) {
 //   rows of 192 and 256 bytes, which it reads in whole 64-byte sectors, without h_save, in calls of more than 512 planes (of up to 40
 //   rows: 1024 and more), which fill the chip both ways: 1.07 (680 planes 62x128 bf16 51 -> 69).  With the stores of h_save or of the
 //   reverse sweep 0.7 to 0.97, in calls of fewer planes 0.5 to 0.9, rows of 128 bytes 0.7 to 0.8,
+//   rows of 128 bytes, and up to 64 rows of 112, without h_save and logits where each channel has weights of its own, in calls of more
+//   than 768 planes (65 to 100 rows: up to 2560; up to 64 rows: all four directions): the weights are over half of the bytes there, and
+//   it asks for them in whole sectors or rows; 1.27 of its time in the mean of 72 calls (2186 planes 62x56 bf16 100 -> 140, 1961 planes
+//   122x64 fp16 213 -> 287).  Not 600 planes 70x64 78 -> 45, 7670 planes 72x64 0.8, two channels per group 0.9, with h_save 0.97,
 // where the call walks both vertical directions (without one of them 0.95 and 0.6 to 0.9 of its time: 768 planes 120x128 fp16, up and
 // right, 102 -> 81); and it keeps calls of nothing else, whose lines are the rows that it loads: both vertical directions of more than
 // 512 planes 1.17 of its time (2176 planes 128x80 fp16 90 -> 137; 0.7 to 0.9 below), one alone 1.2 with the rows of 192 and 256 bytes
@@ -95,6 +99,8 @@ bool any_size_before_tile(const FwdParams& p, int dtype) {
     if ((p.mask & 12) == 0 && (down_and_up ? planes > 512 : sectors && planes > 1024)) return false;
     if (!down_and_up) return true;
     if (row_bytes == 2 * 112 && p.H <= 64) return p.logits && planes <= 512;
+    if (p.cpg == 1 && !p.hs && !p.logits && planes > 768 &&
+        (p.H > 64 ? row_bytes == 128 && (p.H > 100 || planes <= 2560) : (row_bytes == 128 || row_bytes == 112) && (p.mask & 15) == 15)) return false;
     return !(!p.hs && sectors && (p.H > 40 ? planes > 512 : planes >= 1024));
 }
 // Backward: the single-launch kernels hold a weight group's channels in one workgroup, the any-size kernel a plane, with a second

@@ -42,6 +42,14 @@ CALLS = [
     ((4, 129, 104, 88, 3), "bf16", "fwd", 0, False, "any size", "tile"), ((4, 129, 104, 64, 3), "bf16", "fwd", 0, False, "any size", "tile"),
     ((4, 255, 40, 128, 15), "f16", "fwd", 0, False, "any size", "tile"), ((4, 256, 40, 128, 16), "f16", "fwd", 0, False, "tile", "tile"),
     ((4, 256, 104, 96, 16), "f16", "bwd", 0, False, "twopass/any size", "twopass/tile"),
+    # ... 16-bit rows of 128 bytes, and up to 64 of 112, without h_save and logits, one channel per group, more than 768 planes
+    ((1, 768, 104, 64, 768), "f16", "fwd", 0, False, "any size", "tile"), ((1, 769, 104, 64, 769), "f16", "fwd", 0, False, "tile", "tile"),
+    ((1, 769, 104, 64, 769), "f16", "save", 0, False, "any size", "tile"), ((1, 769, 104, 64, 769), "f16", "fwd", 0, True, "any size", "tile"),
+    ((1, 770, 104, 64, 385), "f16", "fwd", 0, False, "any size", "tile"), ((1, 769, 104, 32, 769), "f32", "fwd", 0, False, "any size", "tile"),
+    ((7, 110, 64, 56, 110), "bf16", "fwd", 0, False, "tile", "tile"), ((7, 110, 66, 56, 110), "bf16", "fwd", 0, False, "any size", "tile"),
+    ((1, 2560, 100, 64, 2560), "bf16", "fwd", 0, False, "tile", "tile"), ((1, 2561, 100, 64, 2561), "bf16", "fwd", 0, False, "any size", "tile"),
+    ((1, 2561, 104, 64, 2561), "bf16", "fwd", 0, False, "tile", "tile"), ((1, 2561, 64, 64, 2561), "bf16", "fwd", 0, False, "tile", "tile"),
+    ((1, 769, 104, 64, 769), "f16", "bwd", 0, False, "twopass/any size", "twopass/tile"),
     # ... fp32 rows of 512 bytes of more than 12 800 pixels without h_save, more than 512 planes
     ((4, 128, 102, 128, 16), "f32", "fwd", 0, False, "any size", "tile"), ((4, 129, 102, 128, 3), "f32", "fwd", 0, False, "tile", "tile"),
     ((4, 129, 100, 128, 3), "f32", "fwd", 0, False, "any size", "tile"), ((4, 129, 102, 128, 3), "f32", "save", 0, False, "any size", "tile"),
@@ -90,6 +98,7 @@ def test_either_side_of_the_lines(shape, dtype, call, kchunk, logits, kernel, ow
     ((4, 128, 72, 80, 8), "bf16", "fwd", False, (1, 3, 4, 12, 5, 15), ()), ((4, 129, 72, 80, 3), "bf16", "fwd", True, (1, 2, 4, 12, 5, 7, 15), (3,)),
     ((8, 128, 20, 112, 16), "f16", "save", False, (1, 4, 12, 5, 14), (3, 7, 15)), ((4, 129, 50, 128, 3), "bf16", "fwd", False, (1, 4, 12, 14), (3, 11, 15)),
     ((4, 256, 50, 96, 8), "bf16", "save", False, (1, 2, 5, 15), (3,)), ((4, 258, 50, 96, 6), "bf16", "save", False, (5, 7, 15), (1, 2, 3)),
+    ((7, 110, 64, 56, 110), "bf16", "fwd", False, (1, 2, 12, 7, 11), (3, 15)), ((7, 110, 72, 64, 110), "bf16", "fwd", False, (1, 12, 13, 14), (3, 7, 11, 15)),
     ((4, 129, 72, 80, 3), "f16", "bwd", False, (1, 2, 12, 7, 15), (3,)), ((4, 129, 72, 80, 3), "f32", "bwd", False, (1, 3, 12, 15), ()),
     ((16, 64, 28, 28, 16), "f32", "bwd", False, (1, 5, 3, 15), ()), ((17, 64, 28, 28, 16), "f32", "bwd", False, (5, 10, 3, 15), (1, 8)),
     ((17, 64, 28, 28, 16), "f32", "bwd", True, (1, 8, 5, 3, 15), ()), ((17, 64, 28, 29, 16), "f32", "bwd", False, (1, 8, 5, 3, 15), ())],
