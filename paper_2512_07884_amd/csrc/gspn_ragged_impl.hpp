@@ -2,7 +2,8 @@
 // storage and 1280 in 16-bit storage (1072 with logits): a chunk of eight lines is at most two granules per loading thread.
 // 16-bit forward calls whose merged output the line-by-line kernels sum in fp32 on chip keep the fp32 tile: they need room in the 160 KB
 // for the tile (4 bytes per position) and a chunk of eight lines of either axis in one direction (10 bytes per position and line, 16 with
-// logits), which maps of 435x67, 325x101 and 191x191 no longer have (with logits 386x67, 297x101 and 185x185): those run line by line.
+// logits, and the slots between granules), which maps of 435x67, 325x101 and 190x190 no longer have (with logits 386x67, 297x101 and
+// 184x184): those run line by line, up to the 40 500 pixels that fit there (593x67, 397x101, 201x201).
 // Forward, forward with h_save, and the reverse sweep of the backward call; global scan, GSPN-local, weights as logits.
 //
 // One workgroup owns one (image, channel) plane.  A direction is walked in chunks of K scan lines that pass through LDS:
@@ -28,7 +29,7 @@
 // as running sums, operands unpacked a line ahead and stores behind the next requests.
 //
 // What bounds it, kernel times on buffers in turn.  With many planes the L1s: 1024 planes 64x168 in fp32 162 us for 1.06 GB of requests,
-// 6.5 TB/s, the chip's rate of pulling lines into its L1s; the LDS index unit is active in 38 % of a CU's busy cycles (45 % of them
+// 6.5 TB/s, the chip's rate of pulling lines into its L1s; the LDS index unit is active in 36 % of a CU's busy cycles (45 % of them
 // bank conflicts), the vector ALUs issue in 6 %.  With few planes the chain of the scanning wave (some 180 clocks per line) and the latency
 // of a chunk's requests: 256 planes 80x68 in bf16 26 us, 148 lines each.  Neither where one workgroup per CU takes turns: 2 x 256
 // channels 100x167 in bf16 134 us, with logits 174, of which the scans' chains are a quarter (267 lines a plane, two planes per CU);
