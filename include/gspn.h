@@ -158,6 +158,23 @@ int gspn_scan_bwd_logits(const void* gy, const void* x, const void* z, const voi
                          int B, int C, int H, int W, int G, int kchunk,
                          unsigned dir_mask, int dtype, unsigned flags, void* stream);
 
+/* The three forward calls with a workspace of the caller's.  A call of few planes (B*C up to some hundred, fewer than the chip
+ * has compute units for) leaves most of the chip idle while a workgroup holds a whole plane; given room for the states of
+ * the four directions in fp32 it runs every direction of every plane as a work item of its own and merges them in a second launch:
+ * 64 planes of 256x256 in bf16 123 -> 67 us.  gspn_fwd_workspace_bytes says how many bytes such a call asks for (at most 1 GiB), 0 where it
+ * has no use for them (many planes, some directions only, fp32 with h_save, which holds the states itself, invalid arguments).
+ * The workspace is device memory, 16-byte aligned, overwritten by the call and free again when its work on `stream` is done; calls
+ * that may overlap need one each.  workspace == NULL is the call without one, with the same result up to the rounding of the
+ * storage type; fewer bytes than asked for is GSPN_ERR_SHAPE.  w holds normalised weights (logits == 0) or logits (1);
+ * kchunk as in the GSPN-local calls, GSPN_MAX_LINE for the global scan.
+ * The backward calls need no workspace: their states have room in glam and gu. */
+int gspn_scan_fwd_workspace(const void* x, const void* w, const void* lam, const void* u,
+                            void* y, void* h_save, void* workspace, unsigned long long workspace_bytes,
+                            int B, int C, int H, int W, int G, int kchunk, int logits,
+                            unsigned dir_mask, int dtype, unsigned flags, void* stream);
+unsigned long long gspn_fwd_workspace_bytes(int B, int C, int H, int W, int G, int kchunk, int logits, unsigned dir_mask,
+                                            int dtype, unsigned flags, int has_h_save);
+
 /* Forward scan with the horizontal directions stored transposed (Sec. 4.3 reaches coalesced access by laying the
  * data out along the orthogonal axis; this is that layout offered to a caller who can produce it, e.g. by
  * computing the parameters of the two horizontal directions from a transposed feature map).  Slots 0 and 1 of
@@ -238,7 +255,8 @@ const char* gspn_proxy_plan(int B, int K, int M, int H, int W, int dtype);
  * static string, never NULL.  Host only.
  *
  * (The name is the family whose limits the call meets.  Most calls of the "tile" family, those of the "plane" family with few
- * planes, and the first pass of such "twopass" calls run the any-size kernel of "generic" in its place.)
+ * planes, and the first pass of such "twopass" calls run the any-size kernel of "generic" in its place.  Calls of fewer planes than
+ * compute units run every direction in a workgroup of its own, whatever the plan: gspn_fwd_workspace_bytes.)
  * Environment variables for tests (results are the same whichever kernel runs, up to the rounding of
  * the storage type).  They are read once per process, by the first call that dispatches; a process
  * that changes them afterwards calls gspn_reload_env():
@@ -255,7 +273,8 @@ const char* gspn_proxy_plan(int B, int K, int M, int H, int W, int dtype);
  *                               planes (which normally keep one channel per workgroup: a compute unit holds one workgroup)
  *   GSPN_STREAM_ONE_CHANNEL=1   the "stream" kernel with one channel per workgroup on 256- and 512-row bf16 maps (two channels of a
  *                               weight group share a workgroup and the weights there otherwise)
- *   GSPN_FWD_NO_CHUNK=1   skip the "chunk" kernels of GSPN-local (forward and the reverse sweep of the two-pass backward) */
+ *   GSPN_FWD_NO_CHUNK=1   skip the "chunk" kernels of GSPN-local (forward and the reverse sweep of the two-pass backward)
+ *   GSPN_NO_APART=1   no workgroup per direction in calls of few planes (each of the others implies it) */
 const char* gspn_fwd_plan(int B, int C, int H, int W, int G, unsigned dir_mask, int dtype, unsigned flags, int has_h_save);
 const char* gspn_bwd_plan(int B, int C, int H, int W, int G, unsigned dir_mask, int dtype, unsigned flags);
 /* the same for the GSPN-local calls */

@@ -19,7 +19,7 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
 
 EXPORTS = ("gspn_scan_fwd", "gspn_scan_bwd", "gspn_scan_fwd_local", "gspn_scan_bwd_local",
-           "gspn_scan_fwd_logits", "gspn_scan_bwd_logits",
+           "gspn_scan_fwd_logits", "gspn_scan_bwd_logits", "gspn_scan_fwd_workspace", "gspn_fwd_workspace_bytes",
            "gspn_fwd_plan", "gspn_bwd_plan", "gspn_fwd_local_plan", "gspn_bwd_local_plan",
            "gspn_fwd_logits_plan", "gspn_bwd_logits_plan", "gspn_proxy_project", "gspn_proxy_project_bwd", "gspn_proxy_project_bwd_static", "gspn_proxy_plan",
            "gspn_scan_fwd_transposed", "gspn_fwd_transposed_plan", "gspn_scan_fwd_unfused", "gspn_unfused_workspace_bytes",
@@ -63,6 +63,10 @@ def load_library() -> ctypes.CDLL:
     lib.gspn_scan_fwd_logits.restype = ci
     lib.gspn_scan_bwd_logits.argtypes = [vp] * 10 + [ci] * 6 + [cu, ci, cu, vp]
     lib.gspn_scan_bwd_logits.restype = ci
+    lib.gspn_scan_fwd_workspace.argtypes = [vp] * 7 + [ctypes.c_ulonglong] + [ci] * 7 + [cu, ci, cu, vp]
+    lib.gspn_scan_fwd_workspace.restype = ci
+    lib.gspn_fwd_workspace_bytes.argtypes = [ci] * 7 + [cu, ci, cu, ci]
+    lib.gspn_fwd_workspace_bytes.restype = ctypes.c_ulonglong
     lib.gspn_fwd_logits_plan.argtypes = [ci] * 6 + [cu, ci, cu, ci]
     lib.gspn_fwd_logits_plan.restype = ctypes.c_char_p
     lib.gspn_bwd_logits_plan.argtypes = [ci] * 6 + [cu, ci, cu]
@@ -108,6 +112,7 @@ def gspn_status_string(status: int) -> str:
 def gspn_reload_env() -> None:
     """Makes the library read its GSPN_* environment variables again (it reads them once otherwise)."""
     load_library().gspn_reload_env()
+    _WORKSPACE_BYTES.clear()
 
 
 def gspn_version() -> int:
@@ -147,6 +152,12 @@ def call_kernel(B, C, H, W, G, dtype, call, kchunk=0, logits=False, dir_mask=DIR
     f = load_library().gspn_call_kernel
     f.restype = ctypes.c_char_p
     return f(B, C, H, W, G, kchunk, int(logits), ctypes.c_uint(dir_mask), dtype, ("fwd", "save", "bwd").index(call)).decode()
+
+
+def call_apart(B, C, H, W, G, dtype, call, kchunk=0, logits=False, dir_mask=DIR_ALL) -> int:
+    """1 where the directions of such a call run in workgroups of their own (forward: given a workspace), 2 without a workspace,
+    else 0."""
+    return load_library().gspn_call_apart(B, C, H, W, G, kchunk, int(logits), ctypes.c_uint(dir_mask), dtype, ("fwd", "save", "bwd").index(call))
 
 
 # ---------------------------------------------------------------- marshalling
@@ -207,6 +218,42 @@ def _fwd_args(x, w, lam, u, y, h_save, G, flags):
     return [px, pw, pl, pu, py, ph], (B, C, H, W, G)
 
 
+_WORKSPACE_BYTES = {}          # sizes, type and options of a call -> bytes it asks for
+
+
+def _workspace(x, nbytes, stream):
+    """Device memory for one call, from torch's allocator and in the order of the stream the call runs on; None where there is no
+    room (the call then runs without)."""
+    import torch
+    try:
+        if stream is None:
+            return torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+        if not hasattr(stream, "cuda_stream"):
+            stream = torch.cuda.ExternalStream(int(stream), device=x.device) if int(stream) else torch.cuda.default_stream(x.device)
+        with torch.cuda.stream(stream):
+            return torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
+def _scan_fwd(x, w, lam, u, y, h_save, kchunk, logits, G, dir_mask, flags, stream):
+    ptrs, dims = _fwd_args(x, w, lam, u, y, h_save, G, flags)
+    lib, code, kchunk = load_library(), _dtype_code(x), int(kchunk)
+    key = (dims, kchunk, logits, dir_mask, code, flags, h_save is None)
+    nbytes = _WORKSPACE_BYTES.get(key)
+    if nbytes is None:
+        if len(_WORKSPACE_BYTES) >= 4096:
+            _WORKSPACE_BYTES.clear()
+        nbytes = _WORKSPACE_BYTES[key] = lib.gspn_fwd_workspace_bytes(*dims, kchunk, logits, dir_mask, code, flags, int(h_save is not None))
+    ws = _workspace(x, nbytes, stream) if nbytes else None
+    _check(lib.gspn_scan_fwd_workspace(*ptrs, None if ws is None else ws.data_ptr(), nbytes if ws is not None else 0, *dims, kchunk, logits,
+                                       dir_mask, code, flags, _stream(stream)))
+
+
+def gspn_fwd_workspace_bytes(B, C, H, W, G, kchunk=GLOBAL_SCAN, logits=False, dir_mask=DIR_ALL, dtype=GSPN_F32, flags=0, has_h_save=False) -> int:
+    return int(load_library().gspn_fwd_workspace_bytes(B, C, H, W, G, kchunk, int(logits), dir_mask, dtype, flags, int(has_h_save)))
+
+
 def gspn_scan_fwd(x, w, lam, u, y, h_save=None, *, G: Optional[int] = None, dir_mask: int = DIR_ALL,
                   flags: int = 0, stream=None) -> None:
     """y <- sum over directions of u_d * h_d (Eq. 1-2); optionally saves h_d.
@@ -215,24 +262,19 @@ def gspn_scan_fwd(x, w, lam, u, y, h_save=None, *, G: Optional[int] = None, dir_
     GSPN_FLAG_SHARED_PARAMS); y [B,C,H,W]; h_save [4,B,C,H,W] or None.
     All device tensors of one dtype (float32 / bfloat16 / float16), contiguous.
     """
-    ptrs, dims = _fwd_args(x, w, lam, u, y, h_save, G, flags)
-    _check(load_library().gspn_scan_fwd(*ptrs, *dims, dir_mask, _dtype_code(x), flags, _stream(stream)))
+    _scan_fwd(x, w, lam, u, y, h_save, GLOBAL_SCAN, 0, G, dir_mask, flags, stream)
 
 
 def gspn_scan_fwd_local(x, w, lam, u, y, h_save=None, *, kchunk: int, G: Optional[int] = None,
                         dir_mask: int = DIR_ALL, flags: int = 0, stream=None) -> None:
     """GSPN-local forward (Sec. 3.2): as gspn_scan_fwd, propagation confined to stretches of kchunk lines."""
-    ptrs, dims = _fwd_args(x, w, lam, u, y, h_save, G, flags)
-    _check(load_library().gspn_scan_fwd_local(*ptrs, *dims, int(kchunk), dir_mask, _dtype_code(x), flags,
-                                              _stream(stream)))
+    _scan_fwd(x, w, lam, u, y, h_save, kchunk, 0, G, dir_mask, flags, stream)
 
 
 def gspn_scan_fwd_logits(x, z, lam, u, y, h_save=None, *, kchunk: int = GLOBAL_SCAN, G: Optional[int] = None,
                          dir_mask: int = DIR_ALL, flags: int = 0, stream=None) -> None:
     """As gspn_scan_fwd with the weights given as raw logits z (softmax over the taps that exist, inside the call)."""
-    ptrs, dims = _fwd_args(x, z, lam, u, y, h_save, G, flags)
-    _check(load_library().gspn_scan_fwd_logits(*ptrs, *dims, int(kchunk), dir_mask, _dtype_code(x), flags,
-                                               _stream(stream)))
+    _scan_fwd(x, z, lam, u, y, h_save, kchunk, 1, G, dir_mask, flags, stream)
 
 
 def _bwd_args(gy, x, w, lam, u, h_save, gx, gw, glam, gu, G, flags):

@@ -31,6 +31,7 @@ extern "C" {
 
 static int scan_fwd_any(const void* x, const void* w, const void* lam, const void* u,
                         void* y, void* h_save,
+                        void* workspace, unsigned long long workspace_bytes,
                         int B, int C, int H, int W, int G, int kchunk, int logits,
                         unsigned dir_mask, int dtype, unsigned flags, void* stream) {
     if (!x || !w || !lam || !u || !y) return GSPN_ERR_NULL;
@@ -39,7 +40,7 @@ static int scan_fwd_any(const void* x, const void* w, const void* lam, const voi
     if (kchunk < 1) return GSPN_ERR_SHAPE;
     if (logits && (H > GSPN_MAX_LINE_LOGITS || W > GSPN_MAX_LINE_LOGITS)) return GSPN_ERR_UNSUPPORTED;
     if (misaligned(x) || misaligned(w) || misaligned(lam) || misaligned(u) || misaligned(y) ||
-        (h_save && misaligned(h_save)))
+        (h_save && misaligned(h_save)) || misaligned(workspace))
         return GSPN_ERR_ALIGN;
     FwdParams p = {};
     p.x = x; p.w = w; p.lam = lam; p.u = u; p.y = y; p.hs = h_save;
@@ -47,7 +48,11 @@ static int scan_fwd_any(const void* x, const void* w, const void* lam, const voi
     p.mask = dir_mask; p.shared = (flags & GSPN_FLAG_SHARED_PARAMS) ? 1 : 0;
     p.kchunk = effective_kchunk(kchunk, H, W);
     p.logits = logits;
-    hipError_t e = launch_fwd(p, dtype, (hipStream_t)stream);
+    if (workspace && workspace_bytes < apart_workspace_bytes(p, dtype)) {
+        if (apart_fwd(p, dtype)) return GSPN_ERR_SHAPE;
+        workspace = nullptr;
+    }
+    hipError_t e = launch_fwd(p, dtype, workspace, (hipStream_t)stream);
     return e == hipSuccess ? GSPN_OK : GSPN_ERR_HIP;
 }
 
@@ -63,7 +68,7 @@ int gspn_scan_fwd_transposed(const void* x, const void* xt, const void* w, const
     p.x = x; p.xt = xt; p.w = w; p.lam = lam; p.u = u; p.y = y; p.hs = nullptr;
     p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G;
     p.mask = dir_mask; p.shared = (flags & GSPN_FLAG_SHARED_PARAMS) ? 1 : 0;
-    hipError_t e = launch_fwd(p, dtype, (hipStream_t)stream);
+    hipError_t e = launch_fwd(p, dtype, nullptr, (hipStream_t)stream);
     return e == hipSuccess ? GSPN_OK : GSPN_ERR_HIP;
 }
 
@@ -104,14 +109,35 @@ int gspn_scan_fwd_local(const void* x, const void* w, const void* lam, const voi
                         void* y, void* h_save,
                         int B, int C, int H, int W, int G, int kchunk,
                         unsigned dir_mask, int dtype, unsigned flags, void* stream) {
-    return scan_fwd_any(x, w, lam, u, y, h_save, B, C, H, W, G, kchunk, 0, dir_mask, dtype, flags, stream);
+    return scan_fwd_any(x, w, lam, u, y, h_save, nullptr, 0, B, C, H, W, G, kchunk, 0, dir_mask, dtype, flags, stream);
 }
 
 int gspn_scan_fwd_logits(const void* x, const void* z, const void* lam, const void* u,
                          void* y, void* h_save,
                          int B, int C, int H, int W, int G, int kchunk,
                          unsigned dir_mask, int dtype, unsigned flags, void* stream) {
-    return scan_fwd_any(x, z, lam, u, y, h_save, B, C, H, W, G, kchunk, 1, dir_mask, dtype, flags, stream);
+    return scan_fwd_any(x, z, lam, u, y, h_save, nullptr, 0, B, C, H, W, G, kchunk, 1, dir_mask, dtype, flags, stream);
+}
+
+int gspn_scan_fwd_workspace(const void* x, const void* w, const void* lam, const void* u, void* y, void* h_save,
+                            void* workspace, unsigned long long workspace_bytes,
+                            int B, int C, int H, int W, int G, int kchunk, int logits,
+                            unsigned dir_mask, int dtype, unsigned flags, void* stream) {
+    if (logits != 0 && logits != 1) return GSPN_ERR_SHAPE;
+    return scan_fwd_any(x, w, lam, u, y, h_save, workspace, workspace_bytes, B, C, H, W, G, kchunk, logits, dir_mask, dtype, flags, stream);
+}
+
+unsigned long long gspn_fwd_workspace_bytes(int B, int C, int H, int W, int G, int kchunk, int logits, unsigned dir_mask, int dtype,
+                                            unsigned flags, int has_h_save) {
+    if (check_common(B, C, H, W, G, dir_mask, dtype, flags) != GSPN_OK || kchunk < 1) return 0;
+    if (logits && (H > GSPN_MAX_LINE_LOGITS || W > GSPN_MAX_LINE_LOGITS)) return 0;
+    FwdParams p = {};
+    p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = dir_mask;
+    p.shared = (flags & GSPN_FLAG_SHARED_PARAMS) ? 1 : 0;
+    p.kchunk = effective_kchunk(kchunk, H, W);
+    p.logits = logits;
+    p.hs = has_h_save ? (void*)16 : nullptr;
+    return apart_fwd(p, dtype) ? apart_workspace_bytes(p, dtype) : 0;
 }
 
 int gspn_scan_fwd(const void* x, const void* w, const void* lam, const void* u,

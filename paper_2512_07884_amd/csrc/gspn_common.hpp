@@ -206,6 +206,16 @@ const char* twopass_kernel_name(const BwdParams& p, int dtype);      // for gspn
 int ragged_fwd_threads(const FwdParams& p, int dtype);        // threads per workgroup, 0: not taken
 int ragged_bwd_threads(const BwdParams& p, int dtype);
 bool ragged_shape(const FwdParams& p, int dtype, bool merge_rounds, int out[7]);
+// calls of few planes: a workgroup per direction, the states in fp32 merged by a launch of its own (gspn_apart*.hip)
+bool apart_applicable(const FwdParams& p, int dtype);
+bool apart_bwd_applicable(const BwdParams& p, int dtype);
+size_t apart_workspace_bytes(const FwdParams& p, int dtype);
+hipError_t launch_fwd_apart(const FwdParams& p, int dtype, void* states, hipStream_t s);
+hipError_t launch_bwd_apart(const BwdParams& p, int dtype, hipStream_t s);
+bool apart_fwd(const FwdParams& p, int dtype);               // gspn_dispatch.hip: the calls that run so
+bool apart_bwd(const BwdParams& p, int dtype);
+bool ragged_finish_fits(const BwdParams& p, int dtype);      // the any-size kernels' second pass of the backward call
+hipError_t launch_ragged_finish(const BwdParams& p, int dtype, hipStream_t s);
 hipError_t launch_fwd_tile(const FwdParams& p, int dtype, hipStream_t s);
 bool fwd_tile_applicable(const FwdParams& p, int dtype);
 hipError_t launch_fwd_plane(const FwdParams& p, int dtype, hipStream_t s);
@@ -244,7 +254,7 @@ hipError_t launch_proxy_project_bwd_static(const void* gout, const void* in, con
                                            int B, int K, int M, int N, int dtype, hipStream_t s);
 
 // dispatch (gspn_dispatch.hip): picks the kernel family for the arguments
-hipError_t launch_fwd(const FwdParams& p, int dtype, hipStream_t s);
+hipError_t launch_fwd(const FwdParams& p, int dtype, void* workspace, hipStream_t s);      // workspace: apart_workspace_bytes, or null
 hipError_t launch_bwd(const BwdParams& p, int dtype, hipStream_t s);
 const char* fwd_plan_name(const FwdParams& p, int dtype);
 const char* bwd_plan_name(const BwdParams& p, int dtype);

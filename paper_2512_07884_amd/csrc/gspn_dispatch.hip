@@ -20,8 +20,9 @@ enum BwdPlan { BWD_GENERIC = 0, BWD_TILE = 1, BWD_PLANE = 2, BWD_TWOPASS = 3, BW
 // row per lane instead of the one with whole-line requests; GSPN_FWD_NO_CHUNK=1: skip the per-stretch kernels of GSPN-local
 // (forward and the reverse sweep of the two-pass backward); GSPN_STREAM_ONE_CHANNEL=1: the whole-line stream kernel with one
 // channel per workgroup on the maps where two channels of a group normally share a workgroup; GSPN_STREAM_TWO_CHANNELS=1:
-// two channels per workgroup there also in calls with too few planes to fill the chip that way.
-enum : unsigned { K_FORCE_GENERIC = 1, K_FWD_NO_PLANE = 2, K_BWD_NO_PLANE = 4, K_BWD_NO_TWOPASS = 8, K_FWD_NO_PAIR = 16, K_STREAM_NO_STAGED = 32, K_FWD_NO_CHUNK = 64, K_STREAM_ONE_CHANNEL = 128, K_STREAM_TWO_CHANNELS = 256, K_NO_ANY_SIZE = 512, K_VALID = 1u << 31 };
+// two channels per workgroup there also in calls with too few planes to fill the chip that way; GSPN_NO_APART=1: no workgroup per
+// direction in calls of few planes (each of the others implies it).
+enum : unsigned { K_FORCE_GENERIC = 1, K_FWD_NO_PLANE = 2, K_BWD_NO_PLANE = 4, K_BWD_NO_TWOPASS = 8, K_FWD_NO_PAIR = 16, K_STREAM_NO_STAGED = 32, K_FWD_NO_CHUNK = 64, K_STREAM_ONE_CHANNEL = 128, K_STREAM_TWO_CHANNELS = 256, K_NO_ANY_SIZE = 512, K_NO_APART = 1024, K_VALID = 1u << 31 };
 static std::atomic<unsigned> g_knobs{0};
 static bool env_flag(const char* name) { const char* v = getenv(name); return v && v[0] == '1'; }
 void reload_env_knobs() {
@@ -36,13 +37,14 @@ void reload_env_knobs() {
     if (env_flag("GSPN_STREAM_ONE_CHANNEL")) k |= K_STREAM_ONE_CHANNEL;
     if (env_flag("GSPN_STREAM_TWO_CHANNELS")) k |= K_STREAM_TWO_CHANNELS;
     if (env_flag("GSPN_NO_ANY_SIZE")) k |= K_NO_ANY_SIZE;
+    if (env_flag("GSPN_NO_APART")) k |= K_NO_APART;
     g_knobs.store(k, std::memory_order_release);
 }
-struct Knobs { bool force_generic, fwd_no_plane, bwd_no_plane, bwd_no_twopass, fwd_no_pair, stream_no_staged, fwd_no_chunk, stream_one_channel, stream_two_channels, no_any_size; };
+struct Knobs { bool force_generic, fwd_no_plane, bwd_no_plane, bwd_no_twopass, fwd_no_pair, stream_no_staged, fwd_no_chunk, stream_one_channel, stream_two_channels, no_any_size, any; };
 static Knobs knobs() {
     unsigned k = g_knobs.load(std::memory_order_acquire);
     if (!(k & K_VALID)) { reload_env_knobs(); k = g_knobs.load(std::memory_order_acquire); }
-    return Knobs{(k & K_FORCE_GENERIC) != 0, (k & K_FWD_NO_PLANE) != 0, (k & K_BWD_NO_PLANE) != 0, (k & K_BWD_NO_TWOPASS) != 0, (k & K_FWD_NO_PAIR) != 0, (k & K_STREAM_NO_STAGED) != 0, (k & K_FWD_NO_CHUNK) != 0, (k & K_STREAM_ONE_CHANNEL) != 0, (k & K_STREAM_TWO_CHANNELS) != 0, (k & K_NO_ANY_SIZE) != 0};
+    return Knobs{(k & K_FORCE_GENERIC) != 0, (k & K_FWD_NO_PLANE) != 0, (k & K_BWD_NO_PLANE) != 0, (k & K_BWD_NO_TWOPASS) != 0, (k & K_FWD_NO_PAIR) != 0, (k & K_STREAM_NO_STAGED) != 0, (k & K_FWD_NO_CHUNK) != 0, (k & K_STREAM_ONE_CHANNEL) != 0, (k & K_STREAM_TWO_CHANNELS) != 0, (k & K_NO_ANY_SIZE) != 0, k != K_VALID};
 }
 bool pair_kernels_enabled() { return !knobs().fwd_no_pair; }
 bool staged_stream_enabled() { return !knobs().stream_no_staged; }
@@ -174,7 +176,55 @@ static BwdPlan bwd_kernel(const BwdParams& p, int dtype) {
     return any && ragged_bwd_applicable(p, dtype) ? BWD_ANY_SIZE : plan;
 }
 
-hipError_t launch_fwd(const FwdParams& p, int dtype, hipStream_t s) {
+// Calls of few planes: a workgroup per direction (gspn_apart*.hip) rather than the kernel above, whose workgroups hold whole planes.
+// Timed on 30 000 random calls (8 to 1100 planes, 20 to 1024 positions a side, the three types, stretches, logits); the line lies
+// where the mean of the ratio passes 0.9 and few calls run longer.  Ratio in the mean by planes: 8 0.4, 32 0.5, 64 0.6, 128 0.75;
+// beyond, where every CU has a plane of its own, what the states cost across the memory system counts (160 planes 0.87, 256 1.0, 512
+// 1.1 in 16-bit forward calls, 0.9 with a softmax per weight or where h_save holds the states anyway; the backward call always has
+// them: 256 planes 0.88, 384 0.9, 512 0.97).  Of the kernels in their place: two-channel, 128 planes 128x128 44 -> 28 us, 320 planes 1.6 of its
+// time; stream, 64 planes 256x256 bf16 123 -> 67, 96 planes 0.75, 192 1.4, lines of 1024 0.93 at 64; per-stretch, up to its 256 planes 0.75
+// (backward in 16 bits, which rounds e there and not here: 32 planes 0.85, 64 0.93).  What ran line by line for want of an LDS tile,
+// 0.04 to 0.12 of its time at any number of planes.
+constexpr size_t APART_WORKSPACE = (size_t)1 << 30;             // bytes: no call asks for more
+bool apart_fwd(const FwdParams& p, int dtype) {
+    const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
+    if (knobs().any || p.mask != 15 || p.xt || HW < 400 || planes > 1100 || apart_workspace_bytes(p, dtype) > APART_WORKSPACE) return false;
+    const int longest = p.H > p.W ? p.H : p.W;
+    const bool f32 = dtype == 0;
+    size_t most;
+    switch (fwd_kernel(p, dtype)) {
+        case FWD_PAIR: most = 144; break;
+        case FWD_CHUNK: most = 256; break;
+        case FWD_STREAM: most = f32 ? 128 : longest > 512 ? 64 : 96; break;
+        case FWD_GENERIC: most = HW >= 4096 ? 1100 : 128; break;
+        default: most = p.kchunk > 0 ? 128 : HW < 8000 && (f32 ? p.hs != nullptr : p.logits != 0) ? 384 : HW < 4096 ? 192 : 144;
+    }
+    return planes <= most && apart_applicable(p, dtype);
+}
+bool apart_bwd(const BwdParams& p, int dtype) {
+    const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
+    if (knobs().any || p.mask != 15 || HW < 400 || planes > 1100) return false;
+    const int longest = p.H > p.W ? p.H : p.W;
+    const bool f32 = dtype == 0;
+    size_t most = p.kchunk > 0 ? 128 : 384;
+    const BwdPlan kernel = bwd_kernel(p, dtype);
+    if (kernel == BWD_TWOPASS) {
+        const char* first = twopass_kernel_name(p, dtype) + 8;
+        if (!strcmp(first, "pair")) most = 96;
+        else if (!strcmp(first, "stream")) most = f32 ? 128 : longest > 512 ? 32 : 64;
+        else if (!strcmp(first, "chunk")) most = f32 ? 256 : 32;
+        else if (!strcmp(first, "any size")) most = p.kchunk > 0 ? 128 : 256;
+        else most = 128;
+    } else if (kernel == BWD_GENERIC) {
+        most = HW >= 4096 ? 1100 : 128;
+    } else if (kernel != BWD_ANY_SIZE) {
+        most = 128;
+    }
+    return planes <= most && apart_bwd_applicable(p, dtype);
+}
+
+hipError_t launch_fwd(const FwdParams& p, int dtype, void* workspace, hipStream_t s) {
+    if ((workspace || apart_workspace_bytes(p, dtype) == 0) && apart_fwd(p, dtype)) return launch_fwd_apart(p, dtype, workspace, s);
     switch (fwd_kernel(p, dtype)) {
         case FWD_TILE: return launch_fwd_tile(p, dtype, s);
         case FWD_STREAM: return launch_fwd_stream(p, dtype, s);
@@ -187,6 +237,7 @@ hipError_t launch_fwd(const FwdParams& p, int dtype, hipStream_t s) {
 }
 
 hipError_t launch_bwd(const BwdParams& p, int dtype, hipStream_t s) {
+    if (apart_bwd(p, dtype)) return launch_bwd_apart(p, dtype, s);
     switch (bwd_kernel(p, dtype)) {
         case BWD_TILE: return launch_bwd_tile(p, dtype, s);
         case BWD_PLANE: return launch_bwd_plane(p, dtype, s);
@@ -219,7 +270,8 @@ const char* bwd_plan_name(const BwdParams& p, int dtype) {
 }  // namespace gspn
 
 // For the tests, bench.py and smoke(), not part of the ABI: the kernel a valid call runs -- pass 0 forward, 1 forward with h_save,
-// 2 backward ("twopass/..": its first pass after the slash).  kchunk 0: the global scan.
+// 2 backward ("twopass/..": its first pass after the slash).  kchunk 0: the global scan.  Of a call whose directions run apart
+// (gspn_call_apart): what it runs otherwise.
 extern "C" const char* gspn_call_kernel(int B, int C, int H, int W, int G, int kchunk, int logits, unsigned mask, int dtype, int pass) {
     using namespace gspn;
     if (kchunk >= (H > W ? H : W)) kchunk = 0;
@@ -247,6 +299,23 @@ extern "C" const char* gspn_call_kernel(int B, int C, int H, int W, int G, int k
         case FWD_ANY_SIZE: return "any size";
         default: return "line by line";
     }
+}
+
+// For the tests, bench.py and smoke(), not part of the ABI: 1 where the directions of such a call run in workgroups of their own (a
+// forward call: given the workspace it asks for), 2 where they do without a workspace, else 0.
+extern "C" int gspn_call_apart(int B, int C, int H, int W, int G, int kchunk, int logits, unsigned mask, int dtype, int pass) {
+    using namespace gspn;
+    if (kchunk >= (H > W ? H : W)) kchunk = 0;
+    if (pass == 2) {
+        BwdParams p = {};
+        p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
+        p.glam = (void*)16;
+        return apart_bwd(p, dtype) ? 2 : 0;
+    }
+    FwdParams p = {};
+    p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
+    p.hs = pass ? (void*)16 : nullptr;
+    return !apart_fwd(p, dtype) ? 0 : apart_workspace_bytes(p, dtype) ? 1 : 2;
 }
 
 // For the tests, not part of the ABI: the launch shape of the any-size kernel where a call runs it (see ragged_shape), else 0.

@@ -437,6 +437,9 @@ unsigned long long ragged_finish_blocks(const BwdParams& p, int dtype) {
 
 }  // namespace
 
+// (a launch counts its threads in 32 bits)
+bool ragged_finish_fits(const BwdParams& p, int dtype) { return ragged_finish_blocks(p, dtype) * 256 < (1ull << 32); }
+
 // As for the forward call, with two launches here; line by line a workgroup takes a whole weight group, so more channels per
 // group draw the line nearer.  Line by line -> here: 1712 planes 3x251, 16 per group, top to bottom, 39 -> 70 us; 35488 planes
 // 82x4, left to right, 148 -> 284; 5215 planes 4x7, one per group, three directions, 44 -> 60.  Beyond the lines: 107 planes
@@ -444,16 +447,12 @@ unsigned long long ragged_finish_blocks(const BwdParams& p, int dtype) {
 int ragged_bwd_threads(const BwdParams& p, int dtype) {
     const long long steps = lines_walked(p.mask, p.H, p.W), HW = (long long)p.H * p.W, groups = (long long)p.B * p.G;
     if (steps <= 2 || (steps <= 4 && p.cpg <= 16) || (steps <= 10 && p.cpg <= 2) || (steps * HW <= 520 && groups > 512)) return 0;
-    return ragged_finish_blocks(p, dtype) * 256 < (1ull << 32) ? ragged_threads(ragged_sweep_params(p), dtype, true) : 0;
+    return ragged_finish_fits(p, dtype) ? ragged_threads(ragged_sweep_params(p), dtype, true) : 0;
 }
 bool ragged_bwd_applicable(const BwdParams& p, int dtype) { return ragged_bwd_threads(p, dtype) != 0; }
 
-// The two passes of the backward call on any map: the reverse sweep (merged gx, e per direction in fp32), then the sums
-// over the channels.
-hipError_t launch_bwd_ragged(const BwdParams& p, int dtype, hipStream_t s) {
-    const FwdParams f = ragged_sweep_params(p);
-    hipError_t e = launch_ragged(f, dtype, true, true, dtype == 0 ? nullptr : p.gu, s);
-    if (e != hipSuccess) return e;
+// The second pass: the sums over the channels (e as the first pass left it: glam, in 16-bit storage its halves in glam and gu).
+hipError_t launch_ragged_finish(const BwdParams& p, int dtype, hipStream_t s) {
     int ndirs = 0;
     for (int d = 0; d < 4; ++d) ndirs += (p.mask >> d) & 1u;
     const dim3 grid((unsigned)ragged_finish_blocks(p, dtype)), block(256);
@@ -463,6 +462,14 @@ hipError_t launch_bwd_ragged(const BwdParams& p, int dtype, hipStream_t s) {
                                            : (sliced ? ragged_finish_kernel<f16_t, 4> : ragged_finish_kernel<f16_t, 1>);
     hipLaunchKernelGGL(k, grid, block, 0, s, p, ndirs);
     return hipGetLastError();
+}
+
+// The two passes of the backward call on any map: the reverse sweep (merged gx, e per direction in fp32), then the sums
+// over the channels.
+hipError_t launch_bwd_ragged(const BwdParams& p, int dtype, hipStream_t s) {
+    const FwdParams f = ragged_sweep_params(p);
+    const hipError_t e = launch_ragged(f, dtype, true, true, dtype == 0 ? nullptr : p.gu, s);
+    return e == hipSuccess ? launch_ragged_finish(p, dtype, s) : e;
 }
 
 }  // namespace gspn

@@ -58,23 +58,6 @@ struct RaggedArgs {
 
 namespace {
 
-// element e (compile-time) of a granule in storage bits / widened
-template <typename T> __device__ __forceinline__ uint32_t rg_bits(u32x4 v, int e) {
-    if constexpr (sizeof(T) == 4) return v[e];
-    else return (e & 1) ? v[e >> 1] >> 16 : v[e >> 1] & 0xffffu;
-}
-template <typename T> __device__ __forceinline__ float rg_elem(u32x4 v, int e) {
-    if constexpr (sizeof(T) == 4) return __uint_as_float(v[e]);
-    else return (e & 1) ? word_hi<T>(v[e >> 1]) : word_lo<T>(v[e >> 1]);
-}
-template <typename T> __device__ __forceinline__ void rg_store_bits(T* p, uint32_t bits) {
-    if constexpr (sizeof(T) == 4) *(uint32_t*)p = bits;
-    else *(uint16_t*)p = (uint16_t)bits;
-}
-// LDS by byte address (the pointer form costs an addition of the array's base per access)
-template <typename V> __device__ __forceinline__ V lds_get(uint32_t addr) { return *(const __attribute__((address_space(3))) V*)addr; }
-template <typename V> __device__ __forceinline__ void lds_set(uint32_t addr, V v) { *(__attribute__((address_space(3))) V*)addr = v; }
-
 // One pass over the plane: one direction, or both directions of an axis at once.
 template <typename T, int MODE, bool LOGITS, int NV, bool TILE, bool HORZ>
 struct RaggedPass {

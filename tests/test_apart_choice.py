@@ -1,0 +1,57 @@
+"""Which calls run their directions in workgroups of their own, on either side of each line (host code only): 0 none, 1 given a
+workspace, 2 without one."""
+import os
+
+import pytest
+
+
+@pytest.fixture(scope="module", autouse=True)
+def library():
+    from paper_2512_07884_amd import binding
+    if not os.path.exists(binding.lib_path()):
+        from paper_2512_07884_amd import build
+        build.build(verbose=False)
+
+
+# (B, C, H, W, G), dtype, kchunk, logits: forward, with h_save, backward
+CALLS = [
+    ((1, 64, 256, 256, 8), "bf16", 0, False, (1, 1, 2)), ((1, 96, 256, 256, 8), "bf16", 0, False, (1, 1, 0)),
+    ((1, 104, 256, 256, 8), "bf16", 0, False, (0, 0, 0)), ((1, 128, 256, 256, 8), "f32", 0, False, (1, 2, 2)),
+    ((1, 64, 1024, 512, 8), "bf16", 0, False, (1, 1, 0)), ((1, 128, 1024, 1024, 8), "f32", 0, False, (0, 0, 0)),
+    ((1, 144, 128, 128, 8), "bf16", 0, False, (1, 1, 0)), ((1, 152, 128, 128, 4), "f16", 0, False, (0, 0, 0)),
+    ((1, 96, 128, 128, 8), "f16", 0, False, (1, 1, 2)), ((1, 32, 128, 128, 4), "f32", 32, False, (1, 2, 2)),
+    ((1, 64, 128, 128, 4), "bf16", 32, False, (1, 1, 0)), ((1, 32, 128, 128, 4), "bf16", 32, False, (1, 1, 2)),
+    ((1, 144, 50, 83, 9), "bf16", 0, False, (1, 1, 2)), ((1, 160, 50, 83, 10), "bf16", 0, False, (0, 0, 2)),
+    ((1, 192, 40, 83, 12), "bf16", 0, False, (1, 1, 2)), ((1, 200, 40, 83, 25), "bf16", 0, False, (0, 0, 2)),
+    ((1, 384, 50, 83, 12), "bf16", 0, True, (1, 1, 2)), ((1, 392, 50, 83, 49), "f16", 0, True, (0, 0, 0)),
+    ((1, 384, 50, 83, 12), "f32", 0, False, (0, 2, 2)), ((1, 392, 50, 83, 49), "f32", 0, False, (0, 0, 0)),
+    ((1, 128, 50, 83, 8), "f16", 16, False, (1, 1, 2)), ((1, 136, 50, 83, 17), "f16", 16, False, (0, 0, 0)),
+    ((1, 64, 19, 21, 8), "bf16", 0, False, (0, 0, 0)), ((1, 64, 20, 20, 8), "bf16", 0, False, (1, 1, 2)),
+    ((2, 256, 100, 167, 8), "bf16", 0, True, (0, 0, 0)), ((4, 192, 50, 83, 8), "f32", 0, False, (0, 0, 0)),
+    # 16-bit planes whose fp32 tile does not fit, which ran line by line
+    ((1, 600, 195, 195, 8), "bf16", 0, False, (1, 1, 0)), ((1, 1100, 400, 90, 11), "bf16", 0, False, (1, 1, 0)),
+    ((2, 1024, 195, 195, 16), "bf16", 0, False, (0, 0, 0)),                      # (workspace beyond 1 GiB)
+]
+
+
+@pytest.mark.parametrize("shape,dtype,kchunk,logits,want", CALLS, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+def test_either_side_of_the_lines(shape, dtype, kchunk, logits, want, monkeypatch):
+    from paper_2512_07884_amd import binding
+    code = {"f32": 0, "bf16": 1, "f16": 2}[dtype]
+    f = lambda call, mask=15: binding.call_apart(*shape, code, call, kchunk, logits, mask)
+    assert tuple(f(c) for c in ("fwd", "save", "bwd")) == want
+    for save, w in ((False, want[0]), (True, want[1])):
+        n = binding.gspn_fwd_workspace_bytes(*shape, kchunk or binding.GLOBAL_SCAN, logits, 15, code, 0, save)
+        assert n == (16 * shape[0] * shape[1] * shape[2] * shape[3] if w == 1 else 0)
+    assert f("fwd", 7) == f("bwd", 12) == 0                                       # all four directions only
+    for knob in ("GSPN_NO_APART", "GSPN_FORCE_GENERIC", "GSPN_FWD_NO_PAIR"):
+        monkeypatch.setenv(knob, "1")
+        assert f("fwd") == f("save") == f("bwd") == 0
+        monkeypatch.delenv(knob)
+
+
+def test_invalid_arguments_ask_for_nothing():
+    from paper_2512_07884_amd import binding
+    ask = lambda *a, **k: binding.gspn_fwd_workspace_bytes(*a, **k)
+    assert ask(1, 8, 50, 50, 3) == ask(0, 8, 50, 50, 1) == ask(1, 8, 50, 50, 1, kchunk=0) == ask(1, 8, 50, 50, 1, dtype=7) == 0
+    assert ask(1, 8, 50, 50, 1, flags=8) == ask(1, 8, 50, 5000, 1, logits=True) == 0 < ask(1, 8, 50, 50, 1)
