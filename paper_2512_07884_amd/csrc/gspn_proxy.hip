@@ -258,12 +258,11 @@ __global__ void __launch_bounds__(256) proxy_fma_kernel(const T* __restrict__ in
 // (image, 32 x 32 tile of gP); its NW waves take interleaved 16-pixel steps of n and add their accumulators through
 // LDS in wave order; the per-image sums go to the caller's workspace and a small kernel adds the images in order, so the
 // result does not depend on scheduling.  NW = 8 where four waves per tile would leave the chip short of loads in flight.
-// KT = 2: a tile of 32 x 64, whose rows of gout feed two products (operand rows read from the caches: 96 per 2048 elements
-// of gP against 128).  Whole rows: buffer requests, rows past the end request nothing.  ANY: rows start at any element; a
+// Whole rows: buffer requests, rows past the end request nothing.  ANY: rows start at any element; a
 // wave takes four neighbouring steps (whole 128-byte lines of the rows) and the step that crosses the end of the rows takes
 // the last eight pixels and moves them down, zeros behind them.  (Neighbouring steps and global requests on whole rows were
-// measured slower: 1152 -> 288 on four 96x96 images 171 -> 185 us.)
-template <typename T, int NW, int KT, bool ANY>
+// measured slower: 1152 -> 288 on four 96x96 images 171 -> 185 us.)  For short rows and few tiles (launch_gradw_as).
+template <typename T, int NW, bool ANY>
 __global__ void __launch_bounds__(64 * NW) proxy_gradw_mfma_kernel(const T* __restrict__ gout, const T* __restrict__ in,
                                                                float* __restrict__ partial, int K, int M, int N,
                                                                int mtiles, int ktiles) {
@@ -275,41 +274,32 @@ __global__ void __launch_bounds__(64 * NW) proxy_gradw_mfma_kernel(const T* __re
     const int rem = blockIdx.x - b * per_image;
     const int mt = rem / ktiles, kt = rem - mt * ktiles;
     const int jl = lane & 31, nh = lane >> 5;                  // row of the operand this lane feeds; which 8 of the 16 pixels
-    const int m_lane = mt * 32 + jl, k_lane = kt * 32 * KT + jl;
+    const int m_lane = mt * 32 + jl, k_lane = kt * 32 + jl;
     const rsrc_t gb = make_rsrc(gout + ((size_t)b * M + mt * 32) * N);           // the tile's rows of gout / of in
-    const rsrc_t xb = make_rsrc(in + ((size_t)b * K + kt * 32 * KT) * N);
+    const rsrc_t xb = make_rsrc(in + ((size_t)b * K + kt * 32) * N);
     const uint32_t row_off = (uint32_t)((size_t)jl * N * 2);
     // (ANY: rows past the end are read as the last row, their sums are not stored)
     const T* ga = gout + ((size_t)b * M + min(m_lane, M - 1)) * N;
-    const T* ib[KT];
+    const T* ib = in + ((size_t)b * K + min(k_lane, K - 1)) * N;
+    f32x16_t acc;
 #pragma unroll
-    for (int t = 0; t < KT; ++t) ib[t] = in + ((size_t)b * K + min(k_lane + 32 * t, K - 1)) * N;
-    f32x16_t acc[KT];
-#pragma unroll
-    for (int t = 0; t < KT; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     // four 16-pixel steps per trip: their loads are requested together (steps past the end load nothing and multiply zeros)
     constexpr int HOP = ANY ? 16 : 16 * NW;
     for (int n0 = wave * (ANY ? 64 : 16); n0 < N; n0 += 64 * NW) {
-        u32x4 av[4], bv[KT][4];
+        u32x4 av[4], bv[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int n = n0 + HOP * q + 8 * nh;
-            av[q] = u32x4{0, 0, 0, 0};
-#pragma unroll
-            for (int t = 0; t < KT; ++t) bv[t][q] = u32x4{0, 0, 0, 0};
+            av[q] = u32x4{0, 0, 0, 0}; bv[q] = u32x4{0, 0, 0, 0};
             if constexpr (!ANY) {
                 const uint32_t off = row_off + (uint32_t)(n * 2);
                 if (m_lane < M && n < N) av[q] = __builtin_amdgcn_raw_buffer_load_b128(gb, off, 0, 0);
-#pragma unroll
-                for (int t = 0; t < KT; ++t)
-                    if (k_lane + 32 * t < K && n < N) bv[t][q] = __builtin_amdgcn_raw_buffer_load_b128(xb, off + (uint32_t)(64 * t) * (uint32_t)N, 0, 0);
+                if (k_lane < K && n < N) bv[q] = __builtin_amdgcn_raw_buffer_load_b128(xb, off, 0, 0);
             } else if (n < N) {
                 const int nl = min(n, N - 8);
                 ld_row<T, 16, true>(ga + nl, (uint32_t*)&av[q]);
-#pragma unroll
-                for (int t = 0; t < KT; ++t) ld_row<T, 16, true>(ib[t] + nl, (uint32_t*)&bv[t][q]);
+                ld_row<T, 16, true>(ib + nl, (uint32_t*)&bv[q]);
             }
         }
         if (ANY && n0 + 64 > N) {                              // the end of the rows (a uniform branch)
@@ -318,30 +308,104 @@ __global__ void __launch_bounds__(64 * NW) proxy_gradw_mfma_kernel(const T* __re
                 const int n = n0 + 16 * q + 8 * nh;
                 const int sh = n < N ? max(n - (N - 8), 0) : 0;
                 av[q] = rg_realign<T>(av[q], sh);
-#pragma unroll
-                for (int t = 0; t < KT; ++t) bv[t][q] = rg_realign<T>(bv[t][q], sh);
+                bv[q] = rg_realign<T>(bv[q], sh);
             }
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int t = 0; t < KT; ++t) acc[t] = mfma_k16<T>(av[q], bv[t][q], acc[t]);
+        for (int q = 0; q < 4; ++q) acc = mfma_k16<T>(av[q], bv[q], acc);
     }
 #pragma unroll
-    for (int t = 0; t < KT; ++t) {
-        if (t > 0) __syncthreads();
+    for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r];
+    __syncthreads();
+    // accumulator register r of a lane: row 8*(r/4) + 4*(lane/32) + r%4 of the tile (m), column lane%32 (k)
+    for (int idx = threadIdx.x; idx < 16 * 64; idx += 64 * NW) {
+        const int r = idx >> 6, l = idx & 63;
+        float v = red[0][r][l];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[t][r];
-        __syncthreads();
-        // accumulator register r of a lane: row 8*(r/4) + 4*(lane/32) + r%4 of the tile (m), column lane%32 (k)
-        for (int idx = threadIdx.x; idx < 16 * 64; idx += 64 * NW) {
-            const int r = idx >> 6, l = idx & 63;
-            float v = red[0][r][l];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) v += red[w][r][l];
-            const int m = mt * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3), k = kt * 32 * KT + 32 * t + (l & 31);
-            if (m < M && k < K) partial[((size_t)b * M + m) * K + k] = v;
+        for (int w = 1; w < NW; ++w) v += red[w][r][l];
+        const int m = mt * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3), k = kt * 32 + (l & 31);
+        if (m < M && k < K) partial[((size_t)b * M + m) * K + k] = v;
+    }
+}
+
+// The same with the rows through LDS.  A matrix-core operand is 16 bytes of each of 32 rows: asked for as it is multiplied, a request
+// touches 32 lines for a quarter of each.  Here a request is eight rows of whole 128-byte lines; 128 pixels of the tile's rows make a
+// stage, the stages after it are on their way in registers, and each of the eight waves multiplies every eighth step of 16 pixels, in
+// the order above (the same sums, bit for bit on whole rows).  1152 x 144 on two 64x64 images 30 -> 18 us, on two 128x128 104 -> 53.  Every tile of the longer side is read by as many workgroups as the
+// shorter side has tiles, and each XCD has an L2 of its own: an XCD takes neighbouring tiles of the longer side with all of the
+// shorter one's.
+template <typename T, bool ANY>
+__global__ void __launch_bounds__(512) proxy_gradw_lds_kernel(const T* __restrict__ gout, const T* __restrict__ in,
+                                                              float* __restrict__ partial, int K, int M, int N,
+                                                              int mtiles, int ktiles) {
+    constexpr int ROWS = 64, PITCH = 256 + 16, AHEAD = 3;
+    __shared__ __attribute__((aligned(16))) char stage[2 * ROWS * PITCH];                // (the sums of the waves pass through it at the end)
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int per_image = mtiles * ktiles, item = (int)xcd_contiguous_item(blockIdx.x, gridDim.x);
+    const int b = item / per_image, rem = item - b * per_image;
+    const int mt = mtiles <= ktiles ? rem % mtiles : rem / ktiles, kt = mtiles <= ktiles ? rem / mtiles : rem % ktiles;
+    // this thread's pieces: row threadIdx / 16 of every 32, pixels 8 * (threadIdx % 16) of the stage (rows past the end are read as the
+    // last row, their sums are not stored)
+    const int r0 = threadIdx.x >> 4, c0 = (threadIdx.x & 15) * 8;
+    const T* const gr = gout + ((size_t)b * M + min(mt * 32 + r0, M - 1)) * N;
+    const T* const xr = in + ((size_t)b * K + min(kt * 32 + r0, K - 1)) * N;
+    struct Piece { u32x4 g, x; };
+    const int nstages = (N + 127) / 128;
+    auto fetch = [&](int s, Piece& p) {
+        const int n = min(s, nstages - 1) * 128 + c0, nl = min(n, N - 8);        // (beyond the rows' end: their last eight pixels)
+        ld_row<T, 16, ANY>(gr + nl, (uint32_t*)&p.g);
+        ld_row<T, 16, ANY>(xr + nl, (uint32_t*)&p.x);
+    };
+    char* const place = stage + r0 * PITCH + c0 * 2;
+    auto put = [&](int s, Piece& p) {
+        const int n = s * 128 + c0;
+        if (s == nstages - 1) {                                                  // (uniform) what lies beyond the rows counts as 0
+            const int sh = min(max(n - (N - 8), 0), 8);
+            if constexpr (ANY) { p.g = rg_realign<T>(p.g, sh); p.x = rg_realign<T>(p.x, sh); }
+            if (sh >= 8) p.g = p.x = u32x4{0, 0, 0, 0};
         }
+        *(u32x4*)(place + (s & 1) * ROWS * PITCH) = p.g;
+        *(u32x4*)(place + ((s & 1) * ROWS + 32) * PITCH) = p.x;
+    };
+    f32x16_t acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    const char* const from = stage + (lane & 31) * PITCH + wave * 32 + (lane >> 5) * 16;
+    auto multiply = [&](int s) {
+        const char* f = from + (s & 1) * ROWS * PITCH;
+        acc = mfma_k16<T>(*(const u32x4*)f, *(const u32x4*)(f + 32 * PITCH), acc);
+    };
+    Piece p[AHEAD];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) fetch(i, p[i]);
+    put(0, p[0]);
+    fetch(AHEAD, p[0]);
+    lds_barrier();
+    for (int s0 = 0; s0 < nstages; s0 += AHEAD) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            const int s = s0 + i;
+            if (s < nstages) {
+                if (s + 1 < nstages) put(s + 1, p[(i + 1) % AHEAD]);
+                fetch(s + 1 + AHEAD, p[(i + 1) % AHEAD]);
+                multiply(s);
+                lds_barrier();
+            }
+        }
+    }
+    float (*const red)[16][64] = (float (*)[16][64])stage;
+    static_assert(sizeof(float) * 8 * 16 * 64 <= sizeof(stage), "");
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r];
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < 16 * 64; idx += 512) {
+        const int r = idx >> 6, l = idx & 63;
+        float v = red[0][r][l];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) v += red[w][r][l];
+        const int m = mt * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3), k = kt * 32 + (l & 31);
+        if (m < M && k < K) partial[((size_t)b * M + m) * K + k] = v;
     }
 }
 
@@ -535,7 +599,7 @@ template <typename T>
 static hipError_t launch_gradw_as(const void* gout, const void* in, float* partial, int B, int K, int M, int N, hipStream_t s) {
     const bool mfma = sizeof(T) == 2 && N >= 8;
     const int mtiles = mfma ? (M + 31) / 32 : (M + 7) / 8;
-    int ktiles = (K + 31) / 32;
+    const int ktiles = (K + 31) / 32;
     const long tiles = (long)B * mtiles * ktiles;
     if constexpr (sizeof(T) == 2) {
         // 16 x 16 tiles where 32 x 32 ones are fewer than a quarter of the CUs and the rows are long (two images, 32 x 32 -> 16 x
@@ -548,24 +612,29 @@ static hipError_t launch_gradw_as(const void* gout, const void* in, float* parti
             return hipGetLastError();
         }
     }
-    // 32 x 64 tiles where rows are long, both sides have two tiles to share and the workgroups come out even: all of them at once
-    // instead of a second, partly empty, turn of single tiles, or enough of them (single -> double: 1152 x 144 on two 64x64
-    // images, 360 tiles, 34.5 -> 30.4 us; 96 x 384 on sixteen, 576 tiles, 61 -> 51; 288 x 1152 on four, 1296 tiles, 107 -> 77;
-    // but 144 x 768 on four, 480 tiles in 288 pairs, 37 -> 51; one row tile, 1152 x 8 on sixteen 56x56, 31 -> 35; short rows,
-    // 96 x 768 on 32 images 16x16, 16.2 -> 18.9)
-    const long pairs = (long)B * mtiles * ((ktiles + 1) / 2);
-    const bool pair = mfma && N >= 2048 && mtiles > 1 && ktiles > 1 && tiles > 256 && (pairs <= 256 || tiles >= 576);
-    if (pair) ktiles = (K + 63) / 64;
+    if constexpr (sizeof(T) == 2) {
+        // The rows through LDS where they are long or tiles enough to fill the chip; 4900 random products, share of the time of the
+        // kernel below: 2048 pixels and more 0.6 in the mean, 1024 to 2047 from 64 tiles on 0.8, 512 to 1023 from 256 tiles on 0.83.
+        // Shorter rows are a stage or two each (up to 511 pixels 1.03), few tiles wait for their stages (1024 pixels, 16 tiles 1.03).
+        // With a single tile on one side there is less to share: rows at any element from 1024 pixels on 0.77, whole ones from 4096 pixels
+        // and 256 tiles on 0.72, below that 0.97 (96 x 8 on 64 images 56x56 15.4 -> 16.7).  (A launch counts its threads in 32 bits.)
+        const bool shared = mtiles > 1 && ktiles > 1;
+        if (mfma && tiles <= 0x7fffff && (shared ? (N >= 2048 && tiles >= 16) || (N >= 1024 && tiles >= 64) || (N >= 512 && tiles >= 256)
+                                                        : N % 8 ? N >= 1024 : N >= 4096 && tiles >= 256)) {
+            void (*k)(const T*, const T*, float*, int, int, int, int, int) = N % 8 ? proxy_gradw_lds_kernel<T, true> : proxy_gradw_lds_kernel<T, false>;
+            hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(512), 0, s, (const T*)gout, (const T*)in, partial, K, M, N, mtiles, ktiles);
+            return hipGetLastError();
+        }
+    }
     const long blocks = (long)B * mtiles * ktiles;
     if (blocks > 0x7fffffffl) return hipErrorInvalidValue;
-    const bool wide = pair || blocks * 4 < 2048;     // eight waves per tile while four would leave a compute unit under eight
+    const bool wide = blocks * 4 < 2048;     // eight waves per tile while four would leave a compute unit under eight
     if constexpr (sizeof(T) == 2) {
         if (mfma) {
             const bool any = N % 8 != 0 || (size_t)N * 2 * 64 >= (1ull << 31);         // (whole rows: 32-bit offsets within a tile's rows)
             void (*k)(const T*, const T*, float*, int, int, int, int, int) =
-                pair ? (any ? proxy_gradw_mfma_kernel<T, 8, 2, true> : proxy_gradw_mfma_kernel<T, 8, 2, false>)
-              : wide ? (any ? proxy_gradw_mfma_kernel<T, 8, 1, true> : proxy_gradw_mfma_kernel<T, 8, 1, false>)
-                     : (any ? proxy_gradw_mfma_kernel<T, 4, 1, true> : proxy_gradw_mfma_kernel<T, 4, 1, false>);
+                wide ? (any ? proxy_gradw_mfma_kernel<T, 8, true> : proxy_gradw_mfma_kernel<T, 8, false>)
+                     : (any ? proxy_gradw_mfma_kernel<T, 4, true> : proxy_gradw_mfma_kernel<T, 4, false>);
             hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(wide ? 512 : 256), 0, s, (const T*)gout, (const T*)in, partial, K, M, N, mtiles, ktiles);
             return hipGetLastError();
         }

@@ -56,6 +56,17 @@ def test_weight_gradient_at_the_lines_of_the_dispatch(shape, dtype):
     test_projection_and_gradients(shape, dtype)
 
 
+# ... the rows through LDS: from 2048 pixels on, from 1024 with 64 tiles, from 512 with 256, a single tile on one side from 4096 (1024
+# where rows start anywhere); either side of each, one piece, one pixel and all but one beyond a stage of 128
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", [(1, 72, 40, 8, 256), (1, 72, 40, 1, 2047), (1, 72, 40, 1, 2049), (1, 104, 72, 23, 93), (1, 264, 232, 8, 128), (1, 264, 200, 8, 128),
+                                   (1, 232, 264, 3, 343), (2, 488, 264, 8, 64), (2, 488, 264, 8, 63), (2, 488, 264, 3, 171), (2, 264, 488, 8, 71),
+                                   (1, 96, 24, 64, 64), (1, 24, 96, 9, 113), (1, 96, 24, 31, 33), (2, 96, 24, 9, 127)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_weight_gradient_through_lds(shape, dtype):
+    test_projection_and_gradients(shape, dtype)
+
+
 @pytest.mark.parametrize("K,H,W", [(64, 16, 24), (1152, 16, 24), (64, 13, 7), (72, 11, 13), (1152, 5, 29)])
 def test_selection_matrix_copies(K, H, W):
     rng = np.random.default_rng(31)
