@@ -163,6 +163,8 @@ int gspn_scan_bwd_logits(const void* gy, const void* x, const void* z, const voi
  * the four directions in fp32 it runs every direction of every plane as a work item of its own and merges them in a second launch:
  * 64 planes of 256x256 in bf16 123 -> 67 us.  gspn_fwd_workspace_bytes says how many bytes such a call asks for (at most 1 GiB), 0 where it
  * has no use for them (many planes, some directions only, fp32 with h_save, which holds the states itself, invalid arguments).
+ * On maps the "stream" kernels take in two launches, up to 128 planes, it holds the states between the two halves of a scan (two lines of
+ * fp32 per plane).
  * The workspace is device memory, 16-byte aligned, overwritten by the call and free again when its work on `stream` is done; calls
  * that may overlap need one each.  workspace == NULL is the call without one, with the same result up to the rounding of the
  * storage type; fewer bytes than asked for is GSPN_ERR_SHAPE.  w holds normalised weights (logits == 0) or logits (1);

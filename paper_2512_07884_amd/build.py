@@ -49,6 +49,9 @@ SPILL_ALLOWED = {
     "stream_big_horizontal_kernelItLi32ELb0ELb1": 7, "stream_big_horizontal_kernelItLi32ELb1ELb1": 5,
     "stream_big_horizontal_kernelIfLi16ELb1ELb1": 5,
     "stream_big_horizontal_kernelINS_5f16_tELi32ELb0ELb1": 5, "stream_big_horizontal_kernelINS_5f16_tELi32ELb1ELb1": 1,
+    # ... and a direction of it per workgroup, half a scan per launch
+    "stream_big_horizontal_half_kernelItLi32ELb1ELb0": 10, "stream_big_horizontal_half_kernelItLi32ELb1ELb1": 6,
+    "stream_big_horizontal_half_kernelINS_5f16_tELi32ELb1ELb0": 8, "stream_big_horizontal_half_kernelINS_5f16_tELi32ELb1ELb1": 2,
     # ... with logits normalised on the way in (a softmax per position beside the 128 registers): up to 111 values in
     # scratch memory in the forward call with h_save, 25 in the reverse sweep; these calls ran the generic kernel before
     # (scale1024 with kchunk 128: 46.5 ms there, 4.1 ms on these kernels; with logits 4.3 ms); parity-tested on maps of

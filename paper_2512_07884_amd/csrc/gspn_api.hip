@@ -48,10 +48,7 @@ static int scan_fwd_any(const void* x, const void* w, const void* lam, const voi
     p.mask = dir_mask; p.shared = (flags & GSPN_FLAG_SHARED_PARAMS) ? 1 : 0;
     p.kchunk = effective_kchunk(kchunk, H, W);
     p.logits = logits;
-    if (workspace && workspace_bytes < apart_workspace_bytes(p, dtype)) {
-        if (apart_fwd(p, dtype)) return GSPN_ERR_SHAPE;
-        workspace = nullptr;
-    }
+    if (workspace && workspace_bytes < fwd_workspace_bytes(p, dtype)) return GSPN_ERR_SHAPE;
     hipError_t e = launch_fwd(p, dtype, workspace, (hipStream_t)stream);
     return e == hipSuccess ? GSPN_OK : GSPN_ERR_HIP;
 }
@@ -137,7 +134,7 @@ unsigned long long gspn_fwd_workspace_bytes(int B, int C, int H, int W, int G, i
     p.kchunk = effective_kchunk(kchunk, H, W);
     p.logits = logits;
     p.hs = has_h_save ? (void*)16 : nullptr;
-    return apart_fwd(p, dtype) ? apart_workspace_bytes(p, dtype) : 0;
+    return fwd_workspace_bytes(p, dtype);
 }
 
 int gspn_scan_fwd(const void* x, const void* w, const void* lam, const void* u,

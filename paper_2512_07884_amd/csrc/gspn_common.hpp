@@ -222,6 +222,10 @@ hipError_t launch_fwd_plane(const FwdParams& p, int dtype, hipStream_t s);
 bool fwd_plane_applicable(const FwdParams& p, int dtype);
 hipError_t launch_fwd_stream(const FwdParams& p, int dtype, hipStream_t s);
 bool fwd_stream_applicable(const FwdParams& p, int dtype);
+bool stream_halves_applicable(const FwdParams& p, int dtype);      // ... large maps with a direction per workgroup, given a workspace
+size_t stream_halves_workspace_bytes(const FwdParams& p);
+hipError_t launch_fwd_stream_halves(const FwdParams& p, int dtype, void* carry, hipStream_t s);
+size_t fwd_workspace_bytes(const FwdParams& p, int dtype);         // gspn_dispatch.hip: bytes a forward call asks for
 hipError_t launch_fwd_pair(const FwdParams& p, int dtype, hipStream_t s);
 bool fwd_pair_applicable(const FwdParams& p, int dtype);
 // GSPN-local with one workgroup per (plane, stretch): for calls with few planes (gspn_fwd_chunk.hip)

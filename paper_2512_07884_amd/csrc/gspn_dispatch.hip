@@ -182,7 +182,8 @@ static BwdPlan bwd_kernel(const BwdParams& p, int dtype) {
 // beyond, where every CU has a plane of its own, what the states cost across the memory system counts (160 planes 0.87, 256 1.0, 512
 // 1.1 in 16-bit forward calls, 0.9 with a softmax per weight or where h_save holds the states anyway; the backward call always has
 // them: 256 planes 0.88, 384 0.9, 512 0.97).  Of the kernels in their place: two-channel, 128 planes 128x128 44 -> 28 us, 320 planes 1.6 of its
-// time; stream, 64 planes 256x256 bf16 123 -> 67, 96 planes 0.75, 192 1.4, lines of 1024 0.93 at 64; per-stretch, up to its 256 planes 0.75
+// time; stream, 64 planes 256x256 bf16 123 -> 67, 96 planes 0.75, 192 1.4, lines beyond 512 against the
+// stream kernels in halves: 48 planes 576x256 fp32 0.73, 96 1.13; bf16 64 planes 640x512 0.86, 32 planes 1024x512 0.92, 64 1.29; per-stretch, up to its 256 planes 0.75
 // (backward in 16 bits, which rounds e there and not here: 32 planes 0.85, 64 0.93).  What ran line by line for want of an LDS tile,
 // 0.04 to 0.12 of its time at any number of planes.
 constexpr size_t APART_WORKSPACE = (size_t)1 << 30;             // bytes: no call asks for more
@@ -195,7 +196,7 @@ bool apart_fwd(const FwdParams& p, int dtype) {
     switch (fwd_kernel(p, dtype)) {
         case FWD_PAIR: most = 144; break;
         case FWD_CHUNK: most = 256; break;
-        case FWD_STREAM: most = f32 ? 128 : longest > 512 ? 64 : 96; break;
+        case FWD_STREAM: most = f32 ? (longest > 512 ? 64 : 128) : longest > 768 ? 32 : longest > 512 ? 64 : 96; break;
         case FWD_GENERIC: most = HW >= 4096 ? 1100 : 128; break;
         default: most = p.kchunk > 0 ? 128 : HW < 8000 && (f32 ? p.hs != nullptr : p.logits != 0) ? 384 : HW < 4096 ? 192 : 144;
     }
@@ -223,8 +224,20 @@ bool apart_bwd(const BwdParams& p, int dtype) {
     return planes <= most && apart_bwd_applicable(p, dtype);
 }
 
+// Large maps on the stream kernels, up to 128 planes (256 workgroups, one per compute unit): a direction per workgroup, half a scan per
+// launch.  Time of what one workgroup per plane takes: 1024x1024 fp32, 128 planes 0.80, 64 planes 0.61; 128 planes 1024x512 bf16 0.74 (with
+// h_save 0.89), 640x1024 fp16 0.69 (0.74), 960x512 fp32 0.74 (0.76).
+static bool halves_fwd(const FwdParams& p, int dtype) {
+    return !knobs().any && (size_t)p.B * p.C <= 128 && stream_halves_applicable(p, dtype) && fwd_kernel(p, dtype) == FWD_STREAM;
+}
+size_t fwd_workspace_bytes(const FwdParams& p, int dtype) {
+    if (apart_fwd(p, dtype)) return apart_workspace_bytes(p, dtype);
+    return halves_fwd(p, dtype) ? stream_halves_workspace_bytes(p) : 0;
+}
+
 hipError_t launch_fwd(const FwdParams& p, int dtype, void* workspace, hipStream_t s) {
     if ((workspace || apart_workspace_bytes(p, dtype) == 0) && apart_fwd(p, dtype)) return launch_fwd_apart(p, dtype, workspace, s);
+    if (workspace && halves_fwd(p, dtype)) return launch_fwd_stream_halves(p, dtype, workspace, s);
     switch (fwd_kernel(p, dtype)) {
         case FWD_TILE: return launch_fwd_tile(p, dtype, s);
         case FWD_STREAM: return launch_fwd_stream(p, dtype, s);
@@ -302,7 +315,8 @@ extern "C" const char* gspn_call_kernel(int B, int C, int H, int W, int G, int k
 }
 
 // For the tests, bench.py and smoke(), not part of the ABI: 1 where the directions of such a call run in workgroups of their own (a
-// forward call: given the workspace it asks for), 2 where they do without a workspace, else 0.
+// forward call: given the workspace it asks for), 2 where they do without a workspace, 3 where the stream kernels walk them in halves, given
+// one, else 0.
 extern "C" int gspn_call_apart(int B, int C, int H, int W, int G, int kchunk, int logits, unsigned mask, int dtype, int pass) {
     using namespace gspn;
     if (kchunk >= (H > W ? H : W)) kchunk = 0;
@@ -315,7 +329,7 @@ extern "C" int gspn_call_apart(int B, int C, int H, int W, int G, int kchunk, in
     FwdParams p = {};
     p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
     p.hs = pass ? (void*)16 : nullptr;
-    return !apart_fwd(p, dtype) ? 0 : apart_workspace_bytes(p, dtype) ? 1 : 2;
+    return !apart_fwd(p, dtype) ? (halves_fwd(p, dtype) ? 3 : 0) : apart_workspace_bytes(p, dtype) ? 1 : 2;
 }
 
 // For the tests, not part of the ABI: the launch shape of the any-size kernel where a call runs it (see ragged_shape), else 0.

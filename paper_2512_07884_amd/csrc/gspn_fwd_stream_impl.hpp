@@ -221,6 +221,7 @@ struct HStream {
     float wp0, wp1, wp2;   // BWD: taps of the column swept before
     StretchWalkBack bwalk; // BWD, GSPN-local
     int nchunks;
+    int c_first;           // the chunk the scan begins in: 0, or none where it goes on from a state
     float* mb_out;
     const float* mb_up;
     const float* mb_dn;
@@ -251,6 +252,7 @@ struct HStream {
         hb = make_rsrc(SAVE ? (char*)p.hs + ((size_t)d * planes * HW + plane0) * sizeof(T) : (char*)p.y);
         wp0 = 0.f; wp1 = 0.f; wp2 = 0.f;
         nchunks = W / CS;
+        c_first = 0;
         // mailbox: [part][side: 0 first row, 1 last row][parity]
         mb_out = mailbox + part * 4 + (bot_lane ? 2 : 0);
         mb_up = mailbox + (has_up ? part - 1 : part) * 4 + 2;
@@ -397,7 +399,7 @@ struct HStream {
                 lds_barrier();
                 continue;
             }
-            bool start = (c == 0) && (k == 0);               // scan step 0: its weights are never used
+            bool start = (c == c_first) && (k == 0);         // scan step 0: its weights are never used
             if constexpr (LOCAL) start = walk.start();       // ... nor those of a stretch's first line
             float w0 = elem<T>(b0, e), w1 = elem<T>(b1, e), w2 = elem<T>(b2, e);
             if constexpr (LOGITS) softmax3(w0, w1, w2, img_first, img_last);

@@ -1,5 +1,5 @@
 """Which calls run their directions in workgroups of their own, on either side of each line (host code only): 0 none, 1 given a
-workspace, 2 without one."""
+workspace, 2 without one, 3 stream kernels that walk half a scan per launch, given a workspace."""
 import os
 
 import pytest
@@ -17,7 +17,8 @@ def library():
 CALLS = [
     ((1, 64, 256, 256, 8), "bf16", 0, False, (1, 1, 2)), ((1, 96, 256, 256, 8), "bf16", 0, False, (1, 1, 0)),
     ((1, 104, 256, 256, 8), "bf16", 0, False, (0, 0, 0)), ((1, 128, 256, 256, 8), "f32", 0, False, (1, 2, 2)),
-    ((1, 64, 1024, 512, 8), "bf16", 0, False, (1, 1, 0)), ((1, 128, 1024, 1024, 8), "f32", 0, False, (0, 0, 0)),
+    ((1, 64, 1024, 512, 8), "bf16", 0, False, (3, 3, 0)), ((1, 32, 1024, 512, 8), "bf16", 0, False, (1, 1, 2)), ((1, 128, 1024, 1024, 8), "f32", 0, False, (3, 3, 0)),
+    ((1, 130, 1024, 1024, 13), "f32", 0, False, (0, 0, 0)), ((1, 64, 576, 2048, 8), "f16", 0, False, (3, 3, 0)),
     ((1, 144, 128, 128, 8), "bf16", 0, False, (1, 1, 0)), ((1, 152, 128, 128, 4), "f16", 0, False, (0, 0, 0)),
     ((1, 96, 128, 128, 8), "f16", 0, False, (1, 1, 2)), ((1, 32, 128, 128, 4), "f32", 32, False, (1, 2, 2)),
     ((1, 64, 128, 128, 4), "bf16", 32, False, (1, 1, 0)), ((1, 32, 128, 128, 4), "bf16", 32, False, (1, 1, 2)),
@@ -42,7 +43,8 @@ def test_either_side_of_the_lines(shape, dtype, kchunk, logits, want, monkeypatc
     assert tuple(f(c) for c in ("fwd", "save", "bwd")) == want
     for save, w in ((False, want[0]), (True, want[1])):
         n = binding.gspn_fwd_workspace_bytes(*shape, kchunk or binding.GLOBAL_SCAN, logits, 15, code, 0, save)
-        assert n == (16 * shape[0] * shape[1] * shape[2] * shape[3] if w == 1 else 0)
+        planes = shape[0] * shape[1]
+        assert n == {0: 0, 1: 16 * planes * shape[2] * shape[3], 2: 0, 3: 8 * planes * max(shape[2:4])}[w]
     assert f("fwd", 7) == f("bwd", 12) == 0                                       # all four directions only
     for knob in ("GSPN_NO_APART", "GSPN_FORCE_GENERIC", "GSPN_FWD_NO_PAIR"):
         monkeypatch.setenv(knob, "1")
