@@ -157,7 +157,7 @@ def summarise(cfg, r):
     training = r["training"]
     kchunk = r.get("kchunk", 0)
     args = lambda call: (cfg.B, cfg.C, cfg.H, cfg.W, cfg.G, dt, call, kchunk, bool(r.get("logits")), cfg.dir_mask)
-    kernel = lambda call: "apart" if call_apart(*args(call)) in (1, 2) else call_kernel(*args(call))
+    kernel = lambda call: {1: "apart", 2: "apart", 4: "small"}.get(call_apart(*args(call))) or call_kernel(*args(call))
     fwd_bytes = cfg.fwd_algorithmic_bytes(save_h=training)
     d = {"workload": cfg.name, "B": cfg.B, "C": cfg.C, "H": cfg.H, "W": cfg.W, "G": cfg.G,
          "storage": cfg.dtype, "directions": cfg.n_dirs,
@@ -348,7 +348,7 @@ def unfused_table(steps: int = 3):
             torch.cuda.synchronize()
             times[kind] = (time.perf_counter() - t0) * 1e3 / steps
         rows.append({"shape": name, "B": B, "C": C, "H": H, "W": W, "G": Gr, "storage": dtype,
-                     "fused_kernel": "apart" if call_apart(B, C, H, W, Gr, dt, "fwd") in (1, 2) else call_kernel(B, C, H, W, Gr, dt, "fwd"),
+                     "fused_kernel": {1: "apart", 2: "apart", 4: "small"}.get(call_apart(B, C, H, W, Gr, dt, "fwd")) or call_kernel(B, C, H, W, Gr, dt, "fwd"),
                      "fused_ms": times["fused"], "unfused_ms": times["unfused"],
                      "launches_unfused": 2 * (H + W), "ratio": times["unfused"] / times["fused"]})
         del s, y, ws

@@ -156,7 +156,7 @@ def call_kernel(B, C, H, W, G, dtype, call, kchunk=0, logits=False, dir_mask=DIR
 
 def call_apart(B, C, H, W, G, dtype, call, kchunk=0, logits=False, dir_mask=DIR_ALL) -> int:
     """1 where the directions of such a call run in workgroups of their own (forward: given a workspace), 2 without a workspace, 3 where
-    the stream kernels walk them in halves (given a workspace), else 0."""
+    the stream kernels walk them in halves (given a workspace), 4 where they are waves of one workgroup (small maps), else 0."""
     return load_library().gspn_call_apart(B, C, H, W, G, kchunk, int(logits), ctypes.c_uint(dir_mask), dtype, ("fwd", "save", "bwd").index(call))
 
 

@@ -206,6 +206,9 @@ const char* twopass_kernel_name(const BwdParams& p, int dtype);      // for gspn
 int ragged_fwd_threads(const FwdParams& p, int dtype);        // threads per workgroup, 0: not taken
 int ragged_bwd_threads(const BwdParams& p, int dtype);
 bool ragged_shape(const FwdParams& p, int dtype, bool merge_rounds, int out[7]);
+// few small planes: a wave per direction (gspn_fwd_small.hip)
+bool fwd_small_applicable(const FwdParams& p);
+hipError_t launch_fwd_small(const FwdParams& p, int dtype, hipStream_t s);
 // calls of few planes: a workgroup per direction, the states in fp32 merged by a launch of its own (gspn_apart*.hip)
 bool apart_applicable(const FwdParams& p, int dtype);
 bool apart_bwd_applicable(const BwdParams& p, int dtype);

@@ -20,8 +20,8 @@ enum BwdPlan { BWD_GENERIC = 0, BWD_TILE = 1, BWD_PLANE = 2, BWD_TWOPASS = 3, BW
 // row per lane instead of the one with whole-line requests; GSPN_FWD_NO_CHUNK=1: skip the per-stretch kernels of GSPN-local
 // (forward and the reverse sweep of the two-pass backward); GSPN_STREAM_ONE_CHANNEL=1: the whole-line stream kernel with one
 // channel per workgroup on the maps where two channels of a group normally share a workgroup; GSPN_STREAM_TWO_CHANNELS=1:
-// two channels per workgroup there also in calls with too few planes to fill the chip that way; GSPN_NO_APART=1: no workgroup per
-// direction in calls of few planes (each of the others implies it).
+// two channels per workgroup there also in calls with too few planes to fill the chip that way; GSPN_NO_APART=1: no workgroup (no
+// wave, on small maps) per direction in calls of few planes (each of the others implies it).
 enum : unsigned { K_FORCE_GENERIC = 1, K_FWD_NO_PLANE = 2, K_BWD_NO_PLANE = 4, K_BWD_NO_TWOPASS = 8, K_FWD_NO_PAIR = 16, K_STREAM_NO_STAGED = 32, K_FWD_NO_CHUNK = 64, K_STREAM_ONE_CHANNEL = 128, K_STREAM_TWO_CHANNELS = 256, K_NO_ANY_SIZE = 512, K_NO_APART = 1024, K_VALID = 1u << 31 };
 static std::atomic<unsigned> g_knobs{0};
 static bool env_flag(const char* name) { const char* v = getenv(name); return v && v[0] == '1'; }
@@ -224,6 +224,21 @@ bool apart_bwd(const BwdParams& p, int dtype) {
     return planes <= most && apart_bwd_applicable(p, dtype);
 }
 
+// Small maps, a wave per direction.  Time of what the kernels above take, 14 700 random calls of the three types, with stretches and logits,
+// with h_save and without: lines of up to 8 positions 0.32 in the mean in 16 bits, 0.39 in fp32, the longest 0.77 (timed up to 16 000
+// planes); up to 16 positions 0.42 and 0.48 (beyond these planes calls begin to run longer: 3400 planes of 15x16 fp32 1.2); up to 32 positions, 0.57
+// and 0.60 up to 512 planes and 400 pixels (0.8 to 1.1 in the mean beyond either).  Rows of whole granules serve the any-size kernel's
+// wide requests: 16x16 0.94 in 16 bits, 1.12 in fp32, 26x8 fp32 1.6.
+static bool small_fwd(const FwdParams& p, int dtype) {
+    const size_t planes = (size_t)p.B * p.C;
+    const int longest = p.H > p.W ? p.H : p.W, HW = p.H * p.W;
+    if (knobs().any || !fwd_small_applicable(p)) return false;
+    if (longest <= 8) return planes <= 16000;
+    const bool f32 = dtype == 0, whole = p.W % (f32 ? 4 : 8) == 0;
+    if (longest <= 16 ? planes > (f32 ? 2048 : 4096) : planes > 512 || HW >= 400 || (f32 && whole && HW >= 150)) return false;
+    return !(whole && HW >= 200 && (planes > 1024 || fwd_kernel(p, dtype) == FWD_ANY_SIZE));
+}
+
 // Large maps on the stream kernels, up to 128 planes (256 workgroups, one per compute unit): a direction per workgroup, half a scan per
 // launch.  Time of what one workgroup per plane takes: 1024x1024 fp32, 128 planes 0.80, 64 planes 0.61; 128 planes 1024x512 bf16 0.74 (with
 // h_save 0.89), 640x1024 fp16 0.69 (0.74), 960x512 fp32 0.74 (0.76).
@@ -236,6 +251,7 @@ size_t fwd_workspace_bytes(const FwdParams& p, int dtype) {
 }
 
 hipError_t launch_fwd(const FwdParams& p, int dtype, void* workspace, hipStream_t s) {
+    if (small_fwd(p, dtype)) return launch_fwd_small(p, dtype, s);
     if ((workspace || apart_workspace_bytes(p, dtype) == 0) && apart_fwd(p, dtype)) return launch_fwd_apart(p, dtype, workspace, s);
     if (workspace && halves_fwd(p, dtype)) return launch_fwd_stream_halves(p, dtype, workspace, s);
     switch (fwd_kernel(p, dtype)) {
@@ -316,7 +332,7 @@ extern "C" const char* gspn_call_kernel(int B, int C, int H, int W, int G, int k
 
 // For the tests, bench.py and smoke(), not part of the ABI: 1 where the directions of such a call run in workgroups of their own (a
 // forward call: given the workspace it asks for), 2 where they do without a workspace, 3 where the stream kernels walk them in halves, given
-// one, else 0.
+// one, 4 where they run in waves of one workgroup (small maps), else 0.
 extern "C" int gspn_call_apart(int B, int C, int H, int W, int G, int kchunk, int logits, unsigned mask, int dtype, int pass) {
     using namespace gspn;
     if (kchunk >= (H > W ? H : W)) kchunk = 0;
@@ -329,6 +345,7 @@ extern "C" int gspn_call_apart(int B, int C, int H, int W, int G, int kchunk, in
     FwdParams p = {};
     p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
     p.hs = pass ? (void*)16 : nullptr;
+    if (small_fwd(p, dtype)) return 4;
     return !apart_fwd(p, dtype) ? (halves_fwd(p, dtype) ? 3 : 0) : apart_workspace_bytes(p, dtype) ? 1 : 2;
 }
 

@@ -1,5 +1,6 @@
 """Which calls run their directions in workgroups of their own, on either side of each line (host code only): 0 none, 1 given a
-workspace, 2 without one, 3 stream kernels that walk half a scan per launch, given a workspace."""
+workspace, 2 without one, 3 stream kernels that walk half a scan per launch, given a workspace,
+4 a wave per direction, without one."""
 import os
 
 import pytest
@@ -27,7 +28,12 @@ CALLS = [
     ((1, 384, 50, 83, 12), "bf16", 0, True, (1, 1, 2)), ((1, 392, 50, 83, 49), "f16", 0, True, (0, 0, 0)),
     ((1, 384, 50, 83, 12), "f32", 0, False, (0, 2, 2)), ((1, 392, 50, 83, 49), "f32", 0, False, (0, 0, 0)),
     ((1, 128, 50, 83, 8), "f16", 16, False, (1, 1, 2)), ((1, 136, 50, 83, 17), "f16", 16, False, (0, 0, 0)),
-    ((1, 64, 19, 21, 8), "bf16", 0, False, (0, 0, 0)), ((1, 64, 20, 20, 8), "bf16", 0, False, (1, 1, 2)),
+    ((1, 64, 19, 21, 8), "bf16", 0, False, (4, 4, 0)),
+    # small maps: lines of 8, 16, 32; planes; rows of whole granules
+    ((1, 384, 14, 14, 8), "bf16", 0, False, (4, 4, 0)), ((2, 8000, 8, 8, 8), "f32", 4, True, (4, 4, 0)), ((2, 8001, 8, 7, 1), "f32", 0, False, (0, 0, 0)),
+    ((1, 4096, 14, 14, 8), "f16", 0, False, (4, 4, 0)), ((1, 2056, 14, 14, 8), "f32", 0, False, (0, 0, 0)), ((1, 384, 16, 16, 8), "bf16", 0, False, (0, 0, 0)),
+    ((1, 384, 12, 16, 8), "bf16", 7, False, (4, 4, 0)), ((1, 512, 30, 13, 8), "bf16", 0, True, (4, 4, 0)), ((1, 520, 30, 13, 8), "bf16", 0, True, (0, 0, 0)),
+    ((1, 64, 26, 8, 8), "f32", 0, False, (0, 0, 0)), ((1, 64, 17, 8, 8), "f32", 0, False, (4, 4, 0)), ((1, 64, 33, 4, 8), "f16", 0, False, (0, 0, 0)), ((1, 64, 20, 20, 8), "bf16", 0, False, (1, 1, 2)),
     ((2, 256, 100, 167, 8), "bf16", 0, True, (0, 0, 0)), ((4, 192, 50, 83, 8), "f32", 0, False, (0, 0, 0)),
     # 16-bit planes whose fp32 tile does not fit, which ran line by line
     ((1, 600, 195, 195, 8), "bf16", 0, False, (1, 1, 0)), ((1, 1100, 400, 90, 11), "bf16", 0, False, (1, 1, 0)),
@@ -44,7 +50,7 @@ def test_either_side_of_the_lines(shape, dtype, kchunk, logits, want, monkeypatc
     for save, w in ((False, want[0]), (True, want[1])):
         n = binding.gspn_fwd_workspace_bytes(*shape, kchunk or binding.GLOBAL_SCAN, logits, 15, code, 0, save)
         planes = shape[0] * shape[1]
-        assert n == {0: 0, 1: 16 * planes * shape[2] * shape[3], 2: 0, 3: 8 * planes * max(shape[2:4])}[w]
+        assert n == {0: 0, 4: 0, 1: 16 * planes * shape[2] * shape[3], 2: 0, 3: 8 * planes * max(shape[2:4])}[w]
     assert f("fwd", 7) == f("bwd", 12) == 0                                       # all four directions only
     for knob in ("GSPN_NO_APART", "GSPN_FORCE_GENERIC", "GSPN_FWD_NO_PAIR"):
         monkeypatch.setenv(knob, "1")
