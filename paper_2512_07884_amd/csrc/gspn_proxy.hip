@@ -78,9 +78,10 @@ template <typename T> __device__ __forceinline__ f32x4_t mfma16_k32(const u32x4&
 // the projection w.r.t. its input): a lane then gathers its KS/2 values of P with 2-byte loads a row apart (P is small
 // and stays in cache).
 // SPLIT = 1: a wave owns 32 rows x 256 pixels.  SPLIT = 4: a workgroup owns 32 rows x 128 pixels, its waves every fourth
-// k-step (1152 -> 144 on two 64x64 images 58 -> 18 us).  ANY: rows of `in` / `out` start at any element.  BUF: buffer
-// requests and stores with 32-bit offsets; lanes beyond the row request nothing.
-template <typename T, int KS, bool PT, int SPLIT, bool ANY, bool BUF>
+// k-step (1152 -> 144 on two 64x64 images 58 -> 18 us).  MT = 2 (SPLIT = 4): two row tiles of the same pixels, `in` requested and
+// regrouped once for both, P^T a pair of rows per request (17 -> 14, P^T 18 -> 12; same sums, bit for bit).  ANY: rows of `in` / `out`
+// start at any element.  BUF: buffer requests and stores with 32-bit offsets; lanes beyond the row request nothing.
+template <typename T, int KS, bool PT, int SPLIT, int MT, bool ANY, bool BUF>
 __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ in, const T* __restrict__ P,
                                                          T* __restrict__ out, int B, int K, int M, int N,
                                                          int ntiles, int mtiles) {
@@ -103,20 +104,23 @@ __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ i
     const int n_raw = nt * (32 * PX) + jl * PX;                // first of the lane's pixels
     const bool n_ok = n_raw < N;
     const int n_lane = n_ok ? min(n_raw, N - PX) : 0;          // a row's last lane: its last PX pixels
-    const int m_lane = mt * 32 + jl;                           // row of P this lane feeds as the A operand
-    const bool m_ok = m_lane < M;
+    // row of P this lane feeds as the A operand; MT = 2: and the 32nd after it, or (PT: one request for both) the next
+    constexpr int MY = MT == 2 && PT ? 1 : 32, MJ = MT == 2 && PT ? 2 : 1;
+    const int m_lane = mt * (32 * MT) + MJ * jl;
 
     static_assert(!BUF || (SPLIT == 1 && !ANY), "buffer requests: whole rows, a wave per tile");
     const T* src = in + (size_t)b * K * N + n_lane;
     const rsrc_t inb = make_rsrc(in + (size_t)b * K * N), ob = make_rsrc(out + (size_t)b * M * N);
     const rsrc_t pb = make_rsrc(P);
-    f32x16_t acc[PX];
+    f32x16_t acc[MT][PX];
 #pragma unroll
-    for (int v = 0; v < PX; ++v)
+    for (int y = 0; y < MT; ++y)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[v][r] = 0.f;
+        for (int v = 0; v < PX; ++v)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[y][v][r] = 0.f;
 
-    struct Step { uint32_t q[KL][NB / 4]; uint32_t pa[KL / 2]; };         // the lane's k-rows of `in`; P[m_lane][its k values]
+    struct Step { uint32_t q[KL][NB / 4]; uint32_t pa[MT][KL / 2]; };         // the lane's k-rows of `in`; P[m_lane][its k values]
     auto fetch = [&](int k0, Step& t) {
         const int kr = k0 + KL * kh;
 #pragma unroll
@@ -129,22 +133,45 @@ __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ i
                 ld_row<T, NB, ANY>(src + (size_t)(kr + kk) * N, t.q[kk]);      // (spare lanes: pixel 0)
             }
         }
-#pragma unroll
-        for (int i = 0; i < KL / 2; ++i) t.pa[i] = 0;
-        if (m_ok && PT) {
+        if constexpr (MT == 2 && PT) {                         // (M is even)
 #pragma unroll
             for (int i = 0; i < KL / 2; ++i) {
-                const uint32_t lo = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(pb, (uint32_t)(((size_t)(kr + 2 * i) * M + m_lane) * 2), 0, 0);
-                const uint32_t hi = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(pb, (uint32_t)(((size_t)(kr + 2 * i + 1) * M + m_lane) * 2), 0, 0);
-                t.pa[i] = (lo & 0xffffu) | (hi << 16);
+                uint32_t lo = 0, hi = 0;
+                if (m_lane < M) {
+                    lo = __builtin_amdgcn_raw_buffer_load_b32(pb, (uint32_t)(((size_t)(kr + 2 * i) * M + m_lane) * 2), 0, 0);
+                    hi = __builtin_amdgcn_raw_buffer_load_b32(pb, (uint32_t)(((size_t)(kr + 2 * i + 1) * M + m_lane) * 2), 0, 0);
+                }
+                t.pa[0][i] = lo; t.pa[MT - 1][i] = hi;         // (taken apart where they are multiplied)
             }
-        } else if (m_ok) {
-            const uint32_t po = (uint32_t)(((size_t)m_lane * K + kr) * 2);
-            if constexpr (KS == 8) { const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(pb, po, 0, 0); t.pa[0] = v.x; t.pa[1] = v.y; }
-            else { const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(pb, po, 0, 0); t.pa[0] = v.x; t.pa[1] = v.y; t.pa[2] = v.z; t.pa[3] = v.w; }
+            return;
+        }
+#pragma unroll
+        for (int y = 0; y < MT; ++y) {
+            const int m = m_lane + MY * y;
+#pragma unroll
+            for (int i = 0; i < KL / 2; ++i) t.pa[y][i] = 0;
+            if (m < M && PT) {
+#pragma unroll
+                for (int i = 0; i < KL / 2; ++i) {
+                    const uint32_t lo = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(pb, (uint32_t)(((size_t)(kr + 2 * i) * M + m) * 2), 0, 0);
+                    const uint32_t hi = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(pb, (uint32_t)(((size_t)(kr + 2 * i + 1) * M + m) * 2), 0, 0);
+                    t.pa[y][i] = (lo & 0xffffu) | (hi << 16);
+                }
+            } else if (m < M) {
+                const uint32_t po = (uint32_t)(((size_t)m * K + kr) * 2);
+                if constexpr (KS == 8) { const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(pb, po, 0, 0); t.pa[y][0] = v.x; t.pa[y][1] = v.y; }
+                else { const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(pb, po, 0, 0); t.pa[y][0] = v.x; t.pa[y][1] = v.y; t.pa[y][2] = v.z; t.pa[y][3] = v.w; }
+            }
         }
     };
-    auto multiply = [&](const Step& t) {
+    auto multiply = [&](Step& t) {
+        if constexpr (MT == 2 && PT) {
+#pragma unroll
+            for (int i = 0; i < KL / 2; ++i) {
+                const uint32_t lo = t.pa[0][i], hi = t.pa[MT - 1][i];
+                t.pa[0][i] = __builtin_amdgcn_perm(hi, lo, 0x05040100u); t.pa[MT - 1][i] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+            }
+        }
 #pragma unroll
         for (int v = 0; v < PX; ++v) {
             // pixel v of the lane's, its k values packed in pairs: element v sits in word v/2, half v%2
@@ -152,12 +179,15 @@ __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ i
             uint32_t bb[KL / 2];
 #pragma unroll
             for (int i = 0; i < KL / 2; ++i) bb[i] = __builtin_amdgcn_perm(t.q[2 * i + 1][v >> 1], t.q[2 * i][v >> 1], sel);
-            if constexpr (KS == 8) {
-                const u32x2 av = {t.pa[0], t.pa[1]}, bv = {bb[0], bb[1]};
-                acc[v] = mfma_k8<T>(av, bv, acc[v]);
-            } else {
-                const u32x4 av = {t.pa[0], t.pa[1], t.pa[2], t.pa[3]}, bv = {bb[0], bb[1], bb[2], bb[3]};
-                acc[v] = mfma_k16<T>(av, bv, acc[v]);
+#pragma unroll
+            for (int y = 0; y < MT; ++y) {
+                if constexpr (KS == 8) {
+                    const u32x2 av = {t.pa[y][0], t.pa[y][1]}, bv = {bb[0], bb[1]};
+                    acc[y][v] = mfma_k8<T>(av, bv, acc[y][v]);
+                } else {
+                    const u32x4 av = {t.pa[y][0], t.pa[y][1], t.pa[y][2], t.pa[y][3]}, bv = {bb[0], bb[1], bb[2], bb[3]};
+                    acc[y][v] = mfma_k16<T>(av, bv, acc[y][v]);
+                }
             }
         }
     };
@@ -196,8 +226,8 @@ __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ i
         for (int r = 0; r < 16; ++r) {
             const int m = mt * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
             if (m < M) {
-                const uint32_t o[4] = {pack_word<T>(acc[0][r], acc[1][r]), pack_word<T>(acc[2][r], acc[3][r]),
-                                       pack_word<T>(acc[4][r], acc[5][r]), pack_word<T>(acc[6][r], acc[7][r])};
+                const uint32_t o[4] = {pack_word<T>(acc[0][0][r], acc[0][1][r]), pack_word<T>(acc[0][2][r], acc[0][3][r]),
+                                       pack_word<T>(acc[0][4][r], acc[0][5][r]), pack_word<T>(acc[0][6][r], acc[0][7][r])};
                 if constexpr (BUF) st_b128(ob, (uint32_t)(((size_t)m * N + n_lane) * 2), u32x4{o[0], o[1], o[2], o[3]});
                 else st_row<T, NB, ANY>(dst + (size_t)m * N, o);
             }
@@ -205,26 +235,29 @@ __global__ void __launch_bounds__(256) proxy_mfma_kernel(const T* __restrict__ i
     } else {
         __shared__ float red[SPLIT][16][PX][64];
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
+        for (int y = 0; y < MT; ++y) {
+            if (y) __syncthreads();                            // the row tile before has been read
 #pragma unroll
-            for (int v = 0; v < PX; ++v) red[wave][r][v][lane] = acc[v][r];
-        __syncthreads();
-        if (!n_ok) return;
-        // each wave adds and stores a quarter of the rows
+            for (int r = 0; r < 16; ++r)
 #pragma unroll
-        for (int i = 0; i < 16 / SPLIT; ++i) {
-            const int r = wave * (16 / SPLIT) + i;
-            const int m = mt * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
-            if (m < M) {
-                float t[PX];
+                for (int v = 0; v < PX; ++v) red[wave][r][v][lane] = acc[y][v][r];
+            __syncthreads();
+            // each wave adds and stores a quarter of the rows
 #pragma unroll
-                for (int v = 0; v < PX; ++v) {
-                    t[v] = red[0][r][v][lane];
+            for (int i = 0; i < 16 / SPLIT; ++i) {
+                const int r = wave * (16 / SPLIT) + i;
+                const int m = mt * (32 * MT) + MY * y + MJ * (8 * (r >> 2) + 4 * kh + (r & 3));
+                if (m < M && n_ok) {
+                    float t[PX];
 #pragma unroll
-                    for (int w = 1; w < SPLIT; ++w) t[v] += red[w][r][v][lane];
+                    for (int v = 0; v < PX; ++v) {
+                        t[v] = red[0][r][v][lane];
+#pragma unroll
+                        for (int w = 1; w < SPLIT; ++w) t[v] += red[w][r][v][lane];
+                    }
+                    const uint32_t o[2] = {pack_word<T>(t[0], t[1]), pack_word<T>(t[2], t[3])};
+                    st_row<T, NB, ANY>(dst + (size_t)m * N, o);
                 }
-                const uint32_t o[2] = {pack_word<T>(t[0], t[1]), pack_word<T>(t[2], t[3])};
-                st_row<T, NB, ANY>(dst + (size_t)m * N, o);
             }
         }
     }
@@ -527,22 +560,22 @@ bool proxy_mfma_applicable(int K, int M, int N, int dtype) {
     return dtype != 0 && K % 8 == 0 && N >= 8 && (size_t)M * K * 2 < (1ull << 31);
 }
 
-template <typename T, int KS, bool PT, int SPLIT>
+template <typename T, int KS, bool PT, int SPLIT, int MT = 1>
 static hipError_t launch_project_mfma(const void* in, const void* P, void* out, int B, int K, int M, int N, hipStream_t s) {
     constexpr int tile = SPLIT == 1 ? 256 : 128;
-    const int ntiles = (N + tile - 1) / tile, mtiles = (M + 31) / 32;
+    const int ntiles = (N + tile - 1) / tile, mtiles = (M + 32 * MT - 1) / (32 * MT);
     const long items = (long)B * ntiles * mtiles, blocks = SPLIT == 1 ? (items + 3) / 4 : items;
     if (blocks > 0x7fffffffl) return hipErrorInvalidValue;
     void (*k)(const T*, const T*, T*, int, int, int, int, int, int);
-    if (N % 8 != 0) k = proxy_mfma_kernel<T, KS, PT, SPLIT, true, false>;
-    else k = proxy_mfma_kernel<T, KS, PT, SPLIT, false, false>;
+    if (N % 8 != 0) k = proxy_mfma_kernel<T, KS, PT, SPLIT, MT, true, false>;
+    else k = proxy_mfma_kernel<T, KS, PT, SPLIT, MT, false, false>;
     if constexpr (SPLIT == 1) {
         // Whole rows: buffer requests for P^T (with global ones 18 -> 20 us at 24 -> 1152 channels on two 128x128 images), for
         // steps of 8 (8 -> 1152 there 14.6 -> 15.8) and from four waves per CU on (from memory: 144 -> 192 on 64 images 28x28
         // 21.1 -> 22.3, 288 -> 768 on 64 of 32x32 84 -> 88).  With fewer waves the lanes' own addresses serve better (144 -> 192
         // on eight 64x64 images 17.0 -> 14.8, 288 -> 1152 on two 56x56 24.8 -> 20.6), and they reach images beyond 2^31 bytes.
         const bool fits = (size_t)K * N * 2 < (1ull << 31) && (size_t)M * N * 2 < (1ull << 31);
-        if (N % 8 == 0 && fits && (PT || KS == 8 || items >= 1024)) k = proxy_mfma_kernel<T, KS, PT, 1, false, true>;
+        if (N % 8 == 0 && fits && (PT || KS == 8 || items >= 1024)) k = proxy_mfma_kernel<T, KS, PT, 1, 1, false, true>;
     }
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, s, (const T*)in, (const T*)P, (T*)out, B, K, M, N, ntiles, mtiles);
     return hipGetLastError();
@@ -575,6 +608,14 @@ static hipError_t launch_project_as(const void* in, const void* P, void* out, in
             const long waves = (long)B * ((N + 255) / 256) * ((M + 31) / 32);
             const int steps = K / (K % 16 == 0 ? 16 : 8);
             const bool split = (waves <= 448 && steps >= 16) || (waves <= 768 && steps >= 48);
+            // A workgroup of pairs of row tiles reads `in` once for 64 rows, a compute unit holds one of them (registers) and two of the
+            // others: pairs where they take fewer turns of 256 workgroups.  1152 -> 144 on two 64x64 images (192 for 320) 16.9 -> 13.9 us,
+            // P^T 18.1 -> 12.4; 768 -> 144 on three of 60x60 (261 for 435: two turns either way) 12.9 -> 13.8, 13.7 -> 16.9.  More
+            // than one turn pays for P^T only, whose requests they halve as well: 1152 -> 144 on one 128x128 (384 for 640) 29.3 ->
+            // 21.9, 1152 -> 288 on four 64x64 (640 for 1152) 43.3 -> 31.9; P 24.1 -> 25.5, 36.6 -> 36.4.
+            const long ntiles = (long)B * ((N + 127) / 128), single = ntiles * ((M + 31) / 32), pairs = ntiles * ((M + 63) / 64);
+            const bool paired = split && (PT ? M % 2 == 0 : pairs <= 256) && (pairs + 255) / 256 < (single + 255) / 256;
+            if (paired) return K % 16 == 0 ? launch_project_mfma<T, 16, PT, 4, 2>(in, P, out, B, K, M, N, s) : launch_project_mfma<T, 8, PT, 4, 2>(in, P, out, B, K, M, N, s);
             if (K % 16 == 0) return split ? launch_project_mfma<T, 16, PT, 4>(in, P, out, B, K, M, N, s) : launch_project_mfma<T, 16, PT, 1>(in, P, out, B, K, M, N, s);
             return split ? launch_project_mfma<T, 8, PT, 4>(in, P, out, B, K, M, N, s) : launch_project_mfma<T, 8, PT, 1>(in, P, out, B, K, M, N, s);
         }

@@ -67,6 +67,14 @@ def test_weight_gradient_through_lds(shape, dtype):
     test_projection_and_gradients(shape, dtype)
 
 
+# pairs of row tiles, the last pair with 8 rows: whole rows and rows at any element, k-steps of 16 and 8, the matrix and (outputs and
+# contraction exchanged) its transpose
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", [(1, 256, 136, 8, 832), (1, 264, 136, 60, 111), (1, 136, 256, 60, 111), (1, 136, 264, 8, 832)], ids=lambda s: "x".join(map(str, s)))
+def test_pairs_of_row_tiles(shape, dtype):
+    test_projection_and_gradients(shape, dtype)
+
+
 @pytest.mark.parametrize("K,H,W", [(64, 16, 24), (1152, 16, 24), (64, 13, 7), (72, 11, 13), (1152, 5, 29)])
 def test_selection_matrix_copies(K, H, W):
     rng = np.random.default_rng(31)
