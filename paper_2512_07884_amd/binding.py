@@ -192,10 +192,21 @@ def _ptr(t, name, shape, like):
     return t.data_ptr()
 
 
+_CURRENT = []          # torch's way to the handle of the current device's current stream, found on first use
+
+
+def _current_stream() -> int:
+    # the handle alone: 0.2 us where the stream object takes 3.0 of a small call's 10.8 us of host time
+    if not _CURRENT:
+        import torch
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        _CURRENT.append((lambda: raw(device())) if raw and device else (lambda: torch.cuda.current_stream().cuda_stream))
+    return _CURRENT[0]()
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
+        return ctypes.c_void_p(_current_stream())
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
