@@ -232,17 +232,38 @@ def _fwd_args(x, w, lam, u, y, h_save, G, flags):
 _WORKSPACE_BYTES = {}          # sizes, type and options of a call -> bytes it asks for
 
 
+def _torch_captures(device) -> bool:
+    """Whether memory allocated now, on a stream that is being captured, stays with the graph: torch's allocator then takes it from a
+    pool of the graph's.  It knows captures begun by torch alone; in one begun by the HIP runtime's own calls it hands out ordinary
+    memory, which belongs to another tensor by the time the graph is replayed."""
+    import torch
+    probe = torch.empty(1, dtype=torch.uint8, device=device)
+    try:
+        segments = torch.cuda.memory_snapshot()
+    except RuntimeError:                                  # (an allocator without pools)
+        return False
+    at = probe.data_ptr()
+    return any(s["address"] <= at < s["address"] + s["total_size"] and tuple(s.get("segment_pool_id", (0, 0))) != (0, 0) for s in segments)
+
+
+def _allocate(x, nbytes):
+    import torch
+    if torch.cuda.is_current_stream_capturing() and not _torch_captures(x.device):
+        return None
+    return torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+
+
 def _workspace(x, nbytes, stream):
     """Device memory for one call, from torch's allocator and in the order of the stream the call runs on; None where there is no
-    room (the call then runs without)."""
+    room or where it would not stay the call's own (the call then runs without)."""
     import torch
     try:
         if stream is None:
-            return torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+            return _allocate(x, nbytes)
         if not hasattr(stream, "cuda_stream"):
             stream = torch.cuda.ExternalStream(int(stream), device=x.device) if int(stream) else torch.cuda.default_stream(x.device)
         with torch.cuda.stream(stream):
-            return torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+            return _allocate(x, nbytes)
     except torch.cuda.OutOfMemoryError:
         return None
 
