@@ -257,6 +257,14 @@ def _workspace(x, nbytes, stream):
     """Device memory for one call, from torch's allocator and in the order of the stream the call runs on; None where there is no
     room or where it would not stay the call's own (the call then runs without)."""
     import torch
+    # The allocator gives a block out again in the order of a stream of x's device: the call has to run on that very stream.
+    device = x.get_device()
+    if stream is None or not hasattr(stream, "cuda_stream"):
+        # no stream, and the handle of a device's default stream, mean those of the current device
+        if (stream is None or not int(stream)) and device != torch.cuda.current_device():
+            return None
+    elif stream.device_index != device:
+        return None
     try:
         if stream is None:
             return _allocate(x, nbytes)

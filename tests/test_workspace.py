@@ -63,3 +63,15 @@ def test_captured_call_takes_memory_from_the_graphs_own_pool_or_none(pool, taken
     r = Recorder(monkeypatch, capturing=True, pool=pool)
     want = (r.ADDRESS, r.WANTED) if taken else (None, 0)
     assert r.scan(stream=stream)[:2] == want
+
+
+@pytest.mark.parametrize("device,stream,taken", [
+    (0, None, True), (1, None, False), (0, 0, True), (1, 0, False), (1, 9, True),
+    (0, types.SimpleNamespace(cuda_stream=9, device="cuda:0", device_index=0), True),
+    (1, types.SimpleNamespace(cuda_stream=9, device="cuda:0", device_index=0), False)], ids=str)
+def test_memory_is_given_back_in_the_order_of_the_stream_the_call_runs_on(device, stream, taken, monkeypatch):
+    """Tensors of device `device` while device 0 is current, on no stream of theirs: the allocator would hand the block on, in the order of
+    a stream the call does not run on, while the kernel still writes it."""
+    r = Recorder(monkeypatch, device=device, current_device=0)
+    assert r.scan(stream=stream)[:2] == ((r.ADDRESS, r.WANTED) if taken else (None, 0))
+    assert bool(r.allocated) == taken
