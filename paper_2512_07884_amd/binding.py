@@ -259,17 +259,18 @@ def _workspace(x, nbytes, stream):
     import torch
     # The allocator gives a block out again in the order of a stream of x's device: the call has to run on that very stream.
     device = x.get_device()
-    if stream is None or not hasattr(stream, "cuda_stream"):
+    handle = None if stream is None else stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+    if not handle:
         # no stream, and the handle of a device's default stream, mean those of the current device
-        if (stream is None or not int(stream)) and device != torch.cuda.current_device():
+        if device != torch.cuda.current_device():
             return None
-    elif stream.device_index != device:
+    elif getattr(stream, "device_index", device) != device:
         return None
     try:
         if stream is None:
             return _allocate(x, nbytes)
-        if not hasattr(stream, "cuda_stream"):
-            stream = torch.cuda.ExternalStream(int(stream), device=x.device) if int(stream) else torch.cuda.default_stream(x.device)
+        if not isinstance(stream, torch.cuda.Stream):
+            stream = torch.cuda.ExternalStream(handle, device=x.device) if handle else torch.cuda.default_stream(x.device)
         with torch.cuda.stream(stream):
             return _allocate(x, nbytes)
     except torch.cuda.OutOfMemoryError:

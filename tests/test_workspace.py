@@ -75,3 +75,10 @@ def test_memory_is_given_back_in_the_order_of_the_stream_the_call_runs_on(device
     r = Recorder(monkeypatch, device=device, current_device=0)
     assert r.scan(stream=stream)[:2] == ((r.ADDRESS, r.WANTED) if taken else (None, 0))
     assert bool(r.allocated) == taken
+
+
+@pytest.mark.parametrize("stream", [types.SimpleNamespace(cuda_stream=9), types.SimpleNamespace(cuda_stream=0)], ids=str)
+def test_any_object_with_a_stream_handle_names_a_stream(stream, monkeypatch):
+    r = Recorder(monkeypatch)
+    assert r.scan(stream=stream) == (r.ADDRESS, r.WANTED, stream.cuda_stream or None)
+    assert r.allocated == [(r.WANTED, "cuda:0", stream.cuda_stream)]
