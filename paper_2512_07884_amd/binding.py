@@ -264,6 +264,9 @@ def _workspace(x, nbytes, stream):
         # no stream, and the handle of a device's default stream, mean those of the current device
         if device != torch.cuda.current_device():
             return None
+    elif handle in (1, 2):
+        # the runtime's names for the default stream and for each thread's own
+        return None
     elif getattr(stream, "device_index", device) != device:
         return None
     try:

@@ -82,3 +82,10 @@ def test_any_object_with_a_stream_handle_names_a_stream(stream, monkeypatch):
     r = Recorder(monkeypatch)
     assert r.scan(stream=stream) == (r.ADDRESS, r.WANTED, stream.cuda_stream or None)
     assert r.allocated == [(r.WANTED, "cuda:0", stream.cuda_stream)]
+
+
+@pytest.mark.parametrize("handle", [1, 2])
+def test_the_runtimes_stream_names_take_no_memory(handle, monkeypatch):
+    """One names another stream in each thread: a block given back by one thread could go to the next while the first still writes it."""
+    r = Recorder(monkeypatch)
+    assert r.scan(stream=handle) == (None, 0, handle)
