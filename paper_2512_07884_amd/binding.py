@@ -283,12 +283,18 @@ def _workspace(x, nbytes, stream):
 def _scan_fwd(x, w, lam, u, y, h_save, kchunk, logits, G, dir_mask, flags, stream):
     ptrs, dims = _fwd_args(x, w, lam, u, y, h_save, G, flags)
     lib, code, kchunk = load_library(), _dtype_code(x), int(kchunk)
-    key = (dims, kchunk, logits, dir_mask, code, flags, h_save is None)
-    nbytes = _WORKSPACE_BYTES.get(key)
+    nbytes = None
+    # (other types of integer may change their value or have no hash: they are asked about anew)
+    keep = type(dir_mask) is int and type(flags) is int and type(dims[4]) is int
+    if keep:
+        key = (dims, kchunk, logits, dir_mask, code, flags, h_save is None)
+        nbytes = _WORKSPACE_BYTES.get(key)
     if nbytes is None:
-        if len(_WORKSPACE_BYTES) >= 4096:
-            _WORKSPACE_BYTES.clear()
-        nbytes = _WORKSPACE_BYTES[key] = lib.gspn_fwd_workspace_bytes(*dims, kchunk, logits, dir_mask, code, flags, int(h_save is not None))
+        nbytes = lib.gspn_fwd_workspace_bytes(*dims, kchunk, logits, dir_mask, code, flags, int(h_save is not None))
+        if keep:
+            if len(_WORKSPACE_BYTES) >= 4096:
+                _WORKSPACE_BYTES.clear()
+            _WORKSPACE_BYTES[key] = nbytes
     ws = _workspace(x, nbytes, stream) if nbytes else None
     _check(lib.gspn_scan_fwd_workspace(*ptrs, None if ws is None else ws.data_ptr(), nbytes if ws is not None else 0, *dims, kchunk, logits,
                                        dir_mask, code, flags, _stream(stream)))

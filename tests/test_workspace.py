@@ -1,8 +1,10 @@
 """The memory the Python forward call takes for a call of few planes: when it may, and from which stream's memory.  Host code only: the
 library and torch's device calls are stand-ins, so that cases which would be unsafe on a device are told by what the library is handed."""
 import contextlib
+import ctypes
 import types
 
+import numpy as np
 import pytest
 
 
@@ -89,3 +91,17 @@ def test_the_runtimes_stream_names_take_no_memory(handle, monkeypatch):
     """One names another stream in each thread: a block given back by one thread could go to the next while the first still writes it."""
     r = Recorder(monkeypatch)
     assert r.scan(stream=handle) == (None, 0, handle)
+
+
+@pytest.mark.parametrize("mask", [ctypes.c_uint(15), np.array(15), np.int64(15)], ids=["c_uint", "array", "int64"])
+def test_integers_of_other_types_are_asked_about_by_their_value(mask, monkeypatch):
+    """What ctypes takes for an unsigned int may have no hash (an array), or be another number the next time (a c_uint)."""
+    r = Recorder(monkeypatch)
+    asked = []
+    ask = lambda *a: asked.append(getattr(a[7], "value", a[7])) or r.WANTED
+    monkeypatch.setattr(r.binding.load_library(), "gspn_fwd_workspace_bytes", ask)
+    r.scan(dir_mask=mask)
+    if isinstance(mask, ctypes.c_uint):
+        mask.value = 3
+    r.scan(dir_mask=mask)
+    assert asked == [15, 3 if isinstance(mask, ctypes.c_uint) else 15]
