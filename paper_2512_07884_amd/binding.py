@@ -1,9 +1,16 @@
-"""ctypes binding of libgspn.so: argument marshalling only.
+"""ctypes binding of libgspn.so: argument marshalling, and the workspace of forward calls of few planes.
 
 Same entry-point names as include/gspn.h.  PyTorch tensors are used purely as
 handles to device memory (``data_ptr()``) and for the current HIP stream; every
 step of the scan runs in the library's kernels.  There is no CPU fallback: a
 missing library raises, and so does any non-zero status from the library.
+
+Forward calls for which ``gspn_fwd_workspace_bytes`` names a size (few planes, at
+most 1 GiB) take that much from torch's allocator for as long as they are enqueued,
+unless there is no room or the memory would not stay theirs (``_workspace``); without
+it they run on other kernels, more slowly, and in 16-bit storage y may be rounded
+elsewhere.  ``gspn_scan_fwd_workspace`` takes memory of the caller's instead and
+allocates nothing.
 """
 from __future__ import annotations
 
@@ -311,20 +318,38 @@ def gspn_scan_fwd(x, w, lam, u, y, h_save=None, *, G: Optional[int] = None, dir_
     x [B,C,H,W]; w [4,B,G,3,H,W]; lam, u [4,B,C,H,W] ([1,...] with
     GSPN_FLAG_SHARED_PARAMS); y [B,C,H,W]; h_save [4,B,C,H,W] or None.
     All device tensors of one dtype (float32 / bfloat16 / float16), contiguous.
+
+    A call of few planes takes up to 1 GiB of workspace from torch's allocator; where there is no room it runs on other kernels,
+    and the bits of a 16-bit y are those of their roundings.  gspn_scan_fwd_workspace leaves neither to chance.
     """
     _scan_fwd(x, w, lam, u, y, h_save, GLOBAL_SCAN, 0, G, dir_mask, flags, stream)
 
 
 def gspn_scan_fwd_local(x, w, lam, u, y, h_save=None, *, kchunk: int, G: Optional[int] = None,
                         dir_mask: int = DIR_ALL, flags: int = 0, stream=None) -> None:
-    """GSPN-local forward (Sec. 3.2): as gspn_scan_fwd, propagation confined to stretches of kchunk lines."""
+    """GSPN-local forward (Sec. 3.2): as gspn_scan_fwd (its workspace too), propagation confined to stretches of kchunk lines."""
     _scan_fwd(x, w, lam, u, y, h_save, kchunk, 0, G, dir_mask, flags, stream)
 
 
 def gspn_scan_fwd_logits(x, z, lam, u, y, h_save=None, *, kchunk: int = GLOBAL_SCAN, G: Optional[int] = None,
                          dir_mask: int = DIR_ALL, flags: int = 0, stream=None) -> None:
-    """As gspn_scan_fwd with the weights given as raw logits z (softmax over the taps that exist, inside the call)."""
+    """As gspn_scan_fwd (its workspace too) with the weights given as raw logits z (softmax over the taps that exist, inside the call)."""
     _scan_fwd(x, z, lam, u, y, h_save, kchunk, 1, G, dir_mask, flags, stream)
+
+
+def gspn_scan_fwd_workspace(x, w, lam, u, y, h_save, workspace, *, kchunk: int = GLOBAL_SCAN, logits: bool = False,
+                            G: Optional[int] = None, dir_mask: int = DIR_ALL, flags: int = 0, stream=None) -> None:
+    """The three forward calls above (kchunk, logits) with a workspace of the caller's: a contiguous device tensor of at least
+    gspn_fwd_workspace_bytes bytes, free again when the call's work on the stream is done, or None, the call without one.  Allocates
+    nothing: for captures, streams and memory that the caller looks after."""
+    ptrs, dims = _fwd_args(x, w, lam, u, y, h_save, G, flags)
+    at, nbytes = None, 0
+    if workspace is not None:
+        if not workspace.is_cuda or workspace.device != x.device or not workspace.is_contiguous():
+            raise ValueError("workspace: must be a contiguous tensor on x's device")
+        at, nbytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
+    _check(load_library().gspn_scan_fwd_workspace(*ptrs, at, nbytes, *dims, int(kchunk), int(logits), dir_mask, _dtype_code(x), flags,
+                                                  _stream(stream)))
 
 
 def _bwd_args(gy, x, w, lam, u, h_save, gx, gw, glam, gu, G, flags):
