@@ -7,31 +7,39 @@ hipError_t launch_apart_f32(const ApartArgs& a, bool reverse, int threads, int n
 hipError_t launch_apart_bf16(const ApartArgs& a, bool reverse, int threads, int nv, size_t lds, hipStream_t s);
 hipError_t launch_apart_f16(const ApartArgs& a, bool reverse, int threads, int nv, size_t lds, hipStream_t s);
 
-// The launch shape for a call, or false where no shape fits.
-static bool apart_plan(const FwdParams& p, int dtype, ApartArgs* out, int* threads, int* nv, size_t* lds) {
-    const int H = p.H, W = p.W, es = dtype == 0 ? 4 : 2, E = 16 / es;
-    if (p.xt || (size_t)H * W < 16 || (size_t)H * W >= (1u << 29)) return false;
+// The ranges of lines of either axis (0 vertical, 1 horizontal), and the work items they make: whole stretches of 32 lines and more,
+// shorter ones only while that makes fewer than 1024 work items; a horizontal scan's begin at whole granules
+static size_t apart_ranges(const FwdParams& p, int E, int range[2], int nrange[2]) {
     const size_t planes = (size_t)p.B * p.C;
-    const bool wide = dtype == 0 || p.logits;
-    ApartArgs a = {};
-    a.p = p;
-    // ranges are whole stretches of 32 lines and more, shorter ones only while that makes fewer than 1024 work items; a horizontal
-    // scan's begin at whole granules
     size_t items = 0;
     for (int stretches = 1;; stretches *= 2) {
         items = 0;
         bool longer = false;
         for (int ax = 0; ax < 2; ++ax) {
-            const int S = ax ? W : H;
+            const int S = ax ? p.W : p.H;
             const long long lines = (long long)p.kchunk * stretches;
             const bool cut = p.kchunk > 0 && lines < S && (ax == 0 || lines % E == 0);
-            a.range[ax] = cut ? (int)lines : S;
-            a.nrange[ax] = cut ? (int)((S + lines - 1) / lines) : 1;
-            items += planes * __builtin_popcount(ax ? p.mask & 12 : p.mask & 3) * a.nrange[ax];
+            range[ax] = cut ? (int)lines : S;
+            nrange[ax] = cut ? (int)((S + lines - 1) / lines) : 1;
+            items += planes * __builtin_popcount(ax ? p.mask & 12 : p.mask & 3) * nrange[ax];
             longer |= cut && lines < 32;
         }
-        if (!longer || items < 1024) break;
+        if (!longer || items < 1024) return items;
     }
+}
+size_t apart_items(const FwdParams& p, int dtype) {
+    int range[2], nrange[2];
+    return apart_ranges(p, dtype == 0 ? 4 : 8, range, nrange);
+}
+
+// The launch shape for a call, or false where no shape fits.
+static bool apart_plan(const FwdParams& p, int dtype, ApartArgs* out, int* threads, int* nv, size_t* lds) {
+    const int H = p.H, W = p.W, es = dtype == 0 ? 4 : 2, E = 16 / es;
+    if (p.xt || (size_t)H * W < 16 || (size_t)H * W >= (1u << 29)) return false;
+    const bool wide = dtype == 0 || p.logits;
+    ApartArgs a = {};
+    a.p = p;
+    const size_t items = apart_ranges(p, E, a.range, a.nrange);
     if (items * 1024 >= (1ull << 32)) return false;              // (a launch counts its threads in 32 bits)
     const int longest = H > W ? H : W, v = longest <= 64 ? 1 : longest <= 128 ? 2 : 4;
     // chunks in LDS, bytes of an image row per request in the horizontal directions, workgroups per CU, lines of a vertical chunk at most
@@ -162,7 +170,10 @@ hipError_t launch_states(const ApartArgs& a, int dtype, bool reverse, int thread
     return (dtype == 0 ? launch_apart_f32 : dtype == 1 ? launch_apart_bf16 : launch_apart_f16)(a, reverse, threads, nv, lds, s);
 }
 
-FwdParams sweep_params(const BwdParams& p) {
+}  // namespace
+
+// the reverse sweep as a forward scan
+FwdParams apart_sweep_params(const BwdParams& p) {
     FwdParams f = {};
     f.x = p.gy; f.w = p.w; f.lam = p.u; f.u = p.lam; f.y = p.gx; f.hs = p.glam;
     f.B = p.B; f.C = p.C; f.H = p.H; f.W = p.W; f.G = p.G; f.cpg = p.cpg;
@@ -170,15 +181,13 @@ FwdParams sweep_params(const BwdParams& p) {
     return f;
 }
 
-}  // namespace
-
 bool apart_applicable(const FwdParams& p, int dtype) {
     ApartArgs a;
     int threads, nv;
     size_t lds;
     return apart_plan(p, dtype, &a, &threads, &nv, &lds);
 }
-bool apart_bwd_applicable(const BwdParams& p, int dtype) { return apart_applicable(sweep_params(p), dtype) && ragged_finish_fits(p, dtype); }
+bool apart_bwd_applicable(const BwdParams& p, int dtype) { return apart_applicable(apart_sweep_params(p), dtype) && ragged_finish_fits(p, dtype); }
 // bytes of workspace a forward call needs: the fp32 states, unless h_save holds them
 size_t apart_workspace_bytes(const FwdParams& p, int dtype) {
     return dtype == 0 && p.hs ? 0 : (size_t)16 * p.B * p.C * p.H * p.W;
@@ -199,7 +208,7 @@ hipError_t launch_bwd_apart(const BwdParams& p, int dtype, hipStream_t s) {
     ApartArgs a = {};
     int threads, nv;
     size_t lds;
-    const FwdParams f = sweep_params(p);
+    const FwdParams f = apart_sweep_params(p);
     if (!apart_plan(f, dtype, &a, &threads, &nv, &lds)) return hipErrorInvalidValue;
     a.hs_lo = dtype == 0 ? nullptr : p.gu;
     hipError_t e = launch_states(a, dtype, true, threads, nv, lds, s);

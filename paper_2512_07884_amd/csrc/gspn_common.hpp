@@ -213,6 +213,8 @@ hipError_t launch_fwd_small(const FwdParams& p, int dtype, hipStream_t s);
 bool apart_applicable(const FwdParams& p, int dtype);
 bool apart_bwd_applicable(const BwdParams& p, int dtype);
 size_t apart_workspace_bytes(const FwdParams& p, int dtype);
+size_t apart_items(const FwdParams& p, int dtype);           // work items of the launch of the states
+FwdParams apart_sweep_params(const BwdParams& p);
 hipError_t launch_fwd_apart(const FwdParams& p, int dtype, void* states, hipStream_t s);
 hipError_t launch_bwd_apart(const BwdParams& p, int dtype, hipStream_t s);
 bool apart_fwd(const FwdParams& p, int dtype);               // gspn_dispatch.hip: the calls that run so

@@ -177,30 +177,99 @@ static BwdPlan bwd_kernel(const BwdParams& p, int dtype) {
 }
 
 // Calls of few planes: a workgroup per direction (gspn_apart*.hip) rather than the kernel above, whose workgroups hold whole planes.
-// Timed on 30 000 random calls (8 to 1100 planes, 20 to 1024 positions a side, the three types, stretches, logits); the line lies
-// where the mean of the ratio passes 0.9 and few calls run longer.  Ratio in the mean by planes: 8 0.4, 32 0.5, 64 0.6, 128 0.75;
-// beyond, where every CU has a plane of its own, what the states cost across the memory system counts (160 planes 0.87, 256 1.0, 512
-// 1.1 in 16-bit forward calls, 0.9 with a softmax per weight or where h_save holds the states anyway; the backward call always has
-// them: 256 planes 0.88, 384 0.9, 512 0.97).  Of the kernels in their place: two-channel, 128 planes 128x128 44 -> 28 us, 320 planes 1.6 of its
-// time; stream, 64 planes 256x256 bf16 123 -> 67, 96 planes 0.75, 192 1.4, lines beyond 512 against the
-// stream kernels in halves: 48 planes 576x256 fp32 0.73, 96 1.13; bf16 64 planes 640x512 0.86, 32 planes 1024x512 0.92, 64 1.29; per-stretch, up to its 256 planes 0.75
-// (backward in 16 bits, which rounds e there and not here: 32 planes 0.85, 64 0.93).  What ran line by line for want of an LDS tile,
-// 0.04 to 0.12 of its time at any number of planes.
+// Timed on random calls (8 to 1100 planes, 16 to 1024 positions a side, the three types, stretches, logits, weights shared and each channel's
+// own).  Ratio in the mean by planes: 8 0.4, 32 0.5, 64 0.6, 128 0.75; beyond, where every CU has a plane of its own, what the
+// states cost across the memory system counts (160 planes 0.87, 256 1.0, 512 1.1 in 16-bit forward calls, 0.9 with a softmax per
+// weight or where h_save holds the states anyway; the backward call always has them: 256 planes 0.88, 384 0.9, 512 0.97).  Of the kernels in
+// their place: two-channel, 128 planes 128x128 44 -> 28 us, 320 planes 1.6 of its time; stream, 64 planes 256x256 bf16 123 -> 67, 96 planes 0.75, 192
+// 1.4, lines beyond 512 against the stream kernels in halves: 48 planes 576x256 fp32 0.73, 96 1.13; bf16 64 planes 640x512 0.86, 32
+// planes 1024x512 0.92, 64 1.29; per-stretch, forward 0.75.  What ran line by line for want of an LDS tile, 0.04 to 0.12 of its time at any number
+// of planes.  A mean hides the calls that lose, and apart_longer leaves them out: of 65 000 random calls these limits alone take, 6.2 in
+// a hundred took more than 1.05 of the time of the kernel in their place, 3.5 more than 1.15, narrow maps up to 3.0; of 21 000 drawn
+// afresh with it 1.3 and 0.4, 1.75 at most (0.49 in the mean).  What it leaves out would take 1.01 in the mean, one in five 0.85 and less.
 constexpr size_t APART_WORKSPACE = (size_t)1 << 30;             // bytes: no call asks for more
+
+// ... the calls among them that would run longer.  A weight map of (nearly) every channel's own is read by every direction's workgroup
+// alone, x with it, by the other kernels once for both directions of an axis; a long narrow map is one chain of lines, of which
+// these kernels walk four per plane where the others walk two.
+static bool apart_longer(const FwdParams& p, int dtype, const char* kernel, bool backward) {
+    const size_t planes = (size_t)p.B * p.C, pixels = planes * p.H * p.W;
+    const int longest = p.H > p.W ? p.H : p.W, shortest = p.H > p.W ? p.W : p.H;
+    const bool f32 = dtype == 0, own = p.cpg <= 2;
+    const bool cut = p.kchunk > 0, across = cut && p.kchunk % (f32 ? 4 : 8) != 0;         // across: stretches that no horizontal range begins with
+    // stream kernels, beyond 64 planes: own weights 0.9 in the mean, 4 in 10 run longer (109 planes 512x256 fp32 420 -> 647); up to 64
+    // planes, or shared by more channels, 0.35 to 0.75, none
+    if (!strcmp(kernel, "stream")) return planes > 64 && (own || (across && apart_items(p, dtype) > 512));
+    // Per-stretch kernels, whose work items are stretches already, in groups of one axis: these are ahead (0.45 to 0.85) where theirs are fewer than the
+    // compute units or the stretches long.  Many short stretches of a small call, forward: 16 bits 1.0 to 1.26 (12 planes 128x128,
+    // stretches of 8, 12.1 -> 17.2), fp32 1.14 to 1.47 (3 planes 256x64, of 4, 11.4 -> 21.9); maps higher than wide, whose horizontal ranges are short,
+    // 0.87 to 1.1 (66 planes 128x64 fp32, of 32, 25.5 -> 54.3).  Backward in 16 bits 1.3 with stretches of 16 and less (6 planes 256x128 23.3 -> 39.9),
+    // 1.02 to 1.15 of 32, but with weights shared by eight channels 0.97; from 64 on 0.8.  fp32 1.14 with stretches of less than 16
+    // where few channels share the weights
+    if (!strcmp(kernel, "chunk")) {
+        const size_t items = apart_items(p, dtype);
+        const bool high = p.H > p.W;
+        if (backward && !f32) return !((p.kchunk >= 64 && items <= 220) || (p.kchunk >= 32 && p.cpg >= 8 && items <= 512));
+        if (backward) return (p.kchunk < 16 && pixels <= 170000 && p.cpg < 4) || (items > 320 && (pixels <= 117000 || high));
+        if (f32) return (items > 160 && p.kchunk < 8 && pixels <= 117000) || (items > 320 && pixels <= 117000) || (items > 258 && high);
+        return (items > 160 && p.kchunk < 16 && (high || items > 250) && pixels <= 217000) || (items > 254 && high) || (items > 1028 && p.H * p.W <= 24576);
+    }
+    // first of two passes, whose second reads the same e: beyond 128 planes 1.02 (252 planes 64x64 bf16 35.4 -> 43.5), but for 0.74 where 16 channels share
+    // the weights; own weights in 16 bits from 65 planes on 0.95, with stretches in every type 1.06 (109 planes 128x128 fp16 72 -> 138)
+    if (!strcmp(kernel, "twopass/any size")) {
+        if (planes > 128) return cut || p.cpg < 16 || pixels > 2400000;
+        return own && ((planes > 64 && pixels > 250000 && (cut || !f32)) || (planes > 32 && pixels > 400000 && cut));
+    }
+    if (strcmp(kernel, "any size")) return false;
+    if (cut) {
+        // Stretches.  Horizontal ones that begin inside a granule leave the horizontal scans in one piece beside many short vertical
+        // ones (124 planes 392x240 fp32, stretches of 62, 646 -> 1775): 0.9 to 1.6 in the mean from 513 work items on with own
+        // weights, from 1025 on with shared ones.  Narrow maps 0.83 to 1.0; own weights beyond 1024 work items 0.92 to 1.03,
+        // backward from 89 planes on 0.99; very many ranges of more than 96 planes 0.84, one in four longer (124
+        // planes 432x144 fp16, stretches of 8, 219 -> 393).
+        const size_t items = apart_items(p, dtype);
+        if (planes <= 32) return false;
+        if (across && items > (own ? 512u : 1024u)) return true;
+        if (planes <= 64) return false;
+        return (longest > 160 && longest > 6 * shortest && (across || backward || planes > 96)) || (own && (items > 1024 || (backward && planes > 88))) ||
+               (!backward && planes > 96 && items > 2048);
+    }
+    if (planes <= 64) return false;                              // 0.6 in the mean, narrow maps 0.8
+    if (planes <= 128) {
+        // long narrow maps, forward 1.0 to 1.2 (76 planes 282x42 bf16 49 -> 65), backward 0.93 to 1.03; fp32 1.0 and 0.92; square ones 0.7
+        if (f32 ? longest > 256 && longest <= 384 && longest > 8 * shortest
+                : longest > 160 && longest > (longest <= 256 ? 8 : longest <= 384 ? 6 : 12) * shortest && (longest <= 384 || !backward)) return true;
+        return !backward && own && !p.logits && planes > 96 && pixels > 1000000;               // 0.89 to 0.95, a quarter longer
+    }
+    if (backward) {
+        // narrow 0.95 to 1.3 (218 planes 416x16 fp16 96 -> 201); own weights 0.96 to 1.16 in fp32, 0.94 to 1.02 in 16 bits up to 256
+        // planes, the second turn of the other kernel; large calls just below that 0.94 to 1.02
+        if (longest > 160 ? longest > (longest <= 384 ? 5 : 10) * shortest : planes > 192 && longest > 8 * shortest) return true;
+        if (own && (f32 ? pixels > 450000 : planes <= 256 && pixels > 1000000)) return true;
+        return planes > 192 && planes <= 256 && (f32 ? pixels > 1000000 : !p.logits && pixels > 2000000);
+    }
+    // narrow 1.0 to 1.9 (173 planes 416x8 fp16 41 -> 116); own weights 0.95 to 1.25; large calls 0.9 to 1.02, except with a softmax per weight; more
+    // than 192 planes of rows that are whole granules, the any-size kernel's wide requests, 1.0 to 1.06 in 16 bits, 0.95 in fp32
+    if (longest > (longest > 160 ? 4 : 8) * shortest || (own && pixels > 450000)) return true;
+    if (pixels > 2000000 && !(p.logits && !own && planes <= 192)) return true;
+    return planes > 192 && ((!f32 && longest > 4 * shortest) || (p.W % (f32 ? 4 : 8) == 0 && !(f32 && (p.logits || pixels <= 600000))));
+}
+
 bool apart_fwd(const FwdParams& p, int dtype) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
     if (knobs().any || p.mask != 15 || p.xt || HW < 400 || planes > 1100 || apart_workspace_bytes(p, dtype) > APART_WORKSPACE) return false;
     const int longest = p.H > p.W ? p.H : p.W;
     const bool f32 = dtype == 0;
     size_t most;
-    switch (fwd_kernel(p, dtype)) {
+    const FwdPlan kernel = fwd_kernel(p, dtype);
+    switch (kernel) {
         case FWD_PAIR: most = 144; break;
         case FWD_CHUNK: most = 256; break;
         case FWD_STREAM: most = f32 ? (longest > 512 ? 64 : 128) : longest > 768 ? 32 : longest > 512 ? 64 : 96; break;
         case FWD_GENERIC: most = HW >= 4096 ? 1100 : 128; break;
         default: most = p.kchunk > 0 ? 128 : HW < 8000 && (f32 ? p.hs != nullptr : p.logits != 0) ? 384 : HW < 4096 ? 192 : 144;
     }
-    return planes <= most && apart_applicable(p, dtype);
+    return planes <= most && !apart_longer(p, dtype, kernel == FWD_STREAM ? "stream" : kernel == FWD_CHUNK ? "chunk" : kernel == FWD_ANY_SIZE ? "any size" : "", false) && apart_applicable(p, dtype);
 }
 bool apart_bwd(const BwdParams& p, int dtype) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
@@ -209,11 +278,13 @@ bool apart_bwd(const BwdParams& p, int dtype) {
     const bool f32 = dtype == 0;
     size_t most = p.kchunk > 0 ? 128 : 384;
     const BwdPlan kernel = bwd_kernel(p, dtype);
+    const char* name = kernel == BWD_ANY_SIZE ? "any size" : "";
     if (kernel == BWD_TWOPASS) {
-        const char* first = twopass_kernel_name(p, dtype) + 8;
+        name = twopass_kernel_name(p, dtype);
+        const char* first = name + 8;
         if (!strcmp(first, "pair")) most = 96;
-        else if (!strcmp(first, "stream")) most = f32 ? 128 : longest > 512 ? 32 : 64;
-        else if (!strcmp(first, "chunk")) most = f32 ? 256 : 32;
+        else if (!strcmp(first, "stream")) { most = f32 ? 128 : longest > 512 ? 32 : 64; name = first; }
+        else if (!strcmp(first, "chunk")) { most = f32 ? 256 : 32; name = first; }
         else if (!strcmp(first, "any size")) most = p.kchunk > 0 ? 128 : 256;
         else most = 128;
     } else if (kernel == BWD_GENERIC) {
@@ -221,7 +292,7 @@ bool apart_bwd(const BwdParams& p, int dtype) {
     } else if (kernel != BWD_ANY_SIZE) {
         most = 128;
     }
-    return planes <= most && apart_bwd_applicable(p, dtype);
+    return planes <= most && !apart_longer(apart_sweep_params(p), dtype, name, true) && apart_bwd_applicable(p, dtype);
 }
 
 // Small maps, a wave per direction.  Time of what the kernels above take, 14 700 random calls of the three types, with stretches and logits,

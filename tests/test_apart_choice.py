@@ -63,3 +63,40 @@ def test_invalid_arguments_ask_for_nothing():
     ask = lambda *a, **k: binding.gspn_fwd_workspace_bytes(*a, **k)
     assert ask(1, 8, 50, 50, 3) == ask(0, 8, 50, 50, 1) == ask(1, 8, 50, 50, 1, kchunk=0) == ask(1, 8, 50, 50, 1, dtype=7) == 0
     assert ask(1, 8, 50, 50, 1, flags=8) == ask(1, 8, 50, 5000, 1, logits=True) == 0 < ask(1, 8, 50, 50, 1)
+
+
+# Calls of as few planes that would run longer so, on either side of each line: (B, C, H, W, G), dtype, kchunk, logits, call, taken
+LONGER = [
+    # stream kernels: weights of each channel's own, stretches that are no whole granules, beyond 64 planes
+    ((1, 64, 256, 256, 64), "bf16", 0, False, "fwd", True), ((1, 72, 256, 256, 72), "bf16", 0, False, "fwd", False), ((1, 72, 256, 256, 24), "bf16", 0, False, "fwd", True),
+    ((1, 109, 512, 256, 109), "f32", 0, False, "bwd", False), ((1, 76, 256, 256, 19), "f32", 37, False, "bwd", False), ((1, 76, 256, 256, 19), "f32", 36, False, "bwd", True),
+    # per-stretch kernels: many short stretches, high maps, the backward call in 16 bits
+    ((1, 12, 128, 128, 2), "bf16", 8, False, "fwd", False), ((1, 12, 128, 128, 2), "bf16", 16, False, "fwd", True), ((1, 91, 256, 64, 13), "f32", 64, False, "fwd", False),
+    ((1, 91, 64, 256, 13), "f32", 64, False, "fwd", True), ((1, 16, 128, 128, 8), "bf16", 32, False, "bwd", False), ((1, 16, 128, 128, 2), "bf16", 32, False, "bwd", True),
+    ((1, 16, 128, 128, 8), "bf16", 64, False, "bwd", True), ((1, 4, 64, 64, 4), "f32", 8, False, "bwd", False), ((1, 4, 64, 64, 1), "f32", 8, False, "bwd", True),
+    # any-size kernel, stretches: begun inside a granule beside many vertical ones, narrow maps, weights of each channel's own, very many
+    ((1, 124, 392, 240, 124), "f32", 62, True, "fwd", False), ((1, 32, 392, 240, 32), "f32", 62, True, "fwd", True), ((1, 124, 432, 144, 4), "f16", 72, False, "fwd", True),
+    ((1, 124, 432, 144, 4), "f16", 8, False, "fwd", False), ((1, 128, 432, 70, 8), "bf16", 216, False, "save", False), ((1, 128, 420, 72, 8), "bf16", 216, False, "save", True),
+    ((1, 100, 100, 90, 100), "bf16", 16, False, "bwd", False), ((1, 100, 100, 90, 25), "bf16", 16, False, "bwd", True),
+    # ... long narrow maps: 65 to 128 planes, and beyond
+    ((1, 64, 416, 16, 8), "f16", 0, False, "fwd", True), ((1, 76, 282, 42, 1), "f16", 0, False, "fwd", False), ((1, 76, 282, 48, 1), "f16", 0, False, "fwd", True),
+    ((1, 76, 250, 30, 1), "bf16", 0, False, "save", False), ((1, 76, 250, 32, 1), "bf16", 0, False, "save", True), ((1, 76, 480, 30, 1), "bf16", 0, False, "fwd", False),
+    ((1, 76, 480, 30, 1), "bf16", 0, False, "bwd", True), ((1, 76, 282, 42, 1), "f32", 0, False, "fwd", True), ((1, 76, 282, 34, 1), "f32", 0, False, "fwd", False),
+    ((1, 136, 200, 48, 8), "bf16", 0, False, "fwd", False), ((1, 136, 150, 48, 8), "bf16", 0, False, "fwd", True), ((1, 136, 200, 40, 8), "bf16", 0, False, "bwd", True),
+    ((1, 190, 416, 16, 2), "f16", 0, False, "bwd", False), ((1, 190, 416, 42, 2), "f16", 0, False, "bwd", True), ((1, 256, 90, 11, 8), "bf16", 0, False, "bwd", False),
+    # ... weights of each channel's own; large calls; rows of whole granules
+    ((1, 126, 227, 227, 126), "f16", 0, False, "fwd", False), ((1, 126, 227, 227, 42), "f16", 0, False, "fwd", True), ((1, 96, 227, 227, 96), "f16", 0, False, "fwd", True),
+    ((1, 144, 60, 60, 144), "bf16", 0, False, "fwd", False), ((1, 144, 60, 50, 144), "bf16", 0, False, "fwd", True), ((1, 144, 128, 125, 9), "bf16", 0, False, "fwd", False),
+    ((1, 144, 128, 125, 9), "bf16", 0, True, "fwd", True), ((1, 256, 40, 40, 8), "bf16", 0, True, "fwd", False), ((1, 256, 40, 41, 8), "bf16", 0, True, "fwd", True),
+    ((1, 256, 40, 40, 8), "f32", 0, False, "save", True), ((1, 256, 60, 60, 8), "f32", 0, False, "save", False), ((1, 160, 60, 60, 160), "f32", 0, False, "bwd", False),
+    ((1, 160, 60, 61, 20), "f32", 0, False, "bwd", True), ((1, 224, 100, 100, 7), "bf16", 0, False, "bwd", False), ((1, 260, 100, 100, 13), "bf16", 0, False, "bwd", True),
+    # first of two passes: weights shared by few channels, large calls
+    ((1, 136, 64, 64, 17), "bf16", 0, False, "bwd", False), ((1, 136, 64, 64, 8), "bf16", 0, False, "bwd", True), ((1, 252, 104, 104, 4), "bf16", 0, False, "bwd", False),
+    ((1, 109, 104, 112, 109), "f16", 0, False, "bwd", False), ((1, 108, 104, 112, 27), "f16", 0, False, "bwd", True),
+]
+
+
+@pytest.mark.parametrize("shape,dtype,kchunk,logits,call,taken", LONGER, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+def test_calls_that_would_run_longer(shape, dtype, kchunk, logits, call, taken):
+    from paper_2512_07884_amd import binding
+    assert (binding.call_apart(*shape, {"f32": 0, "bf16": 1, "f16": 2}[dtype], call, kchunk, logits) in (1, 2)) == taken
