@@ -12,6 +12,16 @@ def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs a real MI355X (run with -m gpu on the GPU box)")
 
 
+def pytest_collection_modifyitems(config, items):
+    """test_gpu_whole_planes runs other modules' tests once more with calls of few planes on other kernels.  Calls of fewer than four
+    directions run the same kernel either way: not twice."""
+    again = [i for i in items if i.module.__name__ == "test_gpu_whole_planes"
+             and getattr(getattr(i, "callspec", None), "params", {}).get("mask", 15) not in (15, None)]
+    if again:
+        config.hook.pytest_deselected(items=again)
+        items[:] = [i for i in items if i not in set(again)]
+
+
 def _reload_library_env():
     """The library reads its GSPN_* testing aids once per process; tell it that they changed."""
     from paper_2512_07884_amd import binding

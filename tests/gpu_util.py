@@ -35,6 +35,12 @@ def call_kernel(B, C, H, W, G, dtype, call, kchunk=0, logits=False, mask=15) -> 
     return binding.call_kernel(B, C, H, W, G, {"f32": 0, "bf16": 1, "f16": 2}[dtype], call, kchunk, logits, mask)
 
 
+def kernel_of(shape, dtype, call, kchunk=0, logits=False, mask=15) -> str:
+    """The kernel a call runs, those of calls of few planes included."""
+    from paper_2512_07884_amd import binding
+    return binding.running_kernel(*shape, {"f32": 0, "bf16": 1, "f16": 2}[dtype], call, kchunk, logits, mask)
+
+
 def rel_inf_err(a: np.ndarray, ref: np.ndarray) -> float:
     scale = np.max(np.abs(ref))
     if scale == 0:

@@ -4,12 +4,15 @@ where the launch shape changes: granules of 8 / 4 elements and their tails, rows
 (one position per lane up to 64, two up to 128, three up to 192) and of several (two positions per lane from 193, four from
 449 up), the longest lines, planes beyond the LDS tile, the last chunk of a scan, the middle of the map where the chunks of
 both directions cross, 1024, 512 and 256 threads (from 257 and 513 planes).  Each call is asked which kernel it runs: the plan
-name "generic" is also the line-by-line kernels'."""
+name "generic" is also the line-by-line kernels'.  The calls of few planes among them run a workgroup per direction here and the any-size
+kernel in test_gpu_whole_planes."""
 import ctypes
+import os
 
 import numpy as np
 import pytest
 
+from gpu_util import kernel_of
 from test_gpu_local import check_local
 from test_gpu_logits import check_logits
 
@@ -68,7 +71,7 @@ def test_against_the_line_by_line_kernels(seed, monkeypatch):
     from test_gpu_differential import _run, _rel
     G.binding = binding
     rng = np.random.default_rng(seed)
-    on_any_size = 0
+    kernels = []
     for it in range(14):
         dtype = ["bf16", "f32", "f16"][int(rng.integers(0, 3))]
         H, W = int(2 ** rng.uniform(1, 8.3)), int(2 ** rng.uniform(1, 8.3)) | 1
@@ -79,7 +82,7 @@ def test_against_the_line_by_line_kernels(seed, monkeypatch):
         mask = int(rng.integers(1, 16)) if rng.random() < 0.3 else 15
         kchunk = int(rng.integers(1, max(H, W))) if rng.random() < 0.35 else 0
         logits = bool(rng.random() < 0.3)
-        on_any_size += sum(t > 0 for t in threads((B, C, H, W, Gr), dtype, kchunk, logits, mask))
+        kernels += [kernel_of((B, C, H, W, Gr), dtype, c, kchunk, logits, mask) for c in ("save", "bwd")]
         td = {"bf16": torch.bfloat16, "f32": torch.float32, "f16": torch.float16}[dtype]
         g = torch.Generator(device="cuda"); g.manual_seed(1000 * seed + it)
         z = torch.randn((4, B, Gr, 3, H, W), generator=g, device="cuda")
@@ -107,7 +110,11 @@ def test_against_the_line_by_line_kernels(seed, monkeypatch):
             e = _rel(torch.where(na, torch.zeros_like(a), a), torch.where(nb, torch.zeros_like(b), b))
             assert e <= tol, (case, n, e)
             assert torch.equal(fast[n].view(torch.uint8), again[n].view(torch.uint8)), (case, n, "not the same twice")
-    assert on_any_size >= 14, "most of the calls are to run the kernel under test"
+    # most of the calls are to run the kernel under test, or, four directions of so few planes, the one in its place (kept out of
+    # test_gpu_whole_planes, which runs this again)
+    any_size = sum(k.endswith("any size") for k in kernels)
+    assert any_size + sum(k in ("apart", "small") for k in kernels) >= 14, kernels
+    assert any_size >= 14 or os.environ.get("GSPN_NO_APART") != "1", kernels
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

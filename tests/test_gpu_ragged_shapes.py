@@ -1,7 +1,8 @@
 """The any-size kernel in each of its launch shapes, which every call is asked for: one chunk of lines in LDS or two, both directions
 of an axis at once or one after the other, output merged in LDS or in global memory, one, two and four workgroups per CU, lines of
 one wave or of several that meet, one or two granules per thread, one to four chunks in all (a pipeline that is never full, the crossing of the directions in the first, a middle and the
-last chunk).  States, gu and x * e are the line-by-line kernels' bit for bit; merged outputs within the storage roundings of
+last chunk).  Calls of few planes and four directions run a workgroup per direction here and these launch shapes in
+test_gpu_whole_planes.  States, gu and x * e are the line-by-line kernels' bit for bit; merged outputs within the storage roundings of
 both (at most one per direction on either side)."""
 import pytest
 
