@@ -1,9 +1,12 @@
-"""Seeded random shapes, masks, stretch lengths and call forms: what the fast kernels return (plane, tile, stream,
-two-pass backward) against what the generic kernels return for the same device tensors.  The generic kernels are held
+"""Seeded random shapes, masks, stretch lengths and call forms: what the fast kernels return against what the generic kernels return for
+the same device tensors -- calls of few planes as they run by themselves (most of them a workgroup, or on small maps a wave, per
+direction) and kept on the kernels of whole planes (plane, tile, stream, any size, two-pass backward).  The generic kernels are held
 against the oracle elsewhere (test_gpu_line_by_line, and test_gpu_fwd / test_gpu_bwd, with GSPN_FORCE_GENERIC);
 this test spreads over many more shapes than the oracle could check in the same time."""
 import numpy as np
 import pytest
+
+from gpu_util import kernel_of
 
 pytestmark = pytest.mark.gpu
 
@@ -36,11 +39,24 @@ def _run(G, inp, Gr, mask, kchunk, logits):
 
 @pytest.mark.parametrize("seed", [11, 12, 13])
 def test_fast_kernels_agree_with_the_generic_kernels_on_random_cases(seed, monkeypatch):
+    assert _kernels(seed, monkeypatch) & {"apart", "small"}
+
+
+@pytest.mark.parametrize("seed", [11, 12, 13])
+def test_kernels_of_whole_planes_agree_with_the_generic_kernels_on_random_cases(seed, monkeypatch):
+    monkeypatch.setenv("GSPN_NO_APART", "1")
+    ran = _kernels(seed, monkeypatch)
+    assert not ran & {"apart", "small"} and len(ran) >= 5, ran
+
+
+def _kernels(seed, monkeypatch):
+    """Compares 16 random cases; the kernels that they ran."""
     import torch
     import paper_2512_07884_amd as G
     from paper_2512_07884_amd import binding
     G.binding = binding
     rng = np.random.default_rng(seed)
+    ran = set()
     for it in range(16):
         dtype = "bf16" if rng.random() < 0.5 else "f32"
         cls = int(rng.integers(0, 5))
@@ -69,6 +85,7 @@ def test_fast_kernels_agree_with_the_generic_kernels_on_random_cases(seed, monke
                "u": torch.rand((4, B, C, H, W), generator=g, device="cuda").to(td),
                "gy": torch.randn((B, C, H, W), generator=g, device="cuda").to(td)}
         monkeypatch.delenv("GSPN_FORCE_GENERIC", raising=False)
+        ran |= {kernel_of((B, C, H, W, Gr), dtype, c, kchunk, logits, mask) for c in ("save", "bwd")}
         fast = _run(G, inp, Gr, mask, kchunk, logits)
         monkeypatch.setenv("GSPN_FORCE_GENERIC", "1")
         ref = _run(G, inp, Gr, mask, kchunk, logits)
@@ -83,3 +100,4 @@ def test_fast_kernels_agree_with_the_generic_kernels_on_random_cases(seed, monke
             assert torch.equal(na, nb), (case, n, "slots of unmasked directions differ")
             e = _rel(torch.where(na, torch.zeros_like(a), a), torch.where(nb, torch.zeros_like(b), b))
             assert e <= tol, (case, n, e)
+    return ran
