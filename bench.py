@@ -152,12 +152,11 @@ def run_workload(cfg, steps: int, warmup: int, kchunk: int = 0, logits: bool = F
 
 def summarise(cfg, r):
     import paper_2512_07884_amd as G
-    from paper_2512_07884_amd.binding import call_apart, call_kernel
+    from paper_2512_07884_amd.binding import running_kernel
     dt = {"f32": 0, "bf16": 1, "f16": 2}[cfg.dtype]
     training = r["training"]
     kchunk = r.get("kchunk", 0)
-    args = lambda call: (cfg.B, cfg.C, cfg.H, cfg.W, cfg.G, dt, call, kchunk, bool(r.get("logits")), cfg.dir_mask)
-    kernel = lambda call: {1: "apart", 2: "apart", 4: "small"}.get(call_apart(*args(call))) or call_kernel(*args(call))
+    kernel = lambda call: running_kernel(cfg.B, cfg.C, cfg.H, cfg.W, cfg.G, dt, call, kchunk, bool(r.get("logits")), cfg.dir_mask)
     fwd_bytes = cfg.fwd_algorithmic_bytes(save_h=training)
     d = {"workload": cfg.name, "B": cfg.B, "C": cfg.C, "H": cfg.H, "W": cfg.W, "G": cfg.G,
          "storage": cfg.dtype, "directions": cfg.n_dirs,
@@ -321,7 +320,7 @@ def unfused_table(steps: int = 3):
     C = 8, where it reports 40x end to end on an A100) and on the two target shapes with few channels (Table 1 regime)."""
     import torch
     import paper_2512_07884_amd as G
-    from paper_2512_07884_amd.binding import call_apart, call_kernel
+    from paper_2512_07884_amd.binding import running_kernel
     from paper_2512_07884_amd import workloads as WL
     rows = []
     for name, B, C, H, W, Gr, dtype in (("step-by-step study shape", 16, 8, 1024, 1024, 1, "f32"),
@@ -348,7 +347,7 @@ def unfused_table(steps: int = 3):
             torch.cuda.synchronize()
             times[kind] = (time.perf_counter() - t0) * 1e3 / steps
         rows.append({"shape": name, "B": B, "C": C, "H": H, "W": W, "G": Gr, "storage": dtype,
-                     "fused_kernel": {1: "apart", 2: "apart", 4: "small"}.get(call_apart(B, C, H, W, Gr, dt, "fwd")) or call_kernel(B, C, H, W, Gr, dt, "fwd"),
+                     "fused_kernel": running_kernel(B, C, H, W, Gr, dt, "fwd"),
                      "fused_ms": times["fused"], "unfused_ms": times["unfused"],
                      "launches_unfused": 2 * (H + W), "ratio": times["unfused"] / times["fused"]})
         del s, y, ws
