@@ -1,6 +1,6 @@
 """Proxy projections on images whose pixel count is not a multiple of 8 (requests at element alignment, last pixels taken
-twice), with the k-steps of a tile shared by the waves of a workgroup or not, and the weight gradient in single and double
-tiles: against the fp64 oracle, and bit-for-bit copies with a selection matrix."""
+twice), with the k-steps of a tile shared by the waves of a workgroup or not, and the weight gradient in tiles of 32 x 32 or 16 x
+16, its rows through LDS or not: against the fp64 oracle, and bit-for-bit copies with a selection matrix."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,7 @@ from test_gpu_proxy import run_project, run_project_bwd
 pytestmark = pytest.mark.gpu
 
 # N = 9, 15, 63, 127, 129, 255, 257, 7020; K in whole and half 16-value steps, fewer steps than waves, ragged row tiles; the
-# larger ones have enough tiles for a wave per tile (forward) and for double tiles (weight gradient)
+# larger ones have enough tiles for a wave per tile (forward) and for rows through LDS (weight gradient)
 SHAPES = [(1, 64, 40, 3, 3), (2, 96, 8, 3, 5), (2, 96, 8, 7, 9), (1, 72, 33, 1, 127), (3, 40, 70, 3, 43), (1, 1152, 144, 5, 51),
           (1, 144, 1152, 1, 257), (1, 96, 24, 90, 78), (9, 200, 130, 11, 13), (64, 24, 96, 33, 31), (2, 8, 96, 17, 19), (2, 96, 24, 23, 23), (1, 40, 33, 16, 40)]
 
@@ -45,9 +45,9 @@ def test_whole_rows_at_the_lines_of_the_dispatch(shape, dtype):
     test_projection_and_gradients(shape, dtype)
 
 
-# The weight gradient at the lines of its dispatch: 16 x 16 tiles from 4096 pixels on (1024 where rows start anywhere), 32 x 64
-# tiles with ragged rows and columns in one turn of workgroups and in several, the same sizes just short of 2048 pixels, whole
-# rows of half a 16-pixel step
+# The weight gradient at the lines of its dispatch: 16 x 16 tiles from 4096 pixels on (1024 where rows start anywhere), 32 x 32
+# tiles, their rows through LDS, with ragged rows and columns in one turn of workgroups and in several, the same just short of 2048
+# pixels, whole rows of half a 16-pixel step
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("shape", [(1, 56, 40, 64, 64), (1, 56, 40, 64, 63), (1, 56, 40, 25, 41), (1, 56, 40, 31, 33), (9, 104, 232, 8, 256),
                                    (9, 104, 232, 8, 255), (9, 104, 232, 7, 293), (18, 72, 232, 16, 129), (2, 40, 24, 3, 8)],
