@@ -161,10 +161,11 @@ int gspn_scan_bwd_logits(const void* gy, const void* x, const void* z, const voi
 /* The three forward calls with a workspace of the caller's.  A call of few planes (B*C up to some hundred, fewer than the chip
  * has compute units for) leaves most of the chip idle while a workgroup holds a whole plane; given room for the states of
  * the four directions in fp32 it runs every direction of every plane as a work item of its own and merges them in a second launch:
- * 64 planes of 256x256 in bf16 123 -> 67 us.  gspn_fwd_workspace_bytes says how many bytes such a call asks for (at most 1 GiB), 0 where it
- * has no use for them (many planes, some directions only, fp32 with h_save, which holds the states itself, invalid arguments).
- * On maps the "stream" kernels take in two launches, up to 128 planes, it holds the states between the two halves of a scan (two lines of
- * fp32 per plane).
+ * 64 planes of 256x256 in bf16 123 -> 67 us.  With h_save an fp32 call has that room already and asks for none.
+ * Large maps, which the "stream" kernels take in two launches, ask for a little up to 128 planes, fp32 with h_save too: the states between
+ * the two halves of a scan (two lines of fp32 per plane).
+ * gspn_fwd_workspace_bytes says how many bytes a call asks for (at most 1 GiB), 0 where it has no use for them: more planes, shapes that
+ * would run longer so, some directions only, small maps, invalid arguments.
  * The workspace is device memory, 16-byte aligned, overwritten by the call and free again when its work on `stream` is done; calls
  * that may overlap need one each.  workspace == NULL is the call without one, with the same result up to the rounding of the
  * storage type; fewer bytes than asked for is GSPN_ERR_SHAPE.  w holds normalised weights (logits == 0) or logits (1);
@@ -257,8 +258,9 @@ const char* gspn_proxy_plan(int B, int K, int M, int H, int W, int dtype);
  * static string, never NULL.  Host only.
  *
  * (The name is the family whose limits the call meets.  Most calls of the "tile" family, those of the "plane" family with few
- * planes, and the first pass of such "twopass" calls run the any-size kernel of "generic" in its place.  Calls of fewer planes than
- * compute units run every direction in a workgroup of its own, whatever the plan: gspn_fwd_workspace_bytes.)
+ * planes, and the first pass of such "twopass" calls run the any-size kernel of "generic" in its place.  Calls of few planes and all four
+ * directions run every direction in a workgroup of its own where that is faster, on small maps in a wave, whatever the plan: up to some
+ * hundred planes, up to 1100 of 16-bit maps that would run line by line; most forward calls only with a workspace.)
  * Environment variables for tests (results are the same whichever kernel runs, up to the rounding of
  * the storage type).  They are read once per process, by the first call that dispatches; a process
  * that changes them afterwards calls gspn_reload_env():

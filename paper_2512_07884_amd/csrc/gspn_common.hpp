@@ -263,7 +263,7 @@ hipError_t launch_proxy_project_bwd_static(const void* gout, const void* in, con
                                            int B, int K, int M, int N, int dtype, hipStream_t s);
 
 // dispatch (gspn_dispatch.hip): picks the kernel family for the arguments
-hipError_t launch_fwd(const FwdParams& p, int dtype, void* workspace, hipStream_t s);      // workspace: apart_workspace_bytes, or null
+hipError_t launch_fwd(const FwdParams& p, int dtype, void* workspace, hipStream_t s);      // workspace: fwd_workspace_bytes, or null
 hipError_t launch_bwd(const BwdParams& p, int dtype, hipStream_t s);
 const char* fwd_plan_name(const FwdParams& p, int dtype);
 const char* bwd_plan_name(const BwdParams& p, int dtype);

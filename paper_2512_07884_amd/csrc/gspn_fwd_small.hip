@@ -6,7 +6,7 @@
 // position of all lines of x, lambda, u and the weights at once, element by element (at most 6 * 32 registers; nothing passes
 // through LDS on the way in, so no order or alignment of a row matters), walks the lines with its neighbours' states from DPP, and leaves
 // u * h in LDS, where the four directions meet and are added in their order: 16.2 -> 6.9 us back
-// to back, 768 planes of 7x7 12.5 -> 4.7, 3072 of 14x14 18.0 -> 12.6.  Element requests are an eighth as wide as the plane
+// to back (a call by itself, its host path included, 15.3 -> 8.1), 768 planes of 7x7 12.5 -> 4.7, 3072 of 14x14 18.0 -> 12.6.  Element requests are an eighth as wide as the plane
 // kernels': beyond a few thousand planes those are faster (gspn_dispatch.hip has the lines).
 #include "gspn_tile_common.hpp"
 

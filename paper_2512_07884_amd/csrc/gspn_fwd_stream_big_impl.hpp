@@ -10,9 +10,9 @@
 //      request.  Beyond 1024 rows a lane holds two adjacent rows and 16 B of each per request (forward only).
 // Calls of at most 128 planes, half as many as the chip has compute units, run each launch as two, a workgroup per (plane, direction): the
 // first walks the first halves of both directions, whose pixels are apart, the second the other halves, which add to what the first left
-// in y; the states in between pass through a workspace of the caller's (2 lines of fp32 per plane).  Same pixels, same sums per pixel, twice the
-// workgroups: what bounds these calls is what one compute unit has in flight.  128 planes 1024x1024 fp32 3.89 -> 3.09 ms, 64 planes
-// 3.32 -> 2.03; 128 planes 1024x512 bf16 1.04 -> 0.77 (global scan, normalised weights, up to 1024 rows, forward and h_save).
+// in y; the states in between pass through a workspace of the caller's (2 lines of fp32 per plane).  Same pixels and the same four terms per pixel, the two
+// horizontal ones in the other order in the right half of the plane, from twice the workgroups: what bounds these calls is what one
+// compute unit has in flight.  128 planes 1024x1024 fp32 3.88 -> 3.05 ms, 64 planes 3.32 -> 2.03; 128 planes 1024x512 bf16 1.04 -> 0.77 (global scan, normalised weights, up to 1024 rows, forward and h_save).
 // Launch 2 reads the y of launch 1 (stream order).  h_save and, up to 1024 rows, the reverse sweep of the two-pass
 // backward run on the same kernels (template flags SAVE, BWD), and so do, up to 1024 rows, GSPN-local and logits calls
 // (LOCAL, LOGITS: the stretch bookkeeping and the softmax of the line objects, as in the stream kernel).

@@ -364,7 +364,7 @@ __global__ void __launch_bounds__(64 * NW) proxy_gradw_mfma_kernel(const T* __re
 // The same with the rows through LDS.  A matrix-core operand is 16 bytes of each of 32 rows: asked for as it is multiplied, a request
 // touches 32 lines for a quarter of each.  Here a request is eight rows of whole 128-byte lines; 128 pixels of the tile's rows make a
 // stage, the stages after it are on their way in registers, and each of the eight waves multiplies every eighth step of 16 pixels, in
-// the order above (the same sums, bit for bit on whole rows).  1152 x 144 on two 64x64 images 30 -> 18 us, on two 128x128 104 -> 53.  Every tile of the longer side is read by as many workgroups as the
+// the order of the kernel above with eight waves (on whole rows its sums, bit for bit; launches of 512 tiles and more have four there).  1152 x 144 on two 64x64 images 30 -> 18 us, on two 128x128 104 -> 53.  Every tile of the longer side is read by as many workgroups as the
 // shorter side has tiles, and each XCD has an L2 of its own: an XCD takes neighbouring tiles of the longer side with all of the
 // shorter one's.
 template <typename T, bool ANY>
