@@ -204,22 +204,25 @@ def _ptr(t, name, shape, like):
     return t.data_ptr()
 
 
-_CURRENT = []          # torch's way to the handle of the current device's current stream, found on first use
+_TORCH = []          # torch, and its ways to the current device's number, to the handle of that device's current stream and to whether that is being captured
 
 
-def _current_stream() -> int:
-    # the handle alone: 0.2 us where the stream object takes 3.0 of a small call's 10.8 us of host time
-    if not _CURRENT:
+def _torch():
+    """_TORCH, filled on first use.  The functions themselves rather than their wrappers: calls on small maps wait for the host (the
+    handle of the stream alone takes 0.2 us, the stream object 3.0 of a small call's 10.8)."""
+    if not _TORCH:
         import torch
-        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
-        _CURRENT.append((lambda: raw(device())) if raw and device else (lambda: torch.cuda.current_stream().cuda_stream))
-    return _CURRENT[0]()
+        raw, device, capturing = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice", "_cuda_isCurrentStreamCapturing"))
+        _TORCH[:] = (torch, device or torch.cuda.current_device,
+                     (lambda: raw(device())) if raw and device else (lambda: torch.cuda.current_stream().cuda_stream),
+                     capturing or torch.cuda.is_current_stream_capturing)
+    return _TORCH
 
 
 def _stream(stream):
     if stream is None:
-        return ctypes.c_void_p(_current_stream())
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        return (_TORCH or _torch())[2]()
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check(status: int):
@@ -248,7 +251,7 @@ def _torch_captures(device) -> bool:
     """Whether memory allocated now, on a stream that is being captured, stays with the graph: torch's allocator then takes it from a
     pool of the graph's.  It knows captures begun by torch alone; in one begun by the HIP runtime's own calls it hands out ordinary
     memory, which belongs to another tensor by the time the graph is replayed."""
-    import torch
+    torch = _TORCH[0]
     probe = torch.empty(1, dtype=torch.uint8, device=device)
     try:
         segments = torch.cuda.memory_snapshot()
@@ -259,51 +262,49 @@ def _torch_captures(device) -> bool:
 
 
 def _allocate(x, nbytes):
-    import torch
-    if torch.cuda.is_current_stream_capturing() and not _torch_captures(x.device):
+    torch, _, _, capturing = _TORCH
+    try:
+        if capturing() and not _torch_captures(x.device):
+            return None
+        return torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+    except torch.cuda.OutOfMemoryError:
         return None
-    return torch.empty(nbytes, dtype=torch.uint8, device=x.device)
 
 
 def _workspace(x, nbytes, stream):
     """Device memory for one call, from torch's allocator and in the order of the stream the call runs on; None where there is no
     room or where it would not stay the call's own (the call then runs without)."""
-    import torch
     # The allocator gives a block out again in the order of a stream of x's device: the call has to run on that very stream.
+    torch, current_device, _, _ = _TORCH or _torch()
     device = x.get_device()
-    handle = None if stream is None else stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+    if stream is None:
+        return _allocate(x, nbytes) if device == current_device() else None
+    handle = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
     if not handle:
-        # no stream, and the handle of a device's default stream, mean those of the current device
-        if device != torch.cuda.current_device():
+        if device != current_device():                    # (the current device's default stream)
             return None
-    elif handle in (1, 2):
-        # the runtime's names for the default stream and for each thread's own
+    elif handle in (1, 2):                                # the runtime's names for the default stream and for each thread's own
         return None
     elif getattr(stream, "device_index", device) != device:
         return None
-    try:
-        if stream is None:
-            return _allocate(x, nbytes)
-        if not isinstance(stream, torch.cuda.Stream):
-            stream = torch.cuda.ExternalStream(handle, device=x.device) if handle else torch.cuda.default_stream(x.device)
-        with torch.cuda.stream(stream):
-            return _allocate(x, nbytes)
-    except torch.cuda.OutOfMemoryError:
-        return None
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(handle, device=x.device) if handle else torch.cuda.default_stream(x.device)
+    with torch.cuda.stream(stream):
+        return _allocate(x, nbytes)
 
 
 def _scan_fwd(x, w, lam, u, y, h_save, kchunk, logits, G, dir_mask, flags, stream):
     ptrs, dims = _fwd_args(x, w, lam, u, y, h_save, G, flags)
     lib, code, kchunk = load_library(), _dtype_code(x), int(kchunk)
-    nbytes = None
-    # (other types of integer may change their value or have no hash: they are asked about anew)
-    keep = type(dir_mask) is int and type(flags) is int and type(dims[4]) is int
-    if keep:
-        key = (dims, kchunk, logits, dir_mask, code, flags, h_save is None)
+    key = (dims, kchunk, logits, dir_mask, code, flags, h_save is None)
+    try:
         nbytes = _WORKSPACE_BYTES.get(key)
+    except TypeError:                                     # an integer without a hash (an array)
+        nbytes = None
     if nbytes is None:
         nbytes = lib.gspn_fwd_workspace_bytes(*dims, kchunk, logits, dir_mask, code, flags, int(h_save is not None))
-        if keep:
+        # by plain integers only: others may have no hash or another value the next time
+        if type(dir_mask) is int and type(flags) is int and type(dims[4]) is int:
             if len(_WORKSPACE_BYTES) >= 4096:
                 _WORKSPACE_BYTES.clear()
             _WORKSPACE_BYTES[key] = nbytes

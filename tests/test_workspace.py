@@ -21,11 +21,9 @@ class Recorder:
         lib = types.SimpleNamespace(gspn_fwd_workspace_bytes=lambda *a: self.WANTED, gspn_scan_fwd_workspace=self.launch)
         monkeypatch.setattr(binding, "load_library", lambda: lib)
         monkeypatch.setattr(binding, "_fwd_args", lambda x, w, lam, u, y, h, G, flags: ([16] * 5 + [None], dims))
-        monkeypatch.setattr(binding, "_current_stream", lambda: self.CURRENT_STREAM)
+        monkeypatch.setattr(binding, "_TORCH", [torch, lambda: current_device, lambda: self.CURRENT_STREAM, lambda: capturing])
         monkeypatch.setattr(binding, "_WORKSPACE_BYTES", {})
         monkeypatch.setattr(torch, "empty", self.empty)
-        monkeypatch.setattr(torch.cuda, "current_device", lambda: current_device)
-        monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing)
         monkeypatch.setattr(torch.cuda, "memory_snapshot", lambda: [{"address": self.ADDRESS, "total_size": 8192, "segment_pool_id": pool}])
         monkeypatch.setattr(torch.cuda, "stream", self.on_stream)
         monkeypatch.setattr(torch.cuda, "ExternalStream", lambda handle, device: types.SimpleNamespace(cuda_stream=handle, device=device))
@@ -43,7 +41,7 @@ class Recorder:
         self.streams.pop()
 
     def launch(self, *a):
-        self.got = a[6], a[7], a[-1].value
+        self.got = a[6], a[7], a[-1]
         return 0
 
     def scan(self, **k):
@@ -82,7 +80,7 @@ def test_memory_is_given_back_in_the_order_of_the_stream_the_call_runs_on(device
 @pytest.mark.parametrize("stream", [types.SimpleNamespace(cuda_stream=9), types.SimpleNamespace(cuda_stream=0)], ids=str)
 def test_any_object_with_a_stream_handle_names_a_stream(stream, monkeypatch):
     r = Recorder(monkeypatch)
-    assert r.scan(stream=stream) == (r.ADDRESS, r.WANTED, stream.cuda_stream or None)
+    assert r.scan(stream=stream) == (r.ADDRESS, r.WANTED, stream.cuda_stream)
     assert r.allocated == [(r.WANTED, "cuda:0", stream.cuda_stream)]
 
 
