@@ -184,75 +184,47 @@ static BwdPlan bwd_kernel(const BwdParams& p, int dtype) {
 // their place: two-channel, 128 planes 128x128 44 -> 28 us, 320 planes 1.6 of its time; stream, 64 planes 256x256 bf16 123 -> 67, 96 planes 0.75, 192
 // 1.4, lines beyond 512 against the stream kernels in halves: 48 planes 576x256 fp32 0.73, 96 1.13; bf16 64 planes 640x512 0.86, 32
 // planes 1024x512 0.92, 64 1.29; per-stretch, forward 0.75.  What ran line by line for want of an LDS tile, 0.04 to 0.12 of its time at any number
-// of planes.  A mean hides the calls that lose, and apart_longer leaves them out: of 65 000 random calls these limits alone take, 6.2 in
-// a hundred took more than 1.05 of the time of the kernel in their place, 3.5 more than 1.15, narrow maps up to 3.0; of 21 000 drawn
-// afresh with it 1.3 and 0.4, 1.75 at most (0.49 in the mean).  What it leaves out would take 1.01 in the mean, one in five 0.85 and less.
+// of planes.  A mean hides the calls that lose: apart_longer leaves out the kinds of them that run longer in their own mean (43 000 calls).  Of
+// 17 000 random calls drawn afresh these limits alone take, 2.4 in a hundred took more than 1.05 of the time of the kernel in their place and
+// 1.1 more than 1.15, 2.4 at most; with it 1.8 and 0.7 (0.55 in the mean), the most 2.3 (125 planes 410x380 bf16, stretches of 17).  What it
+// leaves out would take 1.06 in the mean.  Lines that leave out more of those that lose lose more than they save: one round a narrow map,
+// a large call, rows of whole granules and weights of each channel's own at 65 planes and more left 0.2 and 0.05, and took 1.08 of the time
+// in the mean of the calls it turned away, one in twenty of the measured ranges.
 constexpr size_t APART_WORKSPACE = (size_t)1 << 30;             // bytes: no call asks for more
 
 // ... the calls among them that would run longer.  A weight map of (nearly) every channel's own is read by every direction's workgroup
 // alone, x with it, by the other kernels once for both directions of an axis; a long narrow map is one chain of lines, of which
-// these kernels walk four per plane where the others walk two.
+// these kernels walk four per plane where the others walk two.  The figures are times against the kernel in their place, geometric means.
 static bool apart_longer(const FwdParams& p, int dtype, const char* kernel, bool backward) {
     const size_t planes = (size_t)p.B * p.C, pixels = planes * p.H * p.W;
     const int longest = p.H > p.W ? p.H : p.W, shortest = p.H > p.W ? p.W : p.H;
-    const bool f32 = dtype == 0, own = p.cpg <= 2;
-    const bool cut = p.kchunk > 0, across = cut && p.kchunk % (f32 ? 4 : 8) != 0;         // across: stretches that no horizontal range begins with
-    // stream kernels, beyond 64 planes: own weights 0.9 in the mean, 4 in 10 run longer (109 planes 512x256 fp32 420 -> 647); up to 64
-    // planes, or shared by more channels, 0.35 to 0.75, none
-    if (!strcmp(kernel, "stream")) return planes > 64 && (own || (across && apart_items(p, dtype) > 512));
-    // Per-stretch kernels, whose work items are stretches already, in groups of one axis: these are ahead (0.45 to 0.85) where theirs are fewer than the
-    // compute units or the stretches long.  Many short stretches of a small call, forward: 16 bits 1.0 to 1.26 (12 planes 128x128,
-    // stretches of 8, 12.1 -> 17.2), fp32 1.14 to 1.47 (3 planes 256x64, of 4, 11.4 -> 21.9); maps higher than wide, whose horizontal ranges are short,
-    // 0.87 to 1.1 (66 planes 128x64 fp32, of 32, 25.5 -> 54.3).  Backward in 16 bits 1.3 with stretches of 16 and less (6 planes 256x128 23.3 -> 39.9),
-    // 1.02 to 1.15 of 32, but with weights shared by eight channels 0.97; from 64 on 0.8.  fp32 1.14 with stretches of less than 16
-    // where few channels share the weights
+    const bool f32 = dtype == 0, cut = p.kchunk > 0, any_size = !strcmp(kernel, "any size"), second = !strcmp(kernel, "twopass/any size");
+    // Per-stretch kernels, whose work items are stretches already, in groups of one axis: many short stretches of a small call.  Backward
+    // in 16 bits 1.24 with stretches of less than 32 (0.91 from there on, 0.95 with weights shared by more than six channels), in fp32 1.10
+    // on small calls (otherwise 0.70); forward in fp32 1.06 (one in three 1.15 and more; otherwise 0.63), in 16 bits 0.74
     if (!strcmp(kernel, "chunk")) {
-        const size_t items = apart_items(p, dtype);
-        const bool high = p.H > p.W;
-        if (backward && !f32) return !((p.kchunk >= 64 && items <= 220) || (p.kchunk >= 32 && p.cpg >= 8 && items <= 512));
-        if (backward) return (p.kchunk < 16 && pixels <= 170000 && p.cpg < 4) || (items > 320 && (pixels <= 117000 || high));
-        if (f32) return (items > 160 && p.kchunk < 8 && pixels <= 117000) || (items > 320 && pixels <= 117000) || (items > 258 && high);
-        return (items > 160 && p.kchunk < 16 && (high || items > 250) && pixels <= 217000) || (items > 254 && high) || (items > 1028 && p.H * p.W <= 24576);
+        if (backward) return p.kchunk < 32 && (f32 ? p.cpg <= 2 && pixels <= 117000 : p.cpg <= 6);
+        return f32 && apart_items(p, dtype) > 300 && pixels <= 117000;
     }
-    // first of two passes, whose second reads the same e: beyond 128 planes 1.02 (252 planes 64x64 bf16 35.4 -> 43.5), but for 0.74 where 16 channels share
-    // the weights; own weights in 16 bits from 65 planes on 0.95, with stretches in every type 1.06 (109 planes 128x128 fp16 72 -> 138)
-    if (!strcmp(kernel, "twopass/any size")) {
-        if (planes > 128) return cut || p.cpg < 16 || pixels > 2400000;
-        return own && ((planes > 64 && pixels > 250000 && (cut || !f32)) || (planes > 32 && pixels > 400000 && cut));
-    }
-    if (strcmp(kernel, "any size")) return false;
+    if (!any_size && !second && strcmp(kernel, "stream")) return false;
     if (cut) {
-        // Stretches.  Horizontal ones that begin inside a granule leave the horizontal scans in one piece beside many short vertical
-        // ones (124 planes 392x240 fp32, stretches of 62, 646 -> 1775): 0.9 to 1.6 in the mean from 513 work items on with own
-        // weights, from 1025 on with shared ones.  Narrow maps 0.83 to 1.0; own weights beyond 1024 work items 0.92 to 1.03,
-        // backward from 89 planes on 0.99; very many ranges of more than 96 planes 0.84, one in four longer (124
-        // planes 432x144 fp16, stretches of 8, 219 -> 393).
-        const size_t items = apart_items(p, dtype);
-        if (planes <= 32) return false;
-        if (across && items > (own ? 512u : 1024u)) return true;
-        if (planes <= 64) return false;
-        return (longest > 160 && longest > 6 * shortest && (across || backward || planes > 96)) || (own && (items > 1024 || (backward && planes > 88))) ||
-               (!backward && planes > 96 && items > 2048);
+        // Horizontal stretches that begin inside a granule leave the horizontal scans in one piece beside many short vertical ones: 1.04
+        // where at most three channels share the weights, four in ten 1.15 and more, up to 3.0 (90 planes 384x384 fp32, stretches
+        // of 37, 680 -> 1679 us; 0.85 up to 1024 work items, 0.72 up to 64 planes, 0.70 where more channels share them).  Others, weights
+        // of each channel's own, 1.02 beyond 96 planes, three in ten 1.15 and more, up to 2.6 (0.83 below, 0.73 with shared ones)
+        if (planes <= 64 || apart_items(p, dtype) <= 1024) return false;
+        return (p.kchunk % (f32 ? 4 : 8) != 0 && p.cpg <= 3) || (any_size && p.cpg == 1 && planes > 96);
     }
-    if (planes <= 64) return false;                              // 0.6 in the mean, narrow maps 0.8
-    if (planes <= 128) {
-        // long narrow maps, forward 1.0 to 1.2 (76 planes 282x42 bf16 49 -> 65), backward 0.93 to 1.03; fp32 1.0 and 0.92; square ones 0.7
-        if (f32 ? longest > 256 && longest <= 384 && longest > 8 * shortest
-                : longest > 160 && longest > (longest <= 256 ? 8 : longest <= 384 ? 6 : 12) * shortest && (longest <= 384 || !backward)) return true;
-        return !backward && own && !p.logits && planes > 96 && pixels > 1000000;               // 0.89 to 0.95, a quarter longer
-    }
-    if (backward) {
-        // narrow 0.95 to 1.3 (218 planes 416x16 fp16 96 -> 201); own weights 0.96 to 1.16 in fp32, 0.94 to 1.02 in 16 bits up to 256
-        // planes, the second turn of the other kernel; large calls just below that 0.94 to 1.02
-        if (longest > 160 ? longest > (longest <= 384 ? 5 : 10) * shortest : planes > 192 && longest > 8 * shortest) return true;
-        if (own && (f32 ? pixels > 450000 : planes <= 256 && pixels > 1000000)) return true;
-        return planes > 192 && planes <= 256 && (f32 ? pixels > 1000000 : !p.logits && pixels > 2000000);
-    }
-    // narrow 1.0 to 1.9 (173 planes 416x8 fp16 41 -> 116); own weights 0.95 to 1.25; large calls 0.9 to 1.02, except with a softmax per weight; more
-    // than 192 planes of rows that are whole granules, the any-size kernel's wide requests, 1.0 to 1.06 in 16 bits, 0.95 in fp32
-    if (longest > (longest > 160 ? 4 : 8) * shortest || (own && pixels > 450000)) return true;
-    if (pixels > 2000000 && !(p.logits && !own && planes <= 192)) return true;
-    return planes > 192 && ((!f32 && longest > 4 * shortest) || (p.W % (f32 ? 4 : 8) == 0 && !(f32 && (p.logits || pixels <= 600000))));
+    // first of two passes, whose second reads the same e: 16 bits 1.12 (256 planes 80x120 1.12, beyond 3 million pixels 1.21), 0.85
+    // below; fp32 0.93
+    if (second) return !f32 && planes > 128 && pixels > 2200000;
+    if (!any_size || planes <= 128) return false;
+    // high narrow maps in 16 bits: forward 1.54, with h_save 1.34, backward 1.07; from 129 rows on with logits 1.26, 1.27, 1.11,
+    // without 0.87, 0.88, 0.88; wider ones 0.8 to 0.9
+    if (!f32 && p.W <= 44 && p.H > (p.logits ? 128 : 190)) return true;
+    // other very narrow ones, few channels to a weight map, forward: 16 bits 1.06, with h_save 1.04 (up to 2.1; a longer side of five to
+    // eight times the shorter 0.93), fp32 wide ones 1.12 and 1.21; more channels 0.97, backward 0.97 and 1.03
+    return !backward && longest > 128 && p.cpg <= 6 && (f32 ? p.W > 11 * p.H : longest > 8 * shortest);
 }
 
 bool apart_fwd(const FwdParams& p, int dtype) {

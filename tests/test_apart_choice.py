@@ -67,32 +67,32 @@ def test_invalid_arguments_ask_for_nothing():
 
 # Calls of as few planes that would run longer so, on either side of each line: (B, C, H, W, G), dtype, kchunk, logits, call, taken
 LONGER = [
-    # stream kernels: weights of each channel's own, stretches that are no whole granules, beyond 64 planes
-    ((1, 64, 256, 256, 64), "bf16", 0, False, "fwd", True), ((1, 72, 256, 256, 72), "bf16", 0, False, "fwd", False), ((1, 72, 256, 256, 24), "bf16", 0, False, "fwd", True),
-    ((1, 109, 512, 256, 109), "f32", 0, False, "bwd", False), ((1, 76, 256, 256, 19), "f32", 37, False, "bwd", False), ((1, 76, 256, 256, 19), "f32", 36, False, "bwd", True),
-    # per-stretch kernels: many short stretches, high maps, the backward call in 16 bits
-    ((1, 12, 128, 128, 2), "bf16", 8, False, "fwd", False), ((1, 12, 128, 128, 2), "bf16", 16, False, "fwd", True), ((1, 91, 256, 64, 13), "f32", 64, False, "fwd", False),
-    ((1, 91, 64, 256, 13), "f32", 64, False, "fwd", True), ((1, 16, 128, 128, 8), "bf16", 32, False, "bwd", False), ((1, 16, 128, 128, 2), "bf16", 32, False, "bwd", True),
-    ((1, 16, 128, 128, 8), "bf16", 64, False, "bwd", True), ((1, 4, 64, 64, 4), "f32", 8, False, "bwd", False), ((1, 4, 64, 64, 1), "f32", 8, False, "bwd", True),
-    # any-size kernel, stretches: begun inside a granule beside many vertical ones, narrow maps, weights of each channel's own, very many
-    ((1, 124, 392, 240, 124), "f32", 62, True, "fwd", False), ((1, 32, 392, 240, 32), "f32", 62, True, "fwd", True), ((1, 124, 432, 144, 4), "f16", 72, False, "fwd", True),
-    ((1, 124, 432, 144, 4), "f16", 8, False, "fwd", False), ((1, 128, 432, 70, 8), "bf16", 216, False, "save", False), ((1, 128, 420, 72, 8), "bf16", 216, False, "save", True),
-    ((1, 100, 100, 90, 100), "bf16", 16, False, "bwd", False), ((1, 100, 100, 90, 25), "bf16", 16, False, "bwd", True),
-    # ... long narrow maps: 65 to 128 planes, and beyond
-    ((1, 64, 416, 16, 8), "f16", 0, False, "fwd", True), ((1, 76, 282, 42, 1), "f16", 0, False, "fwd", False), ((1, 76, 282, 48, 1), "f16", 0, False, "fwd", True),
-    ((1, 76, 250, 30, 1), "bf16", 0, False, "save", False), ((1, 76, 250, 32, 1), "bf16", 0, False, "save", True), ((1, 76, 480, 30, 1), "bf16", 0, False, "fwd", False),
-    ((1, 76, 480, 30, 1), "bf16", 0, False, "bwd", True), ((1, 76, 282, 42, 1), "f32", 0, False, "fwd", True), ((1, 76, 282, 34, 1), "f32", 0, False, "fwd", False),
-    ((1, 136, 200, 48, 8), "bf16", 0, False, "fwd", False), ((1, 136, 150, 48, 8), "bf16", 0, False, "fwd", True), ((1, 136, 200, 40, 8), "bf16", 0, False, "bwd", True),
-    ((1, 190, 416, 16, 2), "f16", 0, False, "bwd", False), ((1, 190, 416, 42, 2), "f16", 0, False, "bwd", True), ((1, 256, 90, 11, 8), "bf16", 0, False, "bwd", False),
-    # ... weights of each channel's own; large calls; rows of whole granules
-    ((1, 126, 227, 227, 126), "f16", 0, False, "fwd", False), ((1, 126, 227, 227, 42), "f16", 0, False, "fwd", True), ((1, 96, 227, 227, 96), "f16", 0, False, "fwd", True),
-    ((1, 144, 60, 60, 144), "bf16", 0, False, "fwd", False), ((1, 144, 60, 50, 144), "bf16", 0, False, "fwd", True), ((1, 144, 128, 125, 9), "bf16", 0, False, "fwd", False),
-    ((1, 144, 128, 125, 9), "bf16", 0, True, "fwd", True), ((1, 256, 40, 40, 8), "bf16", 0, True, "fwd", False), ((1, 256, 40, 41, 8), "bf16", 0, True, "fwd", True),
-    ((1, 256, 40, 40, 8), "f32", 0, False, "save", True), ((1, 256, 60, 60, 8), "f32", 0, False, "save", False), ((1, 160, 60, 60, 160), "f32", 0, False, "bwd", False),
-    ((1, 160, 60, 61, 20), "f32", 0, False, "bwd", True), ((1, 224, 100, 100, 7), "bf16", 0, False, "bwd", False), ((1, 260, 100, 100, 13), "bf16", 0, False, "bwd", True),
-    # first of two passes: weights shared by few channels, large calls
-    ((1, 136, 64, 64, 17), "bf16", 0, False, "bwd", False), ((1, 136, 64, 64, 8), "bf16", 0, False, "bwd", True), ((1, 252, 104, 104, 4), "bf16", 0, False, "bwd", False),
-    ((1, 109, 104, 112, 109), "f16", 0, False, "bwd", False), ((1, 108, 104, 112, 27), "f16", 0, False, "bwd", True),
+    # per-stretch kernels: many short stretches of a small call
+    ((1, 16, 128, 128, 8), "bf16", 16, False, "bwd", False), ((1, 16, 128, 128, 8), "bf16", 32, False, "bwd", True), ((1, 16, 128, 128, 2), "bf16", 16, False, "bwd", True),
+    ((1, 4, 64, 64, 2), "f32", 8, False, "bwd", False), ((1, 3, 64, 64, 1), "f32", 8, False, "bwd", True), ((1, 4, 64, 64, 2), "f32", 32, False, "bwd", True),
+    ((1, 16, 128, 128, 8), "f32", 8, False, "bwd", True), ((1, 7, 128, 128, 1), "f32", 4, False, "fwd", False), ((1, 8, 128, 128, 1), "f32", 4, False, "fwd", True),
+    ((1, 7, 128, 128, 1), "f32", 16, False, "fwd", True), ((1, 12, 128, 128, 2), "bf16", 8, False, "fwd", True),
+    # stretches begun inside a granule beside many vertical ones, on the any-size and the stream kernel
+    ((1, 90, 384, 384, 45), "f32", 37, False, "fwd", False), ((1, 90, 384, 384, 45), "f32", 36, False, "fwd", True), ((1, 90, 384, 384, 18), "f32", 37, False, "fwd", True),
+    ((1, 64, 384, 384, 32), "f32", 37, False, "fwd", True), ((1, 90, 384, 384, 45), "f32", 97, False, "fwd", True), ((1, 87, 384, 384, 29), "bf16", 37, False, "bwd", False),
+    ((1, 72, 512, 256, 24), "bf16", 37, False, "fwd", False), ((1, 72, 512, 256, 24), "bf16", 40, False, "fwd", True), ((1, 76, 256, 256, 76), "f32", 37, False, "bwd", False),
+    # ... others, weights of each channel's own
+    ((1, 124, 432, 144, 124), "f16", 16, False, "fwd", False), ((1, 96, 432, 144, 96), "f16", 16, False, "fwd", True), ((1, 124, 432, 144, 62), "f16", 16, False, "fwd", True),
+    ((1, 124, 432, 144, 124), "f16", 144, False, "fwd", True), ((1, 100, 100, 90, 100), "bf16", 8, False, "bwd", False), ((1, 100, 100, 90, 50), "bf16", 8, False, "bwd", True),
+    # first of two passes, large calls
+    ((1, 256, 128, 80, 16), "bf16", 0, False, "bwd", False), ((1, 256, 104, 80, 16), "bf16", 0, False, "bwd", True), ((1, 256, 128, 80, 16), "f32", 0, False, "bwd", True),
+    # narrow maps: high ones in 16 bits
+    ((1, 136, 192, 40, 8), "bf16", 0, False, "fwd", False), ((1, 128, 192, 40, 8), "bf16", 0, False, "fwd", True), ((1, 136, 168, 46, 8), "bf16", 0, True, "fwd", True),
+    ((1, 136, 180, 42, 8), "bf16", 0, False, "fwd", True), ((1, 136, 180, 42, 8), "bf16", 0, True, "fwd", False), ((1, 136, 180, 42, 8), "f32", 0, True, "save", True),
+    ((1, 190, 416, 42, 2), "f16", 0, False, "bwd", False), ((1, 190, 416, 46, 2), "f16", 0, False, "bwd", True), ((1, 190, 128, 42, 2), "f16", 0, True, "bwd", True),
+    # ... few channels to a weight map
+    ((1, 136, 24, 200, 34), "bf16", 0, False, "fwd", False), ((1, 136, 25, 200, 34), "bf16", 0, False, "fwd", True), ((1, 136, 24, 200, 17), "bf16", 0, False, "fwd", True),
+    ((1, 136, 24, 200, 34), "bf16", 0, False, "bwd", True), ((1, 136, 16, 200, 34), "f32", 0, False, "save", False), ((1, 136, 20, 200, 34), "f32", 0, False, "save", True),
+    ((1, 136, 200, 16, 34), "f32", 0, False, "save", True),
+    # ... calls that a limit on large, square or whole-granule maps of few planes once kept off: shorter so
+    ((1, 72, 256, 256, 72), "bf16", 0, False, "fwd", True), ((1, 126, 227, 227, 126), "f16", 0, False, "fwd", True), ((2, 144, 64, 64, 18), "bf16", 0, True, "save", True),
+    ((1, 256, 40, 40, 8), "bf16", 0, True, "fwd", True), ((1, 160, 60, 60, 160), "f32", 0, False, "bwd", True), ((1, 224, 100, 100, 7), "bf16", 0, False, "bwd", True),
+    ((1, 136, 64, 64, 17), "bf16", 0, False, "bwd", True),
 ]
 
 
