@@ -21,7 +21,7 @@ static size_t apart_ranges(const FwdParams& p, int E, int range[2], int nrange[2
             const bool cut = p.kchunk > 0 && lines < S && (ax == 0 || lines % E == 0);
             range[ax] = cut ? (int)lines : S;
             nrange[ax] = cut ? (int)((S + lines - 1) / lines) : 1;
-            items += planes * __builtin_popcount(ax ? p.mask & 12 : p.mask & 3) * nrange[ax];
+            items += planes * 2 * nrange[ax];
             longer |= cut && lines < 32;
         }
         if (!longer || items < 1024) return items;
@@ -32,10 +32,10 @@ size_t apart_items(const FwdParams& p, int dtype) {
     return apart_ranges(p, dtype == 0 ? 4 : 8, range, nrange);
 }
 
-// The launch shape for a call, or false where no shape fits.
+// The launch shape for a call (of all four directions), or false where no shape fits.
 static bool apart_plan(const FwdParams& p, int dtype, ApartArgs* out, int* threads, int* nv, size_t* lds) {
     const int H = p.H, W = p.W, es = dtype == 0 ? 4 : 2, E = 16 / es;
-    if (p.xt || (size_t)H * W < 16 || (size_t)H * W >= (1u << 29)) return false;
+    if (p.mask != 15 || p.xt || (size_t)H * W < 16 || (size_t)H * W >= (1u << 29)) return false;
     const bool wide = dtype == 0 || p.logits;
     ApartArgs a = {};
     a.p = p;
@@ -105,7 +105,7 @@ namespace {
 
 // The merge: out = sum over the directions of u * h, in direction order.  h in fp32 (HALVES: its high half in `h`, its low half in
 // `lo`).  Elementwise, 16 bytes of the output per thread.
-struct CombineArgs { const void* u; const void* h; const void* lo; void* out; size_t n; unsigned mask; int shared; };
+struct CombineArgs { const void* u; const void* h; const void* lo; void* out; size_t n; int shared; };
 template <typename T, bool HALVES>
 __global__ void __launch_bounds__(256) combine_kernel(CombineArgs a) {
     constexpr int E = 16 / (int)sizeof(T);
@@ -117,7 +117,6 @@ __global__ void __launch_bounds__(256) combine_kernel(CombineArgs a) {
         for (int e = 0; e < E; ++e) y[e] = 0.f;
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-            if (!((a.mask >> d) & 1u)) continue;
             const u32x4 u = rg_load((const T*)a.u + (a.shared ? 0 : d * a.n) + i);
             if constexpr (HALVES) {
                 const u32x4 hi = rg_load((const T*)a.h + d * a.n + i), lo = rg_load((const T*)a.lo + d * a.n + i);
@@ -145,7 +144,6 @@ __global__ void __launch_bounds__(256) combine_kernel(CombineArgs a) {
         for (size_t j = i; j < a.n; ++j) {
             float s = 0.f;
             for (int d = 0; d < 4; ++d) {
-                if (!((a.mask >> d) & 1u)) continue;
                 float h;
                 if constexpr (HALVES) h = __uint_as_float((uint32_t)((const uint16_t*)a.h)[d * a.n + j] << 16 | ((const uint16_t*)a.lo)[d * a.n + j]);
                 else h = ((const float*)a.h)[d * a.n + j];
@@ -157,7 +155,7 @@ __global__ void __launch_bounds__(256) combine_kernel(CombineArgs a) {
 }
 
 hipError_t launch_combine(const FwdParams& p, int dtype, const void* h, const void* lo, hipStream_t s) {
-    const CombineArgs a = {p.u, h, lo, p.y, (size_t)p.B * p.C * p.H * p.W, p.mask, p.shared};
+    const CombineArgs a = {p.u, h, lo, p.y, (size_t)p.B * p.C * p.H * p.W, p.shared};
     const int E = dtype == 0 ? 4 : 8;
     const dim3 grid((unsigned)((a.n + 256 * E - 1) / (256 * E))), block(256);
     void (*k)(CombineArgs) = dtype == 0 ? combine_kernel<float, false> : dtype == 1 ? (lo ? combine_kernel<bf16_t, true> : combine_kernel<bf16_t, false>)
@@ -172,22 +170,13 @@ hipError_t launch_states(const ApartArgs& a, int dtype, bool reverse, int thread
 
 }  // namespace
 
-// the reverse sweep as a forward scan
-FwdParams apart_sweep_params(const BwdParams& p) {
-    FwdParams f = {};
-    f.x = p.gy; f.w = p.w; f.lam = p.u; f.u = p.lam; f.y = p.gx; f.hs = p.glam;
-    f.B = p.B; f.C = p.C; f.H = p.H; f.W = p.W; f.G = p.G; f.cpg = p.cpg;
-    f.mask = p.mask; f.shared = p.shared; f.kchunk = p.kchunk; f.logits = p.logits;
-    return f;
-}
-
 bool apart_applicable(const FwdParams& p, int dtype) {
     ApartArgs a;
     int threads, nv;
     size_t lds;
     return apart_plan(p, dtype, &a, &threads, &nv, &lds);
 }
-bool apart_bwd_applicable(const BwdParams& p, int dtype) { return apart_applicable(apart_sweep_params(p), dtype) && ragged_finish_fits(p, dtype); }
+bool apart_bwd_applicable(const BwdParams& p, int dtype) { return apart_applicable(reverse_sweep_params(p), dtype) && ragged_finish_fits(p, dtype); }
 // bytes of workspace a forward call needs: the fp32 states, unless h_save holds them
 size_t apart_workspace_bytes(const FwdParams& p, int dtype) {
     return dtype == 0 && p.hs ? 0 : (size_t)16 * p.B * p.C * p.H * p.W;
@@ -208,7 +197,7 @@ hipError_t launch_bwd_apart(const BwdParams& p, int dtype, hipStream_t s) {
     ApartArgs a = {};
     int threads, nv;
     size_t lds;
-    const FwdParams f = apart_sweep_params(p);
+    const FwdParams f = reverse_sweep_params(p);
     if (!apart_plan(f, dtype, &a, &threads, &nv, &lds)) return hipErrorInvalidValue;
     a.hs_lo = dtype == 0 ? nullptr : p.gu;
     hipError_t e = launch_states(a, dtype, true, threads, nv, lds, s);

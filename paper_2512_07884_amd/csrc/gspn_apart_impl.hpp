@@ -707,11 +707,11 @@ __global__ void __launch_bounds__(1024) apart_kernel(ApartArgs a) {
     int q = at / per;
     const int plane = at - q * per + (eighths ? (int)(blockIdx.x & 7) * per : 0);
     const int b = plane / p.C, bg = b * p.G + (plane - b * p.C) / p.cpg;
-    const int nv = __builtin_popcount(p.mask & 3) * a.nrange[0];
+    const int nv = 2 * a.nrange[0];
     const bool horz = q >= nv;
     if (horz) q -= nv;
     const int di = q / a.nrange[horz], first = (q - di * a.nrange[horz]) * a.range[horz];
-    const int m = horz ? p.mask >> 2 : p.mask & 3, d = (m == 3 ? di : m >> 1) + 2 * horz;
+    const int d = di + 2 * horz;
     if (horz) {
         ApartPass<T, MODE, LOGITS, NV, true> v(a, ap_lds);
         v.plane = plane; v.bg = bg;
@@ -725,7 +725,7 @@ __global__ void __launch_bounds__(1024) apart_kernel(ApartArgs a) {
 
 template <typename T, int MODE, bool LOGITS>
 hipError_t launch_apart_one(const ApartArgs& a, int threads, int nv, size_t lds, hipStream_t s) {
-    const int items = __builtin_popcount(a.p.mask & 3) * a.nrange[0] + __builtin_popcount(a.p.mask & 12) * a.nrange[1];
+    const int items = 2 * (a.nrange[0] + a.nrange[1]);
     const dim3 grid((unsigned)((size_t)a.p.B * a.p.C * items)), block(threads);
     void (*k)(ApartArgs) = nv == 1 ? apart_kernel<T, MODE, LOGITS, 1> : nv == 2 ? apart_kernel<T, MODE, LOGITS, 2> : apart_kernel<T, MODE, LOGITS, 4>;
     const hipError_t e = allow_dynamic_lds((const void*)k, 160 * 1024);

@@ -214,14 +214,6 @@ __global__ void __launch_bounds__(256) bwd_finish_kernel(BwdParams p, int ndirs)
     stv<T, VEC>(GW + 2 * (size_t)HW + pix0, a2);
 }
 
-FwdParams reverse_sweep_params(const BwdParams& p) {
-    FwdParams f = {};
-    f.x = p.gy; f.w = p.w; f.lam = p.u; f.u = p.lam; f.y = p.gx; f.hs = p.glam;
-    f.B = p.B; f.C = p.C; f.H = p.H; f.W = p.W; f.G = p.G; f.cpg = p.cpg;
-    f.mask = p.mask; f.shared = p.shared; f.kchunk = p.kchunk; f.logits = p.logits; f.xt = nullptr;
-    return f;
-}
-
 template <typename T, int VEC>
 hipError_t launch_finish(const BwdParams& p, int ndirs, hipStream_t s) {
     const size_t per_dir = (size_t)p.B * p.G * (p.H * p.W / VEC);

@@ -167,6 +167,14 @@ struct BwdParams {
     int kchunk;   // GSPN-local stretch length; 0: global scan
     int logits;   // 1: w holds raw logits and gw receives the gradient w.r.t. them
 };
+// the reverse sweep of the backward call as a forward scan: gy for x, u for lam, gx for y, its states e in glam
+inline FwdParams reverse_sweep_params(const BwdParams& p) {
+    FwdParams f = {};
+    f.x = p.gy; f.w = p.w; f.lam = p.u; f.u = p.lam; f.y = p.gx; f.hs = p.glam;
+    f.B = p.B; f.C = p.C; f.H = p.H; f.W = p.W; f.G = p.G; f.cpg = p.cpg;
+    f.mask = p.mask; f.shared = p.shared; f.kchunk = p.kchunk; f.logits = p.logits; f.xt = nullptr;
+    return f;
+}
 
 // Raises a kernel's dynamic-LDS limit (up to the 160 KB of a gfx950 CU) once per (kernel, device).
 // Later calls are a table lookup, so that a launch made while the stream is being captured issues
@@ -214,7 +222,6 @@ bool apart_applicable(const FwdParams& p, int dtype);
 bool apart_bwd_applicable(const BwdParams& p, int dtype);
 size_t apart_workspace_bytes(const FwdParams& p, int dtype);
 size_t apart_items(const FwdParams& p, int dtype);           // work items of the launch of the states
-FwdParams apart_sweep_params(const BwdParams& p);
 hipError_t launch_fwd_apart(const FwdParams& p, int dtype, void* states, hipStream_t s);
 hipError_t launch_bwd_apart(const BwdParams& p, int dtype, hipStream_t s);
 bool apart_fwd(const FwdParams& p, int dtype);               // gspn_dispatch.hip: the calls that run so

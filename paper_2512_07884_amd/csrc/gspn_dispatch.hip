@@ -264,7 +264,7 @@ bool apart_bwd(const BwdParams& p, int dtype) {
     } else if (kernel != BWD_ANY_SIZE) {
         most = 128;
     }
-    return planes <= most && !apart_longer(apart_sweep_params(p), dtype, name, true) && apart_bwd_applicable(p, dtype);
+    return planes <= most && !apart_longer(reverse_sweep_params(p), dtype, name, true) && apart_bwd_applicable(p, dtype);
 }
 
 // Small maps, a wave per direction.  Time of what the kernels above take, 14 700 random calls of the three types, with stretches and logits,

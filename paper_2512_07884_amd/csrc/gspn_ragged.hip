@@ -416,14 +416,6 @@ __global__ void __launch_bounds__(256) ragged_finish_kernel(BwdParams p, int ndi
     else ragged_finish<T, SL, false>(p, d, blk, red);
 }
 
-FwdParams ragged_sweep_params(const BwdParams& p) {
-    FwdParams f = {};
-    f.x = p.gy; f.w = p.w; f.lam = p.u; f.u = p.lam; f.y = p.gx; f.hs = p.glam;
-    f.B = p.B; f.C = p.C; f.H = p.H; f.W = p.W; f.G = p.G; f.cpg = p.cpg;
-    f.mask = p.mask; f.shared = p.shared; f.kchunk = p.kchunk; f.logits = p.logits; f.xt = nullptr;
-    return f;
-}
-
 // channels of a group over the waves of a workgroup where there are that many
 int ragged_slices(const BwdParams& p) { return p.cpg >= 4 ? 4 : 1; }
 unsigned long long ragged_finish_blocks(const BwdParams& p, int dtype) {
@@ -447,7 +439,7 @@ bool ragged_finish_fits(const BwdParams& p, int dtype) { return ragged_finish_bl
 int ragged_bwd_threads(const BwdParams& p, int dtype) {
     const long long steps = lines_walked(p.mask, p.H, p.W), HW = (long long)p.H * p.W, groups = (long long)p.B * p.G;
     if (steps <= 2 || (steps <= 4 && p.cpg <= 16) || (steps <= 10 && p.cpg <= 2) || (steps * HW <= 520 && groups > 512)) return 0;
-    return ragged_finish_fits(p, dtype) ? ragged_threads(ragged_sweep_params(p), dtype, true) : 0;
+    return ragged_finish_fits(p, dtype) ? ragged_threads(reverse_sweep_params(p), dtype, true) : 0;
 }
 bool ragged_bwd_applicable(const BwdParams& p, int dtype) { return ragged_bwd_threads(p, dtype) != 0; }
 
@@ -467,7 +459,7 @@ hipError_t launch_ragged_finish(const BwdParams& p, int dtype, hipStream_t s) {
 // The two passes of the backward call on any map: the reverse sweep (merged gx, e per direction in fp32), then the sums
 // over the channels.
 hipError_t launch_bwd_ragged(const BwdParams& p, int dtype, hipStream_t s) {
-    const FwdParams f = ragged_sweep_params(p);
+    const FwdParams f = reverse_sweep_params(p);
     const hipError_t e = launch_ragged(f, dtype, true, true, dtype == 0 ? nullptr : p.gu, s);
     return e == hipSuccess ? launch_ragged_finish(p, dtype, s) : e;
 }
