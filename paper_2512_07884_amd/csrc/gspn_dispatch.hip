@@ -187,9 +187,9 @@ static BwdPlan bwd_kernel(const BwdParams& p, int dtype) {
 // of planes.  A mean hides the calls that lose: apart_longer leaves out the kinds of them that run longer in their own mean (43 000 calls).  Of
 // 17 000 random calls drawn afresh these limits alone take, 2.4 in a hundred took more than 1.05 of the time of the kernel in their place and
 // 1.1 more than 1.15, 2.4 at most; with it 1.8 and 0.7 (0.55 in the mean), the most 2.3 (125 planes 410x380 bf16, stretches of 17).  What it
-// leaves out would take 1.06 in the mean.  Lines that leave out more of those that lose lose more than they save: one round a narrow map,
-// a large call, rows of whole granules and weights of each channel's own at 65 planes and more left 0.2 and 0.05, and took 1.08 of the time
-// in the mean of the calls it turned away, one in twenty of the measured ranges.
+// leaves out would take 1.06 in the mean.  Lines that leave out more of those that lose cost more than they save: a set that turned away
+// narrow maps, large calls, rows of whole granules and weights of each channel's own from 65 planes on left 0.2 and 0.05 in a hundred of
+// the maps in use, and took 1.08 of the time in the mean over the one call in twelve that it turned away there.
 constexpr size_t APART_WORKSPACE = (size_t)1 << 30;             // bytes: no call asks for more
 
 // ... the calls among them that would run longer.  A weight map of (nearly) every channel's own is read by every direction's workgroup
