@@ -153,6 +153,8 @@ __device__ __forceinline__ void chain_request_first(const FwdParams& p, int b, i
 // (with the logits normalised on the way in, the forward call with h_save has no register left for even one)
 // a line is a whole wave here, so the lane shifts deliver the zeros at its ends (see line_update); the GSPN-local forward
 // call with h_save in fp16 storage keeps the explicit selects: without them its register allocation went to scratch memory
+// logits in fp16 with h_save: the Newton step of the softmax parks 192 values in accumulation registers, the division 144; 416 us either way
+template <typename T, bool SAVE, bool BWD> constexpr bool pair_divides() { return __is_same(T, f16_t) && SAVE && !BWD; }
 template <typename T, bool SAVE, bool BWD, bool LOCAL> constexpr bool wave_line() { return !(__is_same(T, f16_t) && SAVE && !BWD && LOCAL); }
 
 template <bool SAVE, bool BWD, bool LOGITS = false> constexpr int early_requests() { return SAVE ? (BWD ? 2 : (LOGITS ? 0 : 1)) : 5; }
@@ -211,7 +213,7 @@ __device__ __forceinline__ void vertical_chain(const FwdParams& p, char* region,
         for (int k = 0; k < VBAND; ++k) {
             const int row = chain_row<UP>(s, k);
             float c0[2] = {word_lo<T>(t0[k]), word_hi<T>(t0[k])}, c1[2] = {word_lo<T>(t1[k]), word_hi<T>(t1[k])}, c2[2] = {word_lo<T>(t2[k]), word_hi<T>(t2[k])};
-            if constexpr (LOGITS) { softmax3(c0[0], c1[0], c2[0], first, false); softmax3(c0[1], c1[1], c2[1], false, last); }
+            if constexpr (LOGITS) { softmax3<pair_divides<T, SAVE, BWD>()>(c0[0], c1[0], c2[0], first, false); softmax3<pair_divides<T, SAVE, BWD>()>(c0[1], c1[1], c2[1], false, last); }
             const uint32_t xw = xr[slot][k], lw = lr[slot][k], uw = ur[slot][k];
             float av[2] = {word_lo<T>(lw) * word_lo<T>(xw), word_hi<T>(lw) * word_hi<T>(xw)};
             if constexpr (BWD) {
@@ -463,7 +465,7 @@ __device__ __forceinline__ void pair_body(const FwdParams& p, uint32_t* tiles, c
             float c0[2] = {elem<T>(b00, e), elem<T>(b01, e)};
             float c1[2] = {elem<T>(b10, e), elem<T>(b11, e)};
             float c2[2] = {elem<T>(b20, e), elem<T>(b21, e)};
-            if constexpr (LOGITS) { softmax3(c0[0], c1[0], c2[0], first, false); softmax3(c0[1], c1[1], c2[1], false, last); }
+            if constexpr (LOGITS) { softmax3<pair_divides<T, SAVE, BWD>()>(c0[0], c1[0], c2[0], first, false); softmax3<pair_divides<T, SAVE, BWD>()>(c0[1], c1[1], c2[1], false, last); }
             if constexpr (BWD) {
                 line_update_transposed<2, wave_line<T, SAVE, BWD, LOCAL>()>(h, av, wp0, wp1, wp2, first, last);
                 bool starts = false;
