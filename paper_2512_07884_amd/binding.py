@@ -167,8 +167,16 @@ def call_apart(B, C, H, W, G, dtype, call, kchunk=0, logits=False, dir_mask=DIR_
     return load_library().gspn_call_apart(B, C, H, W, G, kchunk, int(logits), ctypes.c_uint(dir_mask), dtype, ("fwd", "save", "bwd").index(call))
 
 
+def call_lines(B, C, H, W, G, dtype, call, kchunk=0, logits=False, dir_mask=DIR_ALL) -> bool:
+    """Whether a wave walks a line of such a call (a backward call: in its first pass), whatever the two above answer."""
+    return bool(load_library().gspn_call_lines(B, C, H, W, G, kchunk, int(logits), ctypes.c_uint(dir_mask), dtype, ("fwd", "save", "bwd").index(call)))
+
+
 def running_kernel(*args, **kwargs) -> str:
-    """call_kernel, with the kernels of calls of few planes by name: "apart", "stream halves", "small" (given the workspace they ask for)."""
+    """call_kernel, with the kernels that run calls in its place by name: "lines", and of few planes "apart", "stream halves", "small"
+    (given the workspace they ask for)."""
+    if call_lines(*args, **kwargs):
+        return "lines"
     return {1: "apart", 2: "apart", 3: "stream halves", 4: "small"}.get(call_apart(*args, **kwargs)) or call_kernel(*args, **kwargs)
 
 

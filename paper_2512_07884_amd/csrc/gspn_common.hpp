@@ -223,6 +223,9 @@ const char* twopass_kernel_name(const BwdParams& p, int dtype);      // for gspn
 int ragged_fwd_threads(const FwdParams& p, int dtype);        // threads per workgroup, 0: not taken
 int ragged_bwd_threads(const BwdParams& p, int dtype);
 bool ragged_shape(const FwdParams& p, int dtype, bool merge_rounds, int out[7]);
+// a wave per line (gspn_lines*.hip); e_lo: reverse sweep in 16-bit storage, low halves of e
+bool lines_applicable(const FwdParams& p, int dtype);
+hipError_t launch_lines(const FwdParams& p, int dtype, bool reverse, void* e_lo, hipStream_t s);
 // few small planes: a wave per direction (gspn_fwd_small.hip)
 bool fwd_small_applicable(const FwdParams& p);
 hipError_t launch_fwd_small(const FwdParams& p, int dtype, hipStream_t s);
@@ -233,8 +236,6 @@ size_t apart_workspace_bytes(const FwdParams& p, int dtype);
 size_t apart_items(const FwdParams& p, int dtype);           // work items of the launch of the states
 hipError_t launch_fwd_apart(const FwdParams& p, int dtype, void* states, hipStream_t s);
 hipError_t launch_bwd_apart(const BwdParams& p, int dtype, hipStream_t s);
-bool apart_fwd(const FwdParams& p, int dtype);               // gspn_dispatch.hip: the calls that run so
-bool apart_bwd(const BwdParams& p, int dtype);
 bool ragged_finish_fits(const BwdParams& p, int dtype);      // the any-size kernels' second pass of the backward call
 hipError_t launch_ragged_finish(const BwdParams& p, int dtype, hipStream_t s);
 hipError_t launch_fwd_tile(const FwdParams& p, int dtype, hipStream_t s);

@@ -227,13 +227,12 @@ static bool apart_longer(const FwdParams& p, int dtype, const char* kernel, bool
     return !backward && longest > 128 && p.cpg <= 6 && (f32 ? p.W > 11 * p.H : longest > 8 * shortest);
 }
 
-bool apart_fwd(const FwdParams& p, int dtype) {
+static bool apart_in_place_of(const FwdParams& p, int dtype, FwdPlan kernel) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
     if (knobs().any || p.mask != 15 || p.xt || HW < 400 || planes > 1100 || apart_workspace_bytes(p, dtype) > APART_WORKSPACE) return false;
     const int longest = p.H > p.W ? p.H : p.W;
     const bool f32 = dtype == 0;
     size_t most;
-    const FwdPlan kernel = fwd_kernel(p, dtype);
     switch (kernel) {
         case FWD_PAIR: most = 144; break;
         case FWD_CHUNK: most = 256; break;
@@ -243,13 +242,12 @@ bool apart_fwd(const FwdParams& p, int dtype) {
     }
     return planes <= most && !apart_longer(p, dtype, kernel == FWD_STREAM ? "stream" : kernel == FWD_CHUNK ? "chunk" : kernel == FWD_ANY_SIZE ? "any size" : "", false) && apart_applicable(p, dtype);
 }
-bool apart_bwd(const BwdParams& p, int dtype) {
+static bool apart_in_place_of(const BwdParams& p, int dtype, BwdPlan kernel) {
     const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W;
     if (knobs().any || p.mask != 15 || HW < 400 || planes > 1100) return false;
     const int longest = p.H > p.W ? p.H : p.W;
     const bool f32 = dtype == 0;
     size_t most = p.kchunk > 0 ? 128 : 384;
-    const BwdPlan kernel = bwd_kernel(p, dtype);
     const char* name = kernel == BWD_ANY_SIZE ? "any size" : "";
     if (kernel == BWD_TWOPASS) {
         name = twopass_kernel_name(p, dtype);
@@ -265,6 +263,55 @@ bool apart_bwd(const BwdParams& p, int dtype) {
         most = 128;
     }
     return planes <= most && !apart_longer(reverse_sweep_params(p), dtype, name, true) && apart_bwd_applicable(p, dtype);
+}
+
+// Maps of up to 208 positions a side, global scan in all four directions: a wave per line (gspn_lines*.hip) rather than the kernels above, which
+// stage their lines through LDS by waves of their own or load them narrowly.  Both sides timed on 930 random calls (48 to 12 000 planes, the three
+// types, with logits and without, 1 to 96 channels per group); of the calls it takes, time against the kernel in their place in the mean,
+// forward 0.80 (one in 27 above 1.05, 1.3 at most), with h_save 0.83, backward 0.76; of those it leaves 1.15, 1.22, 1.11.
+//   Lines of one wave, up to 64 positions.  Any-size kernel: up to 900 planes, which are on the chip all at once, 0.83 (without maps of
+//   up to 512 pixels and ragged rows from 513 planes on, 1.0, and with h_save narrow ones of whole granules, 0.98); up to 3300 where lines
+//   fill half of a wave, 0.75 to 0.91 (shorter ones 1.1 to 1.3); beyond that large maps, 0.91 (others 1.2 to 1.7).  Plane kernel: weights
+//   of (nearly) every channel's own, which it loads element by element, 0.5 to 0.8 (fp32 lines of up to 28 in more than 1024 planes 1.1); up to 936 planes
+//   0.72; 16-bit planes of more than 6.5 KB 0.7 (its other calls 1.0 to 2.1).  Calls whose directions would run apart, from
+//   65 planes on: 0.79 without h_save, with it up to 90 000 pixels 0.92 (beyond that 1.1; with logits 0.8 to 1.1).
+//   Lines of several waves in the any-size kernel's place, 16 bits, 100 rows and more, no side twice the other: 0.87 (few planes
+//   with logits or of 113 to 128 positions 1.1; fewer rows 1.0, fp32 1.0 to 1.1, narrow maps up to 1.8).
+static bool lines_in_place_of(const FwdParams& p, int dtype, FwdPlan kernel, bool apart) {
+    if (knobs().any || p.H * p.W < 100 || p.H < 8 || !lines_applicable(p, dtype)) return false;
+    const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W, pixels = planes * HW;
+    const int longest = p.H > p.W ? p.H : p.W, shortest = p.H > p.W ? p.W : p.H;
+    const bool f32 = dtype == 0, save = p.hs != nullptr, whole = p.W % (f32 ? 4 : 8) == 0;
+    if (longest > 64)
+        return kernel == FWD_ANY_SIZE && !apart && !f32 && p.H >= 100 && 2 * shortest >= longest &&
+               (planes >= 512 || (!p.logits && (longest <= 112 || longest > 128)));
+    if (apart) return planes > 64 && !p.logits && pixels <= 90000 && shortest >= 14;      // (the same with h_save: y to the bit)
+    if (kernel == FWD_ANY_SIZE || kernel == FWD_TILE) {
+        if (planes <= 900) return !(save && whole && p.W <= 33) && !(planes > 512 && HW <= 512 && !whole);
+        if (planes <= 3300) return save ? p.W > 33 : longest > 32;
+        return longest > 40 && pixels > 6100000 && !(save && HW < 1100);
+    }
+    if (kernel == FWD_PLANE)
+        return planes <= 936 || (!f32 && HW > 3328) || (p.cpg <= 3 && !(longest <= (f32 ? 28 : 16) && planes > 1024));
+    return false;
+}
+// Backward: the same kernel as the reverse sweep, e in fp32 between it and the any-size kernels' second pass, which shares a group's
+// channels between waves where the two-pass kernels' walks them one after the other.  Any-size kernel 0.93 (up to 900 planes; beyond
+// that lines of more than 40 columns up to 2272); single-launch plane kernel 0.59, which holds a group in one workgroup (up to 1536 planes,
+// lines of up to 13 where up to 47 channels share a group; to 3936 from 12 on); two passes whose first is the any-size kernel 0.75 from 15 channels
+// per group on, lines of more than 64 0.78 with up to 15 groups and 0.86 in fp32; the plane kernel 0.75 with few groups or weights of each channel's own.
+static bool lines_in_place_of(const BwdParams& p, int dtype, BwdPlan kernel, bool apart) {
+    if (knobs().any || apart || p.H * p.W < 100 || p.H < 8 || !lines_applicable(reverse_sweep_params(p), dtype) || !ragged_finish_fits(p, dtype)) return false;
+    const size_t planes = (size_t)p.B * p.C, groups = (size_t)p.B * p.G, HW = (size_t)p.H * p.W;
+    const int longest = p.H > p.W ? p.H : p.W, shortest = p.H > p.W ? p.W : p.H;
+    const bool f32 = dtype == 0;
+    const char* first = kernel == BWD_TWOPASS ? twopass_kernel_name(p, dtype) + 8 : "";
+    const bool any_first = !strcmp(first, "any size"), plane_first = !strcmp(first, "plane");
+    if (longest > 64) return any_first && (groups <= 15 || (f32 && 2 * shortest >= longest));
+    if (kernel == BWD_ANY_SIZE) return planes <= 900 || (planes <= 2272 && p.W > 40);
+    if (kernel == BWD_PLANE) return planes >= 128 && ((planes <= 3936 && shortest > 11 && longest > 13) || (planes <= 1536 && (longest > 13 || p.cpg <= 47)));
+    if (plane_first) return groups <= 27 || (groups <= 53 && HW < 1200) || (p.cpg <= 2 && !p.logits);
+    return any_first && p.cpg > 14;
 }
 
 // Small maps, a wave per direction.  Time of what the kernels above take, 14 700 random calls of the three types, with stretches and logits,
@@ -289,15 +336,21 @@ static bool halves_fwd(const FwdParams& p, int dtype) {
     return !knobs().any && (size_t)p.B * p.C <= 128 && stream_halves_applicable(p, dtype) && fwd_kernel(p, dtype) == FWD_STREAM;
 }
 size_t fwd_workspace_bytes(const FwdParams& p, int dtype) {
-    if (apart_fwd(p, dtype)) return apart_workspace_bytes(p, dtype);
+    const FwdPlan kernel = fwd_kernel(p, dtype);
+    const bool apart = apart_in_place_of(p, dtype, kernel);
+    if (lines_in_place_of(p, dtype, kernel, apart)) return 0;
+    if (apart) return apart_workspace_bytes(p, dtype);
     return halves_fwd(p, dtype) ? stream_halves_workspace_bytes(p) : 0;
 }
 
 hipError_t launch_fwd(const FwdParams& p, int dtype, void* workspace, hipStream_t s) {
     if (small_fwd(p, dtype)) return launch_fwd_small(p, dtype, s);
-    if ((workspace || apart_workspace_bytes(p, dtype) == 0) && apart_fwd(p, dtype)) return launch_fwd_apart(p, dtype, workspace, s);
+    const FwdPlan kernel = fwd_kernel(p, dtype);
+    const bool apart = apart_in_place_of(p, dtype, kernel);
+    if (lines_in_place_of(p, dtype, kernel, apart)) return launch_lines(p, dtype, false, nullptr, s);
+    if (apart && (workspace || apart_workspace_bytes(p, dtype) == 0)) return launch_fwd_apart(p, dtype, workspace, s);
     if (workspace && halves_fwd(p, dtype)) return launch_fwd_stream_halves(p, dtype, workspace, s);
-    switch (fwd_kernel(p, dtype)) {
+    switch (kernel) {
         case FWD_TILE: return launch_fwd_tile(p, dtype, s);
         case FWD_STREAM: return launch_fwd_stream(p, dtype, s);
         case FWD_PLANE: return launch_fwd_plane(p, dtype, s);
@@ -309,8 +362,14 @@ hipError_t launch_fwd(const FwdParams& p, int dtype, void* workspace, hipStream_
 }
 
 hipError_t launch_bwd(const BwdParams& p, int dtype, hipStream_t s) {
-    if (apart_bwd(p, dtype)) return launch_bwd_apart(p, dtype, s);
-    switch (bwd_kernel(p, dtype)) {
+    const BwdPlan kernel = bwd_kernel(p, dtype);
+    const bool apart = apart_in_place_of(p, dtype, kernel);
+    if (apart) return launch_bwd_apart(p, dtype, s);
+    if (lines_in_place_of(p, dtype, kernel, apart)) {
+        const hipError_t e = launch_lines(reverse_sweep_params(p), dtype, true, dtype == 0 ? nullptr : p.gu, s);
+        return e == hipSuccess ? launch_ragged_finish(p, dtype, s) : e;
+    }
+    switch (kernel) {
         case BWD_TILE: return launch_bwd_tile(p, dtype, s);
         case BWD_PLANE: return launch_bwd_plane(p, dtype, s);
         case BWD_TWOPASS: return launch_bwd_twopass(p, dtype, s);
@@ -375,7 +434,7 @@ extern "C" const char* gspn_call_kernel(int B, int C, int H, int W, int G, int k
 
 // For the tests, bench.py and smoke(), not part of the ABI: 1 where the directions of such a call run in workgroups of their own (a
 // forward call: given the workspace it asks for), 2 where they do without a workspace, 3 where the stream kernels walk them in halves, given
-// one, 4 where they run in waves of one workgroup (small maps), else 0.
+// one, 4 where they run in waves of one workgroup (small maps), else 0.  Of a call that gspn_call_lines answers: what it runs otherwise.
 extern "C" int gspn_call_apart(int B, int C, int H, int W, int G, int kchunk, int logits, unsigned mask, int dtype, int pass) {
     using namespace gspn;
     if (kchunk >= (H > W ? H : W)) kchunk = 0;
@@ -383,13 +442,33 @@ extern "C" int gspn_call_apart(int B, int C, int H, int W, int G, int kchunk, in
         BwdParams p = {};
         p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
         p.glam = (void*)16;
-        return apart_bwd(p, dtype) ? 2 : 0;
+        return apart_in_place_of(p, dtype, bwd_kernel(p, dtype)) ? 2 : 0;
     }
     FwdParams p = {};
     p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
     p.hs = pass ? (void*)16 : nullptr;
     if (small_fwd(p, dtype)) return 4;
-    return !apart_fwd(p, dtype) ? (halves_fwd(p, dtype) ? 3 : 0) : apart_workspace_bytes(p, dtype) ? 1 : 2;
+    return !apart_in_place_of(p, dtype, fwd_kernel(p, dtype)) ? (halves_fwd(p, dtype) ? 3 : 0) : apart_workspace_bytes(p, dtype) ? 1 : 2;
+}
+
+// For the tests, bench.py and smoke(), not part of the ABI: 1 where a wave walks a line of such a call (gspn_lines*.hip; of a backward call: in
+// its first pass), else 0.
+extern "C" int gspn_call_lines(int B, int C, int H, int W, int G, int kchunk, int logits, unsigned mask, int dtype, int pass) {
+    using namespace gspn;
+    if (kchunk >= (H > W ? H : W)) kchunk = 0;
+    if (pass == 2) {
+        BwdParams p = {};
+        p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
+        p.glam = (void*)16;
+        const BwdPlan kernel = bwd_kernel(p, dtype);
+        return lines_in_place_of(p, dtype, kernel, apart_in_place_of(p, dtype, kernel));
+    }
+    FwdParams p = {};
+    p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = mask; p.kchunk = kchunk; p.logits = logits;
+    p.hs = pass ? (void*)16 : nullptr;
+    if (small_fwd(p, dtype)) return 0;
+    const FwdPlan kernel = fwd_kernel(p, dtype);
+    return lines_in_place_of(p, dtype, kernel, apart_in_place_of(p, dtype, kernel));
 }
 
 // For the tests, not part of the ABI: the launch shape of the any-size kernel where a call runs it (see ragged_shape), else 0.
