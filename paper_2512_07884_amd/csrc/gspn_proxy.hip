@@ -361,84 +361,108 @@ __global__ void __launch_bounds__(64 * NW) proxy_gradw_mfma_kernel(const T* __re
     }
 }
 
-// The same with the rows through LDS.  A matrix-core operand is 16 bytes of each of 32 rows: asked for as it is multiplied, a request
-// touches 32 lines for a quarter of each.  Here a request is eight rows of whole 128-byte lines; 128 pixels of the tile's rows make a
-// stage, the stages after it are on their way in registers, and each of the eight waves multiplies every eighth step of 16 pixels, in
-// the order of the kernel above with eight waves (on whole rows its sums, bit for bit; launches of 512 tiles and more have four there).  1152 x 144 on two 64x64 images 30 -> 18 us, on two 128x128 104 -> 53.  Every tile of the longer side is read by as many workgroups as the
-// shorter side has tiles, and each XCD has an L2 of its own: an XCD takes neighbouring tiles of the longer side with all of the
-// shorter one's.
-template <typename T, bool ANY>
-__global__ void __launch_bounds__(512) proxy_gradw_lds_kernel(const T* __restrict__ gout, const T* __restrict__ in,
-                                                              float* __restrict__ partial, int K, int M, int N,
-                                                              int mtiles, int ktiles) {
-    constexpr int ROWS = 64, PITCH = 256 + 16, AHEAD = 3;
-    __shared__ __attribute__((aligned(16))) char stage[2 * ROWS * PITCH];                // (the sums of the waves pass through it at the end)
+// The same with the rows through LDS, in tiles of 16 MT x 16 KT (v_mfma_f32_16x16x32).  A matrix-core operand is 16 bytes of each of 16
+// rows: asked for as it is multiplied, a request touches 16 lines for a part of each.  Here a request is two rows of 512 bytes, whole lines;
+// 256 pixels of the tile's rows make a stage, the stages after it are on their way in registers (three or four: 96 to 144 KB per CU, which is
+// what a CU's rate goes by), and each of the eight waves multiplies the whole tile over every eighth step of 32 pixels.  Bound by what a
+// CU takes in: 50 to 60 KB per us, of some 75 that its L1 passes on.  1152 x 144 on two 64x64 images 24 -> 15.5 us, on one 128x128 70 -> 23.5, 48 x 768
+// on two of 44x101 22.0 -> 15.8 (with 32 x 32 tiles, stages of 128 pixels and two fewer of them on their way: the figures before).
+// Every tile of the longer side is read by as many workgroups as the shorter side has tiles, and each XCD has an L2 of its own: an XCD takes
+// neighbouring tiles of the longer side with all of the shorter one's.
+// ranges = 2: two workgroups per tile and image, the second of which leaves its half of the pixels' sums in gP.
+template <typename T, bool ANY, int MT, int KT>
+__global__ void __launch_bounds__(512, MT + KT <= 4 ? 4 : 2) proxy_gradw_lds_kernel(const T* __restrict__ gout, const T* __restrict__ in,
+                                                              float* __restrict__ partial, float* __restrict__ gP, int K, int M, int N,
+                                                              int mtiles, int ktiles, int ranges) {
+    constexpr int NP = MT + KT, ROWS = 16 * NP, PX = 256, PITCH = PX * 2 + 16, AHEAD = NP <= 4 ? 3 : 4;
+    extern __shared__ __attribute__((aligned(16))) char stage[];                         // (the sums of the waves pass through it at the end)
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int per_image = mtiles * ktiles, item = (int)xcd_contiguous_item(blockIdx.x, gridDim.x);
-    const int b = item / per_image, rem = item - b * per_image;
+    const int per_image = mtiles * ktiles;
+    int rem = (int)xcd_contiguous_item(blockIdx.x, gridDim.x);
+    const int br = rem / per_image;                            // image and range of its pixels
+    rem -= br * per_image;
+    const int b = br / ranges, range = br - b * ranges;
     const int mt = mtiles <= ktiles ? rem % mtiles : rem / ktiles, kt = mtiles <= ktiles ? rem / mtiles : rem % ktiles;
-    // this thread's pieces: row threadIdx / 16 of every 32, pixels 8 * (threadIdx % 16) of the stage (rows past the end are read as the
+    const int nstages = (N + PX - 1) / PX, s_begin = range * nstages / ranges, s_end = (range + 1) * nstages / ranges;
+    // this thread's pieces: row threadIdx / 32 of every 16, pixels 8 * (threadIdx % 32) of the stage (rows past the end are read as the
     // last row, their sums are not stored)
-    const int r0 = threadIdx.x >> 4, c0 = (threadIdx.x & 15) * 8;
-    const T* const gr = gout + ((size_t)b * M + min(mt * 32 + r0, M - 1)) * N;
-    const T* const xr = in + ((size_t)b * K + min(kt * 32 + r0, K - 1)) * N;
-    struct Piece { u32x4 g, x; };
-    const int nstages = (N + 127) / 128;
+    const int r0 = threadIdx.x >> 5, c0 = (threadIdx.x & 31) * 8;
+    const T* row[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        if (i < MT) row[i] = gout + ((size_t)b * M + min((mt * MT + i) * 16 + r0, M - 1)) * N;
+        else row[i] = in + ((size_t)b * K + min((kt * KT + i - MT) * 16 + r0, K - 1)) * N;
+    }
+    struct Piece { u32x4 v[NP]; };
     auto fetch = [&](int s, Piece& p) {
-        const int n = min(s, nstages - 1) * 128 + c0, nl = min(n, N - 8);        // (beyond the rows' end: their last eight pixels)
-        ld_row<T, 16, ANY>(gr + nl, (uint32_t*)&p.g);
-        ld_row<T, 16, ANY>(xr + nl, (uint32_t*)&p.x);
+        const int nl = min(min(s, s_end - 1) * PX + c0, N - 8);                  // (beyond the rows' end: their last eight pixels)
+#pragma unroll
+        for (int i = 0; i < NP; ++i) ld_row<T, 16, ANY>(row[i] + nl, (uint32_t*)&p.v[i]);
     };
     char* const place = stage + r0 * PITCH + c0 * 2;
     auto put = [&](int s, Piece& p) {
-        const int n = s * 128 + c0;
         if (s == nstages - 1) {                                                  // (uniform) what lies beyond the rows counts as 0
-            const int sh = min(max(n - (N - 8), 0), 8);
-            if constexpr (ANY) { p.g = rg_realign<T>(p.g, sh); p.x = rg_realign<T>(p.x, sh); }
-            if (sh >= 8) p.g = p.x = u32x4{0, 0, 0, 0};
-        }
-        *(u32x4*)(place + (s & 1) * ROWS * PITCH) = p.g;
-        *(u32x4*)(place + ((s & 1) * ROWS + 32) * PITCH) = p.x;
-    };
-    f32x16_t acc;
+            const int sh = min(max(s * PX + c0 - (N - 8), 0), 8);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    const char* const from = stage + (lane & 31) * PITCH + wave * 32 + (lane >> 5) * 16;
+            for (int i = 0; i < NP; ++i) {
+                if constexpr (ANY) p.v[i] = rg_realign<T>(p.v[i], sh);
+                if (sh >= 8) p.v[i] = u32x4{0, 0, 0, 0};
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NP; ++i) *(u32x4*)(place + ((s & 1) * ROWS + 16 * i) * PITCH) = p.v[i];
+    };
+    f32x4_t acc[MT][KT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int k = 0; k < KT; ++k) acc[m][k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const char* const from = stage + (lane & 15) * PITCH + wave * 64 + (lane >> 4) * 16;
     auto multiply = [&](int s) {
-        const char* f = from + (s & 1) * ROWS * PITCH;
-        acc = mfma_k16<T>(*(const u32x4*)f, *(const u32x4*)(f + 32 * PITCH), acc);
+        const char* const f = from + (s & 1) * ROWS * PITCH;
+        u32x4 v[NP];
+#pragma unroll
+        for (int i = 0; i < NP; ++i) v[i] = *(const u32x4*)(f + 16 * i * PITCH);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int k = 0; k < KT; ++k) acc[m][k] = mfma16_k32<T>(v[m], v[MT + k], acc[m][k]);
     };
     Piece p[AHEAD];
 #pragma unroll
-    for (int i = 0; i < AHEAD; ++i) fetch(i, p[i]);
-    put(0, p[0]);
-    fetch(AHEAD, p[0]);
+    for (int i = 0; i < AHEAD; ++i) fetch(s_begin + i, p[i]);
+    put(s_begin, p[0]);
+    fetch(s_begin + AHEAD, p[0]);
     lds_barrier();
-    for (int s0 = 0; s0 < nstages; s0 += AHEAD) {
+    for (int s0 = s_begin; s0 < s_end; s0 += AHEAD) {
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
             const int s = s0 + i;
-            if (s < nstages) {
-                if (s + 1 < nstages) put(s + 1, p[(i + 1) % AHEAD]);
+            if (s < s_end) {
+                if (s + 1 < s_end) put(s + 1, p[(i + 1) % AHEAD]);
                 fetch(s + 1 + AHEAD, p[(i + 1) % AHEAD]);
                 multiply(s);
                 lds_barrier();
             }
         }
     }
-    float (*const red)[16][64] = (float (*)[16][64])stage;
-    static_assert(sizeof(float) * 8 * 16 * 64 <= sizeof(stage), "");
+    float (*const red)[MT * KT * 4][64] = (float (*)[MT * KT * 4][64])stage;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r];
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int k = 0; k < KT; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[wave][(m * KT + k) * 4 + r][lane] = acc[m][k][r];
     __syncthreads();
-    for (int idx = threadIdx.x; idx < 16 * 64; idx += 512) {
-        const int r = idx >> 6, l = idx & 63;
+    float* const to = range == 0 ? partial + (size_t)b * M * K : gP;
+    for (int idx = threadIdx.x; idx < MT * KT * 256; idx += 512) {
+        const int r = idx >> 6, l = idx & 63, t = r >> 2;
         float v = red[0][r][l];
 #pragma unroll
         for (int w = 1; w < 8; ++w) v += red[w][r][l];
-        const int m = mt * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3), k = kt * 32 + (l & 31);
-        if (m < M && k < K) partial[((size_t)b * M + m) * K + k] = v;
+        const int m = (mt * MT + t / KT) * 16 + 4 * (l >> 4) + (r & 3), k = (kt * KT + t % KT) * 16 + (l & 15);
+        if (m < M && k < K) to[(size_t)m * K + k] = v;
     }
 }
 
@@ -535,10 +559,15 @@ __global__ void __launch_bounds__(256) proxy_gradw_fma_kernel(const T* __restric
     if (m < M && k < K) partial[((size_t)b * M + m) * K + k] = acc;
 }
 
-// gP = the per-image sums added in image order
-__global__ void __launch_bounds__(256) proxy_gradw_sum_kernel(const float* __restrict__ partial, float* __restrict__ gP, int B, int MK) {
+// gP = the per-image sums added in image order (halves: of one image, whose second half's sums are in gP)
+__global__ void __launch_bounds__(256) proxy_gradw_sum_kernel(float* __restrict__ partial, float* __restrict__ gP, int B, int MK, bool halves) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= MK) return;
+    if (halves) {
+        const float v = partial[i] + gP[i];
+        partial[i] = v; gP[i] = v;
+        return;
+    }
     float v = 0.f;
     // sixteen images requested at a time (the loads do not depend on the sum), then added in order
     for (int b0 = 0; b0 < B; b0 += 16) {
@@ -635,9 +664,20 @@ hipError_t launch_proxy_project(const void* in, const void* P, void* out, int B,
     return launch_project_as<f16_t, false>(in, P, out, B, K, M, N, mfma, s);
 }
 
-// per-image sums of gout in^T into `partial` (B*M*K floats), storage type T
+template <typename T, int MT, int KT>
+static hipError_t launch_gradw_lds(const void* gout, const void* in, float* partial, float* gP, int B, int K, int M, int N, int ranges, hipStream_t s) {
+    const int mt = (M + 16 * MT - 1) / (16 * MT), kt = (K + 16 * KT - 1) / (16 * KT);
+    constexpr int stages = 2 * 16 * (MT + KT) * (256 * 2 + 16), sums = 8 * MT * KT * 256 * 4, lds = stages > sums ? stages : sums;
+    void (*k)(const T*, const T*, float*, float*, int, int, int, int, int, int) = N % 8 ? proxy_gradw_lds_kernel<T, true, MT, KT> : proxy_gradw_lds_kernel<T, false, MT, KT>;
+    const hipError_t e = allow_dynamic_lds((const void*)k, 160 * 1024);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k, dim3((unsigned)((long)B * ranges * mt * kt)), dim3(512), lds, s, (const T*)gout, (const T*)in, partial, gP, K, M, N, mt, kt, ranges);
+    return hipGetLastError();
+}
+
+// per-image sums of gout in^T into `partial` (B*M*K floats), storage type T; halves: of one image, the sums of its second half into gP
 template <typename T>
-static hipError_t launch_gradw_as(const void* gout, const void* in, float* partial, int B, int K, int M, int N, hipStream_t s) {
+static hipError_t launch_gradw_as(const void* gout, const void* in, float* partial, float* gP, bool* halves, int B, int K, int M, int N, hipStream_t s) {
     const bool mfma = sizeof(T) == 2 && N >= 8;
     const int mtiles = mfma ? (M + 31) / 32 : (M + 7) / 8;
     const int ktiles = (K + 31) / 32;
@@ -645,8 +685,10 @@ static hipError_t launch_gradw_as(const void* gout, const void* in, float* parti
     if constexpr (sizeof(T) == 2) {
         // 16 x 16 tiles where 32 x 32 ones are fewer than a quarter of the CUs and the rows are long (two images, 32 x 32 -> 16 x
         // 16: 8 <- 96 channels on 96x96 26.8 -> 17.0 us; below 4096 pixels no gain in the mean and up to 7 % lost: 48 <- 96 on
-        // 56x56 16.1 -> 17.2.  Rows at any element: 0.94 of the time in the mean from 1024 pixels on)
-        if (mfma && tiles < 64 && N >= (N % 8 ? 1024 : 4096)) {
+        // 56x56 16.1 -> 17.2.  Rows at any element: 0.94 of the time in the mean from 1024 pixels on).  Not for odd rows, half of
+        // whose requests fall between 32-bit words and are worked off in twice the time: there the rows pass once, through LDS
+        // (24 <- 192 on four images 89x111 52 -> 32 us, 24 <- 384 on two of 111x79 55 -> 29).
+        if (mfma && tiles < 64 && N % 2 == 0 && N >= (N % 8 ? 1024 : 4096)) {
             const int mt = (M + 15) / 16, kt = (K + 15) / 16;
             void (*k)(const T*, const T*, float*, int, int, int, int, int) = N % 8 ? proxy_gradw_small_kernel<T, true> : proxy_gradw_small_kernel<T, false>;
             hipLaunchKernelGGL(k, dim3((unsigned)((long)B * mt * kt)), dim3(1024), 0, s, (const T*)gout, (const T*)in, partial, K, M, N, mt, kt);
@@ -654,17 +696,32 @@ static hipError_t launch_gradw_as(const void* gout, const void* in, float* parti
         }
     }
     if constexpr (sizeof(T) == 2) {
-        // The rows through LDS where they are long or tiles enough to fill the chip; 4900 random products, share of the time of the
-        // kernel below: 2048 pixels and more 0.6 in the mean, 1024 to 2047 from 64 tiles on 0.8, 512 to 1023 from 256 tiles on 0.83.
-        // Shorter rows are a stage or two each (up to 511 pixels 1.03), few tiles wait for their stages (1024 pixels, 16 tiles 1.03).
-        // With a single tile on one side there is less to share: rows at any element from 1024 pixels on 0.77, whole ones from 4096 pixels
-        // and 256 tiles on 0.72, below that 0.97 (96 x 8 on 64 images 56x56 15.4 -> 16.7).  (A launch counts its threads in 32 bits.)
-        const bool shared = mtiles > 1 && ktiles > 1;
-        if (mfma && tiles <= 0x7fffff && (shared ? (N >= 2048 && tiles >= 16) || (N >= 1024 && tiles >= 64) || (N >= 512 && tiles >= 256)
-                                                        : N % 8 ? N >= 1024 : N >= 4096 && tiles >= 256)) {
-            void (*k)(const T*, const T*, float*, int, int, int, int, int) = N % 8 ? proxy_gradw_lds_kernel<T, true> : proxy_gradw_lds_kernel<T, false>;
-            hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(512), 0, s, (const T*)gout, (const T*)in, partial, K, M, N, mtiles, ktiles);
-            return hipGetLastError();
+        // The rows through LDS where they are long or tiles enough to fill the chip.  Share of the time of the kernel below in 90 random
+        // products (8 to 1152 channels, 1 to 16 images): 1024 pixels and more 0.4 to 1.0, 512 to 1023 from 256 tiles on 0.9; shorter rows
+        // are a stage or two each (304 x 353 on 14 images of 336 pixels 13.7 -> 20.3 us).  (A launch counts its threads in 32 bits.)
+        if (mfma && tiles <= 0x3fffff && (N >= 1024 || (N >= 512 && tiles >= 256))) {
+            // One image leaves `partial` a single place: its second half's sums go to gP on the way (144 x 1152 channels on
+            // 128x128 32.7 -> 28.6 us, 24 <- 192 on 123x49 23.2 -> 16.3).
+            *halves = B == 1;
+            const int ranges = *halves ? 2 : 1;
+            // The tile: what a CU takes in, rows per tile times turns of 256 workgroups, is what the time goes by.  32 x 32 has two
+            // workgroups on a CU, which hide each other's start and end (0.75 of that); 64 x 64 nearly runs out of registers (1.15).
+            // us with 32 x 32, 48 x 32, 48 x 48, 64 x 64: 144 x 1152 on two 64x64 images 18.3 15.3 17.6 22.6; 48 x 1152 on 14 images 72x81
+            // 66 56 65 48, on six of 105x48 22.4 18.8 21.3 27.2; 144 x 768 on four of 118x18 18.7 25.2 17.7 22.3.  Rows of less than
+            // eight stages are not worth a second start: 144 x 1152 on 16 images 28x28 35 39 36 38.
+            const int shapes[][2] = {{2, 2}, {3, 2}, {2, 3}, {3, 3}, {4, 4}};
+            long best = -1;
+            int mt = 2, kt = 2;
+            for (const auto& t : shapes) {
+                const long wgs = (long)B * ranges * ((M + 16 * t[0] - 1) / (16 * t[0])) * ((K + 16 * t[1] - 1) / (16 * t[1])), turns = (wgs + 255) / 256;
+                const bool pair = t[0] == 2 && t[1] == 2;
+                if (!pair && turns > 1 && N < 2048) continue;
+                const long cost = turns * (t[0] + t[1]) * (pair && turns > 1 ? 75 : t[0] == 4 ? 115 : 100);
+                if (best < 0 || cost < best) { best = cost; mt = t[0]; kt = t[1]; }
+            }
+            return mt == 4 ? launch_gradw_lds<T, 4, 4>(gout, in, partial, gP, B, K, M, N, ranges, s)
+                 : mt == 3 ? (kt == 3 ? launch_gradw_lds<T, 3, 3>(gout, in, partial, gP, B, K, M, N, ranges, s) : launch_gradw_lds<T, 3, 2>(gout, in, partial, gP, B, K, M, N, ranges, s))
+                           : (kt == 3 ? launch_gradw_lds<T, 2, 3>(gout, in, partial, gP, B, K, M, N, ranges, s) : launch_gradw_lds<T, 2, 2>(gout, in, partial, gP, B, K, M, N, ranges, s));
         }
     }
     const long blocks = (long)B * mtiles * ktiles;
@@ -699,12 +756,13 @@ hipError_t launch_proxy_project_bwd(const void* gout, const void* in, const void
     }
     if (gP) {
         if (!partial) return hipErrorInvalidValue;
-        hipError_t e = dtype == 0 ? launch_gradw_as<float>(gout, in, partial, B, K, M, N, s)
-                     : dtype == 1 ? launch_gradw_as<bf16_t>(gout, in, partial, B, K, M, N, s)
-                                  : launch_gradw_as<f16_t>(gout, in, partial, B, K, M, N, s);
+        bool halves = false;
+        hipError_t e = dtype == 0 ? launch_gradw_as<float>(gout, in, partial, gP, &halves, B, K, M, N, s)
+                     : dtype == 1 ? launch_gradw_as<bf16_t>(gout, in, partial, gP, &halves, B, K, M, N, s)
+                                  : launch_gradw_as<f16_t>(gout, in, partial, gP, &halves, B, K, M, N, s);
         if (e != hipSuccess) return e;
         const int MK = M * K;
-        hipLaunchKernelGGL(proxy_gradw_sum_kernel, dim3((unsigned)((MK + 255) / 256)), dim3(256), 0, s, partial, gP, B, MK);
+        hipLaunchKernelGGL(proxy_gradw_sum_kernel, dim3((unsigned)((MK + 255) / 256)), dim3(256), 0, s, partial, gP, B, MK, halves);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
