@@ -17,8 +17,8 @@
 // loaded ONCE per workgroup into LDS and read by all its channels; every request is a complete
 // cache line.  Rows in LDS have an odd pitch so that both access orientations are conflict-free.
 //
-// Maps whose rows are not whole 16 B chunks (7x7, 14x14, 28x28 bf16: the later stages of a classifier) take
-// the FLAT variant: LDS planes without padding, so that a chunk's place in LDS is its place in memory and
+// Maps whose rows are not whole 16 B chunks (7x7, 14x14, 28x28 bf16: the later stages of a classifier), and small
+// maps whose rows are, take the FLAT variant: LDS planes without padding, so that a chunk's place in LDS is its place in memory and
 // chunks may run over row and channel ends; 2, 4 or 8 channels side by side in a wave (32, 16 or 8 lanes
 // each) so that the wave's channels together are whole chunks; weights fetched in the widest pieces their
 // alignment allows.
@@ -255,28 +255,44 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
             const int ew = lw / (int)sizeof(T);            // elements per request; divides nel (host)
             const int t0 = SHARED ? (int)threadIdx.x : lane, tn = SHARED ? nthreads : 64;
             const rsrc_t rs = make_rsrc(wptr(d, SHARED ? g : c0));
-            for (int c = t0; c * ew < nel; c += tn) {
-                const int idx0 = c * ew;
-                const uint32_t bo = (uint32_t)(idx0 * (int)sizeof(T));
-                u32x4 v = {0, 0, 0, 0};
-                if (lw == 16) v = ldg(rs, bo, 0);
-                else if (lw == 8) { const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, bo, 0, 0); v[0] = t.x; v[1] = t.y; }
-                else if (lw == 4) v[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, bo, 0, 0);
-                else v[0] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, bo, 0, 0);
-                int chn = idx0 / (3 * HW);
-                int r = idx0 - chn * 3 * HW;
-                int tap = r / HW;
-                r -= tap * HW;
-                int row = r / W, col = r - row * W;
+            // Weights of the wave's own channels four pieces at a time: piece by piece it waited for the memory up to 24 times per
+            // direction (11136 planes 16x14 fp32 268 -> 226 us).  A group's are few pieces per thread, and the registers cost more there (9216
+            // planes 14x14 f16 20 -> 30).
+            constexpr int WB = SHARED ? 1 : 4;
+            for (int cb = t0; cb * ew < nel; cb += WB * tn) {
+                u32x4 wv4[WB];
 #pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    if (e < ew) {
-                        // a tap that points outside the line is stored as 0, whatever the tensor holds there
-                        const int pos = vert ? col : row;
-                        const bool outside = (tap == 0 && pos == 0) || (tap == 2 && pos == L - 1) || no_pred(row, col);
-                        plds_st(wreg + 4u * (uint32_t)(chn * 4 * HP + 4 * (row * P + col) + tap),
-                                outside ? masked : chunk_elem<T>(v, e));
-                        if (++col == W) { col = 0; if (++row == H) { row = 0; if (++tap == 3) { tap = 0; ++chn; } } }
+                for (int j = 0; j < WB; ++j) {
+                    const int c = cb + j * tn;
+                    const uint32_t bo = (uint32_t)(c * lw);
+                    u32x4 v = {0, 0, 0, 0};
+                    if (c * ew < nel) {
+                        if (lw == 16) v = ldg(rs, bo, 0);
+                        else if (lw == 8) { const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, bo, 0, 0); v[0] = t.x; v[1] = t.y; }
+                        else if (lw == 4) v[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, bo, 0, 0);
+                        else v[0] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, bo, 0, 0);
+                    }
+                    wv4[j] = v;
+                }
+#pragma unroll
+                for (int j = 0; j < WB; ++j) {
+                    const int c = cb + j * tn, idx0 = c * ew;
+                    if (idx0 >= nel) break;
+                    int chn = idx0 / (3 * HW);
+                    int r = idx0 - chn * 3 * HW;
+                    int tap = r / HW;
+                    r -= tap * HW;
+                    int row = r / W, col = r - row * W;
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        if (e < ew) {
+                            // a tap that points outside the line is stored as 0, whatever the tensor holds there
+                            const int pos = vert ? col : row;
+                            const bool outside = (tap == 0 && pos == 0) || (tap == 2 && pos == L - 1) || no_pred(row, col);
+                            plds_st(wreg + 4u * (uint32_t)(chn * 4 * HP + 4 * (row * P + col) + tap),
+                                    outside ? masked : chunk_elem<T>(wv4[j], e));
+                            if (++col == W) { col = 0; if (++row == H) { row = 0; if (++tap == 3) { tap = 0; ++chn; } } }
+                        }
                     }
                 }
             }
@@ -470,18 +486,25 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
 // ---------------------------------------------------------------------------
 static constexpr int FPLANE_LDS_BUDGET = 160 * 1024;
 
-struct FwdPlanePlan { bool ok, flat, small; int K, cpw, lsh, nwaves, pitch, shared_group, wlw; size_t lds; };
+struct FwdPlanePlan { bool ok, flat, small; int most_waves, K, cpw, lsh, nwaves, pitch, shared_group, wlw; size_t lds; };
 
 // waves per workgroup and LDS bytes, given the channels per wave and the bytes of one fp32 plane region
 static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp) {
     if (p.cpg == 1) {
         t.shared_group = 0;
-        // per wave: cpw * (4 weight + 1 a/h) planes; aim at 4 waves per workgroup
-        int nw = 4;
-        while (nw > 1 && (p.C % (nw * t.cpw) || (size_t)nw * t.cpw * 5 * hp > (size_t)FPLANE_LDS_BUDGET)) --nw;
-        if (p.C % (nw * t.cpw) || (size_t)nw * t.cpw * 5 * hp > (size_t)FPLANE_LDS_BUDGET) return false;
-        t.nwaves = nw; t.K = nw * t.cpw;
-        t.lds = (size_t)nw * t.cpw * 5 * hp;
+        // per wave: cpw * (4 weight + 1 a/h) planes; of up to 4 waves per workgroup the number with which the most fit on a CU (LDS comes
+        // in pieces of 1280 bytes), the larger of equals.  24576 planes of 16x16: 4 waves of 87 KB, or twice 3 of 65 KB
+        const size_t wave = (size_t)t.cpw * 5 * hp;
+        int best = 0;
+        for (int nw = 4; nw >= 1; --nw) {
+            if (p.C % (nw * t.cpw) || nw * wave > (size_t)FPLANE_LDS_BUDGET) continue;
+            const int fit = (int)((size_t)FPLANE_LDS_BUDGET / ((nw * wave + 1279) / 1280 * 1280)), waves = (fit < 1 ? 1 : fit) * nw;
+            const int on_cu = waves < t.most_waves ? waves : t.most_waves;
+            if (on_cu > best) { best = on_cu; t.nwaves = nw; }
+        }
+        if (!best) return false;
+        t.K = t.nwaves * t.cpw;
+        t.lds = t.nwaves * wave;
     } else {
         t.shared_group = 1;
         // the most waves (up to 8) whose channels divide the group and whose planes fit beside the weights
@@ -498,27 +521,26 @@ static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp)
     return (size_t)p.B * (p.C / t.K) <= 0x7fffffffull;
 }
 
-static FwdPlanePlan plan_fwd_plane(const FwdParams& p, int dtype) {
+// padded planes (rows of whole 16-byte chunks), one or two channels per wave
+static FwdPlanePlan plan_fwd_plane_padded(const FwdParams& p, int es) {
     FwdPlanePlan t = {};
-    const int es = dtype == 0 ? 4 : 2, E = 16 / es;
-    if (p.H < 2 || p.W < 2 || p.H > 64 || p.W > 64) return t;
-    if (p.xt) return t;                                    // transposed-horizontal layout: tile and generic kernels
-    const int HW = p.H * p.W;
-    const int m = p.H > p.W ? p.H : p.W;
-    if (p.W % E == 0) {
-        // padded planes, one or two channels per wave
-        t.cpw = m <= 32 ? 2 : 1;
-        if ((size_t)t.cpw * HW * es > 8192) {
-            if (t.cpw == 2 && (size_t)HW * es <= 8192) t.cpw = 1; else return t;
-        }
-        if (p.cpg == 1 ? p.C % t.cpw : p.cpg % t.cpw) t.cpw = 1;
-        t.lsh = t.cpw == 2 ? 5 : 6;
-        t.pitch = p.W | 1;
-        const size_t hp = (((size_t)p.H * t.pitch + 3) & ~(size_t)3) * sizeof(float);   // one plane region in LDS
-        t.ok = plan_fwd_plane_waves(p, t, hp);
-        return t;
+    const int HW = p.H * p.W, m = p.H > p.W ? p.H : p.W;
+    t.cpw = m <= 32 ? 2 : 1;
+    if ((size_t)t.cpw * HW * es > 8192) {
+        if (t.cpw == 2 && (size_t)HW * es <= 8192) t.cpw = 1; else return t;
     }
-    // flat planes: the most channels per wave (each on 64 / cpw lanes) that are whole 16 B chunks together
+    if (p.cpg == 1 ? p.C % t.cpw : p.cpg % t.cpw) t.cpw = 1;
+    t.lsh = t.cpw == 2 ? 5 : 6;
+    t.pitch = p.W | 1;
+    t.most_waves = es == 4 ? 8 : 4;                        // (registers, weights of each channel's own)
+    const size_t hp = (((size_t)p.H * t.pitch + 3) & ~(size_t)3) * sizeof(float);   // one plane region in LDS
+    t.ok = plan_fwd_plane_waves(p, t, hp);
+    return t;
+}
+// flat planes: the most channels per wave (each on 64 / cpw lanes) that are whole 16 B chunks together
+static FwdPlanePlan plan_fwd_plane_flat(const FwdParams& p, int es) {
+    FwdPlanePlan t = {};
+    const int HW = p.H * p.W, m = p.H > p.W ? p.H : p.W;
     t.flat = true;
     int lsh = 3;
     while ((1 << lsh) < m) ++lsh;
@@ -533,11 +555,32 @@ static FwdPlanePlan plan_fwd_plane(const FwdParams& p, int dtype) {
     // small maps (at most four 16 B chunks per lane) get an odd pitch like the padded variant; larger ones keep rows packed
     t.small = (size_t)t.cpw * HW * es <= 4 * 64 * 16;
     t.pitch = t.small ? (p.W | 1) : p.W;
+    t.most_waves = !t.small ? 8 : es == 4 ? 16 : 12;
     // shared weights: the widest request that divides a group's block (its start is a multiple of its size)
     const size_t wblock = (size_t)3 * HW * es;
     t.wlw = wblock % 16 == 0 ? 16 : wblock % 8 == 0 ? 8 : wblock % 4 == 0 ? 4 : 2;
     t.ok = plan_fwd_plane_waves(p, t, t.small ? (((size_t)p.H * t.pitch + 3) & ~(size_t)3) * sizeof(float) : (size_t)HW * sizeof(float));
     return t;
+}
+
+// Rows of whole chunks take the padded variant, but for small maps, whose lines leave most lanes of its waves idle (up to 16 positions: two channels
+// per wave where four or eight have their place) or, in fp32 with shared weights, whose chunks need half of its registers.  Both timed on
+// the same calls, us: 36864 planes 8x8 bf16, forward 115 -> 40, 45312 of 11x8 fp32 125 -> 47, 73728 of 16x16 bf16 with logits 243 -> 163, 9216 of
+// 14x12 fp32 38 -> 19, 36864 of 17x16 fp32 121 -> 91; 0.6 in the mean of 120 calls, the longest 1.08 (7680 of 16x16 f16 with stretches).  Beyond the
+// lines: 24x24 f16 48 -> 60, 25x28 fp32 63 -> 76; weights of each channel's own, 20x20 fp32 71 -> 125, 18432 of 16x16 fp32 97 -> 126 (12x12 78 -> 60);
+// too few workgroups, 1152 of 16x16 f16 13.6 -> 16.8, with weights of their own 17 -> 30.
+static FwdPlanePlan plan_fwd_plane(const FwdParams& p, int dtype) {
+    const int es = dtype == 0 ? 4 : 2, m = p.H > p.W ? p.H : p.W;
+    if (p.H < 2 || p.W < 2 || p.H > 64 || p.W > 64) return FwdPlanePlan{};
+    if (p.xt) return FwdPlanePlan{};                       // transposed-horizontal layout: tile and generic kernels
+    if (p.W % (16 / es)) return plan_fwd_plane_flat(p, es);
+    const bool shared_f32 = dtype == 0 && p.cpg > 1;
+    if (m <= 16 || shared_f32) {
+        const FwdPlanePlan t = plan_fwd_plane_flat(p, es);
+        const bool fills = t.ok && (p.cpg > 1 ? (size_t)p.B * (p.C / t.K) >= 192 : (size_t)p.B * (p.C / t.cpw) >= 768 && (es == 2 || p.H * p.W <= 144));
+        if (fills && t.small && (t.cpw > 2 || (shared_f32 && t.cpw == 2))) return t;
+    }
+    return plan_fwd_plane_padded(p, es);
 }
 
 bool fwd_plane_applicable(const FwdParams& p, int dtype) { return plan_fwd_plane(p, dtype).ok; }

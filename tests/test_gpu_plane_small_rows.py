@@ -1,0 +1,59 @@
+"""Small maps whose rows are whole 16-byte chunks, on the plane kernels with two, four and eight channels per wave (lines of up to 32, 16 and
+8 lanes, some as long as the lanes of a channel), against the line-by-line kernels: on either side of each line of the choice -- sides, planes
+per workgroup, weights of each channel's own, fp32 maps of up to 4 KB per wave -- with stretches and logits.
+
+y and the states are sums of four products in fp32 in another order than line by line; gw is summed in storage precision there (fp32 alone
+compares it)."""
+import pytest
+
+from test_gpu_apart import close, inputs
+
+pytestmark = pytest.mark.gpu
+
+# (B, C, H, W, G), dtype, kchunk, logits
+CALLS = [
+    ((2, 1536, 8, 8, 192), "bf16", 0, False), ((2, 1536, 5, 8, 192), "f16", 3, True), ((4, 1536, 4, 4, 192), "f32", 0, False),
+    ((2, 768, 16, 16, 192), "bf16", 0, True), ((2, 768, 9, 16, 192), "f16", 4, False), ((2, 768, 11, 12, 192), "f32", 0, False), ((2, 768, 16, 4, 192), "f32", 5, True),
+    ((1, 768, 16, 8, 191 + 1), "f16", 0, False), ((1, 764, 16, 8, 191), "f16", 0, False),
+    ((1, 384, 17, 16, 192), "f32", 0, False), ((1, 382, 17, 16, 191), "f32", 0, False), ((1, 384, 22, 20, 192), "f32", 0, True), ((1, 384, 24, 24, 192), "f32", 0, False),
+    # weights of each channel's own
+    ((1, 3072, 12, 12, 3072), "f32", 0, False), ((1, 3072, 12, 16, 3072), "f32", 0, False), ((1, 3072, 16, 16, 3072), "f16", 0, True), ((1, 3068, 16, 16, 3068), "bf16", 0, False),
+    ((2, 3072, 7, 8, 3072), "bf16", 2, False), ((1, 510, 28, 28, 510), "f32", 0, True),
+]
+
+
+def run(call, inp, shape, dtype, kchunk, logits, h=None):
+    import torch
+    import paper_2512_07884_amd as G
+    x, w, lam, u = inp["x"], inp["w"], inp["lam"], inp["u"]
+    fresh = lambda t: torch.full_like(t, float("nan"))
+    kw = {"G": shape[4], **({"kchunk": kchunk} if kchunk else {})}
+    kind = "_logits" if logits else "_local" if kchunk else ""
+    if call == "bwd":
+        o = {"gx": fresh(x), "gw": fresh(w), "glam": fresh(lam), "gu": fresh(lam)}
+        getattr(G, "gspn_scan_bwd" + kind)(inp["gy"], x, w, lam, u, h, *o.values(), **kw)
+        if dtype != "f32":
+            del o["gw"]
+    else:
+        o = {"y": fresh(x), **({"h": fresh(lam)} if call == "save" else {})}
+        getattr(G, "gspn_scan_fwd" + kind)(x, w, lam, u, o["y"], o.get("h"), **kw)
+    torch.cuda.synchronize()
+    return o
+
+
+@pytest.mark.parametrize("shape,dtype,kchunk,logits", CALLS, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+def test_against_line_by_line(shape, dtype, kchunk, logits, monkeypatch):
+    from paper_2512_07884_amd import binding
+    inp = inputs(shape, dtype, logits)
+    monkeypatch.setenv("GSPN_FORCE_GENERIC", "1"); binding.gspn_reload_env()
+    ref = run("save", inp, shape, dtype, kchunk, logits)
+    ref_bwd = run("bwd", inp, shape, dtype, kchunk, logits, ref["h"])
+    monkeypatch.delenv("GSPN_FORCE_GENERIC")
+    for knob in ("GSPN_NO_APART", "GSPN_NO_ANY_SIZE", "GSPN_BWD_NO_PLANE"):          # the plane kernels, whatever else would take the call
+        monkeypatch.setenv(knob, "1")
+    binding.gspn_reload_env()
+    code = {"f32": 0, "bf16": 1, "f16": 2}[dtype]
+    for call, want in (("fwd", "plane"), ("save", "plane"), ("bwd", "twopass/plane")):
+        assert binding.running_kernel(*shape, code, call, kchunk, logits) == want, call
+        got = run(call, inp, shape, dtype, kchunk, logits, ref["h"])
+        close(got, ref if call != "bwd" else ref_bwd, dtype, ())
