@@ -83,12 +83,13 @@ struct FwdPlaneArgs {
 // products to the positions those taps read from (e_t = u_t*gy_t + T_{t+1}^T e_{t+1}).  The taps that are stored as 0
 // (out-of-line neighbours, GSPN-local: lines that start a stretch) are the ones that must pass nothing on here too.
 // NCHT: 16 B chunks per lane the register arrays are sized for (8: the wave's channels hold at most 8 KB; 4: small maps
-// of the flat variant, which then has the registers to give its LDS planes an odd pitch too -- every element's place is
+// with weights of each channel's own, and those of the flat variant, which then has the registers to give its LDS planes an odd pitch too -- every element's place is
 // tracked through two bit masks per chunk)
 template <typename T, bool SAVE, bool SHARED, bool WPRE, bool FLAT, bool LOCAL, bool BWD = false, int NCHT = 8>
 __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneArgs a) {
     static_assert(!(FLAT && WPRE), "the flat variant fetches its weights in place");
-    static_assert(NCHT == 8 || (NCHT == 4 && FLAT), "the short register arrays are for small maps of the flat variant");
+    static_assert(NCHT == 8 || (NCHT == 4 && (FLAT || !SHARED)), "the short register arrays are for small maps of the flat variant and with weights of each channel's own");
+    constexpr bool WAHEAD = !SHARED && !FLAT && NCHT == 4;        // at most 4 KB of channels per wave, their weights requested a direction ahead
     constexpr bool PADFLAT = FLAT && NCHT == 4;    // flat variant with padded LDS planes
     static_assert(!BWD || SAVE, "the reverse sweep saves its state");
     constexpr int E = 16 / (int)sizeof(T);        // elements per 16 B chunk
@@ -215,10 +216,23 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
     auto wptr = [&](int dd, int grp) {
         return (const T*)p.w + (p.shared ? (size_t)0 : (size_t)dd * groups * 3 * HW) + ((size_t)b * p.G + grp) * 3 * HW;
     };
-    u32x4 ls[NCH], us[NCH], wsh[WSH];
+    u32x4 ls[NCH], us[NCH], wsh[WSH], wa[WAHEAD ? 3 : 1][NCH];
+    auto load_wahead = [&](int dd) {
+#pragma unroll
+        for (int t = 0; t < (WAHEAD ? 3 : 0); ++t) {
+            const rsrc_t rs = make_rsrc(wptr(dd, c0) + (size_t)t * HW);
+#pragma unroll
+            for (int k = 0; k < NCH; ++k) {
+                u32x4 v = {0, 0, 0, 0};
+                if (vq[k]) v = __builtin_amdgcn_raw_buffer_load_b128(rs, flat + (uint32_t)(ch[k] * 2 * HW * (int)sizeof(T)), k * 1024, CP_STREAM);
+                wa[t][k] = v;
+            }
+        }
+    };
     if (d < 4) {
         load_planes((const T*)p.lam + slot_c(d) + pc, ls);
         if constexpr (SHARED && WPRE) load_wshare(wptr(d, g), wsh);
+        if constexpr (WAHEAD) load_wahead(d);
     }
 
     while (d < 4) {
@@ -337,7 +351,8 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
 #pragma unroll
                 for (int k = 0; k < NCH; ++k) {
                     u32x4 v = {0, 0, 0, 0};
-                    if (vq[k]) v = ldg(rs, (uint32_t)(((ch[k] * 2 * HW) + (k * 64 + lane) * E) * (int)sizeof(T)), 0);
+                    if constexpr (WAHEAD) v = wa[t][k];
+                    else if (vq[k]) v = ldg(rs, (uint32_t)(((ch[k] * 2 * HW) + (k * 64 + lane) * E) * (int)sizeof(T)), 0);
                     wt[k] = v;
                 }
 #pragma unroll
@@ -375,6 +390,7 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
         if (dn < 4) {
             load_planes((const T*)p.lam + slot_c(dn) + pc, ls);
             if constexpr (SHARED && WPRE) load_wshare(wptr(dn, g), wsh);
+            if constexpr (WAHEAD) load_wahead(dn);
         }
         if constexpr (SHARED) lds_barrier();               // weights of this direction are in place (LDS only: the
                                                            // requests above stay in flight across the barrier)
@@ -526,13 +542,18 @@ static FwdPlanePlan plan_fwd_plane_padded(const FwdParams& p, int es) {
     FwdPlanePlan t = {};
     const int HW = p.H * p.W, m = p.H > p.W ? p.H : p.W;
     t.cpw = m <= 32 ? 2 : 1;
+    // Weights of each channel's own: the channels that four chunks per lane hold.  The registers then hold their weights a direction ahead, where eight
+    // chunks per lane waited for the memory three times per direction, on four waves per CU.  6144 planes 28x28 fp32 92 -> 78 us (step
+    // with logits 357 -> 335), 8448 of 36x32 f16 (step) 750 -> 467, 32256 of 19x16 f16 411 -> 152; 0.92 in the mean of 89 calls, the longest 1.03.
+    t.small = p.cpg == 1 && HW * es <= 4096;
+    if (t.small && 2 * HW * es > 4096) t.cpw = 1;
     if ((size_t)t.cpw * HW * es > 8192) {
         if (t.cpw == 2 && (size_t)HW * es <= 8192) t.cpw = 1; else return t;
     }
     if (p.cpg == 1 ? p.C % t.cpw : p.cpg % t.cpw) t.cpw = 1;
     t.lsh = t.cpw == 2 ? 5 : 6;
     t.pitch = p.W | 1;
-    t.most_waves = es == 4 ? 8 : 4;                        // (registers, weights of each channel's own)
+    t.most_waves = es == 4 ? (t.small ? 12 : 8) : t.small ? 8 : 4;      // (registers, weights of each channel's own)
     const size_t hp = (((size_t)p.H * t.pitch + 3) & ~(size_t)3) * sizeof(float);   // one plane region in LDS
     t.ok = plan_fwd_plane_waves(p, t, hp);
     return t;
@@ -567,8 +588,9 @@ static FwdPlanePlan plan_fwd_plane_flat(const FwdParams& p, int es) {
 // per wave where four or eight have their place) or, in fp32 with shared weights, whose chunks need half of its registers.  Both timed on
 // the same calls, us: 36864 planes 8x8 bf16, forward 115 -> 40, 45312 of 11x8 fp32 125 -> 47, 73728 of 16x16 bf16 with logits 243 -> 163, 9216 of
 // 14x12 fp32 38 -> 19, 36864 of 17x16 fp32 121 -> 91; 0.6 in the mean of 120 calls, the longest 1.08 (7680 of 16x16 f16 with stretches).  Beyond the
-// lines: 24x24 f16 48 -> 60, 25x28 fp32 63 -> 76; weights of each channel's own, 20x20 fp32 71 -> 125, 18432 of 16x16 fp32 97 -> 126 (12x12 78 -> 60);
-// too few workgroups, 1152 of 16x16 f16 13.6 -> 16.8, with weights of their own 17 -> 30.
+// lines: 24x24 f16 48 -> 60, 25x28 fp32 63 -> 76; too few workgroups, 1152 of 16x16 f16 13.6 -> 16.8.  Weights of each channel's own: up to
+// 128 pixels in 16 bits (5x8 36 us for 105, 16x8 26 for 32; 13x16 60 for 46, 15x16 30 for 14), 80 in fp32 (10x8 71 for 78; 12x12 28 for 24.5, with
+// stretches 36 for 42), and 768 waves.
 static FwdPlanePlan plan_fwd_plane(const FwdParams& p, int dtype) {
     const int es = dtype == 0 ? 4 : 2, m = p.H > p.W ? p.H : p.W;
     if (p.H < 2 || p.W < 2 || p.H > 64 || p.W > 64) return FwdPlanePlan{};
@@ -577,7 +599,7 @@ static FwdPlanePlan plan_fwd_plane(const FwdParams& p, int dtype) {
     const bool shared_f32 = dtype == 0 && p.cpg > 1;
     if (m <= 16 || shared_f32) {
         const FwdPlanePlan t = plan_fwd_plane_flat(p, es);
-        const bool fills = t.ok && (p.cpg > 1 ? (size_t)p.B * (p.C / t.K) >= 192 : (size_t)p.B * (p.C / t.cpw) >= 768 && (es == 2 || p.H * p.W <= 144));
+        const bool fills = t.ok && (p.cpg > 1 ? (size_t)p.B * (p.C / t.K) >= 192 : p.H * p.W <= (es == 2 ? 128 : p.kchunk > 0 ? 144 : 80) && (size_t)p.B * (p.C / t.cpw) >= 768);
         if (fills && t.small && (t.cpw > 2 || (shared_f32 && t.cpw == 2))) return t;
     }
     return plan_fwd_plane_padded(p, es);
@@ -597,7 +619,7 @@ static hipError_t launch_fplane_kn(const FwdPlaneArgs& a, const FwdPlanePlan& t,
 
 template <typename T, bool SAVE, bool SHARED, bool WPRE, bool FLAT, bool LOCAL, bool BWD = false>
 static hipError_t launch_fplane_kl(const FwdPlaneArgs& a, const FwdPlanePlan& t, hipStream_t s) {
-    if constexpr (FLAT) {
+    if constexpr (FLAT || !SHARED) {
         if (t.small) return launch_fplane_kn<T, SAVE, SHARED, WPRE, FLAT, LOCAL, BWD, 4>(a, t, s);
     }
     return launch_fplane_kn<T, SAVE, SHARED, WPRE, FLAT, LOCAL, BWD, 8>(a, t, s);

@@ -1,6 +1,6 @@
 """Small maps whose rows are whole 16-byte chunks, on the plane kernels with two, four and eight channels per wave (lines of up to 32, 16 and
 8 lanes, some as long as the lanes of a channel), against the line-by-line kernels: on either side of each line of the choice -- sides, planes
-per workgroup, weights of each channel's own, fp32 maps of up to 4 KB per wave -- with stretches and logits.
+per workgroup, weights of each channel's own, maps of up to 4 KB per wave -- with stretches and logits.
 
 y and the states are sums of four products in fp32 in another order than line by line; gw is summed in storage precision there (fp32 alone
 compares it)."""
@@ -18,7 +18,10 @@ CALLS = [
     ((1, 384, 17, 16, 192), "f32", 0, False), ((1, 382, 17, 16, 191), "f32", 0, False), ((1, 384, 22, 20, 192), "f32", 0, True), ((1, 384, 24, 24, 192), "f32", 0, False),
     # weights of each channel's own
     ((1, 3072, 12, 12, 3072), "f32", 0, False), ((1, 3072, 12, 16, 3072), "f32", 0, False), ((1, 3072, 16, 16, 3072), "f16", 0, True), ((1, 3068, 16, 16, 3068), "bf16", 0, False),
-    ((2, 3072, 7, 8, 3072), "bf16", 2, False), ((1, 510, 28, 28, 510), "f32", 0, True),
+    ((2, 3072, 7, 8, 3072), "bf16", 2, False), ((1, 6144, 8, 16, 6144), "bf16", 0, False), ((1, 3072, 9, 16, 3072), "bf16", 0, False),
+    # ... of one and two channels per wave with up to 4 KB of them, and beyond
+    ((1, 510, 28, 28, 510), "f32", 0, True), ((1, 300, 16, 32, 300), "f32", 0, False), ((1, 301, 15, 20, 301), "f32", 6, False), ((1, 300, 32, 32, 300), "f32", 0, False),
+    ((1, 300, 33, 32, 300), "f32", 0, False), ((1, 300, 32, 64, 300), "bf16", 0, True), ((1, 300, 33, 64, 300), "f16", 0, False), ((1, 300, 31, 24, 300), "f16", 5, True),
 ]
 
 
