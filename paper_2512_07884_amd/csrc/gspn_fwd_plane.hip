@@ -41,6 +41,10 @@ __device__ __forceinline__ void plds_st(uint32_t a, float v) { *(plds_f32*)(uint
 typedef float pf32x4a __attribute__((ext_vector_type(4), may_alias));
 typedef __attribute__((address_space(3))) pf32x4a plds_f32x4;
 __device__ __forceinline__ pf32x4a plds_ld4(uint32_t a) { return *(const plds_f32x4*)(uintptr_t)a; }
+typedef uint32_t pu32x2a __attribute__((ext_vector_type(2), may_alias));
+typedef __attribute__((address_space(3))) pu32x2a plds_u32x2;
+__device__ __forceinline__ u32x2 plds_ld2(uint32_t a) { const pu32x2a v = *(const plds_u32x2*)(uintptr_t)a; return u32x2{v.x, v.y}; }
+__device__ __forceinline__ void plds_st2(uint32_t a, uint32_t x, uint32_t y) { *(plds_u32x2*)(uintptr_t)a = pu32x2a{x, y}; }
 __device__ __forceinline__ void plds_st4(uint32_t a, pf32x4a v) { *(plds_f32x4*)(uintptr_t)a = v; }
 
 // element e of a 16 B chunk of storage, widened to fp32
@@ -82,10 +86,13 @@ struct FwdPlaneArgs {
 // against its scan order, and a position multiplies its state by the taps of the line swept before and hands the
 // products to the positions those taps read from (e_t = u_t*gy_t + T_{t+1}^T e_{t+1}).  The taps that are stored as 0
 // (out-of-line neighbours, GSPN-local: lines that start a stretch) are the ones that must pass nothing on here too.
+// W16: a group's weights in LDS as {w0, w1} in 16 bits and w2 in fp32, 8 bytes per position instead of 16, so that a CU holds eight waves in two
+// or more workgroups where it held six in one, which all waited for the memory at once: 6144 planes 56x56 bf16 (cpg 12) 135 -> 103 us, with
+// h_save and backward 501 -> 448, 48x48 f16 104 -> 77, 17280 of 36x32 223 -> 148; 0.92 in the mean of 69 calls, the longest 1.01.
 // NCHT: 16 B chunks per lane the register arrays are sized for (8: the wave's channels hold at most 8 KB; 4: small maps
 // with weights of each channel's own, and those of the flat variant, which then has the registers to give its LDS planes an odd pitch too -- every element's place is
 // tracked through two bit masks per chunk)
-template <typename T, bool SAVE, bool SHARED, bool WPRE, bool FLAT, bool LOCAL, bool BWD = false, int NCHT = 8>
+template <typename T, bool SAVE, bool SHARED, bool WPRE, bool FLAT, bool LOCAL, bool BWD = false, int NCHT = 8, bool W16 = false>
 __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneArgs a) {
     static_assert(!(FLAT && WPRE), "the flat variant fetches its weights in place");
     static_assert(NCHT == 8 || (NCHT == 4 && (FLAT || !SHARED)), "the short register arrays are for small maps of the flat variant and with weights of each channel's own");
@@ -94,7 +101,9 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
     static_assert(!BWD || SAVE, "the reverse sweep saves its state");
     constexpr int E = 16 / (int)sizeof(T);        // elements per 16 B chunk
     constexpr int NCH = NCHT;                     // chunks per lane
-    constexpr int WSH = 4;                        // weight chunks per thread (shared weights)
+    static_assert(!W16 || (sizeof(T) == 2 && WPRE && !LOCAL), "16-bit weights in LDS: the prefetching variant's, normalised, global scan");
+    constexpr int WSH = W16 ? 6 : 4;              // weight chunks per thread (shared weights; W16: the same chunk of the three taps, twice)
+    constexpr uint32_t WPOS = W16 ? 8 : 16;       // bytes per position of the weights in LDS
     const FwdParams& p = a.p;
     const int H = p.H, W = p.W, HW = H * W, P = a.pitch;
     const int HP = (FLAT && !PADFLAT) ? HW : (H * P + 3) & ~3;   // floats per plane region in LDS (16 B granules when padded)
@@ -114,11 +123,11 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
     const int n16p = HW / E;                                           // ... of one plane
 
     // LDS (floats).  Weights are kept interleaved, [H][P][4] = (w0, w1, w2, unused) per position, so that a scan
-    // step fetches its three taps with one 16 B read.  Shared weights: one such region for the direction,
+    // step fetches its three taps with one 16 B read (W16: {w0, w1} in 16 bits, w2 in fp32, 8 bytes).  Shared weights: one such region for the direction,
     // then per wave [cpw][H][P] a/h.  Per-channel weights: per wave [cpw] weight regions, then [cpw][H][P] a/h.
     const uint32_t base = plds_base();
     const uint32_t wreg = SHARED ? base : base + 4u * (uint32_t)(wave * cpw * 5 * HP);
-    const uint32_t ahreg = SHARED ? base + 4u * (uint32_t)(4 * HP + wave * cpw * HP)
+    const uint32_t ahreg = SHARED ? base + 4u * (uint32_t)((W16 ? 2 : 4) * HP + wave * cpw * HP)
                                   : wreg + 4u * (uint32_t)(cpw * 4 * HP);
 
     // flat layout: chunk q = k*64 + lane covers elements [q*E, q*E + E) of the wave's channels
@@ -179,11 +188,11 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
     if constexpr (SHARED && WPRE) {
 #pragma unroll
         for (int j = 0; j < WSH; ++j) {
-            const int c = (int)threadIdx.x + j * nthreads;
-            wv[j] = c < 3 * n16p;
+            const int c = (int)threadIdx.x + (W16 ? j / 3 : j) * nthreads;
+            wv[j] = c < (W16 ? 1 : 3) * n16p;
             const int cc = wv[j] ? c : 0;
-            const int tap = cc / n16p;
-            const int idx0 = (cc - tap * n16p) * E;
+            const int tap = W16 ? j % 3 : cc / n16p;
+            const int idx0 = (W16 ? cc : cc - tap * n16p) * E;
             const int row = idx0 / W;
             wl[j] = 4 * (row * P + (idx0 - row * W)) + tap;
             wrow[j] = row; wcol[j] = idx0 - row * W; wtap[j] = tap;
@@ -312,7 +321,26 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
             }
         } else if constexpr (SHARED) {
             lds_barrier();                                 // every wave is done with the previous direction's weights
-            if constexpr (WPRE) {
+            if constexpr (W16) {
+#pragma unroll
+                for (int j = 0; j < WSH; j += 3) {
+                    if (wv[j]) {
+                        // a tap that points outside the line is stored as 0, whatever the tensor holds there
+                        const uint32_t o = wreg + 2u * (uint32_t)wl[j];
+                        const bool all0 = !vert && wrow[j] == 0, all2 = !vert && wrow[j] == L - 1;
+#pragma unroll
+                        for (int e = 0; e < E; ++e) {
+                            const int pos = wcol[j] + e;
+                            const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+                            uint32_t w01 = __builtin_amdgcn_perm(wsh[j + 1][e >> 1], wsh[j][e >> 1], sel);
+                            float w2 = chunk_elem<T>(wsh[j + 2], e);
+                            w01 &= all0 || (vert && pos == 0) ? 0xffff0000u : 0xffffffffu;
+                            w2 = all2 || (vert && pos == L - 1) ? 0.f : w2;
+                            plds_st2(o + 8u * e, w01, __float_as_uint(w2));
+                        }
+                    }
+                }
+            } else if constexpr (WPRE) {
 #pragma unroll
                 for (int j = 0; j < WSH; ++j) {
                     if (wv[j]) {
@@ -433,15 +461,23 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
         // ---- the scan: h overwrites a
         {
             uint32_t aad = ahreg + 4u * (uint32_t)(half * HP + tpos);
-            uint32_t wad = wreg + 16u * (uint32_t)((SHARED ? 0 : half * HP) + tpos);
+            uint32_t wad = wreg + WPOS * (uint32_t)((SHARED ? 0 : half * HP) + tpos);
             float h = plds_ld(aad);                        // scan step 0: no previous line, its weights are never read
-            pf32x4a wp = plds_ld4(wad);                    // BWD: taps of the line swept before
+            auto taps = [&]() {
+                if constexpr (W16) {
+                    const u32x2 q = plds_ld2(wad);
+                    return pf32x4a{word_lo<T>(q[0]), word_hi<T>(q[0]), __uint_as_float(q[1]), 0.f};
+                } else {
+                    return plds_ld4(wad);
+                }
+            };
+            pf32x4a wp = taps();                           // BWD: taps of the line swept before
             // lanes past the end of the line walk the last position's operands; what they compute is never
             // stored, and the selects below keep it out of the line
             auto step = [&]() {
-                aad += (uint32_t)ss4; wad += (uint32_t)(4 * ss4);
+                aad += (uint32_t)ss4; wad += (uint32_t)((int)WPOS / 4 * ss4);
                 const float av = plds_ld(aad);
-                const pf32x4a w = plds_ld4(wad);
+                const pf32x4a w = taps();
                 if constexpr (BWD) {
                     float lin = from_lane_below(wp.z * h), rin = from_lane_above(wp.x * h);
                     lin = first ? 0.f : lin;
@@ -502,7 +538,7 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
 // ---------------------------------------------------------------------------
 static constexpr int FPLANE_LDS_BUDGET = 160 * 1024;
 
-struct FwdPlanePlan { bool ok, flat, small; int most_waves, K, cpw, lsh, nwaves, pitch, shared_group, wlw; size_t lds; };
+struct FwdPlanePlan { bool ok, flat, small, w16; int most_waves, K, cpw, lsh, nwaves, pitch, shared_group, wlw; size_t lds; };
 
 // waves per workgroup and LDS bytes, given the channels per wave and the bytes of one fp32 plane region
 static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp) {
@@ -523,6 +559,19 @@ static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp)
         t.lds = t.nwaves * wave;
     } else {
         t.shared_group = 1;
+        if (t.w16) {
+            // the number of waves with which the most fit on a CU, eight at most (registers), the larger of equals
+            int best = 0;
+            for (int nw = 8; nw >= 1; --nw) {
+                const size_t lds = (2 + (size_t)nw * t.cpw) * hp;
+                if ((p.cpg / t.cpw) % nw || lds > (size_t)FPLANE_LDS_BUDGET || p.H * p.W / 8 > 2 * 64 * nw) continue;
+                const int by_lds = (int)((size_t)FPLANE_LDS_BUDGET / ((lds + 1279) / 1280 * 1280)), by_regs = 8 / nw;
+                const int waves = (by_lds < 1 ? 1 : by_lds < by_regs ? by_lds : by_regs) * nw;
+                if (waves > best) { best = waves; t.nwaves = nw; t.K = nw * t.cpw; t.lds = lds; }
+            }
+            if (best) return (size_t)p.B * (p.C / t.K) <= 0x7fffffffull;
+            t.w16 = false;
+        }
         // the most waves (up to 8) whose channels divide the group and whose planes fit beside the weights
         int nw = 8;
         for (; nw >= 1; --nw) {
@@ -555,6 +604,8 @@ static FwdPlanePlan plan_fwd_plane_padded(const FwdParams& p, int es) {
     t.pitch = p.W | 1;
     t.most_waves = es == 4 ? (t.small ? 12 : 8) : t.small ? 8 : 4;      // (registers, weights of each channel's own)
     const size_t hp = (((size_t)p.H * t.pitch + 3) & ~(size_t)3) * sizeof(float);   // one plane region in LDS
+    // 16-bit weights that the scan takes as they are stay 16-bit in LDS
+    t.w16 = es == 2 && p.cpg > 1 && p.kchunk <= 0 && !p.logits;
     t.ok = plan_fwd_plane_waves(p, t, hp);
     return t;
 }
@@ -607,9 +658,9 @@ static FwdPlanePlan plan_fwd_plane(const FwdParams& p, int dtype) {
 
 bool fwd_plane_applicable(const FwdParams& p, int dtype) { return plan_fwd_plane(p, dtype).ok; }
 
-template <typename T, bool SAVE, bool SHARED, bool WPRE, bool FLAT, bool LOCAL, bool BWD, int NCH>
+template <typename T, bool SAVE, bool SHARED, bool WPRE, bool FLAT, bool LOCAL, bool BWD, int NCH, bool W16 = false>
 static hipError_t launch_fplane_kn(const FwdPlaneArgs& a, const FwdPlanePlan& t, hipStream_t s) {
-    auto k = fwd_plane_kernel<T, SAVE, SHARED, WPRE, FLAT, LOCAL, BWD, NCH>;
+    auto k = fwd_plane_kernel<T, SAVE, SHARED, WPRE, FLAT, LOCAL, BWD, NCH, W16>;
     hipError_t e = allow_dynamic_lds((const void*)k, FPLANE_LDS_BUDGET);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)((size_t)a.p.B * (a.p.C / a.K))), block(64 * a.nwaves);
@@ -619,6 +670,9 @@ static hipError_t launch_fplane_kn(const FwdPlaneArgs& a, const FwdPlanePlan& t,
 
 template <typename T, bool SAVE, bool SHARED, bool WPRE, bool FLAT, bool LOCAL, bool BWD = false>
 static hipError_t launch_fplane_kl(const FwdPlaneArgs& a, const FwdPlanePlan& t, hipStream_t s) {
+    if constexpr (WPRE && !LOCAL && sizeof(T) == 2) {
+        if (t.w16) return launch_fplane_kn<T, SAVE, SHARED, WPRE, FLAT, LOCAL, BWD, 8, true>(a, t, s);
+    }
     if constexpr (FLAT || !SHARED) {
         if (t.small) return launch_fplane_kn<T, SAVE, SHARED, WPRE, FLAT, LOCAL, BWD, 4>(a, t, s);
     }
@@ -636,7 +690,7 @@ static hipError_t launch_fplane(const FwdPlaneArgs& a, const FwdPlanePlan& t, hi
     if (t.flat) return launch_fplane_k<T, SAVE, SHARED, false, true>(a, t, s);
     if constexpr (SHARED) {
         const int E = 16 / (int)sizeof(T);
-        const bool wpre = 3 * (a.p.H * a.p.W / E) <= 4 * 64 * a.nwaves;   // WSH chunks per thread
+        const bool wpre = t.w16 || 3 * (a.p.H * a.p.W / E) <= 4 * 64 * a.nwaves;   // WSH chunks per thread
         return wpre ? launch_fplane_k<T, SAVE, true, true, false>(a, t, s)
                     : launch_fplane_k<T, SAVE, true, false, false>(a, t, s);
     } else {
@@ -661,7 +715,7 @@ static hipError_t launch_fplane_rev(const FwdPlaneArgs& a, const FwdPlanePlan& t
     if (t.flat) return launch_fplane_rev_k<T, SHARED, false, true>(a, t, s);
     if constexpr (SHARED) {
         const int E = 16 / (int)sizeof(T);
-        const bool wpre = 3 * (a.p.H * a.p.W / E) <= 4 * 64 * a.nwaves;   // WSH chunks per thread
+        const bool wpre = t.w16 || 3 * (a.p.H * a.p.W / E) <= 4 * 64 * a.nwaves;   // WSH chunks per thread
         return wpre ? launch_fplane_rev_k<T, true, true, false>(a, t, s) : launch_fplane_rev_k<T, true, false, false>(a, t, s);
     } else {
         return launch_fplane_rev_k<T, false, false, false>(a, t, s);

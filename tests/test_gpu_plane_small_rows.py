@@ -1,6 +1,6 @@
-"""Small maps whose rows are whole 16-byte chunks, on the plane kernels with two, four and eight channels per wave (lines of up to 32, 16 and
+"""Maps whose rows are whole 16-byte chunks, on the plane kernels with two, four and eight channels per wave (lines of up to 32, 16 and
 8 lanes, some as long as the lanes of a channel), against the line-by-line kernels: on either side of each line of the choice -- sides, planes
-per workgroup, weights of each channel's own, maps of up to 4 KB per wave -- with stretches and logits.
+per workgroup, weights of each channel's own, in 16 bits in LDS, maps of up to 4 KB per wave -- with stretches and logits.
 
 y and the states are sums of four products in fp32 in another order than line by line; gw is summed in storage precision there (fp32 alone
 compares it)."""
@@ -16,6 +16,11 @@ CALLS = [
     ((2, 768, 16, 16, 192), "bf16", 0, True), ((2, 768, 9, 16, 192), "f16", 4, False), ((2, 768, 11, 12, 192), "f32", 0, False), ((2, 768, 16, 4, 192), "f32", 5, True),
     ((1, 768, 16, 8, 191 + 1), "f16", 0, False), ((1, 764, 16, 8, 191), "f16", 0, False),
     ((1, 384, 17, 16, 192), "f32", 0, False), ((1, 382, 17, 16, 191), "f32", 0, False), ((1, 384, 22, 20, 192), "f32", 0, True), ((1, 384, 24, 24, 192), "f32", 0, False),
+    # 16-bit weights in LDS: one and two channels per wave, one and two pieces of weights per thread, workgroups too small for them (64x64, three
+    # channels), lines as long as the lanes of a channel
+    ((1, 36, 56, 56, 3), "bf16", 0, False), ((1, 40, 64, 64, 5), "f16", 0, False), ((1, 9, 64, 64, 3), "bf16", 0, False), ((1, 10, 40, 40, 5), "bf16", 0, False),
+    ((2, 48, 32, 32, 4), "f16", 0, False), ((1, 24, 19, 24, 2), "bf16", 0, False), ((1, 14, 64, 8, 2), "f16", 0, False), ((1, 12, 2, 64, 2), "bf16", 0, False),
+    ((1, 36, 56, 56, 3), "f16", 0, True), ((1, 36, 56, 56, 3), "bf16", 16, False),
     # weights of each channel's own
     ((1, 3072, 12, 12, 3072), "f32", 0, False), ((1, 3072, 12, 16, 3072), "f32", 0, False), ((1, 3072, 16, 16, 3072), "f16", 0, True), ((1, 3068, 16, 16, 3068), "bf16", 0, False),
     ((2, 3072, 7, 8, 3072), "bf16", 2, False), ((1, 6144, 8, 16, 6144), "bf16", 0, False), ((1, 3072, 9, 16, 3072), "bf16", 0, False),
@@ -56,7 +61,8 @@ def test_against_line_by_line(shape, dtype, kchunk, logits, monkeypatch):
         monkeypatch.setenv(knob, "1")
     binding.gspn_reload_env()
     code = {"f32": 0, "bf16": 1, "f16": 2}[dtype]
-    for call, want in (("fwd", "plane"), ("save", "plane"), ("bwd", "twopass/plane")):
+    big = dtype != "f32" and shape[2] * shape[3] * 2 > 6656          # forward calls without h_save: the tile kernel's
+    for call, want in (("fwd", "tile" if big else "plane"), ("save", "plane"), ("bwd", "twopass/plane")):
         assert binding.running_kernel(*shape, code, call, kchunk, logits) == want, call
         got = run(call, inp, shape, dtype, kchunk, logits, ref["h"])
         close(got, ref if call != "bwd" else ref_bwd, dtype, ())
