@@ -538,7 +538,7 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneA
 // ---------------------------------------------------------------------------
 static constexpr int FPLANE_LDS_BUDGET = 160 * 1024;
 
-struct FwdPlanePlan { bool ok, flat, small, w16; int most_waves, K, cpw, lsh, nwaves, pitch, shared_group, wlw; size_t lds; };
+struct FwdPlanePlan { bool ok, flat, small, w16; int es, most_waves, most_shared, K, cpw, lsh, nwaves, pitch, shared_group, wlw; size_t lds; };
 
 // waves per workgroup and LDS bytes, given the channels per wave and the bytes of one fp32 plane region
 static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp) {
@@ -559,29 +559,29 @@ static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp)
         t.lds = t.nwaves * wave;
     } else {
         t.shared_group = 1;
-        if (t.w16) {
-            // the number of waves with which the most fit on a CU, eight at most (registers), the larger of equals
+        // The number of waves (up to 8) whose channels divide the group and of which the most fit on a CU, a smaller one only for a quarter more of
+        // them (its workgroups each bring in the weights: 9216 planes 16x16 fp32 with logits, 3 waves -> 1, 22 -> 31 us); weights that the largest could
+        // request a direction ahead stay so.  In fp32 (flat: small maps) and with 16-bit weights in LDS; else the most waves, whose share of the
+        // weights is the smallest.  Most waves -> this: 49920 planes 7x7 fp32 46 -> 32 us, 36864 of 10x10 56 -> 43, 18432 of 28x28 129 -> 114 (5x5
+        // 43 -> 46); where it stays: 15360 of 36x36 f16 with logits 207 -> 286, 29952 of 10x10 f16 56 -> 69.
+        const int es = t.es, chunks = p.H * p.W * es / 16;
+        auto ahead = [&](int nw) { return t.w16 ? chunks <= 2 * 64 * nw : 3 * chunks <= 4 * 64 * nw; };
+        for (int w16 = t.w16; w16 >= 0; --w16) {
+            t.w16 = w16 != 0;
             int best = 0;
+            bool was_ahead = false;
             for (int nw = 8; nw >= 1; --nw) {
-                const size_t lds = (2 + (size_t)nw * t.cpw) * hp;
-                if ((p.cpg / t.cpw) % nw || lds > (size_t)FPLANE_LDS_BUDGET || p.H * p.W / 8 > 2 * 64 * nw) continue;
-                const int by_lds = (int)((size_t)FPLANE_LDS_BUDGET / ((lds + 1279) / 1280 * 1280)), by_regs = 8 / nw;
-                const int waves = (by_lds < 1 ? 1 : by_lds < by_regs ? by_lds : by_regs) * nw;
-                if (waves > best) { best = waves; t.nwaves = nw; t.K = nw * t.cpw; t.lds = lds; }
+                const size_t lds = ((t.w16 ? 2 : 4) + (size_t)nw * t.cpw) * hp;
+                if ((p.cpg / t.cpw) % nw || lds > (size_t)FPLANE_LDS_BUDGET || (t.w16 && !ahead(nw))) continue;
+                if (was_ahead && !t.flat && !ahead(nw)) continue;
+                const int by_lds = (int)((size_t)FPLANE_LDS_BUDGET / ((lds + 1279) / 1280 * 1280)), by_regs = t.most_shared / nw;
+                const int waves = (by_lds < 1 ? 1 : by_regs < 1 ? 1 : by_lds < by_regs ? by_lds : by_regs) * nw;
+                if (best && (es == 2 ? !t.w16 : t.flat && !t.small)) break;
+                if (!best || 4 * waves >= 5 * best) { best = waves; t.nwaves = nw; t.K = nw * t.cpw; t.lds = lds; was_ahead = !t.flat && ahead(nw); }
             }
-            if (best) return (size_t)p.B * (p.C / t.K) <= 0x7fffffffull;
-            t.w16 = false;
+            if (best) break;
+            if (!w16) return false;
         }
-        // the most waves (up to 8) whose channels divide the group and whose planes fit beside the weights
-        int nw = 8;
-        for (; nw >= 1; --nw) {
-            if ((p.cpg / t.cpw) % nw) continue;
-            if ((4 + (size_t)nw * t.cpw) * hp > (size_t)FPLANE_LDS_BUDGET) continue;
-            break;
-        }
-        if (nw < 1) return false;
-        t.nwaves = nw; t.K = nw * t.cpw;
-        t.lds = (4 + (size_t)nw * t.cpw) * hp;
     }
     return (size_t)p.B * (p.C / t.K) <= 0x7fffffffull;
 }
@@ -605,6 +605,7 @@ static FwdPlanePlan plan_fwd_plane_padded(const FwdParams& p, int es) {
     t.most_waves = es == 4 ? (t.small ? 12 : 8) : t.small ? 8 : 4;      // (registers, weights of each channel's own)
     const size_t hp = (((size_t)p.H * t.pitch + 3) & ~(size_t)3) * sizeof(float);   // one plane region in LDS
     // 16-bit weights that the scan takes as they are stay 16-bit in LDS
+    t.es = es; t.most_shared = 8;
     t.w16 = es == 2 && p.cpg > 1 && p.kchunk <= 0 && !p.logits;
     t.ok = plan_fwd_plane_waves(p, t, hp);
     return t;
@@ -628,6 +629,7 @@ static FwdPlanePlan plan_fwd_plane_flat(const FwdParams& p, int es) {
     t.small = (size_t)t.cpw * HW * es <= 4 * 64 * 16;
     t.pitch = t.small ? (p.W | 1) : p.W;
     t.most_waves = !t.small ? 8 : es == 4 ? 16 : 12;
+    t.es = es; t.most_shared = t.most_waves;
     // shared weights: the widest request that divides a group's block (its start is a multiple of its size)
     const size_t wblock = (size_t)3 * HW * es;
     t.wlw = wblock % 16 == 0 ? 16 : wblock % 8 == 0 ? 8 : wblock % 4 == 0 ? 4 : 2;
