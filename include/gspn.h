@@ -224,6 +224,7 @@ int gspn_proxy_project(const void* in, const void* P, void* out, int B, int K, i
  *   gP      out [M,K] in fp32 whatever the storage type, or NULL (not computed; at least one of gin, gP is required)
  *   partial workspace of the caller's, B*M*K floats, required with gP (NULL otherwise): it receives the per-image
  *           sums, which a second small kernel adds in image order -- no atomics, the result is bitwise repeatable.
+ *           With B == 1 it may be gP itself (the pixels are then summed in one range instead of two: the same up to fp32 rounding).
  * The library still allocates nothing.  16-bit storage with at least 8 pixels runs on the matrix cores (for gin
  * where M is a multiple of 8); other shapes and fp32 storage run plain FMA kernels. */
 int gspn_proxy_project_bwd(const void* gout, const void* in, const void* P, void* gin, float* gP, float* partial,

@@ -675,53 +675,69 @@ static hipError_t launch_gradw_lds(const void* gout, const void* in, float* part
     return hipGetLastError();
 }
 
+// The weight gradient's kernel for 16-bit storage: its tile in units of 16 rows and the ranges of pixels that are summed apart.
+// apart: `partial` and gP share no memory.
+enum GradwKernel { GRADW_PLAIN = 0, GRADW_SMALL = 1, GRADW_LDS = 2 };
+struct GradwPlan { GradwKernel kernel; int mt, kt, ranges; };
+static GradwPlan gradw_plan(int B, int K, int M, int N, bool apart) {
+    GradwPlan p = {GRADW_PLAIN, 2, 2, 1};
+    const long tiles = (long)B * ((M + 31) / 32) * ((K + 31) / 32);
+    if (N < 8) return p;
+    // 16 x 16 tiles where 32 x 32 ones are fewer than a quarter of the CUs and the rows are long (two images, 32 x 32 -> 16 x
+    // 16: 8 <- 96 channels on 96x96 26.8 -> 17.0 us; below 4096 pixels no gain in the mean and up to 7 % lost: 48 <- 96 on
+    // 56x56 16.1 -> 17.2.  Rows at any element: 0.94 of the time in the mean from 1024 pixels on).  Not for odd rows, half of
+    // whose requests fall between 32-bit words and are worked off in twice the time: there the rows pass once, through LDS
+    // (24 <- 192 on four images 89x111 52 -> 32 us, 24 <- 384 on two of 111x79 55 -> 29).
+    if (tiles < 64 && N % 2 == 0 && N >= (N % 8 ? 1024 : 4096)) {
+        p.kernel = GRADW_SMALL; p.mt = p.kt = 1;
+        return p;
+    }
+    // The rows through LDS where they are long or tiles enough to fill the chip.  Share of the time of the kernel below in 90 random
+    // products (8 to 1152 channels, 1 to 16 images): 1024 pixels and more 0.4 to 1.0, 512 to 1023 from 256 tiles on 0.9; shorter rows
+    // are a stage or two each (304 x 353 on 14 images of 336 pixels 13.7 -> 20.3 us).  (A launch counts its threads in 32 bits.)
+    if (tiles > 0x3fffff || !(N >= 1024 || (N >= 512 && tiles >= 256))) return p;
+    p.kernel = GRADW_LDS;
+    // One image leaves `partial` a single place: its second half's sums go to gP on the way (144 x 1152 channels on
+    // 128x128 32.7 -> 28.6 us, 24 <- 192 on 123x49 23.2 -> 16.3), unless that is the same place.
+    p.ranges = B == 1 && apart ? 2 : 1;
+    // The tile: what a CU takes in, rows per tile times turns of 256 workgroups, is what the time goes by.  32 x 32 has two
+    // workgroups on a CU, which hide each other's start and end (0.75 of that); 64 x 64 nearly runs out of registers (1.15).
+    // us with 32 x 32, 48 x 32, 48 x 48, 64 x 64: 144 x 1152 on two 64x64 images 18.3 15.3 17.6 22.6; 48 x 1152 on 14 images 72x81
+    // 66 56 65 48, on six of 105x48 22.4 18.8 21.3 27.2; 144 x 768 on four of 118x18 18.7 25.2 17.7 22.3.  Rows of less than
+    // eight stages are not worth a second start: 144 x 1152 on 16 images 28x28 35 39 36 38.
+    const int shapes[][2] = {{2, 2}, {3, 2}, {2, 3}, {3, 3}, {4, 4}};
+    long best = -1;
+    for (const auto& t : shapes) {
+        const long wgs = (long)B * p.ranges * ((M + 16 * t[0] - 1) / (16 * t[0])) * ((K + 16 * t[1] - 1) / (16 * t[1])), turns = (wgs + 255) / 256;
+        const bool pair = t[0] == 2 && t[1] == 2;
+        if (!pair && turns > 1 && N < 2048) continue;
+        const long cost = turns * (t[0] + t[1]) * (pair && turns > 1 ? 75 : t[0] == 4 ? 115 : 100);
+        if (best < 0 || cost < best) { best = cost; p.mt = t[0]; p.kt = t[1]; }
+    }
+    return p;
+}
+
 // per-image sums of gout in^T into `partial` (B*M*K floats), storage type T; halves: of one image, the sums of its second half into gP
 template <typename T>
 static hipError_t launch_gradw_as(const void* gout, const void* in, float* partial, float* gP, bool* halves, int B, int K, int M, int N, hipStream_t s) {
     const bool mfma = sizeof(T) == 2 && N >= 8;
     const int mtiles = mfma ? (M + 31) / 32 : (M + 7) / 8;
     const int ktiles = (K + 31) / 32;
-    const long tiles = (long)B * mtiles * ktiles;
     if constexpr (sizeof(T) == 2) {
-        // 16 x 16 tiles where 32 x 32 ones are fewer than a quarter of the CUs and the rows are long (two images, 32 x 32 -> 16 x
-        // 16: 8 <- 96 channels on 96x96 26.8 -> 17.0 us; below 4096 pixels no gain in the mean and up to 7 % lost: 48 <- 96 on
-        // 56x56 16.1 -> 17.2.  Rows at any element: 0.94 of the time in the mean from 1024 pixels on).  Not for odd rows, half of
-        // whose requests fall between 32-bit words and are worked off in twice the time: there the rows pass once, through LDS
-        // (24 <- 192 on four images 89x111 52 -> 32 us, 24 <- 384 on two of 111x79 55 -> 29).
-        if (mfma && tiles < 64 && N % 2 == 0 && N >= (N % 8 ? 1024 : 4096)) {
+        const size_t MK = (size_t)M * K;
+        const GradwPlan t = gradw_plan(B, K, M, N, gP + MK <= partial || partial + MK <= gP);
+        if (t.kernel == GRADW_SMALL) {
             const int mt = (M + 15) / 16, kt = (K + 15) / 16;
             void (*k)(const T*, const T*, float*, int, int, int, int, int) = N % 8 ? proxy_gradw_small_kernel<T, true> : proxy_gradw_small_kernel<T, false>;
             hipLaunchKernelGGL(k, dim3((unsigned)((long)B * mt * kt)), dim3(1024), 0, s, (const T*)gout, (const T*)in, partial, K, M, N, mt, kt);
             return hipGetLastError();
         }
-    }
-    if constexpr (sizeof(T) == 2) {
-        // The rows through LDS where they are long or tiles enough to fill the chip.  Share of the time of the kernel below in 90 random
-        // products (8 to 1152 channels, 1 to 16 images): 1024 pixels and more 0.4 to 1.0, 512 to 1023 from 256 tiles on 0.9; shorter rows
-        // are a stage or two each (304 x 353 on 14 images of 336 pixels 13.7 -> 20.3 us).  (A launch counts its threads in 32 bits.)
-        if (mfma && tiles <= 0x3fffff && (N >= 1024 || (N >= 512 && tiles >= 256))) {
-            // One image leaves `partial` a single place: its second half's sums go to gP on the way (144 x 1152 channels on
-            // 128x128 32.7 -> 28.6 us, 24 <- 192 on 123x49 23.2 -> 16.3).
-            *halves = B == 1;
-            const int ranges = *halves ? 2 : 1;
-            // The tile: what a CU takes in, rows per tile times turns of 256 workgroups, is what the time goes by.  32 x 32 has two
-            // workgroups on a CU, which hide each other's start and end (0.75 of that); 64 x 64 nearly runs out of registers (1.15).
-            // us with 32 x 32, 48 x 32, 48 x 48, 64 x 64: 144 x 1152 on two 64x64 images 18.3 15.3 17.6 22.6; 48 x 1152 on 14 images 72x81
-            // 66 56 65 48, on six of 105x48 22.4 18.8 21.3 27.2; 144 x 768 on four of 118x18 18.7 25.2 17.7 22.3.  Rows of less than
-            // eight stages are not worth a second start: 144 x 1152 on 16 images 28x28 35 39 36 38.
-            const int shapes[][2] = {{2, 2}, {3, 2}, {2, 3}, {3, 3}, {4, 4}};
-            long best = -1;
-            int mt = 2, kt = 2;
-            for (const auto& t : shapes) {
-                const long wgs = (long)B * ranges * ((M + 16 * t[0] - 1) / (16 * t[0])) * ((K + 16 * t[1] - 1) / (16 * t[1])), turns = (wgs + 255) / 256;
-                const bool pair = t[0] == 2 && t[1] == 2;
-                if (!pair && turns > 1 && N < 2048) continue;
-                const long cost = turns * (t[0] + t[1]) * (pair && turns > 1 ? 75 : t[0] == 4 ? 115 : 100);
-                if (best < 0 || cost < best) { best = cost; mt = t[0]; kt = t[1]; }
-            }
-            return mt == 4 ? launch_gradw_lds<T, 4, 4>(gout, in, partial, gP, B, K, M, N, ranges, s)
-                 : mt == 3 ? (kt == 3 ? launch_gradw_lds<T, 3, 3>(gout, in, partial, gP, B, K, M, N, ranges, s) : launch_gradw_lds<T, 3, 2>(gout, in, partial, gP, B, K, M, N, ranges, s))
-                           : (kt == 3 ? launch_gradw_lds<T, 2, 3>(gout, in, partial, gP, B, K, M, N, ranges, s) : launch_gradw_lds<T, 2, 2>(gout, in, partial, gP, B, K, M, N, ranges, s));
+        if (t.kernel == GRADW_LDS) {
+            *halves = t.ranges == 2;
+            const int ranges = t.ranges;
+            return t.mt == 4 ? launch_gradw_lds<T, 4, 4>(gout, in, partial, gP, B, K, M, N, ranges, s)
+                 : t.mt == 3 ? (t.kt == 3 ? launch_gradw_lds<T, 3, 3>(gout, in, partial, gP, B, K, M, N, ranges, s) : launch_gradw_lds<T, 3, 2>(gout, in, partial, gP, B, K, M, N, ranges, s))
+                             : (t.kt == 3 ? launch_gradw_lds<T, 2, 3>(gout, in, partial, gP, B, K, M, N, ranges, s) : launch_gradw_lds<T, 2, 2>(gout, in, partial, gP, B, K, M, N, ranges, s));
         }
     }
     const long blocks = (long)B * mtiles * ktiles;
@@ -808,3 +824,10 @@ hipError_t launch_proxy_project_bwd_static(const void* gout, const void* in, con
 }
 
 }  // namespace gspn
+
+// For the tests, not part of the ABI: the kernel (0 rows from memory, 1 16 x 16 tiles, 2 rows through LDS), the rows and columns of its tile
+// and the ranges of pixels of the weight gradient in 16-bit storage; apart: `partial` and gP share no memory.
+extern "C" void gspn_proxy_gradw_shape(int B, int K, int M, int H, int W, int apart, int* shape) {
+    const gspn::GradwPlan t = gspn::gradw_plan(B, K, M, H * W, apart != 0);
+    shape[0] = t.kernel; shape[1] = 16 * t.mt; shape[2] = 16 * t.kt; shape[3] = t.ranges;
+}

@@ -162,6 +162,28 @@ def test_weight_gradient_through_lds_in_each_tile(shape):
     assert rel_inf_err(gP.double().cpu().numpy(), ref.sum(0)) <= 1e-5
 
 
+# (K, M, H, W, dtype): the kernels that sum one image in halves, each where the sums have a place of their own; whole and odd rows
+ONE_IMAGE = [(1152, 144, 32, 32, "bf16"), (70, 41, 25, 41, "f16"), (144, 1152, 33, 32, "f16"), (40, 33, 45, 29, "bf16")]
+
+
+@pytest.mark.parametrize("shape", ONE_IMAGE, ids=lambda s: "x".join(map(str, s)))
+def test_weight_gradient_of_one_image_with_its_sums_in_the_same_place(shape):
+    """partial may be gP itself with one image: two ranges of pixels would write the same addresses and be doubled."""
+    import torch
+    import paper_2512_07884_amd as G
+    K, M, H, W, dtype = shape
+    rng = np.random.default_rng([31, K, M])
+    x = WL.to_storage(rng.standard_normal((1, K, H, W)), dtype)
+    g = WL.to_storage(rng.standard_normal((1, M, H, W)), dtype)
+    P = WL.to_storage(rng.standard_normal((M, K)), dtype)
+    gP = torch.full((M, K), float("nan"), device="cuda")
+    G.gspn_proxy_project_bwd(to_device(g, dtype), to_device(x, dtype), to_device(P, dtype), None, gP, gP.view(1, M, K))
+    torch.cuda.synchronize()
+    ref = np.matmul(WL.storage_to_f64(g, dtype).reshape(M, H * W), WL.storage_to_f64(x, dtype).reshape(K, H * W).T)
+    # (products exact in fp32, some 1300 of them in eight chains of fp32 additions: below 170 * 2^-24 = 1e-5 of the largest sum)
+    assert rel_inf_err(gP.double().cpu().numpy(), ref) <= 1e-5
+
+
 def test_projection_gradients_one_at_a_time_and_bitwise_repeatable():
     rng = np.random.default_rng(17)
     B, K, M, H, W = 3, 96, 8, 28, 28
