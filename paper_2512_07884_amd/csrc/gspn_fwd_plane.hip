@@ -92,8 +92,10 @@ struct FwdPlaneArgs {
 // NCHT: 16 B chunks per lane the register arrays are sized for (8: the wave's channels hold at most 8 KB; 4: small maps
 // with weights of each channel's own, and those of the flat variant, which then has the registers to give its LDS planes an odd pitch too -- every element's place is
 // tracked through two bit masks per chunk)
+// (fp32 planes of the flat variant with eight chunks per lane need 167 to 171 registers as the compiler lays them out; 168 are what three waves
+// per SIMD may have: 1872 planes 38x38 fp32 with logits and stretches, h_save, 59 us with three, 86 with two)
 template <typename T, bool SAVE, bool SHARED, bool WPRE, bool FLAT, bool LOCAL, bool BWD = false, int NCHT = 8, bool W16 = false>
-__global__ void __launch_bounds__(SHARED ? 512 : 256) fwd_plane_kernel(FwdPlaneArgs a) {
+__global__ void __launch_bounds__(SHARED ? 512 : 256, sizeof(T) == 4 && FLAT && NCHT == 8 ? 3 : SHARED ? 2 : 1) fwd_plane_kernel(FwdPlaneArgs a) {
     static_assert(!(FLAT && WPRE), "the flat variant fetches its weights in place");
     static_assert(NCHT == 8 || (NCHT == 4 && (FLAT || !SHARED)), "the short register arrays are for small maps of the flat variant and with weights of each channel's own");
     constexpr bool WAHEAD = !SHARED && !FLAT && NCHT == 4;        // at most 4 KB of channels per wave, their weights requested a direction ahead
