@@ -540,7 +540,11 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256, sizeof(T) == 4 && FLAT && 
 // ---------------------------------------------------------------------------
 static constexpr int FPLANE_LDS_BUDGET = 160 * 1024;
 
-struct FwdPlanePlan { bool ok, flat, small, w16; int es, most_waves, most_shared, K, cpw, lsh, nwaves, pitch, shared_group, wlw; size_t lds; };
+// on_cu: channels that a CU holds at a time
+struct FwdPlanePlan { bool ok, flat, small, w16; int es, most_waves, most_shared, K, cpw, lsh, nwaves, pitch, shared_group, wlw, on_cu; size_t lds; };
+
+// how often the chip is filled until a call's planes are through, `on_cu` of them on each of its 256 CUs
+static long plane_rounds(const FwdParams& p, int on_cu) { return ((long)p.B * p.C + 256l * on_cu - 1) / (256l * on_cu); }
 
 // waves per workgroup and LDS bytes, given the channels per wave and the bytes of one fp32 plane region
 static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp) {
@@ -557,6 +561,7 @@ static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp)
             if (on_cu > best) { best = on_cu; t.nwaves = nw; }
         }
         if (!best) return false;
+        t.on_cu = best * t.cpw;
         t.K = t.nwaves * t.cpw;
         t.lds = t.nwaves * wave;
     } else {
@@ -581,7 +586,7 @@ static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp)
                 if (best && (es == 2 ? !t.w16 : t.flat && !t.small)) break;
                 if (!best || 4 * waves >= 5 * best) { best = waves; t.nwaves = nw; t.K = nw * t.cpw; t.lds = lds; was_ahead = !t.flat && ahead(nw); }
             }
-            if (best) break;
+            if (best) { t.on_cu = best * t.cpw; break; }
             if (!w16) return false;
         }
     }
@@ -640,24 +645,29 @@ static FwdPlanePlan plan_fwd_plane_flat(const FwdParams& p, int es) {
 }
 
 // Rows of whole chunks take the padded variant, but for small maps, whose lines leave most lanes of its waves idle (up to 16 positions: two channels
-// per wave where four or eight have their place) or, in fp32 with shared weights, whose chunks need half of its registers.  Both timed on
-// the same calls, us: 36864 planes 8x8 bf16, forward 115 -> 40, 45312 of 11x8 fp32 125 -> 47, 73728 of 16x16 bf16 with logits 243 -> 163, 9216 of
-// 14x12 fp32 38 -> 19, 36864 of 17x16 fp32 121 -> 91; 0.6 in the mean of 120 calls, the longest 1.08 (7680 of 16x16 f16 with stretches).  Beyond the
-// lines: 24x24 f16 48 -> 60, 25x28 fp32 63 -> 76; too few workgroups, 1152 of 16x16 f16 13.6 -> 16.8.  Weights of each channel's own: up to
-// 128 pixels in 16 bits (5x8 36 us for 105, 16x8 26 for 32; 13x16 60 for 46, 15x16 30 for 14), 80 in fp32 (10x8 71 for 78; 12x12 28 for 24.5, with
-// stretches 36 for 42), and 768 waves.
+// per wave where four or eight have their place) or, in fp32 with shared weights, whose chunks need half of its registers, in calls that
+// fill the chip with it more often than with the flat one: what that gains is channels per CU, and what it costs is that the weights are
+// waited for in each direction.  Both timed on 1480 random calls: 0.78 in the mean where the chip is filled less often, 1.13 where as
+// often (up to 4096 planes of two channels per wave; 2048 planes 20x20 fp32 17.6 against 25 us, 2624 of 16x16 f16 13.5 against 21.6).
+// us: 36864 planes 8x8 bf16, forward 115 -> 40, 45312 of 11x8 fp32 125 -> 47, 73728 of 16x16 bf16 with logits 243 -> 163.  Workgroups of
+// five and more waves, which wait for each other, in place of such as need not, 1.03 (5120 planes 9x4 fp32 25 against 21); a wave that
+// fetches a group's weights by itself, beyond 340 pixels 1.04 (8896 planes 25x20 fp32 60 against 76).
+// Beyond the lines: 24x24 f16 48 -> 60, 25x28 fp32 63 -> 76.  Weights of each channel's own: up to 128 pixels in 16 bits (5x8 36 us for 105,
+// 16x8 26 for 32; 13x16 60 for 46, 15x16 30 for 14), 80 in fp32 (10x8 71 for 78; 12x12 28 for 24.5, with stretches 36 for 42).
 static FwdPlanePlan plan_fwd_plane(const FwdParams& p, int dtype) {
     const int es = dtype == 0 ? 4 : 2, m = p.H > p.W ? p.H : p.W;
     if (p.H < 2 || p.W < 2 || p.H > 64 || p.W > 64) return FwdPlanePlan{};
     if (p.xt) return FwdPlanePlan{};                       // transposed-horizontal layout: tile and generic kernels
     if (p.W % (16 / es)) return plan_fwd_plane_flat(p, es);
     const bool shared_f32 = dtype == 0 && p.cpg > 1;
+    const FwdPlanePlan padded = plan_fwd_plane_padded(p, es);
     if (m <= 16 || shared_f32) {
         const FwdPlanePlan t = plan_fwd_plane_flat(p, es);
-        const bool fills = t.ok && (p.cpg > 1 ? (size_t)p.B * (p.C / t.K) >= 192 : p.H * p.W <= (es == 2 ? 128 : p.kchunk > 0 ? 144 : 80) && (size_t)p.B * (p.C / t.cpw) >= 768);
-        if (fills && t.small && (t.cpw > 2 || (shared_f32 && t.cpw == 2))) return t;
+        const bool size = t.ok && t.small && (t.cpw > 2 || (shared_f32 && t.cpw == 2)) && (p.cpg > 1 || p.H * p.W <= (es == 2 ? 128 : p.kchunk > 0 ? 144 : 80));
+        const bool waits = size && p.cpg > 1 && (t.nwaves == 1 ? p.H * p.W > 340 : t.nwaves >= 5 && padded.nwaves <= (es == 2 ? 2 : 1));
+        if (size && padded.ok && !waits && plane_rounds(p, t.on_cu) < plane_rounds(p, padded.on_cu)) return t;
     }
-    return plan_fwd_plane_padded(p, es);
+    return padded;
 }
 
 bool fwd_plane_applicable(const FwdParams& p, int dtype) { return plan_fwd_plane(p, dtype).ok; }
@@ -751,3 +761,13 @@ hipError_t launch_fwd_plane(const FwdParams& p, int dtype, hipStream_t s) {
 }
 
 }  // namespace gspn
+
+// For the tests, not part of the ABI: {flat variant, channels per wave, waves per workgroup, channels on a CU at a time} of the plane kernel's
+// forward call, 0 where it does not take the shape.
+extern "C" int gspn_plane_shape(int B, int C, int H, int W, int G, int kchunk, int logits, int dtype, int* shape) {
+    gspn::FwdParams p = {};
+    p.B = B; p.C = C; p.H = H; p.W = W; p.G = G; p.cpg = C / G; p.mask = 15; p.kchunk = kchunk; p.logits = logits;
+    const gspn::FwdPlanePlan t = gspn::plan_fwd_plane(p, dtype);
+    shape[0] = t.flat; shape[1] = t.cpw; shape[2] = t.nwaves; shape[3] = t.on_cu;
+    return t.ok;
+}
