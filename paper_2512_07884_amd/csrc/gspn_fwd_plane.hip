@@ -567,9 +567,12 @@ static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp)
     } else {
         t.shared_group = 1;
         // The number of waves (up to 8) whose channels divide the group and of which the most fit on a CU, a smaller one only for a quarter more of
-        // them (its workgroups each bring in the weights: 9216 planes 16x16 fp32 with logits, 3 waves -> 1, 22 -> 31 us); weights that the largest could
-        // request a direction ahead stay so.  In fp32 (flat: small maps) and with 16-bit weights in LDS; else the most waves, whose share of the
-        // weights is the smallest.  Most waves -> this: 49920 planes 7x7 fp32 46 -> 32 us, 36864 of 10x10 56 -> 43, 18432 of 28x28 129 -> 114 (5x5
+        // them (its workgroups each bring in the weights: 9216 planes 16x16 fp32 with logits, 3 waves -> 1, 22 -> 31 us) and, in fp32, where the chip
+        // is then filled less often, or three times and more (1303 random calls that had the choice: 0.82 in the mean there, 1.01 elsewhere; 17280 planes
+        // 14x14 with logits 39 -> 53 us, 1080 of 20x23 with h_save 53 -> 73); the flat variant's not five in six's place, which spread unevenly over
+        // the four SIMDs (nine calls 1.06, 7200 planes 12x63 90 -> 113 us); weights that the largest could request a
+        // direction ahead stay so.  In fp32 (flat: small maps) and with 16-bit weights in LDS; else the most waves, whose share of the weights is
+        // the smallest.  Most waves -> this: 49920 planes 7x7 fp32 46 -> 32 us, 36864 of 10x10 56 -> 43, 18432 of 28x28 129 -> 114 (5x5
         // 43 -> 46); where it stays: 15360 of 36x36 f16 with logits 207 -> 286, 29952 of 10x10 f16 56 -> 69.
         const int es = t.es, chunks = p.H * p.W * es / 16;
         auto ahead = [&](int nw) { return t.w16 ? chunks <= 2 * 64 * nw : 3 * chunks <= 4 * 64 * nw; };
@@ -584,7 +587,8 @@ static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp)
                 const int by_lds = (int)((size_t)FPLANE_LDS_BUDGET / ((lds + 1279) / 1280 * 1280)), by_regs = t.most_shared / nw;
                 const int waves = (by_lds < 1 ? 1 : by_regs < 1 ? 1 : by_lds < by_regs ? by_lds : by_regs) * nw;
                 if (best && (es == 2 ? !t.w16 : t.flat && !t.small)) break;
-                if (!best || 4 * waves >= 5 * best) { best = waves; t.nwaves = nw; t.K = nw * t.cpw; t.lds = lds; was_ahead = !t.flat && ahead(nw); }
+                const bool fewer = es == 2 || !best || ((!t.flat || nw <= 4) && (plane_rounds(p, best * t.cpw) > 2 || plane_rounds(p, best * t.cpw) > plane_rounds(p, waves * t.cpw)));
+                if (!best || (fewer && 4 * waves >= 5 * best)) { best = waves; t.nwaves = nw; t.K = nw * t.cpw; t.lds = lds; was_ahead = !t.flat && ahead(nw); }
             }
             if (best) { t.on_cu = best * t.cpw; break; }
             if (!w16) return false;

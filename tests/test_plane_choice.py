@@ -31,3 +31,12 @@ def plane_shape(B, C, H, W, G, dtype, kchunk=0, logits=False):
 ], ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
 def test_flat_where_the_chip_is_filled_less_often(shape, dtype, kchunk, logits, flat):
     assert plane_shape(*shape, dtype, kchunk, logits)[0] == flat
+
+
+# fp32, shared weights: fewer waves per workgroup only where the chip is then filled less often, and not five in six's place
+@pytest.mark.parametrize("shape,logits,waves", [
+    ((1, 21120, 3, 3, 8), True, 6), ((1, 49920, 7, 7, 8), False, 4), ((1, 17280, 14, 14, 1), True, 8), ((16, 540, 20, 23, 1), False, 6), ((2, 3600, 12, 63, 8), True, 3), ((1, 25920, 7, 12, 8), False, 3),
+    ((32, 192, 28, 28, 8), False, 6), ((96, 192, 28, 28, 8), False, 4), ((1, 1536, 28, 28, 8), False, 8),
+], ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+def test_fewer_waves_where_the_chip_is_filled_less_often(shape, logits, waves):
+    assert plane_shape(*shape, "f32", 0, logits)[2] == waves
