@@ -283,26 +283,15 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256, sizeof(T) == 4 && FLAT && 
             // Weights of the wave's own channels four pieces at a time: piece by piece it waited for the memory up to 24 times per
             // direction (11136 planes 16x14 fp32 268 -> 226 us).  A group's are few pieces per thread, and the registers cost more there (9216
             // planes 14x14 f16 20 -> 30).
-            constexpr int WB = SHARED ? 1 : 4;
-            for (int cb = t0; cb * ew < nel; cb += WB * tn) {
-                u32x4 wv4[WB];
-#pragma unroll
-                for (int j = 0; j < WB; ++j) {
-                    const int c = cb + j * tn;
-                    const uint32_t bo = (uint32_t)(c * lw);
+            if constexpr (SHARED) {
+                for (int c = t0; c * ew < nel; c += tn) {
+                    const int idx0 = c * ew;
+                    const uint32_t bo = (uint32_t)(idx0 * (int)sizeof(T));
                     u32x4 v = {0, 0, 0, 0};
-                    if (c * ew < nel) {
-                        if (lw == 16) v = ldg(rs, bo, 0);
-                        else if (lw == 8) { const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, bo, 0, 0); v[0] = t.x; v[1] = t.y; }
-                        else if (lw == 4) v[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, bo, 0, 0);
-                        else v[0] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, bo, 0, 0);
-                    }
-                    wv4[j] = v;
-                }
-#pragma unroll
-                for (int j = 0; j < WB; ++j) {
-                    const int c = cb + j * tn, idx0 = c * ew;
-                    if (idx0 >= nel) break;
+                    if (lw == 16) v = ldg(rs, bo, 0);
+                    else if (lw == 8) { const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, bo, 0, 0); v[0] = t.x; v[1] = t.y; }
+                    else if (lw == 4) v[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, bo, 0, 0);
+                    else v[0] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, bo, 0, 0);
                     int chn = idx0 / (3 * HW);
                     int r = idx0 - chn * 3 * HW;
                     int tap = r / HW;
@@ -315,8 +304,47 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256, sizeof(T) == 4 && FLAT && 
                             const int pos = vert ? col : row;
                             const bool outside = (tap == 0 && pos == 0) || (tap == 2 && pos == L - 1) || no_pred(row, col);
                             plds_st(wreg + 4u * (uint32_t)(chn * 4 * HP + 4 * (row * P + col) + tap),
-                                    outside ? masked : chunk_elem<T>(wv4[j], e));
+                                    outside ? masked : chunk_elem<T>(v, e));
                             if (++col == W) { col = 0; if (++row == H) { row = 0; if (++tap == 3) { tap = 0; ++chn; } } }
+                        }
+                    }
+                }
+            } else {
+                constexpr int WB = 4;
+                for (int cb = t0; cb * ew < nel; cb += WB * tn) {
+                    u32x4 wv4[WB];
+#pragma unroll
+                    for (int j = 0; j < WB; ++j) {
+                        const int c = cb + j * tn;
+                        const uint32_t bo = (uint32_t)(c * lw);
+                        u32x4 v = {0, 0, 0, 0};
+                        if (c * ew < nel) {
+                            if (lw == 16) v = ldg(rs, bo, 0);
+                            else if (lw == 8) { const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, bo, 0, 0); v[0] = t.x; v[1] = t.y; }
+                            else if (lw == 4) v[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, bo, 0, 0);
+                            else v[0] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, bo, 0, 0);
+                        }
+                        wv4[j] = v;
+                    }
+#pragma unroll
+                    for (int j = 0; j < WB; ++j) {
+                        const int c = cb + j * tn, idx0 = c * ew;
+                        if (idx0 >= nel) break;
+                        int chn = idx0 / (3 * HW);
+                        int r = idx0 - chn * 3 * HW;
+                        int tap = r / HW;
+                        r -= tap * HW;
+                        int row = r / W, col = r - row * W;
+#pragma unroll
+                        for (int e = 0; e < E; ++e) {
+                            if (e < ew) {
+                                // a tap that points outside the line is stored as 0, whatever the tensor holds there
+                                const int pos = vert ? col : row;
+                                const bool outside = (tap == 0 && pos == 0) || (tap == 2 && pos == L - 1) || no_pred(row, col);
+                                plds_st(wreg + 4u * (uint32_t)(chn * 4 * HP + 4 * (row * P + col) + tap),
+                                        outside ? masked : chunk_elem<T>(wv4[j], e));
+                                if (++col == W) { col = 0; if (++row == H) { row = 0; if (++tap == 3) { tap = 0; ++chn; } } }
+                            }
                         }
                     }
                 }
