@@ -261,7 +261,9 @@ const char* gspn_proxy_plan(int B, int K, int M, int H, int W, int dtype);
  * (The name is the family whose limits the call meets.  Most calls of the "tile" family, those of the "plane" family with few
  * planes, and the first pass of such "twopass" calls run the any-size kernel of "generic" in its place.  Calls of few planes and all four
  * directions run every direction in a workgroup of its own where that is faster, on small maps in a wave, whatever the plan: up to some
- * hundred planes, up to 1100 of 16-bit maps that would run line by line; most forward calls only with a workspace.)
+ * hundred planes, up to 1100 of 16-bit maps that would run line by line; most forward calls only with a workspace.  Maps of up to 208
+ * positions a side, the global scan in all four directions, run a wave per line, as a forward call and as the first pass of a backward
+ * one, where that is faster than the kernel that the lines above name: whatever the plan, any number of planes, no workspace.)
  * Environment variables for tests (results are the same whichever kernel runs, up to the rounding of
  * the storage type).  They are read once per process, by the first call that dispatches; a process
  * that changes them afterwards calls gspn_reload_env():
@@ -279,7 +281,8 @@ const char* gspn_proxy_plan(int B, int K, int M, int H, int W, int dtype);
  *   GSPN_STREAM_ONE_CHANNEL=1   the "stream" kernel with one channel per workgroup on 256- and 512-row bf16 maps (two channels of a
  *                               weight group share a workgroup and the weights there otherwise)
  *   GSPN_FWD_NO_CHUNK=1   skip the "chunk" kernels of GSPN-local (forward and the reverse sweep of the two-pass backward)
- *   GSPN_NO_APART=1   no workgroup per direction in calls of few planes (each of the others implies it) */
+ *   GSPN_NO_APART=1   no workgroup per direction in calls of few planes (each of the others implies it)
+ *   GSPN_NO_LINES=1   no wave per line (each of the others implies it; it implies none of them) */
 const char* gspn_fwd_plan(int B, int C, int H, int W, int G, unsigned dir_mask, int dtype, unsigned flags, int has_h_save);
 const char* gspn_bwd_plan(int B, int C, int H, int W, int G, unsigned dir_mask, int dtype, unsigned flags);
 /* the same for the GSPN-local calls */

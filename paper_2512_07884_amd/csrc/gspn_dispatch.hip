@@ -21,8 +21,9 @@ enum BwdPlan { BWD_GENERIC = 0, BWD_TILE = 1, BWD_PLANE = 2, BWD_TWOPASS = 3, BW
 // (forward and the reverse sweep of the two-pass backward); GSPN_STREAM_ONE_CHANNEL=1: the whole-line stream kernel with one
 // channel per workgroup on the maps where two channels of a group normally share a workgroup; GSPN_STREAM_TWO_CHANNELS=1:
 // two channels per workgroup there also in calls with too few planes to fill the chip that way; GSPN_NO_APART=1: no workgroup (no
-// wave, on small maps) per direction in calls of few planes (each of the others implies it).
-enum : unsigned { K_FORCE_GENERIC = 1, K_FWD_NO_PLANE = 2, K_BWD_NO_PLANE = 4, K_BWD_NO_TWOPASS = 8, K_FWD_NO_PAIR = 16, K_STREAM_NO_STAGED = 32, K_FWD_NO_CHUNK = 64, K_STREAM_ONE_CHANNEL = 128, K_STREAM_TWO_CHANNELS = 256, K_NO_ANY_SIZE = 512, K_NO_APART = 1024, K_VALID = 1u << 31 };
+// wave, on small maps) per direction in calls of few planes (each of the others implies it); GSPN_NO_LINES=1: no wave per line (each of the
+// others implies it; it implies none).
+enum : unsigned { K_FORCE_GENERIC = 1, K_FWD_NO_PLANE = 2, K_BWD_NO_PLANE = 4, K_BWD_NO_TWOPASS = 8, K_FWD_NO_PAIR = 16, K_STREAM_NO_STAGED = 32, K_FWD_NO_CHUNK = 64, K_STREAM_ONE_CHANNEL = 128, K_STREAM_TWO_CHANNELS = 256, K_NO_ANY_SIZE = 512, K_NO_APART = 1024, K_NO_LINES = 2048, K_VALID = 1u << 31 };
 static std::atomic<unsigned> g_knobs{0};
 static bool env_flag(const char* name) { const char* v = getenv(name); return v && v[0] == '1'; }
 void reload_env_knobs() {
@@ -38,13 +39,14 @@ void reload_env_knobs() {
     if (env_flag("GSPN_STREAM_TWO_CHANNELS")) k |= K_STREAM_TWO_CHANNELS;
     if (env_flag("GSPN_NO_ANY_SIZE")) k |= K_NO_ANY_SIZE;
     if (env_flag("GSPN_NO_APART")) k |= K_NO_APART;
+    if (env_flag("GSPN_NO_LINES")) k |= K_NO_LINES;
     g_knobs.store(k, std::memory_order_release);
 }
-struct Knobs { bool force_generic, fwd_no_plane, bwd_no_plane, bwd_no_twopass, fwd_no_pair, stream_no_staged, fwd_no_chunk, stream_one_channel, stream_two_channels, no_any_size, any; };
+struct Knobs { bool force_generic, fwd_no_plane, bwd_no_plane, bwd_no_twopass, fwd_no_pair, stream_no_staged, fwd_no_chunk, stream_one_channel, stream_two_channels, no_any_size, no_lines, any; };
 static Knobs knobs() {
     unsigned k = g_knobs.load(std::memory_order_acquire);
     if (!(k & K_VALID)) { reload_env_knobs(); k = g_knobs.load(std::memory_order_acquire); }
-    return Knobs{(k & K_FORCE_GENERIC) != 0, (k & K_FWD_NO_PLANE) != 0, (k & K_BWD_NO_PLANE) != 0, (k & K_BWD_NO_TWOPASS) != 0, (k & K_FWD_NO_PAIR) != 0, (k & K_STREAM_NO_STAGED) != 0, (k & K_FWD_NO_CHUNK) != 0, (k & K_STREAM_ONE_CHANNEL) != 0, (k & K_STREAM_TWO_CHANNELS) != 0, (k & K_NO_ANY_SIZE) != 0, k != K_VALID};
+    return Knobs{(k & K_FORCE_GENERIC) != 0, (k & K_FWD_NO_PLANE) != 0, (k & K_BWD_NO_PLANE) != 0, (k & K_BWD_NO_TWOPASS) != 0, (k & K_FWD_NO_PAIR) != 0, (k & K_STREAM_NO_STAGED) != 0, (k & K_FWD_NO_CHUNK) != 0, (k & K_STREAM_ONE_CHANNEL) != 0, (k & K_STREAM_TWO_CHANNELS) != 0, (k & K_NO_ANY_SIZE) != 0, k != K_VALID, (k & ~K_NO_LINES) != K_VALID};
 }
 bool pair_kernels_enabled() { return !knobs().fwd_no_pair; }
 bool staged_stream_enabled() { return !knobs().stream_no_staged; }
@@ -266,52 +268,86 @@ static bool apart_in_place_of(const BwdParams& p, int dtype, BwdPlan kernel) {
 }
 
 // Maps of up to 208 positions a side, global scan in all four directions: a wave per line (gspn_lines*.hip) rather than the kernels above, which
-// stage their lines through LDS by waves of their own or load them narrowly.  Both sides timed on 930 random calls (48 to 12 000 planes, the three
-// types, with logits and without, 1 to 96 channels per group); of the calls it takes, time against the kernel in their place in the mean,
-// forward 0.80 (one in 27 above 1.05, 1.3 at most), with h_save 0.83, backward 0.76; of those it leaves 1.15, 1.22, 1.11.
-//   Lines of one wave, up to 64 positions.  Any-size kernel: up to 900 planes, which are on the chip all at once, 0.83 (without maps of
-//   up to 512 pixels and ragged rows from 513 planes on, 1.0, and with h_save narrow ones of whole granules, 0.98); up to 3300 where lines
-//   fill half of a wave, 0.75 to 0.91 (shorter ones 1.1 to 1.3); beyond that large maps, 0.91 (others 1.2 to 1.7).  Plane kernel: weights
-//   of (nearly) every channel's own, which it loads element by element, 0.5 to 0.8 (fp32 lines of up to 28 in more than 1024 planes 1.1); up to 936 planes
-//   0.72; 16-bit planes of more than 6.5 KB 0.7 (its other calls 1.0 to 2.1).  Calls whose directions would run apart, from
-//   65 planes on: 0.79 without h_save, with it up to 90 000 pixels 0.92 (beyond that 1.1; with logits 0.8 to 1.1).
-//   Lines of several waves in the any-size kernel's place, 16 bits, 100 rows and more, no side twice the other: 0.87 (few planes
-//   with logits or of 113 to 128 positions 1.1; fewer rows 1.0, fp32 1.0 to 1.1, narrow maps up to 1.8).
+// stage their lines through LDS by waves of their own or load them narrowly.  Both sides timed by graph replay on 106 000 random calls (48 to
+// 12 000 planes, the three types, with logits and without, 1 to 1000 channels per group), this kernel forced and left out (GSPN_NO_LINES=1);
+// time against the kernel in its place in the mean, with the share of calls above 1.05: of the calls it takes, forward 0.78 (2 %), with h_save
+// 0.82 (2 %), backward 0.74 (1 %); of those next to the lines that it leaves, 1.01 (39 %), 1.03 (42 %), 1.04 (39 %).
+//   Lines of one wave, up to 64 positions, in the any-size kernel's place.  Up to 512 planes, two per CU, 0.73, but
+// rows of whole granules, which the any-size kernel reads as fast: with logits fp32 up to 900 000 pixels 1.09 (71 %), 16 bits with sides of up to 32
+// positions 1.04 (44 %); in fp32 beyond 256 planes up to 1024 pixels 1.03 (29 %; beyond them 0.90); with h_save rows of 33 and fewer;
+// 16 bits with h_save and logits, sides of up to 16 positions, 1.08 (60 %).
+// More planes queue for the CUs, and lanes beyond a line's end count.  Up to 1024 planes, 16 bits: shorter side 17 to 24 positions 0.84 (8 %), 9 to 16 0.95
+// (32 %), beyond three planes per CU no side above 32 0.99 (47 %); with h_save 34 to 40 0.83 (1 %), 25 to 33 0.97 (32 %).  Beyond them fp32 sides of 9 and more (shorter 1.10 (64 %)) and up to 1024
+// weight maps (more 0.98 (17 %)), 16 bits with up to 24 weight maps (0.87 (5 %)) or more than 2048 pixels (others 0.91 (20 %)); beyond 3300
+// planes only large maps, 0.91 (others 1.2 to 1.7).
+//   In the plane kernel's place, which holds several channels per workgroup: up to 1024 planes 0.77 (2 %; 1025 to 1400 0.92 (52 %)), fp32 768, 0.73 (769 to
+// 1024 0.87 (15 %)); beyond them weights of up to three channels, which that kernel loads for them alone, by pixels per channel of the group: 16 bits
+// from 512 on, 0.76 (6 %; 256 to 511 0.97 (44 %)), rows of whole granules from 1024 on, 0.69 (7 %; 768 to 1023 1.03 (51 %)), fp32 768, 0.68
+// (512 to 767 0.92 (28 %)), whole granules with logits 1024; 16-bit planes of more than 6.5 KB 0.7.
+//   Calls whose directions would run apart: 16 bits, 65 planes and more, up to 90 000 pixels 0.95 (6 %); with h_save 1.10 (80 %), fp32 1.02
+// (33 %), with both 1.26 (98 %), with logits 1.1 to 1.5.
+//   Lines of several waves in the any-size kernel's place, 16 bits, no side twice the other: more than 96 rows.  Widths of up to 128: 85 to 90 rows 0.89
+// (7 %), 91 to 96 0.88 (4 %), 97 to 102 0.78 (1 %); wider ones, whose horizontal scans leave half of the waves idle, 1.01 (46 %), 0.98 (32 %),
+// 0.94 (12 %); with h_save these lose up to 112 rows, 0.99 (30 %).  With logits from 256 planes on, one per CU: 192 to 255 0.92 (15 %), 256
+// to 319 0.88 (8 %).  113 to 128 positions without logits from 512 planes on.  fp32 1.0 to 1.1.
 static bool lines_in_place_of(const FwdParams& p, int dtype, FwdPlan kernel, bool apart) {
-    if (knobs().any || p.H * p.W < 100 || p.H < 8 || !lines_applicable(p, dtype)) return false;
-    const size_t planes = (size_t)p.B * p.C, HW = (size_t)p.H * p.W, pixels = planes * HW;
+    if (knobs().no_lines || p.H * p.W < 100 || p.H < 8 || !lines_applicable(p, dtype)) return false;
+    const size_t planes = (size_t)p.B * p.C, groups = (size_t)p.B * p.G, HW = (size_t)p.H * p.W, pixels = planes * HW;
     const int longest = p.H > p.W ? p.H : p.W, shortest = p.H > p.W ? p.W : p.H;
-    const bool f32 = dtype == 0, save = p.hs != nullptr, whole = p.W % (f32 ? 4 : 8) == 0;
-    if (longest > 64)
-        return kernel == FWD_ANY_SIZE && !apart && !f32 && p.H >= 100 && 2 * shortest >= longest &&
-               (planes >= 512 || (!p.logits && (longest <= 112 || longest > 128)));
-    if (apart) return planes > 64 && !p.logits && pixels <= 90000 && shortest >= 14;      // (the same with h_save: y to the bit)
-    if (kernel == FWD_ANY_SIZE || kernel == FWD_TILE) {
-        if (planes <= 900) return !(save && whole && p.W <= 33) && !(planes > 512 && HW <= 512 && !whole);
-        if (planes <= 3300) return save ? p.W > 33 : longest > 32;
-        return longest > 40 && pixels > 6100000 && !(save && HW < 1100);
+    const bool f32 = dtype == 0, save = p.hs != nullptr, logits = p.logits, whole = p.W % (f32 ? 4 : 8) == 0;
+    if (longest > 64) {
+        if (kernel != FWD_ANY_SIZE || apart || f32 || p.H <= 96 || 2 * shortest < longest || (save && !logits && p.W > 128 && p.H <= 112)) return false;
+        const bool two = longest > 112 && longest <= 128;             // (positions per lane)
+        return logits ? planes >= 256 && !(save && two && planes < 512) : planes >= 512 || !two;
     }
-    if (kernel == FWD_PLANE)
-        return planes <= 936 || (!f32 && HW > 3328) || (p.cpg <= 3 && !(longest <= (f32 ? 28 : 16) && planes > 1024));
-    return false;
+    if (apart) return !save && !f32 && !logits && planes > 64 && pixels <= 90000 && shortest >= 14;      // (y to the bit the one of calls with h_save)
+    if (kernel == FWD_ANY_SIZE || kernel == FWD_TILE) {
+        if (whole) {
+            if (f32 && planes > 256 && (HW <= 1024 || ((logits || save) && pixels <= 900000))) return false;
+            if (f32 && logits && pixels <= 900000) return false;
+            if (!f32 && logits && shortest <= 32) return planes <= 256;
+            if (save && p.W <= 33) return false;
+        }
+        if (planes <= 512) return f32 || !save || !logits || shortest > 16;
+        if (!whole && HW <= 512) return false;
+        const bool many = planes <= 3300 || (longest > 40 && pixels > 6100000 && !(save && HW < 1100));
+        if (f32) return planes <= 1024 || (many && shortest > 8 && longest > 32 && groups <= 1024 && !(save && p.W <= 33));
+        if (save) return many && shortest > 33;
+        return many && shortest > 16 && (planes <= 768 || longest > 32) && (planes <= 1024 || groups <= 24 || HW > 2048);
+    }
+    if (kernel != FWD_PLANE) return false;
+    if (planes <= (f32 ? 768 : 1024)) return true;
+    if (p.cpg > 3) return !f32 && HW > 3328;
+    if (f32) return whole ? logits && HW > 1024 * (size_t)p.cpg : HW > 768 * (size_t)p.cpg;
+    return HW > (whole ? 1024 : 512) * (size_t)p.cpg;
 }
 // Backward: the same kernel as the reverse sweep, e in fp32 between it and the any-size kernels' second pass, which shares a group's
-// channels between waves where the two-pass kernels' walks them one after the other.  Any-size kernel 0.93 (up to 900 planes; beyond
-// that lines of more than 40 columns up to 2272); single-launch plane kernel 0.59, which holds a group in one workgroup (up to 1536 planes,
-// lines of up to 13 where up to 47 channels share a group; to 3936 from 12 on); two passes whose first is the any-size kernel 0.75 from 15 channels
-// per group on, lines of more than 64 0.78 with up to 15 groups and 0.86 in fp32; the plane kernel 0.75 with few groups or weights of each channel's own.
+// channels between waves where the two-pass kernels' walks them one after the other.  Figures as above.  Any-size kernel 0.90: up to 256
+// planes all, in 16 bits beyond them sides of 33 and more, or up to 512 planes without logits (401 to 512 0.96 (2 %), 513 to 700 1.00
+// (25 %)), fp32 up to 900 planes, and then lines of more than 40 columns up to 2272.  Single-launch plane kernel 0.5, which holds a group in one
+// workgroup: up to 1536 planes, lines of up to 13 where up to 47 channels share a group; to 3936 from 12 on; more than 1024 planes of up to 21
+// channels per group with logits only (without 0.83 (23 %)).  Two passes whose first is the any-size kernel 0.7 from 15 channels per group on (in 16
+// bits not small calls of narrow maps, 0.88 (17 %)), lines of more than 64 0.6 with up to 15 groups and in fp32 0.85.  The plane kernel as the first
+// pass 0.65 with few groups; with weights of each channel's own up to 256 planes 0.70 (257 to 400 0.84 (22 %), more than 1000 1.13
+// (65 %)), and more than 2048 pixels with one or two channels per group 0.66.
 static bool lines_in_place_of(const BwdParams& p, int dtype, BwdPlan kernel, bool apart) {
-    if (knobs().any || apart || p.H * p.W < 100 || p.H < 8 || !lines_applicable(reverse_sweep_params(p), dtype) || !ragged_finish_fits(p, dtype)) return false;
+    if (knobs().no_lines || apart || p.H * p.W < 100 || p.H < 8 || !lines_applicable(reverse_sweep_params(p), dtype) || !ragged_finish_fits(p, dtype)) return false;
     const size_t planes = (size_t)p.B * p.C, groups = (size_t)p.B * p.G, HW = (size_t)p.H * p.W;
     const int longest = p.H > p.W ? p.H : p.W, shortest = p.H > p.W ? p.W : p.H;
     const bool f32 = dtype == 0;
     const char* first = kernel == BWD_TWOPASS ? twopass_kernel_name(p, dtype) + 8 : "";
     const bool any_first = !strcmp(first, "any size"), plane_first = !strcmp(first, "plane");
     if (longest > 64) return any_first && (groups <= 15 || (f32 && 2 * shortest >= longest));
-    if (kernel == BWD_ANY_SIZE) return planes <= 900 || (planes <= 2272 && p.W > 40);
-    if (kernel == BWD_PLANE) return planes >= 128 && ((planes <= 3936 && shortest > 11 && longest > 13) || (planes <= 1536 && (longest > 13 || p.cpg <= 47)));
-    if (plane_first) return groups <= 27 || (groups <= 53 && HW < 1200) || (p.cpg <= 2 && !p.logits);
-    return any_first && p.cpg > 14;
+    if (kernel == BWD_ANY_SIZE) {
+        if (planes <= 256) return true;
+        if (planes <= 900) return f32 || shortest > 32 || (planes <= 512 && !p.logits);
+        return planes <= 2272 && p.W > 40 && (f32 || shortest > 32);
+    }
+    if (kernel == BWD_PLANE)
+        return planes >= 128 && (planes <= 1024 || p.cpg > 21 || p.logits) &&
+               ((planes <= 3936 && shortest > 11 && longest > 13) || (planes <= 1536 && (longest > 13 || p.cpg <= 47)));
+    if (plane_first) return groups <= 27 || (groups <= 53 && HW < 1200) || (p.cpg <= 2 && !p.logits && (HW > 2048 || (p.cpg == 1 && groups <= 256)));
+    return any_first && p.cpg > 14 && (f32 || planes * HW > 150000 || p.W > 17);
 }
 
 // Small maps, a wave per direction.  Time of what the kernels above take, 14 700 random calls of the three types, with stretches and logits,
