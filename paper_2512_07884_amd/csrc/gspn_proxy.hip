@@ -361,6 +361,88 @@ __global__ void __launch_bounds__(64 * NW) proxy_gradw_mfma_kernel(const T* __re
     }
 }
 
+// The same with the rows through LDS.  A matrix-core operand is 16 bytes of each of 32 rows: asked for as it is multiplied, a request
+// touches 32 lines for a quarter of each.  Here a request is eight rows of whole 128-byte lines; 128 pixels of the tile's rows make a
+// stage, the stages after it are on their way in registers, and each of the eight waves multiplies every eighth step of 16 pixels, in
+// the order of the kernel above with eight waves (on whole rows its sums, bit for bit; launches of 512 tiles and more have four there).
+// 1152 x 144 on two 64x64 images 30 -> 18 us, on 16 of 28x28 32.7 -> 29.5 (in stages of 256 pixels 37).  Every tile of the longer side is read by as many workgroups as the
+// shorter side has tiles, and each XCD has an L2 of its own: an XCD takes neighbouring tiles of the longer side with all of the
+// shorter one's.
+template <typename T, bool ANY>
+__global__ void __launch_bounds__(512) proxy_gradw_tile_kernel(const T* __restrict__ gout, const T* __restrict__ in,
+                                                              float* __restrict__ partial, int K, int M, int N,
+                                                              int mtiles, int ktiles) {
+    constexpr int ROWS = 64, PITCH = 256 + 16, AHEAD = 3;
+    __shared__ __attribute__((aligned(16))) char stage[2 * ROWS * PITCH];                // (the sums of the waves pass through it at the end)
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int per_image = mtiles * ktiles, item = (int)xcd_contiguous_item(blockIdx.x, gridDim.x);
+    const int b = item / per_image, rem = item - b * per_image;
+    const int mt = mtiles <= ktiles ? rem % mtiles : rem / ktiles, kt = mtiles <= ktiles ? rem / mtiles : rem % ktiles;
+    // this thread's pieces: row threadIdx / 16 of every 32, pixels 8 * (threadIdx % 16) of the stage (rows past the end are read as the
+    // last row, their sums are not stored)
+    const int r0 = threadIdx.x >> 4, c0 = (threadIdx.x & 15) * 8;
+    const T* const gr = gout + ((size_t)b * M + min(mt * 32 + r0, M - 1)) * N;
+    const T* const xr = in + ((size_t)b * K + min(kt * 32 + r0, K - 1)) * N;
+    struct Piece { u32x4 g, x; };
+    const int nstages = (N + 127) / 128;
+    auto fetch = [&](int s, Piece& p) {
+        const int n = min(s, nstages - 1) * 128 + c0, nl = min(n, N - 8);        // (beyond the rows' end: their last eight pixels)
+        ld_row<T, 16, ANY>(gr + nl, (uint32_t*)&p.g);
+        ld_row<T, 16, ANY>(xr + nl, (uint32_t*)&p.x);
+    };
+    char* const place = stage + r0 * PITCH + c0 * 2;
+    auto put = [&](int s, Piece& p) {
+        const int n = s * 128 + c0;
+        if (s == nstages - 1) {                                                  // (uniform) what lies beyond the rows counts as 0
+            const int sh = min(max(n - (N - 8), 0), 8);
+            if constexpr (ANY) { p.g = rg_realign<T>(p.g, sh); p.x = rg_realign<T>(p.x, sh); }
+            if (sh >= 8) p.g = p.x = u32x4{0, 0, 0, 0};
+        }
+        *(u32x4*)(place + (s & 1) * ROWS * PITCH) = p.g;
+        *(u32x4*)(place + ((s & 1) * ROWS + 32) * PITCH) = p.x;
+    };
+    f32x16_t acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    const char* const from = stage + (lane & 31) * PITCH + wave * 32 + (lane >> 5) * 16;
+    auto multiply = [&](int s) {
+        const char* f = from + (s & 1) * ROWS * PITCH;
+        acc = mfma_k16<T>(*(const u32x4*)f, *(const u32x4*)(f + 32 * PITCH), acc);
+    };
+    Piece p[AHEAD];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) fetch(i, p[i]);
+    put(0, p[0]);
+    fetch(AHEAD, p[0]);
+    lds_barrier();
+    for (int s0 = 0; s0 < nstages; s0 += AHEAD) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            const int s = s0 + i;
+            if (s < nstages) {
+                if (s + 1 < nstages) put(s + 1, p[(i + 1) % AHEAD]);
+                fetch(s + 1 + AHEAD, p[(i + 1) % AHEAD]);
+                multiply(s);
+                lds_barrier();
+            }
+        }
+    }
+    float (*const red)[16][64] = (float (*)[16][64])stage;
+    static_assert(sizeof(float) * 8 * 16 * 64 <= sizeof(stage), "");
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r];
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < 16 * 64; idx += 512) {
+        const int r = idx >> 6, l = idx & 63;
+        float v = red[0][r][l];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) v += red[w][r][l];
+        const int m = mt * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3), k = kt * 32 + (l & 31);
+        if (m < M && k < K) partial[((size_t)b * M + m) * K + k] = v;
+    }
+}
+
 // The same with the rows through LDS, in tiles of 16 MT x 16 KT (v_mfma_f32_16x16x32).  A matrix-core operand is 16 bytes of each of 16
 // rows: asked for as it is multiplied, a request touches 16 lines for a part of each.  Here a request is two rows of 512 bytes, whole lines;
 // 256 pixels of the tile's rows make a stage, the stages after it are on their way in registers (three or four: 96 to 144 KB per CU, which is
@@ -559,15 +641,10 @@ __global__ void __launch_bounds__(256) proxy_gradw_fma_kernel(const T* __restric
     if (m < M && k < K) partial[((size_t)b * M + m) * K + k] = acc;
 }
 
-// gP = the per-image sums added in image order (halves: of one image, whose second half's sums are in gP)
-__global__ void __launch_bounds__(256) proxy_gradw_sum_kernel(float* __restrict__ partial, float* __restrict__ gP, int B, int MK, bool halves) {
+// gP = the per-image sums added in image order
+__global__ void __launch_bounds__(256) proxy_gradw_sum_kernel(const float* __restrict__ partial, float* __restrict__ gP, int B, int MK) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= MK) return;
-    if (halves) {
-        const float v = partial[i] + gP[i];
-        partial[i] = v; gP[i] = v;
-        return;
-    }
     float v = 0.f;
     // sixteen images requested at a time (the loads do not depend on the sum), then added in order
     for (int b0 = 0; b0 < B; b0 += 16) {
@@ -578,6 +655,13 @@ __global__ void __launch_bounds__(256) proxy_gradw_sum_kernel(float* __restrict_
         for (int j = 0; j < 16; ++j) if (b0 + j < B) v += t[j];
     }
     gP[i] = v;
+}
+// ... of one image, the sums of whose second half of pixels are in gP
+__global__ void __launch_bounds__(256) proxy_gradw_halves_kernel(float* __restrict__ partial, float* __restrict__ gP, int MK) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= MK) return;
+    const float v = partial[i] + gP[i];
+    partial[i] = v; gP[i] = v;
 }
 
 }  // namespace
@@ -677,44 +761,68 @@ static hipError_t launch_gradw_lds(const void* gout, const void* in, float* part
 
 // The weight gradient's kernel for 16-bit storage: its tile in units of 16 rows and the ranges of pixels that are summed apart.
 // apart: `partial` and gP share no memory.
-enum GradwKernel { GRADW_PLAIN = 0, GRADW_SMALL = 1, GRADW_LDS = 2 };
+enum GradwKernel { GRADW_PLAIN = 0, GRADW_SMALL = 1, GRADW_LDS = 2, GRADW_TILE = 3 };
 struct GradwPlan { GradwKernel kernel; int mt, kt, ranges; };
-static GradwPlan gradw_plan(int B, int K, int M, int N, bool apart) {
-    GradwPlan p = {GRADW_PLAIN, 2, 2, 1};
-    const long tiles = (long)B * ((M + 31) / 32) * ((K + 31) / 32);
-    if (N < 8) return p;
-    // 16 x 16 tiles where 32 x 32 ones are fewer than a quarter of the CUs and the rows are long (two images, 32 x 32 -> 16 x
-    // 16: 8 <- 96 channels on 96x96 26.8 -> 17.0 us; below 4096 pixels no gain in the mean and up to 7 % lost: 48 <- 96 on
-    // 56x56 16.1 -> 17.2.  Rows at any element: 0.94 of the time in the mean from 1024 pixels on).  Not for odd rows, half of
-    // whose requests fall between 32-bit words and are worked off in twice the time: there the rows pass once, through LDS
-    // (24 <- 192 on four images 89x111 52 -> 32 us, 24 <- 384 on two of 111x79 55 -> 29).
-    if (tiles < 64 && N % 2 == 0 && N >= (N % 8 ? 1024 : 4096)) {
-        p.kernel = GRADW_SMALL; p.mt = p.kt = 1;
-        return p;
-    }
-    // The rows through LDS where they are long or tiles enough to fill the chip.  Share of the time of the kernel below in 90 random
-    // products (8 to 1152 channels, 1 to 16 images): 1024 pixels and more 0.4 to 1.0, 512 to 1023 from 256 tiles on 0.9; shorter rows
-    // are a stage or two each (304 x 353 on 14 images of 336 pixels 13.7 -> 20.3 us).  (A launch counts its threads in 32 bits.)
-    if (tiles > 0x3fffff || !(N >= 1024 || (N >= 512 && tiles >= 256))) return p;
-    p.kernel = GRADW_LDS;
-    // One image leaves `partial` a single place: its second half's sums go to gP on the way (144 x 1152 channels on
-    // 128x128 32.7 -> 28.6 us, 24 <- 192 on 123x49 23.2 -> 16.3), unless that is the same place.
-    p.ranges = B == 1 && apart ? 2 : 1;
-    // The tile: what a CU takes in, rows per tile times turns of 256 workgroups, is what the time goes by.  32 x 32 has two
-    // workgroups on a CU, which hide each other's start and end (0.75 of that); 64 x 64 nearly runs out of registers (1.15).
-    // us with 32 x 32, 48 x 32, 48 x 48, 64 x 64: 144 x 1152 on two 64x64 images 18.3 15.3 17.6 22.6; 48 x 1152 on 14 images 72x81
-    // 66 56 65 48, on six of 105x48 22.4 18.8 21.3 27.2; 144 x 768 on four of 118x18 18.7 25.2 17.7 22.3.  Rows of less than
-    // eight stages are not worth a second start: 144 x 1152 on 16 images 28x28 35 39 36 38.
+
+// The tile of the kernel with stages of 256 pixels: what a CU takes in, rows per tile times turns of 256 workgroups, is what the time goes
+// by.  32 x 32 has two workgroups on a CU, which hide each other's start and end (0.75 of that); 64 x 64 nearly runs out of registers (1.15).
+// us with 32 x 32, 48 x 32, 48 x 48, 64 x 64: 144 x 1152 on two 64x64 images 18.3 15.3 17.6 22.6; 48 x 1152 on 14 images 72x81
+// 66 56 65 48, on six of 105x48 22.4 18.8 21.3 27.2; 144 x 768 on four of 118x18 18.7 25.2 17.7 22.3.  Rows of less than
+// eight stages are not worth a second start.  One image leaves `partial` a single place: its second half's sums go to gP on the way
+// (144 x 1152 channels on 128x128 32.7 -> 28.6 us, 24 <- 192 on 123x49 23.2 -> 16.3), unless that is the same place.
+static GradwPlan gradw_stages(int B, int K, int M, int N, bool apart, long* wgs) {
+    GradwPlan p = {GRADW_LDS, 2, 2, B == 1 && apart ? 2 : 1};
     const int shapes[][2] = {{2, 2}, {3, 2}, {2, 3}, {3, 3}, {4, 4}};
     long best = -1;
     for (const auto& t : shapes) {
-        const long wgs = (long)B * p.ranges * ((M + 16 * t[0] - 1) / (16 * t[0])) * ((K + 16 * t[1] - 1) / (16 * t[1])), turns = (wgs + 255) / 256;
+        const long n = (long)B * p.ranges * ((M + 16 * t[0] - 1) / (16 * t[0])) * ((K + 16 * t[1] - 1) / (16 * t[1])), turns = (n + 255) / 256;
         const bool pair = t[0] == 2 && t[1] == 2;
         if (!pair && turns > 1 && N < 2048) continue;
         const long cost = turns * (t[0] + t[1]) * (pair && turns > 1 ? 75 : t[0] == 4 ? 115 : 100);
-        if (best < 0 || cost < best) { best = cost; p.mt = t[0]; p.kt = t[1]; }
+        if (best < 0 || cost < best) { best = cost; p.mt = t[0]; p.kt = t[1]; *wgs = n; }
     }
     return p;
+}
+
+// Where the rows are long they pass through LDS in stages of 256 pixels, elsewhere by the kernel that the products had before it.  The four
+// timed on 19 600 random products of 512 pixels and more (2 to 1400 channels, 1 to 64 images; graph replays): what it takes 0.80 of the time of the
+// kernel in its place in the mean, 1 in a hundred above 1.05; the others would take 1.13, 1.02 and 1.04 with it.
+//   In place of the 16 x 16 tiles (there where 32 x 32 ones are fewer than a quarter of the CUs and the rows are long: two images, 8 <- 96 channels on
+// 96x96 26.8 -> 17.0 us; below 4096 pixels no gain in the mean and up to 7 % lost: 48 <- 96 on 56x56 16.1 -> 17.2; rows at any element from
+// 1024 pixels on 0.94): odd rows, half of whose requests fall between 32-bit words and are worked off in twice the time (24 <- 192 on four
+// images 89x111 52 -> 32 us), from 3072 pixels on with more than ten channels on the smaller side (0.71), 5120 with more than 16 on the larger (0.88;
+// up to 16 1.1, shorter rows 1.2); of one image sooner.  Whole words: of one image only (0.80; several 1.3 to 1.5).
+//   In place of the 32 x 32 tiles with stages of 128 pixels, four of which a CU holds (2048 pixels and 16 tiles, 1024 and 64, 512 and 256; a single tile
+// on one side rows at any element from 1024 pixels on, whole ones from 4096 and 256 tiles on; timed against the kernel without LDS on 4900
+// products, 0.6 to 0.83): fewer and longer stages lose where the rows are short or many workgroups queue.  Granules: one turn of the CUs 0.75,
+// more from 2560 pixels on with a larger tile (0.81), 4096 with 32 x 32 (0.95; below 1.1: 144 x 1152 on 16 images 28x28 29.5 against 37 us).  Other even
+// rows: from 2560 pixels on (one turn 0.84), 3072 with a larger tile (0.81), 5632 with 32 x 32 (0.93; below 1.1 to 1.3).  Odd rows: from 2560 on
+// with a larger tile (0.78), 8192 with 32 x 32 (0.95; below 1.0 to 1.4).  Of one image from 2048 pixels on, with whole granules any.
+//   In place of the kernel without LDS: from 2049 pixels on with more than 16 channels on the smaller side (0.67), 64 workgroups or one image (0.78;
+// others 1.09); shorter rows of more than 16 channels from 1409 pixels on (0.86), odd ones from 833 (0.83; shorter ones 1.06 to 1.2).
+static GradwPlan gradw_plan(int B, int K, int M, int N, bool apart) {
+    GradwPlan p = {GRADW_PLAIN, 2, 2, 1};
+    const int mtiles = (M + 31) / 32, ktiles = (K + 31) / 32, fewer = M < K ? M : K, more = M < K ? K : M;
+    const long tiles = (long)B * mtiles * ktiles;
+    if (N < 512 || tiles > 0x7fffff) return p;                 // (a launch counts its threads in 32 bits)
+    const bool odd = N % 2 != 0, granules = N % 8 == 0;
+    long wgs = 0;
+    const GradwPlan stages = gradw_stages(B, K, M, N, apart, &wgs);
+    const bool pair = stages.mt == 2 && stages.kt == 2;
+    bool take;
+    if (tiles < 64 && N >= (granules ? 4096 : 1024)) {
+        p.kernel = GRADW_SMALL; p.mt = p.kt = 1;
+        take = B == 1 ? (odd ? N > 3072 || fewer > 16 : N > 5120 && fewer > 16) : odd && more > 16 && ((fewer > 10 && N > 3072) || N > 5120);
+    } else if (mtiles > 1 && ktiles > 1 ? (N >= 2048 && tiles >= 16) || (N >= 1024 && tiles >= 64) || tiles >= 256
+                                        : granules ? N >= 4096 && tiles >= 256 : N >= 1024) {
+        p.kernel = GRADW_TILE;
+        take = N >= (B == 1 ? (granules ? 0 : 2048)
+                   : granules ? (wgs <= 256 ? 0 : pair ? 4096 : 2560)
+                   : odd ? (pair ? 8192 : 2560) : wgs <= 256 ? 2560 : pair ? 5632 : 3072);
+    } else {
+        take = N > 2048 ? fewer > 16 || wgs > 64 || B == 1 : fewer > 16 && (N > 1408 || (odd && N > 832));
+    }
+    return take && tiles <= 0x3fffff ? stages : p;
 }
 
 // per-image sums of gout in^T into `partial` (B*M*K floats), storage type T; halves: of one image, the sums of its second half into gP
@@ -730,6 +838,11 @@ static hipError_t launch_gradw_as(const void* gout, const void* in, float* parti
             const int mt = (M + 15) / 16, kt = (K + 15) / 16;
             void (*k)(const T*, const T*, float*, int, int, int, int, int) = N % 8 ? proxy_gradw_small_kernel<T, true> : proxy_gradw_small_kernel<T, false>;
             hipLaunchKernelGGL(k, dim3((unsigned)((long)B * mt * kt)), dim3(1024), 0, s, (const T*)gout, (const T*)in, partial, K, M, N, mt, kt);
+            return hipGetLastError();
+        }
+        if (t.kernel == GRADW_TILE) {
+            void (*k)(const T*, const T*, float*, int, int, int, int, int) = N % 8 ? proxy_gradw_tile_kernel<T, true> : proxy_gradw_tile_kernel<T, false>;
+            hipLaunchKernelGGL(k, dim3((unsigned)((long)B * mtiles * ktiles)), dim3(512), 0, s, (const T*)gout, (const T*)in, partial, K, M, N, mtiles, ktiles);
             return hipGetLastError();
         }
         if (t.kernel == GRADW_LDS) {
@@ -778,7 +891,8 @@ hipError_t launch_proxy_project_bwd(const void* gout, const void* in, const void
                                   : launch_gradw_as<f16_t>(gout, in, partial, gP, &halves, B, K, M, N, s);
         if (e != hipSuccess) return e;
         const int MK = M * K;
-        hipLaunchKernelGGL(proxy_gradw_sum_kernel, dim3((unsigned)((MK + 255) / 256)), dim3(256), 0, s, partial, gP, B, MK, halves);
+        if (halves) hipLaunchKernelGGL(proxy_gradw_halves_kernel, dim3((unsigned)((MK + 255) / 256)), dim3(256), 0, s, partial, gP, MK);
+        else hipLaunchKernelGGL(proxy_gradw_sum_kernel, dim3((unsigned)((MK + 255) / 256)), dim3(256), 0, s, partial, gP, B, MK);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -825,7 +939,7 @@ hipError_t launch_proxy_project_bwd_static(const void* gout, const void* in, con
 
 }  // namespace gspn
 
-// For the tests, not part of the ABI: the kernel (0 rows from memory, 1 16 x 16 tiles, 2 rows through LDS), the rows and columns of its tile
+// For the tests, not part of the ABI: the kernel (0 rows from memory, 1 16 x 16 tiles, 2 and 3 rows through LDS in stages of 256 and 128 pixels), the rows and columns of its tile
 // and the ranges of pixels of the weight gradient in 16-bit storage; apart: `partial` and gP share no memory.
 extern "C" void gspn_proxy_gradw_shape(int B, int K, int M, int H, int W, int apart, int* shape) {
     const gspn::GradwPlan t = gspn::gradw_plan(B, K, M, H * W, apart != 0);

@@ -137,17 +137,22 @@ def test_weight_gradient_with_either_wave_count_and_more_images_than_one_batch_o
     assert np.array_equal(gP, gP2)
 
 
-# (B, K, M, H, W, dtype): each tile of the kernel that takes the rows through LDS, with channels that end inside a tile and rows that end
-# inside a stage of 256 pixels, a granule, a word: 32 x 32 (one image: in two halves), 48 x 32, 32 x 48, 48 x 48, 64 x 64
-LDS_TILES = [(2, 40, 33, 33, 33, "bf16"), (1, 40, 33, 22, 50, "bf16"), (1, 70, 41, 25, 41, "f16"), (2, 1152, 144, 25, 41, "bf16"), (2, 144, 1248, 27, 38, "f16"),
-             (3, 1150, 142, 32, 32, "bf16"), (12, 1150, 46, 37, 29, "bf16"), (8, 384, 144, 24, 24, "f16")]
+# (B, K, M, H, W, dtype), (kernel, rows and columns of its tile, ranges of pixels): each tile of the kernels that take the rows through LDS, in
+# stages of 256 pixels (2) and of 128 (3), with channels that end inside a tile and rows that end inside a stage, a granule, a word; of
+# one image in two ranges, of many in one turn of the CUs and in several
+LDS_TILES = [((2, 40, 33, 57, 55, "bf16"), (2, 32, 32, 1)), ((1, 70, 41, 25, 41, "f16"), (2, 32, 32, 2)), ((1, 1152, 144, 32, 32, "bf16"), (2, 48, 32, 2)), ((1, 48, 1150, 40, 44, "f16"), (2, 32, 32, 2)),
+             ((2, 1152, 144, 64, 64, "bf16"), (2, 48, 32, 1)), ((2, 144, 1248, 62, 42, "f16"), (2, 32, 48, 1)), ((3, 1150, 142, 32, 32, "bf16"), (2, 48, 48, 1)),
+             ((12, 1150, 46, 57, 49, "bf16"), (2, 64, 64, 1)), ((2, 1152, 144, 25, 41, "bf16"), (3, 32, 32, 1)), ((2, 144, 1248, 27, 38, "f16"), (3, 32, 32, 1)),
+             ((8, 384, 144, 24, 24, "f16"), (3, 32, 32, 1)), ((64, 40, 8, 33, 33, "bf16"), (3, 32, 32, 1)), ((2, 40, 33, 33, 34, "bf16"), (1, 16, 16, 1)), ((6, 70, 41, 28, 28, "f16"), (0, 32, 32, 1))]
 
 
-@pytest.mark.parametrize("shape", LDS_TILES, ids=lambda s: "x".join(map(str, s)))
-def test_weight_gradient_through_lds_in_each_tile(shape):
+@pytest.mark.parametrize("shape,kernel", LDS_TILES, ids=lambda s: "x".join(map(str, s)))
+def test_weight_gradient_through_lds_in_each_tile(shape, kernel):
     import torch
     import paper_2512_07884_amd as G
+    from test_gradw_choice import gradw_shape
     B, K, M, H, W, dtype = shape
+    assert gradw_shape(B, K, M, H, W) == kernel
     rng = np.random.default_rng([29, B, K, M])
     x = WL.to_storage(rng.standard_normal((B, K, H, W)), dtype)
     g = WL.to_storage(rng.standard_normal((B, M, H, W)), dtype)
@@ -157,7 +162,8 @@ def test_weight_gradient_through_lds_in_each_tile(shape):
     G.gspn_proxy_project_bwd(to_device(g, dtype), to_device(x, dtype), to_device(P, dtype), None, gP, partial)
     torch.cuda.synchronize()
     ref = np.matmul(WL.storage_to_f64(g, dtype).reshape(B, M, H * W), WL.storage_to_f64(x, dtype).reshape(B, K, H * W).transpose(0, 2, 1))
-    # products are exact in fp32; 1100 of them in eight chains of fp32 additions: below 140 * 2^-24 = 8e-6 of the largest sum
+    # products are exact in fp32; up to 4100 of them in eight chains of fp32 additions, whose roundings go either way: some
+    # sqrt(512) * 2^-24 = 1.4e-6 of the largest sum, seven times that allowed
     assert rel_inf_err(partial.double().cpu().numpy(), ref) <= 1e-5
     assert rel_inf_err(gP.double().cpu().numpy(), ref.sum(0)) <= 1e-5
 
