@@ -243,11 +243,10 @@ bwd_plane_kernel(BwdPlaneArgs a) {
                 next(idx, s);
             }
         };
-        // LOGITS: softmax over the taps whose neighbour exists, per scan step; step 0 has no predecessor: no weight.  (Per-channel weights
-        // divide: 32 x 192 channels 28x28 fp32 225 us, 239 with the Newton step.)
+        // LOGITS: softmax over the taps whose neighbour exists, per scan step; step 0 has no predecessor: no weight
         auto normalise = [&](float (&w0r)[SMAX], float (&w1r)[SMAX], float (&w2r)[SMAX]) {
 #pragma unroll
-            for (int s = 1; s < SMAX; ++s) softmax3<!SHARED>(w0r[s], w1r[s], w2r[s], first, last);
+            for (int s = 1; s < SMAX; ++s) softmax3(w0r[s], w1r[s], w2r[s], first, last);
             w0r[0] = 0.f; w1r[0] = 0.f; w2r[0] = 0.f;
         };
         for (int pair = wave; pair < pairs; pair += a.nwaves) {

@@ -161,7 +161,7 @@ struct VStream {
             for (int v = 0; v < V; ++v) {
                 av[v] = elem<T>(cur.l, v) * elem<T>(cur.x, v);
                 w0[v] = elem<T>(cur.w0, v); w1[v] = elem<T>(cur.w1, v); w2[v] = elem<T>(cur.w2, v);
-                if constexpr (LOGITS) softmax3<sizeof(T) == 2 && !SAVE>(w0[v], w1[v], w2[v], first && v == 0, last && v == V - 1);     // (as the horizontal phases)
+                if constexpr (LOGITS) softmax3(w0[v], w1[v], w2[v], first && v == 0, last && v == V - 1);
                 if (LOCAL || k == 0) { w0[v] = start ? 0.f : w0[v]; w1[v] = start ? 0.f : w1[v]; w2[v] = start ? 0.f : w2[v]; }
                 if constexpr (LOCAL) h[v] = start ? 0.f : h[v];
             }

@@ -183,7 +183,7 @@ __device__ __forceinline__ void horizontal_rows(const FwdParams& p, char* blk_a,
             const float av = elem<T>(bl, e) * elem<T>(bx, e);
             float c0 = elem<T>(b0, e), c1 = elem<T>(b1, e), c2 = elem<T>(b2, e);
             // raw logits: normalised here over the taps whose neighbour row exists (Sec. 3.2)
-            if constexpr (LOGITS) softmax3<!SAVE && !BWD>(c0, c1, c2, img_first, img_last);        // (512 planes 512x512 bf16: division 1092 us, Newton step 1111)
+            if constexpr (LOGITS) softmax3(c0, c1, c2, img_first, img_last);
             if constexpr (BWD) {
                 // the edge rows publish the products that cross into the neighbouring part: tap 0 of a part's first row
                 // reads the row above it, tap 2 of its last row the row below
@@ -356,7 +356,7 @@ __device__ __forceinline__ void horizontal_rows2(const FwdParams& p, char* blk_a
             const float av = elem<T>(bl, e) * elem<T>(bx, e);
             float c0 = elem<T>(b0, e), c1 = elem<T>(b1, e), c2 = elem<T>(b2, e);
             // raw logits: normalised here over the taps whose neighbour row exists (Sec. 3.2)
-            if constexpr (LOGITS) softmax3<!SAVE && !BWD>(c0, c1, c2, img_first, img_last);        // (512 planes 512x512 bf16: division 1092 us, Newton step 1111)
+            if constexpr (LOGITS) softmax3(c0, c1, c2, img_first, img_last);
             if constexpr (BWD) {
                 const float q0 = wp0 * h, q2 = wp2 * h;
                 float up = from_lane_below(q2), dn = from_lane_above(q0);

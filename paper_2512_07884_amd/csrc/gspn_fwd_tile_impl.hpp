@@ -38,6 +38,11 @@ struct TileArgs {
     int parts;    // row-split horizontal phases: waves per line (each owns H/parts image rows)
 };
 
+// Logits of fp32 maps are normalised by division (softmax3).  With the Newton step the registers do not hold rows of 112 bytes (four waves 217 ->
+// 302 with accumulation registers, eight waves 51 spilled), nor the reverse sweep of 64-byte rows (one); rows of 512 bytes would gain, 0.95 of
+// the time in the mean of 524 calls.
+template <typename T> constexpr bool tile_divides() { return sizeof(T) == 4; }
+
 // ---------------------------------------------------------------------------
 // vertical direction (d = 0 top->bottom, 1 bottom->top): lines are image rows
 // ---------------------------------------------------------------------------
@@ -144,7 +149,7 @@ __device__ __forceinline__ void vertical_pass(const TileArgs& a, float* tile, in
 #pragma unroll
             for (int v = 0; v < V; ++v) {
                 float c0 = elem<T>(cur.w0, v), c1 = elem<T>(cur.w1, v), c2 = elem<T>(cur.w2, v);
-                if constexpr (LOGITS) softmax3<sizeof(T) == 4>(c0, c1, c2, first && v == 0, last && v == V - 1);
+                if constexpr (LOGITS) softmax3<tile_divides<T>()>(c0, c1, c2, first && v == 0, last && v == V - 1);
                 // a tap that points outside the line takes nothing, whatever the tensor holds there
                 wp0[v] = ((first && v == 0) || starts) ? 0.f : c0;
                 wp1[v] = starts ? 0.f : c1;
@@ -172,7 +177,7 @@ __device__ __forceinline__ void vertical_pass(const TileArgs& a, float* tile, in
             av[v] = elem<T>(cur.l, v) * elem<T>(cur.x, v);
             w0[v] = elem<T>(cur.w0, v); w1[v] = elem<T>(cur.w1, v); w2[v] = elem<T>(cur.w2, v);
             uv[v] = elem<T>(cur.u, v);
-            if constexpr (LOGITS) softmax3<sizeof(T) == 4>(w0[v], w1[v], w2[v], first && v == 0, last && v == V - 1);
+            if constexpr (LOGITS) softmax3<tile_divides<T>()>(w0[v], w1[v], w2[v], first && v == 0, last && v == V - 1);
             if (maybe_start) {
                 w0[v] = scan_start ? 0.f : w0[v]; w1[v] = scan_start ? 0.f : w1[v]; w2[v] = scan_start ? 0.f : w2[v];
             }
@@ -312,7 +317,7 @@ struct HorizontalPass {
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
                     float c0 = elem<T>(s.w0[v], e), c1 = elem<T>(s.w1[v], e), c2 = elem<T>(s.w2[v], e);
-                    if constexpr (LOGITS) softmax3<sizeof(T) == 4>(c0, c1, c2, first && v == 0, last && v == V - 1);
+                    if constexpr (LOGITS) softmax3<tile_divides<T>()>(c0, c1, c2, first && v == 0, last && v == V - 1);
                     wp0[v] = ((first && v == 0) || starts) ? 0.f : c0;
                     wp1[v] = starts ? 0.f : c1;
                     wp2[v] = ((last && v == V - 1) || starts) ? 0.f : c2;
@@ -328,7 +333,7 @@ struct HorizontalPass {
             for (int v = 0; v < V; ++v) {
                 av[v] = elem<T>(s.l[v], e) * elem<T>(s.x[v], e);
                 w0[v] = elem<T>(s.w0[v], e); w1[v] = elem<T>(s.w1[v], e); w2[v] = elem<T>(s.w2[v], e);
-                if constexpr (LOGITS) softmax3<sizeof(T) == 4>(w0[v], w1[v], w2[v], first && v == 0, last && v == V - 1);
+                if constexpr (LOGITS) softmax3<tile_divides<T>()>(w0[v], w1[v], w2[v], first && v == 0, last && v == V - 1);
                 if (LOCAL || k == 0) { w0[v] = start ? 0.f : w0[v]; w1[v] = start ? 0.f : w1[v]; w2[v] = start ? 0.f : w2[v]; }
                 if constexpr (LOCAL) h[v] = start ? 0.f : h[v];
             }
@@ -477,7 +482,7 @@ struct HorizontalSplitPass {
                 bool starts = false;                      // GSPN-local: this column starts a stretch in scan order
                 if constexpr (LOCAL) starts = bwalk.start(c == nchunks - 1 && k == CS - 1);
                 float c0 = elem<T>(b0, e), c1 = elem<T>(b1, e), c2 = elem<T>(b2, e);
-                if constexpr (LOGITS) softmax3<sizeof(T) == 4>(c0, c1, c2, img_first, img_last);
+                if constexpr (LOGITS) softmax3<tile_divides<T>()>(c0, c1, c2, img_first, img_last);
                 wp0 = (img_first || starts) ? 0.f : c0;
                 wp1 = starts ? 0.f : c1;
                 wp2 = (img_last || starts) ? 0.f : c2;
@@ -490,7 +495,7 @@ struct HorizontalSplitPass {
             bool start = (c == 0) && (k == 0);
             if constexpr (LOCAL) start = walk.start();
             float w0 = elem<T>(b0, e), w1 = elem<T>(b1, e), w2 = elem<T>(b2, e);
-            if constexpr (LOGITS) softmax3<sizeof(T) == 4>(w0, w1, w2, img_first, img_last);
+            if constexpr (LOGITS) softmax3<tile_divides<T>()>(w0, w1, w2, img_first, img_last);
             if (LOCAL || k == 0) { w0 = start ? 0.f : w0; w1 = start ? 0.f : w1; w2 = start ? 0.f : w2; }
             const float av = elem<T>(bl, e) * elem<T>(bx, e);
             float up = from_lane_below(h), dn = from_lane_above(h);
