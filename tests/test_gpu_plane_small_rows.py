@@ -7,6 +7,7 @@ compares it)."""
 import pytest
 
 from test_gpu_apart import close, inputs
+from test_plane_choice import plane_shape
 
 pytestmark = pytest.mark.gpu
 
@@ -27,6 +28,16 @@ CALLS = [
     # ... of one and two channels per wave with up to 4 KB of them, and beyond
     ((1, 510, 28, 28, 510), "f32", 0, True), ((1, 300, 16, 32, 300), "f32", 0, False), ((1, 301, 15, 20, 301), "f32", 6, False), ((1, 300, 32, 32, 300), "f32", 0, False),
     ((1, 300, 33, 32, 300), "f32", 0, False), ((1, 300, 32, 64, 300), "bf16", 0, True), ((1, 300, 33, 64, 300), "f16", 0, False), ((1, 300, 31, 24, 300), "f16", 5, True),
+]
+
+
+# ... and with planes enough that the flat variant fills the chip less often (below, the padded one runs): four and eight channels per wave, lines of
+# 17 to 32 positions in fp32, weights of each channel's own
+FLAT = [
+    ((4, 1536, 8, 8, 192), "bf16", 0, False), ((4, 1536, 5, 8, 192), "f16", 3, True), ((4, 1536, 4, 4, 192), "f32", 0, False), ((8, 1536, 8, 4, 192), "f32", 5, True),
+    ((4, 1536, 16, 16, 16), "f16", 0, False), ((4, 1536, 9, 16, 16), "bf16", 4, True), ((4, 1536, 11, 12, 8), "f32", 0, False),
+    ((1, 4160, 20, 20, 8), "f32", 0, False), ((1, 4528, 17, 12, 8), "f32", 7, False), ((1, 6144, 20, 12, 8), "f32", 0, True),
+    ((1, 24576, 16, 8, 24576), "bf16", 0, False), ((1, 24576, 5, 8, 24576), "f16", 2, True), ((1, 16384, 9, 8, 16384), "f32", 0, False), ((1, 16384, 12, 12, 16384), "f32", 5, False),
 ]
 
 
@@ -66,3 +77,9 @@ def test_against_line_by_line(shape, dtype, kchunk, logits, monkeypatch):
         assert binding.running_kernel(*shape, code, call, kchunk, logits) == want, call
         got = run(call, inp, shape, dtype, kchunk, logits, ref["h"])
         close(got, ref if call != "bwd" else ref_bwd, dtype, ())
+
+
+@pytest.mark.parametrize("shape,dtype,kchunk,logits", FLAT, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+def test_flat_variant_against_line_by_line(shape, dtype, kchunk, logits, monkeypatch):
+    assert plane_shape(*shape, dtype, kchunk, logits)[0] == 1
+    test_against_line_by_line(shape, dtype, kchunk, logits, monkeypatch)
