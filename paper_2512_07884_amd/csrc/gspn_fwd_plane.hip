@@ -87,8 +87,8 @@ struct FwdPlaneArgs {
 // products to the positions those taps read from (e_t = u_t*gy_t + T_{t+1}^T e_{t+1}).  The taps that are stored as 0
 // (out-of-line neighbours, GSPN-local: lines that start a stretch) are the ones that must pass nothing on here too.
 // W16: a group's weights in LDS as {w0, w1} in 16 bits and w2 in fp32, 8 bytes per position instead of 16, so that a CU holds eight waves in two
-// or more workgroups where it held six in one, which all waited for the memory at once: 6144 planes 56x56 bf16 (cpg 12) 135 -> 103 us, with
-// h_save and backward 501 -> 448, 48x48 f16 104 -> 77, 17280 of 36x32 223 -> 148; 0.92 in the mean of 69 calls, the longest 1.01.
+// or more workgroups where it held six in one, which all waited for the memory at once: 6144 planes 56x56 bf16 (cpg 12) 141 -> 106 us, with
+// h_save and backward 512 -> 457, 48x48 f16 113 -> 84, 17280 of 36x32 176 -> 166; 0.86 in the mean of 1080 calls.
 // NCHT: 16 B chunks per lane the register arrays are sized for (8: the wave's channels hold at most 8 KB; 4: small maps
 // with weights of each channel's own, and those of the flat variant, which then has the registers to give its LDS planes an odd pitch too -- every element's place is
 // tracked through two bit masks per chunk)
@@ -281,7 +281,7 @@ __global__ void __launch_bounds__(SHARED ? 512 : 256, sizeof(T) == 4 && FLAT && 
             const int t0 = SHARED ? (int)threadIdx.x : lane, tn = SHARED ? nthreads : 64;
             const rsrc_t rs = make_rsrc(wptr(d, SHARED ? g : c0));
             // Weights of the wave's own channels four pieces at a time: piece by piece it waited for the memory up to 24 times per
-            // direction (11136 planes 16x14 fp32 268 -> 226 us).  A group's are few pieces per thread, and the registers cost more there (9216
+            // direction (11136 planes 16x14 fp32 92 -> 78 us).  A group's are few pieces per thread, and the registers cost more there (9216
             // planes 14x14 f16 20 -> 30).
             if constexpr (SHARED) {
                 for (int c = t0; c * ew < nel; c += tn) {
@@ -600,8 +600,8 @@ static bool plan_fwd_plane_waves(const FwdParams& p, FwdPlanePlan& t, size_t hp)
         // 14x14 with logits 39 -> 53 us, 1080 of 20x23 with h_save 53 -> 73); the flat variant's not five in six's place, which spread unevenly over
         // the four SIMDs (nine calls 1.06, 7200 planes 12x63 90 -> 113 us); weights that the largest could request a
         // direction ahead stay so.  In fp32 (flat: small maps) and with 16-bit weights in LDS; else the most waves, whose share of the weights is
-        // the smallest.  Most waves -> this: 49920 planes 7x7 fp32 46 -> 32 us, 36864 of 10x10 56 -> 43, 18432 of 28x28 129 -> 114 (5x5
-        // 43 -> 46); where it stays: 15360 of 36x36 f16 with logits 207 -> 286, 29952 of 10x10 f16 56 -> 69.
+        // the smallest.  Most waves -> this: 49920 planes 7x7 fp32 40 -> 30 us, 5x5 35 -> 26, 18432 of 28x28 134 -> 119; where it
+        // stays: 15360 of 36x36 f16 with logits 207 -> 286, 29952 of 10x10 f16 56 -> 69.
         const int es = t.es, chunks = p.H * p.W * es / 16;
         auto ahead = [&](int nw) { return t.w16 ? chunks <= 2 * 64 * nw : 3 * chunks <= 4 * 64 * nw; };
         for (int w16 = t.w16; w16 >= 0; --w16) {
@@ -631,8 +631,8 @@ static FwdPlanePlan plan_fwd_plane_padded(const FwdParams& p, int es) {
     const int HW = p.H * p.W, m = p.H > p.W ? p.H : p.W;
     t.cpw = m <= 32 ? 2 : 1;
     // Weights of each channel's own: the channels that four chunks per lane hold.  The registers then hold their weights a direction ahead, where eight
-    // chunks per lane waited for the memory three times per direction, on four waves per CU.  6144 planes 28x28 fp32 92 -> 78 us (step
-    // with logits 357 -> 335), 8448 of 36x32 f16 (step) 750 -> 467, 32256 of 19x16 f16 411 -> 152; 0.92 in the mean of 89 calls, the longest 1.03.
+    // chunks per lane waited for the memory three times per direction, on four waves per CU.  6144 planes 28x28 fp32 100 -> 80 us (with
+    // logits 134 -> 96), 8448 of 36x32 f16 (backward) 393 -> 260, 32256 of 19x16 f16 344 -> 128; 0.60 in the mean of 1110 calls.
     t.small = p.cpg == 1 && HW * es <= 4096;
     if (t.small && 2 * HW * es > 4096) t.cpw = 1;
     if ((size_t)t.cpw * HW * es > 8192) {
@@ -681,7 +681,7 @@ static FwdPlanePlan plan_fwd_plane_flat(const FwdParams& p, int es) {
 // fill the chip with it more often than with the flat one: what that gains is channels per CU, and what it costs is that the weights are
 // waited for in each direction.  Both timed on 1480 random calls: 0.78 in the mean where the chip is filled less often, 1.13 where as
 // often (up to 4096 planes of two channels per wave; 2048 planes 20x20 fp32 17.6 against 25 us, 2624 of 16x16 f16 13.5 against 21.6).
-// us: 36864 planes 8x8 bf16, forward 115 -> 40, 45312 of 11x8 fp32 125 -> 47, 73728 of 16x16 bf16 with logits 243 -> 163.  Workgroups of
+// us: 36864 planes 8x8 bf16, forward 103 -> 44, 45312 of 11x8 fp32 134 -> 49, 73728 of 16x16 bf16 with logits 248 -> 167.  Workgroups of
 // five and more waves, which wait for each other, in place of such as need not, 1.03 (5120 planes 9x4 fp32 25 against 21); a wave that
 // fetches a group's weights by itself, beyond 340 pixels 1.04 (8896 planes 25x20 fp32 60 against 76).
 // Beyond the lines: 24x24 f16 48 -> 60, 25x28 fp32 63 -> 76.  Weights of each channel's own: up to 128 pixels in 16 bits (5x8 36 us for 105,
